@@ -1,17 +1,16 @@
-// Direct (bit-sliced) evaluation of the Toeplitz hash over GF(2), with no
-// transform and no floating point: y_i = parity(popcount(AND of the seed
-// window at i with the reversed key)), the definition of section 2.1 (Eq. 1)
-// read word-parallel.  With xr[t] = x[n-1-t] (the key reversed),
+// Direct evaluation of the Toeplitz hash over GF(2), with no transform and no
+// rounding: y_i = parity(popcount(AND of the seed window at i with the reversed
+// key)), the definition of section 2.1 (Eq. 1).  With xr[t] = x[n-1-t] (the key
+// reversed),
 //
-//     y_i = XOR_{t<n} ( s[i+t] AND xr[t] ),
+//     y_i = XOR_{t<n} ( s[i+t] AND xr[t] ).
 //
-// so output i needs the 32-bit seed words at bit offsets i + 32k, each a
-// funnel shift (v_alignbit) of two aligned words, AND-ed with reversed-key
-// word k and XOR-accumulated; the output bit is the parity of the
-// accumulator.  Cost: ceil(n/32) word steps per output (two VALU operations
-// each), against about 24 L bytes of HBM traffic per FFT tile: the direct
-// path is the faster one for short outputs, and it evaluates any chosen
-// outputs exactly (a verifier of the FFT path that shares nothing with it).
+// Whole outputs are computed as a bit contraction on the matrix cores
+// (k_direct_mm); chosen outputs word-parallel on the vector units
+// (k_direct_select): the 32-bit seed words at bit offsets i + 32k, each a
+// funnel shift (v_alignbit) of two aligned words, AND-ed with reversed-key word
+// k and XOR-accumulated.  Both share nothing with the FFT path, and the second
+// serves as its verifier.
 //
 // Seed bits past n+m-1 (and reads past the seed's last word, which return 0)
 // only ever meet reversed-key bits t >= n, which are zero.
@@ -54,41 +53,151 @@ k_direct_prep(const uint64_t* __restrict__ key, uint64_t n, uint32_t* __restrict
     if (g < nzero) zero[g] = 0ull;
 }
 
-// Outputs [i_base + 256 bx, +256) over reversed-key words [k_base + kc by,
-// +kc): each thread owns one output; the workgroup stages its seed words and
-// key words in LDS and XORs the parity bits of its waves into out.
-__global__ void __launch_bounds__(kDirectThreads)
-k_direct(const uint32_t* __restrict__ seed32, uint64_t sw32, const uint32_t* __restrict__ kr, uint64_t kw4,
-         uint64_t k_base, uint32_t kc, uint64_t i_base, uint64_t m, uint64_t* __restrict__ out) {
-    __shared__ uint32_t S[kDirectChunk + 12];
-    __shared__ __align__(16) uint32_t K[kDirectChunk];
-    const int tid = threadIdx.x;
-    const uint64_t i0 = i_base + (uint64_t)blockIdx.x * kDirectThreads;
-    const uint64_t k0 = k_base + (uint64_t)blockIdx.y * kc;
-    const uint32_t nk = (uint32_t)(kw4 - k0 < kc ? kw4 - k0 : kc);   // multiple of 4
-    const uint64_t sbase = (i0 >> 5) + k0;
-    for (uint32_t q = tid; q < nk + 9; q += kDirectThreads) {
-        const uint64_t gq = sbase + q;
-        S[q] = gq < sw32 ? seed32[gq] : 0u;
+// ---- the product on the matrix cores
+// Output i = i0 + r + 64 d of a tile (r < 64, d < 16 NB) is
+//     y_i = XOR_p ( s[i0 + r + p] AND xr[p - 64 d] ),    p = t + 64 d,
+// a contraction over p of A[r][p] = s[i0 + r + p] (64 shifts of one seed
+// stream) with B[p][d] = xr[p - 64 d] (16 NB word shifts of one key stream).
+// Both hold bits, so 4-bit floating operands (e2m1) carry them exactly and the
+// FP32 accumulators hold the exact counts (a wave adds at most 127 * 128
+// products, far below 2^24); y_i is the count's low bit.
+//
+// Operands.  A lane of v_mfma_f32_16x16x128_f8f6f4 holds 32 elements of one
+// row (or column) for one of four K groups.  The K order is free as long as A
+// and B share it, so the 32 elements of a lane are the bits of one word, taken
+// as four masks: bits 0, 4, .. / 1, 5, .. / 2, 6, .. / 3, 7, .. of the word in
+// place are nibbles of value 0.5, 1 and 2 in A, matched by 2, 1 and 0.5 in B, so
+// that every product of set bits is 1.  Expanding a word costs 5 (A) or 7 (B)
+// operations beside A's funnel shift, no table.  The four K groups of each
+// wave walk their own consecutive words, so a lane loads one new seed word and
+// NB key words per step.
+//
+// Bound by the matrix cores for NB = 4 (16 products of 16 cycles per step beside
+// 48 vector operations of 4) and by the vector operations that prepare a step
+// for NB = 1 (30, and 4 products).  Measured on MI355X: n = 12,345,679, m = 1000
+// 10 us (the word-parallel kernel before it, one output per lane: 55 us); n =
+// 10^6, m = 200,000 3.1e15 bit products per second (2.2e14 before).
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int kMmThreads = 512;                          // 8 waves
+constexpr int kMmStreams = kMmThreads / 16;              // K groups of a workgroup
+constexpr uint32_t kMmMaxSeg = 127;                      // words per K group and workgroup
+constexpr uint32_t kMmMinSeg = 7;
+constexpr uint32_t kMmMaxChunk = kMmStreams * kMmMaxSeg;
+
+// A's nibbles of the bits of w: 0.5, 1, 2, 2 by bit position mod 4.
+__device__ __forceinline__ v8i mm_expand_a(uint32_t w) {
+    return v8i{(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u),
+               (int)((w >> 1) & 0x44444444u), 0, 0, 0, 0};
+}
+// B's: 2, 1, 0.5, 0.5.
+__device__ __forceinline__ v8i mm_expand_b(uint32_t w) {
+    return v8i{(int)((w << 2) & 0x44444444u), (int)(w & 0x22222222u), (int)((w >> 2) & 0x11111111u),
+               (int)((w >> 3) & 0x11111111u), 0, 0, 0, 0};
+}
+
+// Workgroup (x, y) of a job: outputs [1024 NB x, + 1024 NB) over words
+// [kc y, + kc) of the p axis (p < n + 64 (16 NB - 1)), kc = 32 seg.  `merge`:
+// XOR the words into out (several workgroups along y; out cleared before), else
+// store.  njobs = 0: one job by value, x and y from the grid and its bases;
+// else the workgroups of all jobs of `many` in a row (wg_begin), x fastest.
+template <int NB>
+__global__ void __launch_bounds__(kMmThreads)
+k_direct_mm(DirectJob one, const DirectJob* __restrict__ many, uint32_t njobs, uint64_t x_base, uint64_t y_base) {
+    constexpr uint32_t XO = 32 * NB;                     // key words before the chunk (>= 2 (16 NB - 1))
+    __shared__ uint32_t S[kMmMaxChunk + 4];
+    __shared__ uint32_t X[kMmMaxChunk + XO];
+    __shared__ unsigned long long red[kMmThreads / 64][16 * NB];
+    const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+    DirectJob jd = one;
+    uint64_t bx = x_base + blockIdx.x, by = y_base + blockIdx.y;
+    if (njobs) {
+        uint32_t lo = 0, hi = njobs - 1;
+        while (lo < hi) {   // last job with wg_begin <= blockIdx.x
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (many[mid].wg_begin <= blockIdx.x) lo = mid; else hi = mid - 1;
+        }
+        jd = many[lo];
+        const uint32_t q = blockIdx.x - jd.wg_begin;
+        bx = q % jd.bx;
+        by = q / jd.bx;
     }
-    for (uint32_t q = tid; q < nk; q += kDirectThreads) K[q] = kr[k0 + q];
+    const uint64_t n = jd.n, m = jd.m, sw32 = 2 * ((n + m - 1 + 63) >> 6);
+    const uint32_t* __restrict__ seed32 = reinterpret_cast<const uint32_t*>(jd.seed);
+    const uint64_t* __restrict__ key = jd.key;
+    uint64_t* __restrict__ out = jd.out;
+    const uint32_t seg = jd.seg;
+    const uint32_t kc = kMmStreams * seg;
+    const uint64_t w0 = by * kc;                         // first word of the chunk
+    const uint64_t sbase = bx * (32 * NB) + w0;               // its seed word
+    for (uint32_t q = tid; q < kc + 3; q += kMmThreads) {
+        const uint64_t g = sbase + q;
+        S[q] = g < sw32 ? seed32[g] : 0u;
+    }
+    const uint64_t kw = (n + 31) >> 5;
+    for (uint32_t q = tid; q < kc + XO; q += kMmThreads) {
+        const int64_t w = (int64_t)(w0 + q) - (int64_t)XO;   // reversed-key word; none outside [0, kw)
+        X[q] = (w >= 0 && (uint64_t)w < kw)
+                   ? __builtin_bitreverse32(key_bits32(key, (int64_t)n - 32 - 32 * w)) : 0u;
+    }
     __syncthreads();
 
-    const int b = tid >> 5, sh = tid & 31;   // output i0 + tid: word offset b, shift sh
-    uint32_t lo = S[b], acc = 0u;
-    for (uint32_t kk = 0; kk < nk; kk += 4) {
-        const uint32_t h0 = S[b + kk + 1], h1 = S[b + kk + 2], h2 = S[b + kk + 3], h3 = S[b + kk + 4];
-        const uint4 kv = *reinterpret_cast<const uint4*>(&K[kk]);
-        acc ^= __builtin_amdgcn_alignbit(h0, lo, sh) & kv.x;
-        acc ^= __builtin_amdgcn_alignbit(h1, h0, sh) & kv.y;
-        acc ^= __builtin_amdgcn_alignbit(h2, h1, sh) & kv.z;
-        acc ^= __builtin_amdgcn_alignbit(h3, h2, sh) & kv.w;
-        lo = h3;
+    const int r = l & 15, g = l >> 4;
+    const uint32_t q0 = (uint32_t)(wv * 4 + g) * seg;         // this K group's words q0 .. q0 + seg - 1
+    const uint32_t* __restrict__ xs = X + q0 + XO - 2 * r;    // column d = 16 b + r reads xs[h - 32 b]
+    v4f acc[4][NB];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+    uint32_t s0 = S[q0], s1 = S[q0 + 1];
+#pragma unroll 2
+    for (uint32_t h = 0; h < seg; ++h) {
+        const uint32_t s2 = S[q0 + h + 2];
+        v8i B[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) B[b] = mm_expand_b(xs[(int)h - 32 * b]);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            // row 16 a + r: the 32 seed bits from bit 16 a + r of (s0, s1, s2)
+            const uint32_t w = a < 2 ? __builtin_amdgcn_alignbit(s1, s0, 16 * a + r)
+                                     : __builtin_amdgcn_alignbit(s2, s1, 16 * (a - 2) + r);
+            const v8i A = mm_expand_a(w);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B[b], acc[a][b], 4, 4, 0, 0, 0, 0);
+        }
+        s0 = s1;
+        s1 = s2;
     }
-    const uint64_t i = i0 + (uint64_t)tid;
-    const bool bit = i < m && (__popc(acc) & 1);
-    const unsigned long long bal = __ballot(bit);
-    if ((tid & 63) == 0 && bal) atomicXor((unsigned long long*)&out[(i0 >> 6) + (tid >> 6)], bal);
+    // lane (r, g) holds rows 16 a + 4 g + v of column 16 b + r: the parities of
+    // one column are the 64 bits of one output word
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        uint64_t word = 0;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                word |= (uint64_t)((uint32_t)acc[a][b][v] & 1u) << (16 * a + v);
+        word <<= 4 * g;
+        word ^= __shfl_xor(word, 16);
+        word ^= __shfl_xor(word, 32);
+        if (g == 0) red[wv][16 * b + r] = word;
+    }
+    __syncthreads();
+    if (tid < 16 * NB) {
+        uint64_t word = 0;
+#pragma unroll
+        for (int w = 0; w < kMmThreads / 64; ++w) word ^= red[w][tid];
+        const uint64_t o = bx * (16 * NB) + (uint64_t)tid, ow = (m + 63) >> 6;
+        if (o < ow) {
+            if (o == ow - 1 && (m & 63)) word &= (1ull << (m & 63)) - 1ull;
+            if (!jd.merge) out[o] = word;
+            else if (word) atomicXor((unsigned long long*)&out[o], (unsigned long long)word);
+        }
+    }
 }
 
 // Selected outputs idx[g] (g < count), bit g of res: each thread walks the
@@ -144,38 +253,135 @@ uint64_t direct_key_words(uint64_t n) { return cdiv(cdiv(n, 32), 4) * 4; }
 
 // Grid slabs: at most 2^20 workgroups along x and 2^15 along y per launch.
 constexpr uint64_t kSlabX = 1ull << 20, kSlabY = 1ull << 15;
+// Workgroups of one batched launch.
+constexpr uint64_t kMmBatchWgs = 1ull << 24;
 
-int launch_direct_prep(const uint64_t* key, uint64_t n, uint64_t m, uint64_t* out, uint32_t* kr, void* stream,
-                       uint64_t* launches) {
-    const uint64_t kw4 = direct_key_words(n), ow = cdiv(m, 64);
-    const uint64_t prep = std::max(kw4, ow);
-    hipLaunchKernelGGL(k_direct_prep, dim3((uint32_t)cdiv(prep, kDirectThreads)), dim3(kDirectThreads), 0,
-                       (hipStream_t)stream, key, n, kr, kw4, out, ow);
+// Column blocks of a tile: 1024 NB outputs.  A step of 128 key bits takes
+// about 120, 144 and 256 cycles of a SIMD at NB = 1, 2, 4 (operand preparation
+// bounds the first two, the matrix cores the last).
+static int mm_blocks(uint64_t m) {
+    int best = 1;
+    double cost = 1e300;
+    for (int nb : {1, 2, 4}) {
+        const double c = (double)cdiv(m, 1024 * nb) * (nb == 1 ? 120.0 : nb == 2 ? 144.0 : 256.0);
+        if (c < cost) cost = c, best = nb;
+    }
+    return best;
+}
+
+// Grid of one job: K groups of `seg` words.  The number is odd, so that the LDS
+// reads of a wave's K groups start on different banks.
+static uint64_t mm_words(uint64_t n, int nb) { return cdiv(n, 32) + 2 * (16 * (uint64_t)nb - 1); }
+static uint32_t mm_seg(uint64_t words_per_group) {
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(kMmMinSeg, words_per_group) | 1, kMmMaxSeg);
+}
+static uint64_t mm_chunks(uint64_t n, int nb, uint32_t seg) { return cdiv(mm_words(n, nb), (uint64_t)seg * kMmStreams); }
+// Workgroups that a launch aims at when the outputs alone do not fill the
+// device, and at most: two of 8 waves per CU, one round of the device.
+constexpr uint64_t kMmTarget = 512;
+
+template <int NB>
+static int mm_launch(dim3 grid, const DirectJob& one, const DirectJob* many, uint32_t njobs, uint64_t x0, uint64_t y0,
+                     hipStream_t s, uint64_t* launches) {
+    hipLaunchKernelGGL((k_direct_mm<NB>), grid, dim3(kMmThreads), 0, s, one, many, njobs, x0, y0);
     if (hipGetLastError() != hipSuccess) return -1;
     *launches += 1;
     return 0;
 }
+static int mm_launch_nb(int nb, dim3 grid, const DirectJob& one, const DirectJob* many, uint32_t njobs, uint64_t x0,
+                        uint64_t y0, hipStream_t s, uint64_t* launches) {
+    return nb == 1   ? mm_launch<1>(grid, one, many, njobs, x0, y0, s, launches)
+           : nb == 2 ? mm_launch<2>(grid, one, many, njobs, x0, y0, s, launches)
+                     : mm_launch<4>(grid, one, many, njobs, x0, y0, s, launches);
+}
 
-int launch_direct_main(const uint64_t* seed, uint64_t n, uint64_t m, uint64_t* out, const uint32_t* kr,
-                       void* stream, uint64_t* launches) {
-    hipStream_t s = (hipStream_t)stream;
-    const uint64_t kw4 = direct_key_words(n), sw32 = 2 * cdiv(n + m - 1, 64);
-    // about 1024 workgroups (4 per CU), each with at least 1024 key words:
-    // split the key when the outputs are few (measured on MI355X against
-    // 512..8192 workgroups and 256-word chunks)
-    const uint64_t bx = cdiv(m, kDirectThreads);
-    const uint64_t want_y = std::max<uint64_t>(1, cdiv(1024, bx));
-    uint64_t kc = std::max<uint64_t>(1024, cdiv(kw4, want_y));
-    kc = std::min<uint64_t>(cdiv(kc, 4) * 4, kDirectChunk);
-    const uint64_t by = cdiv(kw4, kc);
+static DirectJob mm_single(const uint64_t* seed, const uint64_t* key, uint64_t n, uint64_t m, uint64_t* out, int* nb) {
+    *nb = mm_blocks(m);
+    const uint64_t bx = cdiv(m, 1024 * (uint64_t)*nb), want_y = std::max<uint64_t>(1, kMmTarget / bx);
+    DirectJob j{};
+    j.seed = seed;
+    j.key = key;
+    j.out = out;
+    j.n = n;
+    j.m = m;
+    j.seg = mm_seg(cdiv(mm_words(n, *nb), want_y * kMmStreams));
+    j.merge = mm_chunks(n, *nb, j.seg) > 1 ? 1u : 0u;
+    return j;
+}
+
+int launch_direct_prep(uint64_t n, uint64_t m, uint64_t* out, void* stream, uint64_t* launches) {
+    int nb;
+    if (!mm_single(nullptr, nullptr, n, m, out, &nb).merge) return 0;
+    if (launch_xor_words(out, out, cdiv(m, 64), stream)) return -1;
+    *launches += 1;
+    return 0;
+}
+
+int launch_direct_main(const uint64_t* seed, const uint64_t* key, uint64_t n, uint64_t m, uint64_t* out, void* stream,
+                       uint64_t* launches) {
+    int nb;
+    const DirectJob j = mm_single(seed, key, n, m, out, &nb);
+    const uint64_t bx = cdiv(m, 1024 * (uint64_t)nb), by = mm_chunks(n, nb, j.seg);
     for (uint64_t x0 = 0; x0 < bx; x0 += kSlabX)
         for (uint64_t y0 = 0; y0 < by; y0 += kSlabY) {
             const dim3 grid((uint32_t)std::min(kSlabX, bx - x0), (uint32_t)std::min(kSlabY, by - y0));
-            hipLaunchKernelGGL(k_direct, grid, dim3(kDirectThreads), 0, s, (const uint32_t*)seed, sw32, kr, kw4,
-                               y0 * kc, (uint32_t)kc, x0 * kDirectThreads, m, out);
-            if (hipGetLastError() != hipSuccess) return -1;
-            *launches += 1;
+            if (mm_launch_nb(nb, grid, j, nullptr, 0, x0, y0, (hipStream_t)stream, launches)) return -1;
         }
+    return 0;
+}
+
+// Clears the outputs of the jobs that several workgroups merge into.
+__global__ void __launch_bounds__(kDirectThreads) k_direct_clear(const DirectJob* __restrict__ many) {
+    const DirectJob jd = many[blockIdx.x];
+    if (!jd.merge) return;
+    const uint64_t ow = (jd.m + 63) >> 6;
+    for (uint64_t o = threadIdx.x; o < ow; o += kDirectThreads) jd.out[o] = 0ull;
+}
+
+uint64_t direct_batch_plan(DirectJob* jobs, uint32_t count, DirectBatch* plan) {
+    // order by column blocks; K groups sized so that all jobs together give
+    // about four times the workgroups of a single job
+    std::stable_sort(jobs, jobs + count, [](const DirectJob& a, const DirectJob& b) { return mm_blocks(a.m) < mm_blocks(b.m); });
+    uint64_t total = 0;   // tile words
+    for (uint32_t k = 0; k < count; ++k) {
+        const int nb = mm_blocks(jobs[k].m);
+        total += cdiv(jobs[k].m, 1024 * (uint64_t)nb) * mm_words(jobs[k].n, nb);
+    }
+    const uint32_t seg = mm_seg(cdiv(total, 4 * kMmTarget * kMmStreams));
+    *plan = DirectBatch{};
+    uint64_t taken = 0;
+    for (int i = 0; i < 3; ++i) {
+        uint64_t wgs = 0;
+        plan->first[i] = (uint32_t)taken;
+        for (; taken < count && mm_blocks(jobs[taken].m) == 1 << i; ++taken) {
+            DirectJob& j = jobs[taken];
+            const uint64_t bx = cdiv(j.m, 1024ull << i), by = mm_chunks(j.n, 1 << i, seg);
+            if (bx > kSlabX || by > kSlabX || wgs + bx * by > kMmBatchWgs) return 0;
+            j.seg = seg;
+            j.bx = (uint32_t)bx;
+            j.wg_begin = (uint32_t)wgs;
+            j.merge = by > 1 ? 1u : 0u;
+            plan->clears |= j.merge;
+            wgs += bx * by;
+        }
+        plan->jobs[i] = (uint32_t)taken - plan->first[i];
+        plan->wgs[i] = (uint32_t)wgs;
+    }
+    return taken;
+}
+
+int launch_direct_batch(const DirectBatch& plan, const DirectJob* many, uint32_t count, void* stream,
+                        uint64_t* launches) {
+    hipStream_t s = (hipStream_t)stream;
+    if (plan.clears) {
+        hipLaunchKernelGGL(k_direct_clear, dim3(count), dim3(kDirectThreads), 0, s, many);
+        if (hipGetLastError() != hipSuccess) return -1;
+        *launches += 1;
+    }
+    for (int i = 0; i < 3; ++i)
+        if (plan.jobs[i] && mm_launch_nb(1 << i, dim3(plan.wgs[i]), DirectJob{}, many + plan.first[i], plan.jobs[i], 0, 0,
+                                         s, launches))
+            return -1;
     return 0;
 }
 

@@ -381,9 +381,11 @@ void Lane::release(Ctx* c) {
     jobs_dev.release(c);
     io.release(c);
     aux.release(c);
+    direct_dev.release(c);
     if (stream) (void)hipStreamSynchronize(stream);   // the frees above are in its order
     meta_host.release();
     jobs_host.release();
+    direct_host.release();
     io_host.release();
     timer.destroy();
     if (done) (void)hipEventDestroy(done);
@@ -633,19 +635,40 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
 
 pa_status Lane::direct(Ctx* c, const uint64_t* seed, const uint64_t* key, uint64_t n, uint64_t m, uint64_t* out,
                        bool timing, pa_stats* stats) {
-    pa_status st = aux.ensure(c, direct_key_words(n) * 4, stream);
-    if (st != PA_OK) return st;
-    // PA_TIMING: ms_pass[0] the prep kernel, ms_pass[1] the product kernels
+    (void)c;
+    // PA_TIMING: ms_pass[0] the clearing of out, ms_pass[1] the product kernels
     hipEvent_t a = timing ? timer.mark(stream) : nullptr;
-    if (launch_direct_prep(key, n, m, out, (uint32_t*)aux.ptr, stream, &stats->launches)) return PA_EDEVICE;
+    if (launch_direct_prep(n, m, out, stream, &stats->launches)) return PA_EDEVICE;
     hipEvent_t b = timing ? timer.mark(stream) : nullptr;
-    if (launch_direct_main(seed, n, m, out, (const uint32_t*)aux.ptr, stream, &stats->launches)) return PA_EDEVICE;
+    if (launch_direct_main(seed, key, n, m, out, stream, &stats->launches)) return PA_EDEVICE;
     if (timing) {
         timer.spans.push_back({0, {a, b}});
         timer.spans.push_back({1, {b, timer.mark(stream)}});
     }
     stats->direct_jobs += 1;
     stats->model_bytes += (words_of(n + m - 1) + words_of(n) + words_of(m)) * 8;
+    return PA_OK;
+}
+
+pa_status Lane::direct_batch(Ctx* c, std::vector<DirectJob>& js, pa_stats* stats) {
+    DirectBatch plan;
+    const uint32_t count = (uint32_t)js.size();
+    if (count < 2 || direct_batch_plan(js.data(), count, &plan) != count) {
+        pa_status st = PA_OK;
+        for (size_t k = 0; k < js.size() && st == PA_OK; ++k)
+            st = direct(c, js[k].seed, js[k].key, js[k].n, js[k].m, js[k].out, false, stats);
+        return st;
+    }
+    const size_t bytes = count * sizeof(DirectJob);
+    pa_status st = direct_dev.ensure(c, bytes, stream);
+    if (st == PA_OK) st = direct_host.ensure(bytes);
+    if (st != PA_OK) return st;
+    memcpy(direct_host.ptr, js.data(), bytes);
+    if (hipMemcpyAsync(direct_dev.ptr, direct_host.ptr, bytes, hipMemcpyHostToDevice, stream) != hipSuccess)
+        return PA_EDEVICE;
+    if (launch_direct_batch(plan, (const DirectJob*)direct_dev.ptr, count, stream, &stats->launches)) return PA_EDEVICE;
+    stats->direct_jobs += count;
+    for (const DirectJob& j : js) stats->model_bytes += (words_of(j.n + j.m - 1) + words_of(j.n) + words_of(j.m)) * 8;
     return PA_OK;
 }
 
@@ -901,7 +924,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         for (uint64_t i = 0; i < count; ++i) {
             TilePlan p;
             if (!c->plan_cached(ns[i], ms[i], policy, &p)) return PA_EINVAL;
-            is_direct[i] = choose_direct(flags, ns[i], ms[i], cm, p);
+            is_direct[i] = choose_direct_shared(flags, ns[i], ms[i], cm, p);
             if (!is_direct[i]) {
                 fidx.push_back(i);
                 fns.push_back(ns[i]);
@@ -991,13 +1014,15 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
     // direct jobs on the context's stream, beside the side streams' groups
     pa_stats dst{};
     const size_t ndirect = (size_t)std::count(is_direct.begin(), is_direct.end(), (char)1);
-    for (uint64_t i = 0; i < count && s == PA_OK; ++i) {
-        if (!is_direct[i]) continue;
-        const pa_status ds = ln.direct(c, all[i].seed, all[i].key, all[i].n, all[i].m, all[i].out, false, &dst);
-        if (ds != PA_OK) {
-            status[i] = ds;
-            s = ds;
-        }
+    if (ndirect) {
+        std::vector<DirectJob> dj;
+        dj.reserve(ndirect);
+        for (uint64_t i = 0; i < count; ++i)
+            if (is_direct[i]) dj.push_back(DirectJob{all[i].seed, all[i].key, all[i].out, all[i].n, all[i].m, 0, 0, 0, 0});
+        s = ln.direct_batch(c, dj, &dst);
+        if (s != PA_OK)
+            for (uint64_t i = 0; i < count; ++i)
+                if (is_direct[i]) status[i] = s;
     }
     bool stop = s != PA_OK;
     std::vector<size_t> order(groups.size());

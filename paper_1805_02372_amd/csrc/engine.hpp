@@ -12,6 +12,7 @@
 #include <tuple>
 #include <vector>
 
+#include "direct.hpp"
 #include "pa.h"
 #include "pa_internal.hpp"
 #include "planner.hpp"
@@ -91,7 +92,9 @@ struct Lane {
     bool own_stream = false;
     uint64_t cap = 0;     // workspace cap in bytes (0: the context budget)
     DevBuf ws, part, meta, jobs_dev, io;
-    DevBuf aux;           // direct path: reversed key, selected indices and bits
+    DevBuf aux;           // pa_hash_select: reversed key, indices and bits
+    DevBuf direct_dev;    // descriptors of a batch of direct jobs
+    HostBuf direct_host;
     HostBuf meta_host, jobs_host;
     HostBuf io_host;      // pinned staging of host inputs and outputs
     PassTimer timer;
@@ -118,6 +121,8 @@ struct Lane {
     // written completely.  Asynchronous on this lane's stream.
     pa_status direct(Ctx* c, const uint64_t* seed, const uint64_t* key, uint64_t n, uint64_t m, uint64_t* out,
                      bool timing, pa_stats* stats);
+    // The same for several jobs (seed, key, out, n, m set) in shared launches.
+    pa_status direct_batch(Ctx* c, std::vector<DirectJob>& js, pa_stats* stats);
 };
 
 // GPU resources of a block stream (pa_stream_*): its lane, a copy stream and

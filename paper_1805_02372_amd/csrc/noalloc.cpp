@@ -5,8 +5,8 @@
 // library runs on holds its own copy until the process ends):
 //
 //   [0, 132 MiB)            tile workspace (pass 1 -> 2 -> 3: two FP32 tiles
-//                           of 2^23 points with their 2 MiB bit planes), or
-//                           the reversed key of the direct product
+//                           of 2^23 points with their 2 MiB bit planes); the
+//                           direct product needs none of it
 //   + 512 KiB               per-tile partial key weights (pass 1 -> 2)
 //   + 256 KiB               per-tile certificates (at most 16384 tiles)
 //   + 8 x 512 KiB           twiddle tables of up to 8 length classes
@@ -86,7 +86,8 @@ pa_status noalloc_setup(int device) {
     d.ptr = (unsigned char*)p;
     Lane& ln = d.lane;
     fixed_view(&ln.ws, d.ptr, kWsBytes);
-    fixed_view(&ln.aux, d.ptr, kWsBytes);   // the direct path uses no tile workspace
+    fixed_view(&ln.aux, nullptr, 0);        // pa_hash_select only
+    fixed_view(&ln.direct_dev, nullptr, 0); // batches only
     fixed_view(&ln.part, d.ptr + kWsBytes, kPartBytes);
     fixed_view(&ln.meta, d.ptr + kWsBytes + kPartBytes, kMetaBytes);
     fixed_view(&ln.jobs_dev, nullptr, 0);   // one job per call: descriptors go by value
@@ -95,6 +96,7 @@ pa_status noalloc_setup(int device) {
     ln.meta_host.bytes = kMetaBytes;
     ln.meta_host.fixed = true;
     ln.jobs_host.fixed = true;
+    ln.direct_host.fixed = true;
     ln.static_tables = true;
     d.ready = true;
     return PA_OK;

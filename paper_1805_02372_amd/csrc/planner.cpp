@@ -208,9 +208,9 @@ double rigorous_bound(int prec, uint64_t L, uint64_t Bi, uint64_t Bo) {
 
 CostModel::CostModel() {
     launch_s = 12e-6;
-    // two VALU operations per output and key word at half the vector rate
-    // (256 CUs x 64 lanes x 2.4 GHz)
-    direct_s = 1.0e-13;
+    // 32 bit products on the matrix cores at 2.9e15 per second (measured on
+    // MI355X at n = 12,345,679, m = 20,000)
+    direct_s = 1.1e-14;
     direct_launch_s = 12e-6;
     for (int p = 0; p < 3; ++p)
         for (int id = 0; id < 64; ++id) {
@@ -321,13 +321,20 @@ const CostModel& default_cost_model() {
 
 double direct_cost(uint64_t n, uint64_t m, const CostModel& cm) {
     const double outs = (double)(ceil_div(m, 256) * 256), words = (double)(ceil_div(ceil_div(n, 32), 4) * 4);
-    return cm.direct_launch_s + cm.direct_s * outs * words;
+    return 1.1 * (cm.direct_launch_s + cm.direct_s * outs * words);
 }
 
 bool choose_direct(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft) {
     const uint32_t p = flags & PA_PREC_MASK;
     if (p == PA_PREC_DIRECT) return true;
     return p == PA_PREC_AUTO && direct_cost(n, m, cm) < fft.cost;
+}
+
+bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft) {
+    const uint32_t p = flags & PA_PREC_MASK;
+    if (p == PA_PREC_DIRECT) return true;
+    return p == PA_PREC_AUTO &&
+           2.0 * (direct_cost(n, m, cm) - 1.1 * cm.direct_launch_s) < fft.cost - cm.first(fft.prec, fft.cls);
 }
 
 bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out) {

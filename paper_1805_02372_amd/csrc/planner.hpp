@@ -42,7 +42,7 @@ struct CostModel {
     double first_s[3][64];  // extra cost of a launch (its first tile)
     double launch_s;        // launch cost of a class without its own first_s
     double direct_s;        // direct GF(2) path: seconds per output per 32-bit key word
-    double direct_launch_s; // direct GF(2) path: fixed cost of a job (its two launches)
+    double direct_launch_s; // direct GF(2) path: fixed cost of a job (its launches)
     CostModel();
     double tile(int prec, int cls) const;
     double first(int prec, int cls) const;
@@ -86,13 +86,23 @@ double error_kappa();
 // certificate (half the rounding margin of 0.5).
 constexpr double kPlanErrorLimit = 0.25;
 
-// Modeled time of the direct GF(2) path for one job: outputs are processed in
-// blocks of 256, each against ceil(n/32) key words (rounded up to 4).
+// Modeled time of the direct GF(2) path for one job: a fixed cost and a cost per
+// output (in blocks of 256) and key word (ceil(n/32), rounded up to 4), plus 10%
+// so that near-ties within the noise of the measured costs stay with the FFT
+// (measured on MI355X at n = 10^6: m = 50,000 direct 40 us, FFT 57; m = 100,000
+// 55 and 57; m = 200,000 84 and 64).
 double direct_cost(uint64_t n, uint64_t m, const CostModel& cm);
 // Whether the precision bits of `flags` put job (n, m) on the direct path:
 // always for PA_PREC_DIRECT; for PA_PREC_AUTO when the direct path is modeled
 // cheaper than the FFT plan `fft`.
 bool choose_direct(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft);
+
+// The same for a job of a batch or a serving launch, where both paths share
+// their launches with other jobs: the costs beyond the launches are compared.
+// The direct path has to be modeled twice as fast: a class's marginal tile cost
+// is measured with 16 tiles per launch, and larger launches fill the device
+// better.
+bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft);
 
 // Best (Bi, Bo) for job (n, m) at a fixed class; false if impossible.
 bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out);

@@ -77,7 +77,7 @@ static bool request_direct(Ctx* c, uint64_t n, uint64_t m) {
         std::lock_guard<std::mutex> pl(c->plan_mu);
         cm = c->cost;
     }
-    return choose_direct(PA_PREC_AUTO, n, m, cm, p);
+    return choose_direct_shared(PA_PREC_AUTO, n, m, cm, p);
 }
 
 void Ctx::serve_loop() {
@@ -146,7 +146,7 @@ void Ctx::serve_loop() {
                 int cls = 0;
                 uint64_t b;
                 if (request_direct(this, r->n, r->m)) {
-                    b = bmin = ((r->n + 127) / 128) * 16;   // the reversed key
+                    b = bmin = ((r->n + 127) / 128) * 16;   // its key
                 } else {
                     b = request_bytes(this, r->n, r->m, &bmin, &cls);
                 }
@@ -175,13 +175,13 @@ void Ctx::serve_loop() {
             }
             lk.unlock();
             if (cls0 == 0) {
-                // direct products, one after another on the lane's stream
+                // direct products, in shared launches
                 Lane& ln = lanes[i];
                 lane_stats[i] = pa_stats{};
-                pa_status s = PA_OK;
-                for (size_t k = 0; k < batch.size() && s == PA_OK; ++k)
-                    s = ln.direct(this, batch[k]->seed, batch[k]->key, ns[k], ms[k], batch[k]->out, false,
-                                  &lane_stats[i]);
+                std::vector<DirectJob> dj(batch.size());
+                for (size_t k = 0; k < batch.size(); ++k)
+                    dj[k] = DirectJob{batch[k]->seed, batch[k]->key, batch[k]->out, ns[k], ms[k], 0, 0, 0, 0};
+                pa_status s = ln.direct_batch(this, dj, &lane_stats[i]);
                 ln.jobs.clear();
                 ln.total_tiles = 0;
                 if (s == PA_OK && !ln.done && hipEventCreateWithFlags(&ln.done, hipEventDisableTiming) != hipSuccess)

@@ -67,8 +67,9 @@ static pa_status time_launch(Ctx* c, int prec, int k, const TilePlan& p, int cou
     return PA_OK;
 }
 
-// Per class: kernel time of one launch with 1 tile (T1) and with 4 tiles (T4);
-// the marginal tile cost (T4 - T1) / 3 goes to the class's tile_s, the rest of
+// Per class: kernel time of one launch with 1 tile (T1) and with N tiles (TN, N =
+// 4, or 16 up to 2^20 points, where 4 tiles still leave the device idle); the
+// marginal tile cost (TN - T1) / (N - 1) goes to the class's tile_s, the rest of
 // T1 (ramp-up and tail of the launch, and what one tile leaves of the device
 // idle) to its first_s; the median of the latter is the launch cost of the
 // direct path.
@@ -83,7 +84,7 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
         default: return PA_EINVAL;
     }
     if (reps < 1) reps = 1;
-    constexpr int kMany = 4;
+    constexpr int kMany = 4;   // tiles of the longer launch from 2^20 points on
     const uint64_t maxL = 1ull << 24;
     // synthetic job: n = L/2, m = L/2 + 1 fills one tile of class L exactly
     const uint64_t words = (maxL + 64) / 64 + 2, out_words = maxL / 2 / 64 + 2;
@@ -114,25 +115,28 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
             const uint64_t L = class_len(k);
             TilePlan p;
             if (!plan_at_class(L / 2, L / 2 + 1, prec, k, cm, &p) || p.tiles() != 1) continue;
-            double t1 = 0, t4 = 0;
-            st = time_launch(c, prec, k, p, 1, dseed, dkey, douts, out_words, reps, &t1);
-            if (st == PA_OK) st = time_launch(c, prec, k, p, kMany, dseed, dkey, douts, out_words, reps, &t4);
+            double t1 = 0, tn = 0;
+            const int many = L <= (1ull << 20) ? 4 * kMany : kMany;
+            const uint64_t stride = L / 2 / 64 + 2;   // many * stride <= kMany * out_words
+            st = time_launch(c, prec, k, p, 1, dseed, dkey, douts, stride, reps, &t1);
+            if (st == PA_OK) st = time_launch(c, prec, k, p, many, dseed, dkey, douts, stride, reps, &tn);
             if (st != PA_OK) {
                 buf.release(c);
                 return st;
             }
-            if (t1 >= 1e30 || t4 >= 1e30) continue;
-            const double marginal = std::max((t4 - t1) / (kMany - 1), 0.1 * t1);
+            if (t1 >= 1e30 || tn >= 1e30) continue;
+            const double marginal = std::max((tn - t1) / (many - 1), 0.01 * t1);
             cm.set(prec, k, marginal);
             cm.set_first(prec, k, std::max(t1 - marginal, 0.0));
             fixed.push_back(std::max(t1 - marginal, 0.0));
         }
     }
-    // direct path: the slope between two output lengths at n = 2^22 is the
-    // cost per output and 32-bit key word
+    // direct path: the slope between two output lengths at n = 2^20 (full tiles
+    // of 4096 outputs, the lengths between which AUTO changes paths) is the cost
+    // per output and 32-bit key word
     const uint32_t pbits = flags & PA_PREC_MASK;
     if (pbits == PA_PREC_AUTO || pbits == PA_PREC_DIRECT) {
-        const uint64_t n = 1ull << 22, ms[2] = {1024, 4096};
+        const uint64_t n = 1ull << 20, ms[2] = {4096, 98304};
         double t[2] = {1e30, 1e30};
         for (int q = 0; q < 2 && st == PA_OK; ++q)
             for (int r = 0; r <= reps && st == PA_OK; ++r) {
@@ -141,7 +145,7 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
                 st = c->main.direct(c, dseed, dkey, n, ms[q], douts, true, &ps);
                 if (st == PA_OK && hipStreamSynchronize(c->main.stream) != hipSuccess) st = PA_EDEVICE;
                 c->main.timer.collect(ps.ms_pass);
-                const double ms = ps.ms_pass[0] + ps.ms_pass[1];   // prep and product kernels
+                const double ms = ps.ms_pass[0] + ps.ms_pass[1];   // clearing and product kernels
                 if (r > 0 && ms > 0) t[q] = std::min(t[q], ms * 1e-3);
             }
         if (st != PA_OK) {

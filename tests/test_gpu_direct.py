@@ -208,3 +208,40 @@ def test_tune_measures_direct_cost(pa, tmp_path):
             pa.pa_destroy(c2)
     finally:
         pa.pa_destroy(c)
+
+
+# tile edges of the matrix-core product (1024, 2048 and 4096 outputs per tile,
+# 64 per word) and of its key split (one workgroup up to 224 words, then several)
+EDGES = [(n, m) for m in (63, 1023, 1025, 2049, 4095, 4097, 9000) for n in (33, 4000, 5153, 7168, 200_001)]
+
+
+@pytest.mark.parametrize("n,m", EDGES)
+def test_direct_tile_edges(pa, ctx, n, m):
+    """Exact against the oracle; the words after the output stay untouched."""
+    from gpu_util import to_dev, from_dev, empty_dev, describe
+    p = synth.random_problem(np.random.default_rng(n + 31 * m), n, m)
+    words = synth.words_for(m)
+    out = empty_dev(words + 8)
+    assert pa.pa_hash(ctx, to_dev(p.seed), n, m, to_dev(p.key), out, pa.PA_PREC_DIRECT) == pa.PA_OK
+    y = from_dev(out)
+    ref = oracle.hash_words(p.seed, n, m, p.key)
+    assert np.array_equal(y[:words], ref), describe(y[:words], ref, m)
+    assert np.all(y[words:] == np.uint64(0xFFFFFFFFFFFFFFFF))
+
+
+def test_direct_batch_of_mixed_widths(pa, ctx):
+    """One batch over all tile widths and key splits, ragged sizes: the jobs
+    share their launches and each equals the oracle."""
+    import torch
+    from gpu_util import from_dev
+    rng = np.random.default_rng(46)
+    probs = [synth.random_problem(rng, n, m) for n, m in EDGES + [(1, 1), (1, 30_000), (900_000, 5)]]
+    dev = [_dev_job(p) for p in probs]
+    st, per = pa.pa_hash_batch(ctx, dev, pa.PA_PREC_DIRECT)
+    torch.cuda.synchronize()
+    assert st == pa.PA_OK and all(x == pa.PA_OK for x in per)
+    s = pa.pa_last_stats(ctx)
+    assert s["direct_jobs"] == len(probs) and s["launches"] <= 4, s
+    for p, d in zip(probs, dev):
+        assert np.array_equal(from_dev(d[2])[: synth.words_for(p.m)],
+                              oracle.hash_words(p.seed, p.n, p.m, p.key)), (p.n, p.m)
