@@ -42,17 +42,27 @@ __device__ __forceinline__ JobDesc find_job(const JobTable& jt, uint32_t t) {
     return jt.many[lo];
 }
 
+__device__ __forceinline__ JobDesc find_group_job(const JobTable& jt, uint32_t g) {
+    if (jt.njobs == 0) return jt.one;
+    uint32_t lo = 0, hi = jt.njobs - 1;
+    while (lo < hi) {  // last job with group_begin <= g
+        uint32_t mid = (lo + hi + 1) >> 1;
+        if (jt.many[mid].group_begin <= g) lo = mid; else hi = mid - 1;
+    }
+    return jt.many[lo];
+}
+
 struct TileGeo {
     uint64_t j0, bi, i0, bo, sigma;
     uint64_t* dst;        // output words of this tile's window (bit 0 = output i0)
     uint64_t dst_words;
-    bool accumulate;      // several key chunks: XOR into dst (cleared by the chunk-0 tile)
+    bool accumulate;      // several chunk groups: XOR into dst (cleared by the chunk-0 tile)
     bool clears;          // this tile is chunk 0 of an accumulated window
 };
 
-__device__ __forceinline__ TileGeo tile_geo(const JobDesc& jd, uint32_t lt) {
+// Chunk b of window o.
+__device__ __forceinline__ TileGeo chunk_geo(const JobDesc& jd, uint32_t b, uint32_t o) {
     TileGeo g;
-    const uint32_t b = lt / jd.nouts, o = lt % jd.nouts;
     const uint64_t hi = jd.n - (uint64_t)b * jd.Bi;
     const uint64_t lo = hi > jd.Bi ? hi - jd.Bi : 0;
     g.j0 = lo;
@@ -63,9 +73,34 @@ __device__ __forceinline__ TileGeo tile_geo(const JobDesc& jd, uint32_t lt) {
     g.sigma = g.i0 + jd.n - hi;
     g.dst = jd.out + (g.i0 >> 6);
     g.dst_words = (g.bo + 63) >> 6;
-    g.accumulate = jd.nchunks > 1;
+    g.accumulate = jd.nchunks > jd.cgroup;
     g.clears = g.accumulate && b == 0 && !jd.no_clear;
     return g;
+}
+// Local tile lt: chunk group q holds the tiles of its window 0, window 1, ...
+// (one window: tile = chunk, without the divisions).
+__device__ __forceinline__ TileGeo tile_geo(const JobDesc& jd, uint32_t lt) {
+    uint32_t b = lt, o = 0;
+    if (jd.nouts > 1) {
+        const uint32_t per = jd.nouts * jd.cgroup, q = lt / per, rem = lt - q * per;
+        const uint32_t left = jd.nchunks - q * jd.cgroup, gs = left < jd.cgroup ? left : jd.cgroup;
+        o = gs > 1 ? rem / gs : rem;
+        b = q * jd.cgroup + (rem - o * gs);
+    }
+    return chunk_geo(jd, b, o);
+}
+// Local group lg: its window's geometry (that of its first chunk), its first
+// local tile and its number of tiles.
+__device__ __forceinline__ TileGeo group_geo(const JobDesc& jd, uint32_t lg, uint32_t* first, uint32_t* gs) {
+    uint32_t q = lg, o = 0;
+    if (jd.nouts > 1) {
+        q = lg / jd.nouts;
+        o = lg - q * jd.nouts;
+    }
+    const uint32_t left = jd.nchunks - q * jd.cgroup;
+    *gs = left < jd.cgroup ? left : jd.cgroup;
+    *first = q * jd.nouts * jd.cgroup + o * *gs;
+    return chunk_geo(jd, q * jd.cgroup, o);
 }
 
 // Pass 1 of a chunk-0 tile of an accumulated job clears the window's words;
@@ -77,7 +112,7 @@ __device__ __forceinline__ void clear_window(const TileGeo& g, uint32_t part, ui
 
 // Write B output bits at bit offset `off` (a multiple of B) of the window:
 // a plain store, or an XOR into the 32-bit word holding them when the job
-// accumulates chunks (zero groups are skipped).
+// accumulates chunk groups (zero bit groups are skipped).
 template <int B>
 __device__ __forceinline__ void put_bits(const TileGeo& g, uint64_t off, uint32_t bits) {
     static_assert(B == 8 || B == 16 || B == 32, "bit group");
@@ -129,16 +164,18 @@ template <int A, int B> constexpr int cmax() { return A > B ? A : B; }
 
 // ------------------------------------------------------------------ pass 1
 // NT2: length of the root table tw of the column transforms (a multiple of N2).
-// FP64 column passes take the split exchange where their complex buffer
-// would leave room for one workgroup per compute unit, and their registers
-// are budgeted for two workgroups (the mixed-radix columns of 1280 to 1792
-// points, no spills).  FP32 column workgroups of eight and more waves then
-// get 128 registers or fewer and spill: measured slower.
+// Column passes take the split exchange where their complex buffer does not
+// fit the LDS (columns of 2560 to 3584 points), and in FP64 also where it would
+// leave room for one workgroup per compute unit; the registers of the latter
+// are budgeted for two workgroups (no spills).  FP32 column workgroups of eight
+// and more waves would then get 128 registers or fewer and spill: measured
+// slower.
 template <typename T, int N, int F> constexpr bool column_split() {
-    return split_exchange<T, N, F>() && sizeof(T) == 8;
+    return (size_t)lds_slots<N, F>() * sizeof(cx<T>) > 150000 || (split_exchange<T, N, F>() && sizeof(T) == 8);
 }
 template <typename T, int N, int F, int THREADS> constexpr int column_waves_per_eu() {
-    return column_split<T, N, F>() ? (2 * THREADS / 64 + 3) / 4 : 1;
+    constexpr int wgs = (size_t)lds_slots<N, F>() * sizeof(T) > 81920 ? 1 : 2;
+    return column_split<T, N, F>() ? (wgs * THREADS / 64 + 3) / 4 : 1;
 }
 template <typename T, int N1, int N2, int B, int R, int NT2>
 __global__ void __launch_bounds__(B * (N2 / R))
@@ -241,6 +278,8 @@ __device__ __forceinline__ void mirror(cx<T> (&b)[R], cx<T>* lds, int j) {
 }
 
 // NT1: length of the root table tw of the row transforms (a multiple of N1).
+// The groups of these classes are single tiles (summing several products here
+// took 260-510 registers).
 template <typename T, int N1, int N2, int R, int NCB1, int NT1>
 __global__ void __launch_bounds__(N1 / R)
 k_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
@@ -339,11 +378,12 @@ k_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta, 
     __shared__ cx<T> lds[XSPLIT ? (lds_slots<N2h, B>() + 1) / 2 : lds_slots<N2h, B>()];
     __shared__ uint32_t s_res, s_abs, s_bad;
 
-    const uint32_t lt = blockIdx.x / NCB;
+    const uint32_t t = jt.group0 + blockIdx.x / NCB;   // group
     const uint32_t cb = blockIdx.x % NCB;
-    const uint32_t t = jt.tile0 + lt;
-    const JobDesc jd = find_job(jt, t);
-    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+    const JobDesc jd = find_group_job(jt, t);
+    uint32_t first, gs;
+    const TileGeo g = group_geo(jd, t - jd.group_begin, &first, &gs);
+    const uint32_t lt = jd.tile_begin + first - jt.tile0;
     const cx<T>* __restrict__ V = ws + (size_t)lt * L;
     const int tid = threadIdx.x, f = tid % B, j = tid / B;
     const uint32_t t1 = cb * B + f;
@@ -448,7 +488,7 @@ struct ClassImpl {
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     static int pass3(const JobTable& jt, void* ws, uint32_t*, TileMeta* meta, const Tables& tb, void* stream) {
-        dim3 grid(jt.ntiles * (N1 / B3)), block(B3 * (N2 / 2 / RC));
+        dim3 grid(jt.ngroups * (N1 / B3)), block(B3 * (N2 / 2 / RC));
         hipLaunchKernelGGL((k_pass3<T, N1, N2, B3, RC, NT2>), grid, block, 0, (hipStream_t)stream, jt,
                            (const cx<T>*)ws, meta, (const cx<T>*)tb.tw2);
         return hipGetLastError() == hipSuccess ? 0 : -1;

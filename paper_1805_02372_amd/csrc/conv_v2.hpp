@@ -22,8 +22,6 @@
 
 namespace pa {
 
-constexpr int kN1 = 8192;  // row length of the long classes
-
 template <typename T, int N2> struct P1Geom {
     static constexpr int W = N2 > 1024 ? N2 / 1024 : 1;    // waves per column
     static constexpr int M = N2 > 1024 ? 1024 : N2;        // wave transform size
@@ -94,12 +92,12 @@ __device__ __forceinline__ uint32_t xcd_block() {
 // key plane holds the placed key bits at positions 8 cb + 8192 r .. + 7 (bit
 // q: position + q), the seed plane the seed bits there (zero from the window
 // end on).  Pass 1 then reads n2 contiguous bytes of each.
-template <int N2> struct BitPlanes {
-    static constexpr size_t kPlane = (size_t)N2 * (kN1 / 8);
+template <int N1, int N2> struct BitPlanes {
+    static constexpr size_t kPlane = (size_t)N2 * (N1 / 8);
     static constexpr size_t kTile = 2 * kPlane;   // key plane, then seed plane
     template <typename T>
     __device__ static const uint8_t* key(const cx<T>* ws, uint32_t ntiles, uint32_t lt) {
-        return reinterpret_cast<const uint8_t*>(ws + (size_t)ntiles * ((size_t)kN1 * N2)) + (size_t)lt * kTile;
+        return reinterpret_cast<const uint8_t*>(ws + (size_t)ntiles * ((size_t)N1 * N2)) + (size_t)lt * kTile;
     }
 };
 
@@ -179,12 +177,12 @@ constexpr int kBitsRows = 128, kBitsCols = 8;
 __device__ __forceinline__ int bits_slot(int r, int w) {
     return (r ^ ((r >> 3) & 3)) * kBitsCols + (w ^ ((r >> 3) & 7));
 }
-template <int N2>
+template <int N1, int N2>
 __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict__ planes) {
     constexpr int R = kBitsRows, WC = kBitsCols, RPL = R * WC / 256;   // rows per lane
-    constexpr int NRB = N2 / R, NWB = kN1 / 64 / WC;
-    constexpr uint32_t L = (uint32_t)kN1 * N2;
-    static_assert(N2 % R == 0 && (kN1 / 64) % WC == 0 && RPL == 4 && WC * 16 * 2 == 256, "workgroup block");
+    constexpr int NRB = N2 / R, NWB = N1 / 64 / WC;
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    static_assert(N2 % R == 0 && (N1 / 64) % WC == 0 && RPL == 4 && WC * 16 * 2 == 256, "workgroup block");
     __shared__ uint64_t wbits[2][R * WC];   // key words, seed words
     const uint32_t b = blockIdx.x;
     const uint32_t lt = b / (NRB * NWB), rem = b % (NRB * NWB);
@@ -203,7 +201,7 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
 #pragma unroll
         for (int q = 0; q < RPL; ++q) {
             const int rl = tid / WC + (256 / WC) * q;
-            const uint32_t s0 = wc * 64 + (uint32_t)kN1 * (rb * R + (uint32_t)rl);
+            const uint32_t s0 = wc * 64 + (uint32_t)N1 * (rb * R + (uint32_t)rl);
             pk[q] = placed_key64(g.j0, bi, L, s0);
             const uint32_t nv = s0 < win ? ((win - s0) < 64u ? (win - s0) : 64u) : 0u;
             se[q] = ext64(g.sigma + s0, nv);
@@ -229,21 +227,21 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = wbits[pl][bits_slot(8 * p + i, wl)];
     transpose8x8(x);
-    uint8_t* dst = planes + (size_t)lt * BitPlanes<N2>::kTile + (size_t)pl * BitPlanes<N2>::kPlane +
+    uint8_t* dst = planes + (size_t)lt * BitPlanes<N1, N2>::kTile + (size_t)pl * BitPlanes<N1, N2>::kPlane +
                    (size_t)((wb * WC + (uint32_t)wl) * 8) * N2 + rb * R + 8 * p;
 #pragma unroll
     for (int c = 0; c < 8; ++c) *reinterpret_cast<uint64_t*>(dst + (size_t)c * N2) = x[c];
 }
 
-template <typename T, int N2>
+template <typename T, int N1, int N2>
 __global__ void __launch_bounds__((P1Geom<T, N2>::THREADS))
 k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
          const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
          int fshift) {
     using Gm = P1Geom<T, N2>;
     constexpr int C = Gm::C, G = Gm::G, W = Gm::W, M = Gm::M, NJ = M / 16;
-    constexpr uint32_t L = (uint32_t)kN1 * N2;
-    constexpr int NCB = kN1 / C;
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int NCB = N1 / C;
     constexpr int SLOTS = (Gm::WAVES * kWaveSlots > N2 * C) ? Gm::WAVES * kWaveSlots : N2 * C;
     static_assert(2 * N2 * sizeof(uint64_t) <= SLOTS * sizeof(cx<T>), "bit rows fit the LDS union");
     static_assert(G * 16 * sizeof(Root64) <= kWaveSlots * sizeof(cx<T>), "twiddle factors fit a wave region");
@@ -272,7 +270,7 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
     uint64_t kb[RPT], sb[RPT];
     constexpr bool kPlanes = Gm::kPlanes;
     const uint8_t* kp = nullptr;
-    if constexpr (kPlanes) kp = BitPlanes<N2>::key(ws, jt.ntiles, lt) + (size_t)cb * N2;
+    if constexpr (kPlanes) kp = BitPlanes<N1, N2>::key(ws, jt.ntiles, lt) + (size_t)cb * N2;
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int r = tid + q * Gm::THREADS;
@@ -281,9 +279,9 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
         if (r < N2) {
             if constexpr (kPlanes) {
                 kb[q] = kp[r];
-                sb[q] = kp[BitPlanes<N2>::kPlane + r];
+                sb[q] = kp[BitPlanes<N1, N2>::kPlane + r];
             } else {
-                const uint32_t s0 = cb * C + (uint32_t)kN1 * (uint32_t)r;
+                const uint32_t s0 = cb * C + (uint32_t)N1 * (uint32_t)r;
                 kb[q] = placed_key_bits<C>(jd.key, g.j0, bi, L, s0);
                 const uint32_t nv = s0 < win ? ((win - s0) < (uint32_t)C ? (win - s0) : (uint32_t)C) : 0u;
                 sb[q] = extract_bits(jd.seed, g.sigma + s0, nv);
@@ -338,7 +336,7 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
         const uint32_t kw = kb32[2 * r], sw = sb32[2 * r];
         const T xb = ((kw >> fs) & 1u) ? T(1) : T(0);
         const T sv = ((sw >> fs) & 1u) ? T(1) : T(-1);
-        const T wb = (t1 + (uint32_t)kN1 * (uint32_t)r < win) ? sv : T(0);
+        const T wb = (t1 + (uint32_t)N1 * (uint32_t)r < win) ? sv : T(0);
         return cx<T>{xb, wb};
     };
     cx<T> v[16];
@@ -351,7 +349,7 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
             // radix-2 split of the 2048-point column: half ka, twiddle w_2048^{e ka}
             const cx<T> a = z(e), b = z(e + 1024);
             if (ka == 0) v[i] = a + b;
-            else v[i] = cmul(a - b, tw[e * (kN1 / 2048)]);
+            else v[i] = cmul(a - b, tw[e * (N1 / 2048)]);
         }
     }
     __syncthreads();  // bits consumed; LDS becomes wave regions
@@ -394,7 +392,7 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
 #pragma unroll
     for (int q = 0; q < SPT; ++q) {
         const int idx = tid + q * Gm::THREADS;
-        Y[(size_t)(idx / C) * kN1 + cb * C + (idx % C)] = o[q];
+        Y[(size_t)(idx / C) * N1 + cb * C + (idx % C)] = o[q];
     }
     if (tid == 0) part[(size_t)lt * NCB + cb] = wsum;
 }
@@ -413,13 +411,13 @@ struct P1hArgs {
     uint32_t lt, cb, ntiles;
 };
 
-template <typename T, int KA>
+template <typename T, int N1, int KA>
 __device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __restrict__ ws, cx<T>* lds,
                                                     const cx<T>* st, const cx<T>* __restrict__ tw,
                                                     const cx<double>* __restrict__ fa64,
                                                     const cx<double>* __restrict__ fb64, int fshift) {
     constexpr int N2 = 2048, M = 1024, C = 8, THREADS = 512, NJ = M / 16;
-    constexpr uint32_t L = (uint32_t)kN1 * N2;
+    constexpr uint32_t L = (uint32_t)N1 * N2;
     const int tid = threadIdx.x, wv = tid >> 6, j = tid & 63;
     const TileGeo& g = A.g;
     const uint32_t bi = (uint32_t)g.bi, win = (uint32_t)(g.bi + g.bo - 1);
@@ -428,10 +426,10 @@ __device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __r
     uint16_t* fld = reinterpret_cast<uint16_t*>(lds);   // per row: key bits (low byte), seed bits (high byte)
     uint32_t pc = 0;
     __syncthreads();   // the previous half's stores have read the LDS
-    const uint8_t* kp = BitPlanes<N2>::key(ws, A.ntiles, A.lt) + (size_t)A.cb * N2;
+    const uint8_t* kp = BitPlanes<N1, N2>::key(ws, A.ntiles, A.lt) + (size_t)A.cb * N2;
     for (int r = tid; r < N2; r += THREADS) {
         const uint32_t kb = kp[r];
-        const uint32_t sb = kp[BitPlanes<N2>::kPlane + r];
+        const uint32_t sb = kp[BitPlanes<N1, N2>::kPlane + r];
         fld[r] = (uint16_t)(kb | (sb << 8));
         pc += (uint32_t)__popc(kb);
     }
@@ -444,7 +442,7 @@ __device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __r
         const uint32_t w = fld[r];
         const T xb = ((w >> f) & 1u) ? T(1) : T(0);
         const T sv = ((w >> (8 + f)) & 1u) ? T(1) : T(-1);
-        return cx<T>{xb, (t1 + (uint32_t)kN1 * (uint32_t)r < win) ? sv : T(0)};
+        return cx<T>{xb, (t1 + (uint32_t)N1 * (uint32_t)r < win) ? sv : T(0)};
     };
     cx<T> v[16];
 #pragma unroll
@@ -452,7 +450,7 @@ __device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __r
         const int e = j + i * NJ;
         const cx<T> a = z(e), b = z(e + M);
         if constexpr (KA == 0) v[i] = a + b;
-        else v[i] = cmul(a - b, tw[e * (kN1 / N2)]);
+        else v[i] = cmul(a - b, tw[e * (N1 / N2)]);
     }
     __syncthreads();   // bits consumed; LDS becomes wave regions
     cx<T>* reg = lds + wv * kWaveSlots;
@@ -479,7 +477,7 @@ __device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __r
 #pragma unroll
     for (int q = 0; q < SPT; ++q) {
         const int idx = tid + q * THREADS;
-        Y[(size_t)(2 * (idx / C) + KA) * kN1 + A.cb * C + (idx % C)] = o[q];
+        Y[(size_t)(2 * (idx / C) + KA) * N1 + A.cb * C + (idx % C)] = o[q];
     }
     return pc;
 }
@@ -487,13 +485,13 @@ __device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __r
 // Each half in a workgroup of its own: logical block 2 b + KA
 // takes half KA of column block b (the two read the same bit words, through
 // the L2 of one XCD).  Half 0 clears the window and reports the weight.
-template <typename T>
+template <typename T, int N1>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 k2_pass1s(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
           const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
           int fshift) {
     constexpr int M = 1024, C = 8, THREADS = 512;
-    constexpr int NCB = kN1 / C;
+    constexpr int NCB = N1 / C;
     constexpr int SLOTS = 8 * kWaveSlots;
     static_assert(M * C <= SLOTS && 2048 * (int)sizeof(uint16_t) <= SLOTS * (int)sizeof(cx<T>), "LDS union");
     __shared__ __align__(16) cx<T> lds[SLOTS];
@@ -514,285 +512,314 @@ k2_pass1s(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, cons
     if (!second) clear_window(A.g, A.cb, NCB, tid, THREADS);
     wfft_load_lds<T, M>(st, stw, tid, THREADS);
     if (second) {
-        (void)pass1_half_body<T, 1>(A, ws, lds, st, tw, fa64, fb64, fshift);
+        (void)pass1_half_body<T, N1, 1>(A, ws, lds, st, tw, fa64, fb64, fshift);
         return;
     }
-    const uint32_t pc = pass1_half_body<T, 0>(A, ws, lds, st, tw, fa64, fb64, fshift);
+    const uint32_t pc = pass1_half_body<T, N1, 0>(A, ws, lds, st, tw, fa64, fb64, fshift);
     atomicAdd(&wsum, pc);
     __syncthreads();
     if (tid == 0) part[(size_t)A.lt * NCB + A.cb] = wsum;
 }
 
 // ------------------------------------------------------------------ pass 2
-// Shared memory of the row pass: the row exchange / wave regions, the stage
-// tables of the 1024-point transforms, and the first-stage twiddles
-// w_8192^{ka nb}, ka = 1..7: FP32 holds them all, t8[(ka-1) 1024 + nb]; FP64,
-// whose row region leaves no room for that, forms them as the product of two
-// short tables, w_8192^e = w8a[e >> 6] w8b[e & 63] (135.7 KB for FP32, 156 KB
-// for FP64).
-template <typename T> struct RowSmem {
-    static constexpr bool kLds = sizeof(T) == 4;   // the full first-stage table (FP32 only)
-    cx<T> data[8 * kWaveSlots];
-    cx<T> st[wfft_lds_entries(1024)];
-    cx<T> t8[kLds ? 7 * 1024 : 1];
-    cx<T> w8a[kLds ? 1 : 128];
-    cx<T> w8b[kLds ? 1 : 64];
+// Row pass.  A workgroup transforms rows of N1 points, PT per lane, in W =
+// N1 / (64 PT) waves: a radix-W stage across the waves (decimation in frequency,
+// registers only), one workgroup exchange, one transform of M = 64 PT points per
+// wave; the inverse runs the same steps in reverse.  Two workgroup barriers per
+// row transform.  Rows of 4096 take 8 points per lane (8 x 8 x 8 x 8: a mirror
+// pair and the group's sum are 48 registers per lane in FP32, so that two
+// workgroups of 8 waves share a CU); rows of 8192 take 16 (8 x 4 x 16 x 16).
+template <typename T, int N1> struct RowGeom {
+    static constexpr int PT = N1 >= 8192 ? 16 : 8;
+    static constexpr int W = N1 / (64 * PT), M = 64 * PT, S = PT / W, THREADS = N1 / PT;
+    static constexpr int SLOTS = M + M / (PT == 16 ? 16 : 8);   // LDS slots of a wave's region
+    static_assert(W == 8 && S * W == PT, "row geometry");
+    __device__ static __forceinline__ int slot(int e) { return PT == 16 ? e + (e >> 4) : e + (e >> 3); }
 };
 
-// FP32: thread tid writes t8 entries e = tid (mod 512) and the forward
-// transform's thread tid reads only such entries (nb = tid + 512 s), so the
-// first unit needs no barrier after this load; the stage tables are first
-// read after one.  FP64 reads w8a / w8b entries other threads wrote: the
-// kernel waits at a barrier after this load.
-template <typename T>
-__device__ __forceinline__ void row_smem_load(RowSmem<T>& S, const cx<T>* __restrict__ tw,
-                                              const cx<T>* __restrict__ stw, int tid) {
-    wfft_load_lds<T, 1024>(S.st, stw, tid, 512);
-    if constexpr (RowSmem<T>::kLds) {
-        for (int e = tid; e < 7 * 1024; e += 512) S.t8[e] = tw[(1 + e / 1024) * (e % 1024)];
-    } else {
-        if (tid < 128) S.w8a[tid] = tw[64 * tid];
-        if (tid < 64) S.w8b[tid] = tw[tid];
-    }
-}
+// A lane's points of one row.
+template <typename T, int N1> using RowVec = cx<T>[RowGeom<T, N1>::PT];
 
-// Last-stage twiddles of the 1024-point transform held in registers for the
-// whole row pass (FP32): w_1024^{l r}, r = 1..15.
-template <typename T> struct RowReg {
-    cx<T> tr[RowSmem<T>::kLds ? 15 : 1];
+// Shared memory: the row exchange / wave regions; rows of 4096 the second
+// stage's twiddles w_64^{k r} at st[8 (r - 1) + k]; rows of 8192 the stage tables
+// of the 1024-point transforms.
+template <typename T, int N1> struct RowSmem {
+    using G = RowGeom<T, N1>;
+    static_assert(G::PT == 8 || sizeof(T) == 4, "FP64 rows are 4096 points");
+    cx<T> data[G::W * G::SLOTS];
+    cx<T> st[G::PT == 16 ? wfft_lds_entries(1024) : 7 * 8];
 };
 
-// 1024-point wave transform of the row pass, stage tables from LDS (FP32:
-// the last stage's from registers)
-template <typename T, int DIR>
-__device__ __forceinline__ void row_wave_fft(cx<T> (&v)[16], cx<T>* __restrict__ reg, int l, const RowSmem<T>& S,
-                                             const RowReg<T>& R, const cx<T>* __restrict__ stw) {
-    (void)stw;
-    if constexpr (RowSmem<T>::kLds) wave_fft1024_lds_reg<T, DIR>(v, reg, l, S.st, R.tr);
-    else wave_fft_lds<T, DIR, 1024>(v, reg, l, S.st);
-}
+// Twiddles of a lane held in registers for the whole pass (both directions use
+// the same ones): first stage w_N1^{ka nb}, nb = tid + THREADS s, at tw1[s (W-1)
+// + ka - 1]; rows of 4096 also the last stage, w_512^{l r} at t3[r - 1].
+template <typename T, int N1> struct RowReg {
+    using G = RowGeom<T, N1>;
+    cx<T> tw1[G::S * (G::W - 1)];
+    cx<T> t3[G::PT == 8 ? 7 : 1];
+};
 
-// w_8192^{ka nb}, 1 <= ka < 8, nb < 1024
-template <typename T>
-__device__ __forceinline__ cx<T> w8192(const RowSmem<T>& S, const cx<T>* __restrict__ tw, int ka, int nb) {
-    if constexpr (RowSmem<T>::kLds) {
-        return S.t8[(ka - 1) * 1024 + nb];
+template <typename T, int N1>
+__device__ __forceinline__ void row_setup(RowSmem<T, N1>& S, RowReg<T, N1>& R, const cx<T>* __restrict__ tw,
+                                          const cx<T>* __restrict__ stw, int tid) {
+    using G = RowGeom<T, N1>;
+#pragma unroll
+    for (int s = 0; s < G::S; ++s)
+#pragma unroll
+        for (int ka = 1; ka < G::W; ++ka) R.tw1[s * (G::W - 1) + ka - 1] = tw[ka * (tid + G::THREADS * s)];
+    if constexpr (G::PT == 8) {
+        const int l = tid & 63;
+#pragma unroll
+        for (int r = 1; r < 8; ++r) R.t3[r - 1] = tw[l * r * (N1 / 512)];
+        if (tid < 56) S.st[tid] = tw[(tid & 7) * ((tid >> 3) + 1) * (N1 / 64)];
     } else {
-        const int e = ka * nb;   // < 7168
-        return cmul(S.w8a[e >> 6], S.w8b[e & 63]);
+        wfft_load_lds<T, 1024>(S.st, stw, tid, G::THREADS);
+    }
+    __syncthreads();
+}
+
+// Transform of M points by one wave, register i holding element l + 64 i before
+// and after; `reg` is the wave's own LDS region.  512 points: three Stockham
+// stages of radix 8 (wave_fft.hpp holds the 1024-point transform).
+template <typename T, int N1, int DIR>
+__device__ __forceinline__ void row_wave_fft(RowVec<T, N1>& v, cx<T>* __restrict__ reg, int l,
+                                             const RowSmem<T, N1>& S, const RowReg<T, N1>& R) {
+    if constexpr (RowGeom<T, N1>::PT == 16) {
+        wave_fft_lds<T, DIR, 1024>(v, reg, l, S.st);
+    } else {
+        dft8<DIR>(v);
+        wave_sync();
+        // span 1: butterfly l writes 8 l + r (slot 9 l + r); lanes read l + 64 i
+        cx<T>* __restrict__ w1 = reg + 9 * l;
+        cx<T>* __restrict__ rd = reg + l + (l >> 3);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) w1[r] = v[r];
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = rd[72 * i];
+#pragma unroll
+        for (int r = 1; r < 8; ++r) v[r] = twmul<DIR>(v[r], S.st[8 * (r - 1) + (l & 7)]);
+        dft8<DIR>(v);
+        wave_sync();
+        // span 8: butterfly l writes 64 (l / 8) + l mod 8 + 8 r
+        cx<T>* __restrict__ w2 = reg + 72 * (l >> 3) + (l & 7);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) w2[9 * r] = v[r];
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = rd[72 * i];
+#pragma unroll
+        for (int r = 1; r < 8; ++r) v[r] = twmul<DIR>(v[r], R.t3[r - 1]);
+        dft8<DIR>(v);
+        wave_sync();
     }
 }
 
-template <typename T>
-__device__ __forceinline__ void row_load(cx<T> (&a)[16], const cx<T>* __restrict__ row, int wv, int l) {
+// a[s W + na] = row[nb + M na], nb = tid + THREADS s
+template <typename T, int N1>
+__device__ __forceinline__ void row_load(RowVec<T, N1>& a, const cx<T>* __restrict__ row, int tid) {
+    using G = RowGeom<T, N1>;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int nb = wv * 64 + l + 512 * s;
+    for (int s = 0; s < G::S; ++s)
 #pragma unroll
-        for (int na = 0; na < 8; ++na) a[s * 8 + na] = row[nb + 1024 * na];
-    }
+        for (int na = 0; na < G::W; ++na) a[s * G::W + na] = row[tid + G::THREADS * s + G::M * na];
 }
 
-// Forward transform of one 8192-point row loaded by row_load (a is consumed).
-// Thread (wave w, lane l) ends with X[8 k_b + w] in register i, k_b = l + 64 i.
-template <typename T>
-__device__ __forceinline__ void row_forward(cx<T> (&a)[16], cx<T> (&X)[16], RowSmem<T>& S, const RowReg<T>& R,
-                                            int wv, int l, const cx<T>* __restrict__ tw,
-                                            const cx<T>* __restrict__ stw) {
-    constexpr int SS = kWaveSlots;
+// Forward transform of a row loaded by row_load: lane l of wave w ends with
+// X[W k_b + w] in register i, k_b = l + 64 i.
+template <typename T, int N1>
+__device__ __forceinline__ void row_forward(RowVec<T, N1>& a, RowSmem<T, N1>& S, const RowReg<T, N1>& R,
+                                            int tid) {
+    using G = RowGeom<T, N1>;
+    const int wv = tid >> 6, l = tid & 63;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int nb = wv * 64 + l + 512 * s;
-        dft8<-1>(&a[s * 8]);
+    for (int s = 0; s < G::S; ++s) {
+        dft<G::W, -1>(&a[s * G::W]);
 #pragma unroll
-        for (int ka = 1; ka < 8; ++ka) a[s * 8 + ka] = cmul(a[s * 8 + ka], w8192<T>(S, tw, ka, nb));
+        for (int ka = 1; ka < G::W; ++ka) a[s * G::W + ka] = cmul(a[s * G::W + ka], R.tw1[s * (G::W - 1) + ka - 1]);
     }
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int nb = wv * 64 + l + 512 * s;
+    for (int s = 0; s < G::S; ++s)
 #pragma unroll
-        for (int ka = 0; ka < 8; ++ka) S.data[ka * SS + wslot(nb)] = a[s * 8 + ka];
-    }
+        for (int ka = 0; ka < G::W; ++ka) S.data[ka * G::SLOTS + G::slot(tid + G::THREADS * s)] = a[s * G::W + ka];
     __syncthreads();
-    cx<T>* reg = S.data + wv * SS;
+    cx<T>* reg = S.data + wv * G::SLOTS;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) X[i] = reg[wslot(l + 64 * i)];
+    for (int i = 0; i < G::PT; ++i) a[i] = reg[G::slot(l) + G::slot(64) * i];
     wave_sync();
-    row_wave_fft<T, -1>(X, reg, l, S, R, stw);
+    row_wave_fft<T, N1, -1>(a, reg, l, S, R);
 }
 
-// Inverse transform of a row held as P[8 k_b + w] (register i, k_b = l + 64 i);
-// returns a[t_b + 1024 t_a] in a[s * 8 + t_a] for t_b = w * 64 + l + 512 s.
-template <typename T>
-__device__ __forceinline__ void row_inverse(cx<T> (&P)[16], cx<T> (&a)[16], RowSmem<T>& S, const RowReg<T>& R,
-                                            int wv, int l, const cx<T>* __restrict__ tw,
-                                            const cx<T>* __restrict__ stw) {
-    constexpr int SS = kWaveSlots;
-    cx<T>* reg = S.data + wv * SS;
+// Inverse transform of a row held as P[W k_b + w] (register i, k_b = l + 64 i);
+// ends with a[t_b + M t_a] in a[s W + t_a], t_b = tid + THREADS s.
+template <typename T, int N1>
+__device__ __forceinline__ void row_inverse(RowVec<T, N1>& a, RowSmem<T, N1>& S, const RowReg<T, N1>& R,
+                                            int tid) {
+    using G = RowGeom<T, N1>;
+    const int wv = tid >> 6, l = tid & 63;
+    cx<T>* reg = S.data + wv * G::SLOTS;
     __syncthreads();  // every wave is done with its region
-    row_wave_fft<T, +1>(P, reg, l, S, R, stw);
-    if (wv > 0) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) P[i] = cmulc(P[i], w8192<T>(S, tw, wv, l + 64 * i));
-    }
+    row_wave_fft<T, N1, +1>(a, reg, l, S, R);
     wave_sync();   // the wave's own region: no other wave uses it until the barrier below
 #pragma unroll
-    for (int i = 0; i < 16; ++i) reg[wslot(l + 64 * i)] = P[i];
+    for (int i = 0; i < G::PT; ++i) reg[G::slot(l) + G::slot(64) * i] = a[i];
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int tb = wv * 64 + l + 512 * s;
+    for (int s = 0; s < G::S; ++s) {
 #pragma unroll
-        for (int ka = 0; ka < 8; ++ka) a[s * 8 + ka] = S.data[ka * SS + wslot(tb)];
-        dft8<+1>(&a[s * 8]);
+        for (int ka = 0; ka < G::W; ++ka) a[s * G::W + ka] = S.data[ka * G::SLOTS + G::slot(tid + G::THREADS * s)];
+#pragma unroll
+        for (int ka = 1; ka < G::W; ++ka) a[s * G::W + ka] = cmulc(a[s * G::W + ka], R.tw1[s * (G::W - 1) + ka - 1]);
+        dft<G::W, +1>(&a[s * G::W]);
     }
 }
 
 // Replace X (row layout of row_forward) by the values at the mirrored
-// frequency: -k mod 8192 when `zero`, else 8191 - k.
-template <typename T>
-__device__ __forceinline__ void row_mirror(cx<T> (&X)[16], cx<T>* lds, int wv, int l, bool zero) {
-    constexpr int S = kWaveSlots;
+// frequency: -k mod N1 when `zero`, else N1 - 1 - k.
+template <typename T, int N1>
+__device__ __forceinline__ void row_mirror(RowVec<T, N1>& X, cx<T>* lds, int tid, bool zero) {
+    using G = RowGeom<T, N1>;
+    const int wv = tid >> 6, l = tid & 63;
     wave_sync();   // X was produced in the wave's own region, which no other wave touches
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds[wv * S + wslot(l + 64 * i)] = X[i];
+    for (int i = 0; i < G::PT; ++i) lds[wv * G::SLOTS + G::slot(l) + G::slot(64) * i] = X[i];
     __syncthreads();
-    const int sw = zero ? ((8 - wv) & 7) : (7 - wv);
+    const int sw = zero ? ((G::W - wv) & (G::W - 1)) : (G::W - 1 - wv);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < G::PT; ++i) {
         const int kb = l + 64 * i;
-        const int sb = (zero && wv == 0) ? ((1024 - kb) & 1023) : (1023 - kb);
-        X[i] = lds[sw * S + wslot(sb)];
+        const int sb = (zero && wv == 0) ? ((G::M - kb) & (G::M - 1)) : (G::M - 1 - kb);
+        X[i] = lds[sw * G::SLOTS + G::slot(sb)];
     }
 }
 
-// Store V row `row` (inverse four-step twiddle w_L^{-row t1}): t1 = x + 1024 ta
-// with x = w 64 + l + 512 s, so w_L^{row t1} = w_L^{row x} w_L^{1024 row ta},
-// an FP64 product rounded once.  `real`: keep the real part only.
-template <typename T>
-__device__ __forceinline__ void row_store(cx<T>* __restrict__ Yrow, cx<T> (&a)[16], uint32_t row, bool real,
-                                          int wv, int l, const cx<double>* __restrict__ fa64,
+// Store V row `row` (inverse four-step twiddle w_L^{-row t1}): t1 = x + M ta
+// with x = tid + THREADS s, so w_L^{row t1} = w_L^{row x} w_L^{M row ta}, an FP64
+// product rounded once.  `real`: keep the real part only.
+template <typename T, int N1>
+__device__ __forceinline__ void row_store(cx<T>* __restrict__ Yrow, RowVec<T, N1>& a, uint32_t row,
+                                          bool real, int tid, const cx<double>* __restrict__ fa64,
                                           const cx<double>* __restrict__ fb64, int fshift) {
+    using G = RowGeom<T, N1>;
     if constexpr (sizeof(T) == 8) {
         // FP64 (register-bound): one table product per point
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < G::S; ++s)
 #pragma unroll
-            for (int ta = 0; ta < 8; ++ta) {
-                const uint32_t t1 = (uint32_t)(wv * 64 + l + 512 * s + 1024 * ta);
-                cx<T> vv = cmulc(a[s * 8 + ta], rounded<T>(root64(fa64, fb64, fshift, row * t1)));
+            for (int ta = 0; ta < G::W; ++ta) {
+                const uint32_t t1 = (uint32_t)(tid + G::THREADS * s + G::M * ta);
+                cx<T> vv = cmulc(a[s * G::W + ta], rounded<T>(root64(fa64, fb64, fshift, row * t1)));
                 if (real) vv.im = T(0);
                 Yrow[t1] = vv;
             }
         return;
     }
-    Root64 b[2];
+    Root64 b[G::S];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) b[s] = root64(fa64, fb64, fshift, row * (uint32_t)(wv * 64 + l + 512 * s));
+    for (int s = 0; s < G::S; ++s) b[s] = root64(fa64, fb64, fshift, row * (uint32_t)(tid + G::THREADS * s));
 #pragma unroll
-    for (int ta = 0; ta < 8; ++ta) {
-        const Root64 c = root64(fa64, fb64, fshift, 1024u * row * (uint32_t)ta);
+    for (int ta = 0; ta < G::W; ++ta) {
+        Root64 c{1.0, 0.0};
+        if (ta) c = root64(fa64, fb64, fshift, (uint32_t)G::M * row * (uint32_t)ta);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const uint32_t x = (uint32_t)(wv * 64 + l + 512 * s);
-            cx<T> vv = cmulc(a[s * 8 + ta], rounded<T>(mul64(b[s], c)));
+        for (int s = 0; s < G::S; ++s) {
+            cx<T> vv = cmulc(a[s * G::W + ta], rounded<T>(ta ? mul64(b[s], c) : b[s]));
             if (real) vv.im = T(0);
-            Yrow[x + 1024u * (uint32_t)ta] = vv;
+            Yrow[tid + G::THREADS * s + G::M * ta] = vv;
         }
     }
 }
 
-// Row pass over units: units 0 .. ntiles (n2/2 - 1) - 1 are mirror pairs (row
-// pr >= 1 with n2 - pr), the last ntiles units the self rows 0 and n2/2 of
-// each tile.  The pass is persistent: workgroup b walks u = b, b + G, ...,
-// G = one workgroup per CU (LDS-bound), tables loaded once.
-template <typename T> constexpr bool kRowPersistent = sizeof(T) == 4;
-// One unit of the row pass.
-template <typename T, int N2, int NCB1>
+// Row units: units 0 .. ngroups (n2/2 - 1) - 1 are mirror pairs (row pr >= 1
+// with n2 - pr), the last ngroups units the self rows 0 and n2/2 of each group.
+// A unit transforms its rows of every tile of the group, sums their spectrum
+// products and inverts the sum into the first tile's row pr.
+template <typename T, int N1, int N2, int NCB1>
 __device__ __forceinline__ void row_unit(uint32_t u, const JobTable& jt, cx<T>* __restrict__ ws,
                                          const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
-                                         RowSmem<T>& S, const RowReg<T>& R, uint32_t& wsum,
-                                         const cx<T>* __restrict__ tw,
-                                         const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64,
-                                         const cx<double>* __restrict__ fb64, int fshift) {
-    constexpr uint32_t L = (uint32_t)kN1 * N2;
-    constexpr int NP = N2 / 2;
-    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
+                                         RowSmem<T, N1>& S, const RowReg<T, N1>& R, uint32_t& wsum,
+                                         const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
+                                         int fshift) {
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int NP = N2 / 2, PT = RowGeom<T, N1>::PT;
+    const int tid = threadIdx.x;
     const T quarter = T(0.25) / T(L);
-    const uint32_t npairs = jt.ntiles * (uint32_t)(NP - 1);
+    const uint32_t npairs = jt.ngroups * (uint32_t)(NP - 1);
     const bool pair = u < npairs;
-    const uint32_t lt = pair ? u / (uint32_t)(NP - 1) : u - npairs;
+    const uint32_t gl = pair ? u / (uint32_t)(NP - 1) : u - npairs;
     const uint32_t pr = pair ? 1u + u % (uint32_t)(NP - 1) : 0u;
+    const JobDesc jd = find_group_job(jt, jt.group0 + gl);
+    uint32_t first, gs;
+    (void)group_geo(jd, jt.group0 + gl - jd.group_begin, &first, &gs);
+    const uint32_t lt = jd.tile_begin + first - jt.tile0;
     cx<T>* __restrict__ Y = ws + (size_t)lt * L;
     if (pair) {
-        // FP32 issues the second row's loads before the first transform;
-        // FP64 has no registers to spare for that
-        constexpr bool kHoist = sizeof(T) == 4;
-        cx<T> ra[16], rb[16], A[16], B[16], a[16];
-        row_load<T>(ra, Y + (size_t)pr * kN1, wv, l);
-        if constexpr (kHoist) row_load<T>(rb, Y + (size_t)(N2 - pr) * kN1, wv, l);
-        row_forward<T>(ra, A, S, R, wv, l, tw, stw);
-        if constexpr (!kHoist) row_load<T>(rb, Y + (size_t)(N2 - pr) * kN1, wv, l);
-        row_forward<T>(rb, B, S, R, wv, l, tw, stw);
-        row_mirror<T>(B, S.data, wv, l, false);
+        cx<T> acc[PT];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) A[i] = spectrum_product(A[i], B[i], quarter);
-        row_inverse<T>(A, a, S, R, wv, l, tw, stw);
-        row_store<T>(Y + (size_t)pr * kN1, a, pr, false, wv, l, fa64, fb64, fshift);
+        for (int i = 0; i < PT; ++i) acc[i] = cx<T>{T(0), T(0)};
+        for (uint32_t c = 0; c < gs; ++c) {
+            const cx<T>* __restrict__ Yc = Y + (size_t)c * L;
+            cx<T> A[PT], B[PT];
+            row_load<T, N1>(A, Yc + (size_t)pr * N1, tid);
+            row_forward<T, N1>(A, S, R, tid);
+            row_load<T, N1>(B, Yc + (size_t)(N2 - pr) * N1, tid);
+            row_forward<T, N1>(B, S, R, tid);
+            row_mirror<T, N1>(B, S.data, tid, false);
+#pragma unroll
+            for (int i = 0; i < PT; ++i) acc[i] = acc[i] + spectrum_product(A[i], B[i], quarter);
+        }
+        row_inverse<T, N1>(acc, S, R, tid);
+        row_store<T, N1>(Y + (size_t)pr * N1, acc, pr, false, tid, fa64, fb64, fshift);
     } else {
-        // key-chunk weight from the pass-1 partial sums; reset the certificate
+        // weight of the group's chunks from the pass-1 partial sums; reset the certificate
         __syncthreads();
         if (tid == 0) wsum = 0;
         __syncthreads();
         uint32_t sum = 0;
-        for (int c = tid; c < NCB1; c += 512) sum += part[(size_t)lt * NCB1 + c];
+        for (uint32_t c = tid; c < gs * NCB1; c += RowGeom<T, N1>::THREADS) sum += part[(size_t)lt * NCB1 + c];
         atomicAdd(&wsum, sum);
         __syncthreads();
-        if (tid == 0) meta[jt.tile0 + lt] = TileMeta{wsum, 0u, 0u, 0u};
+        if (tid == 0) meta[jt.group0 + gl] = TileMeta{wsum, 0u, 0u, 0u};
         // rows 0 and n2/2 are their own mirrors and their V rows are real:
         // each goes to the real parts of its own row
 #pragma nounroll
         for (int v = 0; v < 2; ++v) {
             const uint32_t row = v == 0 ? 0u : (uint32_t)NP;
-            cx<T> ra[16], A[16], B[16], a[16];
-            row_load<T>(ra, Y + (size_t)row * kN1, wv, l);
-            row_forward<T>(ra, A, S, R, wv, l, tw, stw);
+            cx<T> acc[PT];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) B[i] = A[i];
-            row_mirror<T>(B, S.data, wv, l, v == 0);
+            for (int i = 0; i < PT; ++i) acc[i] = cx<T>{T(0), T(0)};
+            for (uint32_t c = 0; c < gs; ++c) {
+                cx<T> A[PT], B[PT];
+                row_load<T, N1>(A, Y + (size_t)c * L + (size_t)row * N1, tid);
+                row_forward<T, N1>(A, S, R, tid);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) A[i] = spectrum_product(A[i], B[i], quarter);
-            row_inverse<T>(A, a, S, R, wv, l, tw, stw);
-            row_store<T>(Y + (size_t)row * kN1, a, row, true, wv, l, fa64, fb64, fshift);
+                for (int i = 0; i < PT; ++i) B[i] = A[i];
+                row_mirror<T, N1>(B, S.data, tid, v == 0);
+#pragma unroll
+                for (int i = 0; i < PT; ++i) acc[i] = acc[i] + spectrum_product(A[i], B[i], quarter);
+            }
+            row_inverse<T, N1>(acc, S, R, tid);
+            row_store<T, N1>(Y + (size_t)row * N1, acc, row, true, tid, fa64, fb64, fshift);
         }
     }
 }
 
-template <typename T, int N2, int NCB1>
-__global__ void __launch_bounds__(512)
+// Workgroups per CU: rows of 4096 in FP32 two (16 waves), else one.
+template <typename T, int N1> constexpr int row_wgs_per_cu() { return N1 == 4096 && sizeof(T) == 4 ? 2 : 1; }
+template <typename T, int N1, int N2, int NCB1>
+__global__ void __launch_bounds__((RowGeom<T, N1>::THREADS))
+__attribute__((amdgpu_waves_per_eu(row_wgs_per_cu<T, N1>() * RowGeom<T, N1>::THREADS / 256)))
 k2_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
          const cx<T>* __restrict__ tw, const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64,
          const cx<double>* __restrict__ fb64, int fshift) {
-    __shared__ __align__(16) RowSmem<T> S;
+    __shared__ __align__(16) RowSmem<T, N1> S;
     __shared__ uint32_t wsum;
-    const uint32_t units = jt.ntiles * (uint32_t)(N2 / 2);
-    row_smem_load<T>(S, tw, stw, threadIdx.x);
-    if constexpr (!RowSmem<T>::kLds) __syncthreads();
-    RowReg<T> R;
-    if constexpr (RowSmem<T>::kLds) {
-        // w_1024^{l r} = w_8192^{8 l r}, l r < 1024
-        const int l = threadIdx.x & 63;
-#pragma unroll
-        for (int r = 1; r < 16; ++r) R.tr[r - 1] = tw[8 * l * r];
-    }
-    if constexpr (kRowPersistent<T>) {
-        for (uint32_t u = blockIdx.x; u < units; u += gridDim.x)
-            row_unit<T, N2, NCB1>(u, jt, ws, part, meta, S, R, wsum, tw, stw, fa64, fb64, fshift);
-    } else {
-        if (blockIdx.x < units)
-            row_unit<T, N2, NCB1>(blockIdx.x, jt, ws, part, meta, S, R, wsum, tw, stw, fa64, fb64, fshift);
-    }
+    const uint32_t units = jt.ngroups * (uint32_t)(N2 / 2);
+    RowReg<T, N1> R;
+    row_setup<T, N1>(S, R, tw, stw, threadIdx.x);
+    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x)
+        row_unit<T, N1, N2, NCB1>(u, jt, ws, part, meta, S, R, wsum, fa64, fb64, fshift);
 }
 
 // ------------------------------------------------------------------ pass 3
@@ -803,15 +830,15 @@ __device__ __forceinline__ uint32_t low2(double r) {
     return (uint32_t)(int)((q - floor(q)) * 4.0) & 3u;
 }
 
-template <typename T, int N2>
+template <typename T, int N1, int N2>
 __global__ void __launch_bounds__((P3Geom<T, N2>::THREADS))
 __attribute__((amdgpu_waves_per_eu(P3Geom<T, N2>::MIN_WG * P3Geom<T, N2>::WAVES / 4)))
 k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta, const cx<T>* __restrict__ tw,
          const cx<T>* __restrict__ stw) {
     using Gm = P3Geom<T, N2>;
     constexpr int C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16, CW = Gm::CW;
-    constexpr uint32_t L = (uint32_t)kN1 * N2;
-    constexpr int NCB = kN1 / C;
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int NCB = N1 / C;
     constexpr bool LT = Gm::LDS_TAB;
     constexpr int NHT = LT ? M : 1;
     constexpr int NLB = Gm::WAVES * 64;
@@ -827,11 +854,12 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
     __shared__ T hrow[C];
     __shared__ uint32_t s_res, s_abs, s_bad;
 
-    const uint32_t lt = blockIdx.x / NCB;
+    const uint32_t t = jt.group0 + blockIdx.x / NCB;   // group
     const uint32_t cb = blockIdx.x % NCB;
-    const uint32_t t = jt.tile0 + lt;
-    const JobDesc jd = find_job(jt, t);
-    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+    const JobDesc jd = find_group_job(jt, t);
+    uint32_t first, gs;
+    const TileGeo g = group_geo(jd, t - jd.group_begin, &first, &gs);
+    const uint32_t lt = jd.tile_begin + first - jt.tile0;
     const cx<T>* __restrict__ V = ws + (size_t)lt * L;
     const int tid = threadIdx.x;
     if (tid == 0) { s_res = 0; s_abs = 0; s_bad = 0; }
@@ -842,12 +870,12 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
 #pragma unroll
         for (int q = 0; q < LPT; ++q) {
             const int idx = tid + q * Gm::THREADS;
-            in[q] = V[(size_t)(idx / C) * kN1 + cb * C + (idx % C)];
+            in[q] = V[(size_t)(idx / C) * N1 + cb * C + (idx % C)];
         }
-        if (tid < C) hrow[tid] = V[(size_t)M * kN1 + cb * C + tid].re;   // H[n2/2], real
+        if (tid < C) hrow[tid] = V[(size_t)M * N1 + cb * C + tid].re;   // H[n2/2], real
         if constexpr (LT) {
             wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
-            for (int k = tid; k < M; k += Gm::THREADS) U.htw[k] = tw[k * (kN1 / N2)];
+            for (int k = tid; k < M; k += Gm::THREADS) U.htw[k] = tw[k * (N1 / N2)];
         }
 #pragma unroll
         for (int q = 0; q < LPT; ++q) {
@@ -874,7 +902,7 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
         } else {
             const cx<T> hm = conj(lds[tslot<C>(M - k, f)]);
             const cx<T> e = h + hm;
-            const cx<T> wk = LT ? U.htw[k] : tw[k * (kN1 / N2)];
+            const cx<T> wk = LT ? U.htw[k] : tw[k * (N1 / N2)];
             const cx<T> o = cmulc(h - hm, wk);
             v[i] = cx<T>{e.re - o.im, e.im + o.re};
         }
@@ -888,7 +916,7 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
     // of rint(z) + weight matter, bit = bit 1, parity check = bit 0
     const uint32_t wlow = meta[t].popcnt & 3u;
     const uint32_t bo = (uint32_t)g.bo;
-    const uint32_t rows = (bo + (uint32_t)kN1 - 1u) / (uint32_t)kN1;  // rows t2 holding outputs
+    const uint32_t rows = (bo + (uint32_t)N1 - 1u) / (uint32_t)N1;  // rows t2 holding outputs
     float mres = 0.f, mabs = 0.f;
     uint32_t bad = 0;
     uint32_t mybits = 0;
@@ -898,7 +926,7 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const uint32_t t2 = 2u * (uint32_t)(j + i * NJ) + (uint32_t)e;
-            const bool valid = t1 + (uint32_t)kN1 * t2 < bo;
+            const bool valid = t1 + (uint32_t)N1 * t2 < bo;
             const T zz = e ? v[i].im : v[i].re;
             const T r = round_even(zz);
             const uint32_t s2 = low2(r) + wlow;
@@ -926,7 +954,7 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
             const int col = 32 * (int)c + q;
             word |= ((U.lbits[(col / G) * 64 + (col % G) * NJ + jj] >> sh) & 1u) << q;
         }
-        const uint64_t off = (uint64_t)cb * C + 32u * c + (uint64_t)kN1 * t2;
+        const uint64_t off = (uint64_t)cb * C + 32u * c + (uint64_t)N1 * t2;
         if (off >= limit) continue;
         put_bits<WB>(g, off, word);
     }
@@ -937,77 +965,76 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
     }
 }
 
-// Workgroups of the persistent row pass: one per compute unit (LDS-bound).
+// Compute units of the current device.
 int row_pass_workgroups();
 
-template <typename T, int N2>
+template <typename T, int N1, int N2, int NCB1>
+int launch_row_pass(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
+    const uint32_t units = jt.ngroups * (N2 / 2);
+    const uint32_t wgs = (uint32_t)(row_pass_workgroups() * row_wgs_per_cu<T, N1>());
+    hipLaunchKernelGGL((k2_pass2<T, N1, N2, NCB1>), dim3(units < wgs ? units : wgs),
+                       dim3(RowGeom<T, N1>::THREADS), 0,
+                       (hipStream_t)stream, jt, (cx<T>*)ws, (const uint32_t*)part, meta, (const cx<T>*)tb.tw,
+                       (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <typename T, int N1, int N2>
 struct ClassImpl2 {
     using G1 = P1Geom<T, N2>;
     using G3 = P3Geom<T, N2>;
     static constexpr int C1 = G1::C, C3 = G3::C;
     // workspace bytes per tile beyond its points: the bit planes
-    static constexpr size_t kWsExtra = G1::kPlanes ? BitPlanes<N2>::kTile : 0;
+    static constexpr size_t kWsExtra = G1::kPlanes ? BitPlanes<N1, N2>::kTile : 0;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
-        dim3 grid(jt.ntiles * (kN1 / C1)), block(G1::THREADS);
+        dim3 grid(jt.ntiles * (N1 / C1)), block(G1::THREADS);
         if constexpr (G1::kPlanes) {
-            uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)kN1 * N2));
-            hipLaunchKernelGGL((k2_bits<N2>), dim3(jt.ntiles * (N2 / kBitsRows) * (kN1 / 64 / kBitsCols)), dim3(256), 0,
-                               (hipStream_t)stream, jt, planes);
+            uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
+            hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (N2 / kBitsRows) * (N1 / 64 / kBitsCols)), dim3(256),
+                               0, (hipStream_t)stream, jt, planes);
         }
         if constexpr (sizeof(T) == 4 && N2 == 2048) {
             static_assert(C1 == 8, "eight columns per workgroup");
-            hipLaunchKernelGGL((k2_pass1s<T>), dim3(2 * grid.x), dim3(512), 0, (hipStream_t)stream, jt, (cx<T>*)ws, part,
-                               (const cx<T>*)tb.tw, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
+            hipLaunchKernelGGL((k2_pass1s<T, N1>), dim3(2 * grid.x), dim3(512), 0, (hipStream_t)stream, jt, (cx<T>*)ws,
+                               part, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
                                (const cx<double>*)tb.fb64, tb.fshift);
         } else {
-            hipLaunchKernelGGL((k2_pass1<T, N2>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws, part,
+            hipLaunchKernelGGL((k2_pass1<T, N1, N2>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws, part,
                                (const cx<T>*)tb.tw, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
                                (const cx<double>*)tb.fb64, tb.fshift);
         }
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     static int pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
-        const uint32_t units = jt.ntiles * (N2 / 2);
-        const uint32_t wgs = kRowPersistent<T> ? (uint32_t)row_pass_workgroups() : units;
-        dim3 grid(units < wgs ? units : wgs), block(512);
-        hipLaunchKernelGGL((k2_pass2<T, N2, kN1 / C1>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws,
-                           (const uint32_t*)part, meta, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
-                           (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
-        return hipGetLastError() == hipSuccess ? 0 : -1;
+        return launch_row_pass<T, N1, N2, N1 / C1>(jt, ws, part, meta, tb, stream);
     }
     static int pass3(const JobTable& jt, void* ws, uint32_t*, TileMeta* meta, const Tables& tb, void* stream) {
-        dim3 grid(jt.ntiles * (kN1 / C3)), block(G3::THREADS);
-        hipLaunchKernelGGL((k2_pass3<T, N2>), grid, block, 0, (hipStream_t)stream, jt, (const cx<T>*)ws, meta,
+        dim3 grid(jt.ngroups * (N1 / C3)), block(G3::THREADS);
+        hipLaunchKernelGGL((k2_pass3<T, N1, N2>), grid, block, 0, (hipStream_t)stream, jt, (const cx<T>*)ws, meta,
                            (const cx<T>*)tb.tw, (const cx<T>*)tb.stw);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
 };
 
-// Mixed-radix classes with rows of 8192 (L = 8192 n2, n2 = P 2^b): the
+// Mixed-radix classes with rows of 4096 (L = 4096 n2, n2 = P 2^b): the
 // wave-level row pass above (it does not depend on how n2 factors) between
 // the workgroup-wide Stockham column passes of conv_kernels.hpp, whose columns
 // carry the radix-P stage (RC points per thread).
 template <typename T, int N2, int B1, int B3, int RC>
 struct ClassImplS {
-    static constexpr int NCB1 = kN1 / B1;
+    static constexpr int N1 = 4096, NCB1 = N1 / B1;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
         dim3 grid(jt.ntiles * NCB1), block(B1 * (N2 / RC));
-        hipLaunchKernelGGL((k_pass1<T, kN1, N2, B1, RC, N2>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws,
+        hipLaunchKernelGGL((k_pass1<T, N1, N2, B1, RC, N2>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws,
                            part, (const cx<T>*)tb.tw2, (const cx<T>*)tb.fa, (const cx<T>*)tb.fb, tb.fshift);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     static int pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
-        const uint32_t units = jt.ntiles * (N2 / 2);
-        const uint32_t wgs = kRowPersistent<T> ? (uint32_t)row_pass_workgroups() : units;
-        dim3 grid(units < wgs ? units : wgs), block(512);
-        hipLaunchKernelGGL((k2_pass2<T, N2, NCB1>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws,
-                           (const uint32_t*)part, meta, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
-                           (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
-        return hipGetLastError() == hipSuccess ? 0 : -1;
+        return launch_row_pass<T, N1, N2, NCB1>(jt, ws, part, meta, tb, stream);
     }
     static int pass3(const JobTable& jt, void* ws, uint32_t*, TileMeta* meta, const Tables& tb, void* stream) {
-        dim3 grid(jt.ntiles * (kN1 / B3)), block(B3 * (N2 / 2 / RC));
-        hipLaunchKernelGGL((k_pass3<T, kN1, N2, B3, RC, N2, true>), grid, block, 0, (hipStream_t)stream, jt,
+        dim3 grid(jt.ngroups * (N1 / B3)), block(B3 * (N2 / 2 / RC));
+        hipLaunchKernelGGL((k_pass3<T, N1, N2, B3, RC, N2, true>), grid, block, 0, (hipStream_t)stream, jt,
                            (const cx<T>*)ws, meta, (const cx<T>*)tb.tw2);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }

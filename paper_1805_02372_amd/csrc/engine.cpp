@@ -371,6 +371,7 @@ void fill_job(JobDesc* jd, const uint64_t* seed, const uint64_t* key, uint64_t* 
     jd->Bo = p.Bo;
     jd->nchunks = (uint32_t)p.nchunks;
     jd->nouts = (uint32_t)p.nouts;
+    jd->cgroup = (uint32_t)p.cgroup;
     jd->out_words = (uint32_t)words_of(m);
 }
 
@@ -394,21 +395,28 @@ void Lane::release(Ctx* c) {
     stream = nullptr;
 }
 
-// Tiles [first, end) through the three passes, G tiles per launch.
-static pa_status run_passes(const ClassKernels* K, JobTable jt, uint32_t first, uint32_t end, size_t G, Lane* ln,
-                            const Tables& tb, bool timing, uint64_t* launches) {
-    for (uint32_t t0 = first; t0 < end; t0 += (uint32_t)G) {
-        jt.tile0 = t0;
-        jt.ntiles = (uint32_t)std::min<size_t>(G, end - t0);
-        const launch_fn fns[3] = {K->pass1, K->pass2, K->pass3};
-        for (int p = 0; p < 3; ++p) {
-            hipEvent_t a = timing ? ln->timer.mark(ln->stream) : nullptr;
-            // 0: launched; 1: nothing to launch (one-kernel tiles); < 0: error
-            const int r = fns[p](jt, ln->ws.ptr, (uint32_t*)ln->part.ptr, (TileMeta*)ln->meta.ptr, tb, ln->stream);
-            if (r < 0) return PA_EDEVICE;
-            if (r == 0) *launches += 1;
-            if (timing) ln->timer.spans.push_back({p, {a, ln->timer.mark(ln->stream)}});
-        }
+static uint32_t chunk_groups(const JobDesc& jd) { return (jd.nchunks + jd.cgroup - 1) / jd.cgroup; }
+
+// A run of whole groups: tiles [tile, tile + ntiles), groups [group, group + ngroups).
+struct Span {
+    uint32_t tile, ntiles, group, ngroups;
+};
+
+// The three passes over one span.
+static pa_status run_span(const ClassKernels* K, JobTable jt, const Span& sp, Lane* ln, const Tables& tb, bool timing,
+                          uint64_t* launches) {
+    jt.tile0 = sp.tile;
+    jt.ntiles = sp.ntiles;
+    jt.group0 = sp.group;
+    jt.ngroups = sp.ngroups;
+    const launch_fn fns[3] = {K->pass1, K->pass2, K->pass3};
+    for (int p = 0; p < 3; ++p) {
+        hipEvent_t a = timing ? ln->timer.mark(ln->stream) : nullptr;
+        // 0: launched; 1: nothing to launch (one-kernel tiles); < 0: error
+        const int r = fns[p](jt, ln->ws.ptr, (uint32_t*)ln->part.ptr, (TileMeta*)ln->meta.ptr, tb, ln->stream);
+        if (r < 0) return PA_EDEVICE;
+        if (r == 0) *launches += 1;
+        if (timing) ln->timer.spans.push_back({p, {a, ln->timer.mark(ln->stream)}});
     }
     return PA_OK;
 }
@@ -420,18 +428,10 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     prec = prec_;
     cls = cls_;
     const ClassCfg& cfg = K->cfg;
-    // Tiles in job order; within a job chunk 0 comes first, so a window is
-    // cleared (pass 1 of its chunk-0 tile) before any chunk XORs into it, also
-    // when the tiles are split over several launches.
     uint32_t total = 0;
-    for (JobDesc& jd : js) {
-        jd.tile_begin = total;
-        total += jd.nchunks * jd.nouts;
-    }
+    for (const JobDesc& jd : js) total += jd.nchunks * jd.nouts;
     Tables tb;
     pa_status st = lane_tables(c, *this, prec, cls, &tb);
-    if (st != PA_OK) return st;
-    st = meta.ensure(c, (size_t)total * sizeof(TileMeta), stream);
     if (st != PA_OK) return st;
 
     if (js.size() > 1) {  // descriptors first: they are small but must fit
@@ -464,6 +464,37 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     }
     if (st != PA_OK) return st;
 
+    // Tiles in job order, whole groups to a launch (a group that does not fit
+    // one is cut into smaller ones, whose partial hashes are XOR-ed).  Within a
+    // job the chunk groups come in order, so a window is cleared (pass 1 of its
+    // chunk-0 tile) before any group XORs into it, also when the tiles are split
+    // over several launches.
+    std::vector<Span> spans;
+    uint32_t tiles = 0, groups = 0;
+    Span cur{0, 0, 0, 0};
+    for (JobDesc& jd : js) {
+        jd.cgroup = (uint32_t)std::max<size_t>(1, std::min<size_t>({(size_t)jd.cgroup, (size_t)jd.nchunks, G}));
+        if (!cfg.sums) jd.cgroup = 1;
+        jd.tile_begin = tiles;
+        jd.group_begin = groups;
+        for (uint32_t q = 0; q < chunk_groups(jd); ++q) {
+            const uint32_t gs = std::min(jd.cgroup, jd.nchunks - q * jd.cgroup);
+            for (uint32_t o = 0; o < jd.nouts; ++o) {
+                if (cur.ntiles + gs > G) {
+                    spans.push_back(cur);
+                    cur = Span{tiles, 0, groups, 0};
+                }
+                cur.ntiles += gs;
+                cur.ngroups += 1;
+                tiles += gs;
+                groups += 1;
+            }
+        }
+    }
+    spans.push_back(cur);
+    st = meta.ensure(c, (size_t)groups * sizeof(TileMeta), stream);
+    if (st != PA_OK) return st;
+
     JobTable jt{};
     if (js.size() == 1) {
         jt.one = js[0];
@@ -475,23 +506,25 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
             return PA_EDEVICE;
         jt.many = (const JobDesc*)jobs_dev.ptr;
         jt.njobs = (uint32_t)js.size();
-        for (const JobDesc& jd : js) jt.clears |= (jd.nchunks > 1 && !jd.no_clear) ? 1u : 0u;
+        for (const JobDesc& jd : js) jt.clears |= (jd.nchunks > jd.cgroup && !jd.no_clear) ? 1u : 0u;
     }
     if (timing) timer.reset();
-    st = run_passes(K, jt, 0, total, G, this, tb, timing, &stats->launches);
-    if (st != PA_OK) return st;
-    if (fetch_meta) {
-        st = meta_host.ensure((size_t)total * sizeof(TileMeta));
+    for (const Span& sp : spans) {
+        st = run_span(K, jt, sp, this, tb, timing, &stats->launches);
         if (st != PA_OK) return st;
-        if (hipMemcpyAsync(meta_host.ptr, meta.ptr, (size_t)total * sizeof(TileMeta), hipMemcpyDeviceToHost,
+    }
+    if (fetch_meta) {
+        st = meta_host.ensure((size_t)groups * sizeof(TileMeta));
+        if (st != PA_OK) return st;
+        if (hipMemcpyAsync(meta_host.ptr, meta.ptr, (size_t)groups * sizeof(TileMeta), hipMemcpyDeviceToHost,
                            stream) != hipSuccess)
             return PA_EDEVICE;
     }
     if (!done && hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) return PA_EDEVICE;
     if (hipEventRecord(done, stream) != hipSuccess) return PA_EDEVICE;
     jobs = js;
-    total_tiles = total;
-    stats->tiles += total;
+    total_groups = groups;
+    stats->tiles += tiles;
     return PA_OK;
 }
 
@@ -520,7 +553,7 @@ static hipError_t wait_event(hipEvent_t e) {
 pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_status>* per_job) {
     if (wait_event(done) != hipSuccess) return PA_EDEVICE;
     if (flags & PA_TIMING) timer.collect(stats->ms_pass);
-    const uint32_t total = total_tiles;
+    const uint32_t total = total_groups;
     const TileMeta* mt = (const TileMeta*)meta_host.ptr;
     std::vector<uint32_t> failed;
     for (uint32_t t = 0; t < total; ++t) {
@@ -535,7 +568,7 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         size_t lo = 0, hi = jobs.size() - 1;
         while (lo < hi) {
             size_t mid = (lo + hi + 1) / 2;
-            if (jobs[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
+            if (jobs[mid].group_begin <= t) lo = mid; else hi = mid - 1;
         }
         return lo;
     };
@@ -545,10 +578,12 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
             for (uint32_t t : failed) (*per_job)[job_of(t)] = PA_EPRECISION;
         return PA_EPRECISION;
     }
-    // Re-run in FP64 with the same geometry and length class.
-    //  * One-chunk job: the failed tile alone (its window is overwritten).
-    //  * Job that accumulates chunks (Eq. 7): per failed tile, the FP32 tile
-    //    again and then the FP64 tile, both XOR-ing into the window without
+    // Re-run in FP64 with the same geometry and length class, one chunk at a
+    // time (the chunks' partial hashes XOR into the window, Eq. 7).
+    //  * Job of one chunk group: the failed group's chunks alone (its window is
+    //    overwritten, or cleared by chunk 0 and XOR-ed into).
+    //  * Job that accumulates chunk groups: per failed group, the FP32 group
+    //    again and then its FP64 chunks, all XOR-ing into the window without
     //    clearing it; the FP32 run is deterministic, so its bits cancel the
     //    first run's.  If the repeat's certificate is not bit-identical to the
     //    first run's, the whole job is rebuilt in FP64 instead (its windows
@@ -558,21 +593,19 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
     pa_status st = lane_tables(c, *this, PREC_FP64, cls, &tb);
     if (st == PA_OK) st = lane_tables(c, *this, PREC_FP32, cls, &tb32);
     if (st != PA_OK) return st;
-    // the FP64 tile, or the FP32 tile with its bit planes
+    // the FP64 tile, or the FP32 tiles of a group with their bit planes
+    size_t most = 1;
+    for (uint32_t t : failed) {
+        const JobDesc& jd = jobs[job_of(t)];
+        if (jd.nchunks > jd.cgroup) most = std::max<size_t>(most, jd.cgroup);
+    }
     st = ws.ensure(c, std::max<size_t>((size_t)class_len(cls) * 16,
-                                       (size_t)class_len(cls) * 8 + (K32 ? K32->cfg.ws_extra : 0)),
+                                       most * ((size_t)class_len(cls) * 8 + (K32 ? K32->cfg.ws_extra : 0))),
                    stream);
     if (st != PA_OK) return st;
-    const size_t part_words = std::max<size_t>(K64->cfg.n1 / K64->cfg.b1, K32 ? K32->cfg.n1 / K32->cfg.b1 : 0);
+    const size_t part_words = std::max<size_t>(K64->cfg.n1 / K64->cfg.b1, K32 ? most * (K32->cfg.n1 / K32->cfg.b1) : 0);
     st = part.ensure(c, part_words * sizeof(uint32_t), stream);
     if (st != PA_OK) return st;
-    // (job, local tile, mode): 0 one-chunk tile, 1 accumulated tile, 2 whole job
-    struct Run { size_t job; uint32_t tile; int mode; };
-    std::vector<Run> runs;
-    for (uint32_t t : failed) {
-        const size_t jx = job_of(t);
-        runs.push_back({jx, t - jobs[jx].tile_begin, jobs[jx].nchunks > 1 ? 1 : 0});
-    }
     std::vector<uint8_t> rebuilt(jobs.size(), 0);
     auto fetch_meta = [&](uint32_t first, uint32_t end, std::vector<TileMeta>* out) -> pa_status {
         out->resize(end - first);
@@ -583,51 +616,58 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         return PA_OK;
     };
     pa_status result = PA_OK;
-    for (size_t q = 0; q < runs.size(); ++q) {
-        Run r = runs[q];
-        const size_t jx = r.job;
+    for (uint32_t t : failed) {
+        const size_t jx = job_of(t);
         if (rebuilt[jx]) continue;
-        const uint32_t ntiles = jobs[jx].nchunks * jobs[jx].nouts;
+        const JobDesc& jd = jobs[jx];
+        const uint32_t lg = t - jd.group_begin, q = lg / jd.nouts, o = lg % jd.nouts;
+        const uint32_t b0 = q * jd.cgroup, gs = std::min(jd.cgroup, jd.nchunks - b0);
         JobTable jt{};
-        jt.one = jobs[jx];
+        jt.one = jd;
         jt.one.tile_begin = 0;
+        jt.one.group_begin = 0;
         jt.njobs = 0;
-        st = meta.ensure(c, (size_t)ntiles * sizeof(TileMeta), stream);
+        st = meta.ensure(c, (size_t)jd.nchunks * jd.nouts * sizeof(TileMeta), stream);
         if (st != PA_OK) return st;
-        if (r.mode == 1) {
+        bool whole = false;
+        if (jd.nchunks > jd.cgroup) {
             jt.one.no_clear = 1;
             bool same = K32 != nullptr;
             if (same) {
-                st = run_passes(K32, jt, r.tile, r.tile + 1, 1, this, tb32, false, &stats->launches);
+                const Span sp{q * jd.nouts * jd.cgroup + o * gs, gs, lg, 1};
+                st = run_span(K32, jt, sp, this, tb32, false, &stats->launches);
                 if (st != PA_OK) return st;
                 std::vector<TileMeta> again;
-                st = fetch_meta(r.tile, r.tile + 1, &again);
+                st = fetch_meta(lg, lg + 1, &again);
                 if (st != PA_OK) return st;
-                const TileMeta& o = mt[jobs[jx].tile_begin + r.tile];
-                same = memcmp(&again[0], &o, sizeof(TileMeta)) == 0;
-                stats->tiles += 1;
+                same = memcmp(&again[0], &mt[t], sizeof(TileMeta)) == 0;
+                stats->tiles += gs;
             }
             if (!same) {   // rebuild the whole job
-                r.mode = 2;
+                whole = true;
                 jt.one.no_clear = 0;
                 rebuilt[jx] = 1;
             }
         }
-        const uint32_t first = r.mode == 2 ? 0u : r.tile, end = r.mode == 2 ? ntiles : r.tile + 1;
-        st = run_passes(K64, jt, first, end, 1, this, tb, false, &stats->launches);
-        if (st != PA_OK) return st;
-        stats->fallback_tiles += end - first;
-        stats->tiles += end - first;
-        std::vector<TileMeta> m64;
-        st = fetch_meta(first, end, &m64);
-        if (st != PA_OK) return st;
-        for (const TileMeta& m : m64) {
+        // FP64: a tile is a group of its own, numbered chunk b, window o -> b nouts + o
+        jt.one.cgroup = 1;
+        std::vector<uint32_t> again;
+        for (uint32_t b = whole ? 0u : b0; b < (whole ? jd.nchunks : b0 + gs); ++b)
+            for (uint32_t w = whole ? 0u : o; w < (whole ? jd.nouts : o + 1); ++w) again.push_back(b * jd.nouts + w);
+        for (uint32_t k : again) {
+            st = run_span(K64, jt, Span{k, 1, k, 1}, this, tb, false, &stats->launches);
+            if (st != PA_OK) return st;
+            std::vector<TileMeta> m64;
+            st = fetch_meta(k, k + 1, &m64);
+            if (st != PA_OK) return st;
             double rr, aa;
-            if (!tile_ok(PREC_FP64, m, &rr, &aa)) {
+            if (!tile_ok(PREC_FP64, m64[0], &rr, &aa)) {
                 result = PA_EPRECISION;
                 if (per_job) (*per_job)[jx] = PA_EPRECISION;
             }
         }
+        stats->fallback_tiles += again.size();
+        stats->tiles += again.size();
     }
     if (hipStreamSynchronize(stream) != hipSuccess) return PA_EDEVICE;
     return result;

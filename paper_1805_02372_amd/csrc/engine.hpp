@@ -102,7 +102,7 @@ struct Lane {
 
     // In-flight state of an asynchronous launch (serving).
     int prec = 0, cls = 0;
-    uint32_t total_tiles = 0;
+    uint32_t total_groups = 0;
     std::vector<JobDesc> jobs;
     hipEvent_t done = nullptr;
 

@@ -24,6 +24,14 @@ namespace pa {
 
 template <typename T> struct cx { T re, im; };
 
+// Returns p unchanged, but the compiler cannot see through it: loads through
+// the result cannot be hoisted above this point (keeps each stage's twiddle
+// loads next to their use instead of all of them live at once).
+template <typename P> __device__ __forceinline__ P opaque(P p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 template <typename T> __device__ __forceinline__ cx<T> mk(T a, T b) { return cx<T>{a, b}; }
 template <typename T> __device__ __forceinline__ cx<T> operator+(cx<T> a, cx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T> __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }

@@ -8,10 +8,14 @@ namespace pa {
 // One hash job as the kernels see it.  A job is cut into `nchunks` key chunks
 // (taken from the top of the key: chunk b covers key bits
 // [max(0, n-(b+1)Bi), n-b*Bi)) and `nouts` output windows (window o covers
-// outputs [o*Bo, min(m, (o+1)*Bo))); tile (b, o) is local tile b*nouts + o.
-// With several chunks the tiles' partial hashes are XOR-accumulated into
-// `out` (Eq. 7): pass 1 of the chunk-0 tile clears its window's words, pass 3
-// of every tile XORs its bits in.
+// outputs [o*Bo, min(m, (o+1)*Bo))).  The tiles of `cgroup` consecutive chunks
+// and one window form a group: their products are summed before the inverse
+// transform (the convolution is linear), so a group has one inverse, one
+// rounding and one certificate.  Group (q, o), q = chunk group, is local group
+// q*nouts + o; its tiles are consecutive in the job's tile numbering.  With
+// several chunk groups the groups' partial hashes are XOR-accumulated into
+// `out` (Eq. 7): pass 1 of the window's chunk-0 tile clears its words, pass 3
+// of every group XORs its bits in.
 // Tile (b, o) with chunk start j0, length bi, window start i0, length bo uses
 // seed bits [sigma, sigma+bi+bo-1) with sigma = i0 - j0 + n - bi: by the
 // constant diagonals of T its outputs are the window [bi-1, bi-1+bo) of the
@@ -23,7 +27,9 @@ struct JobDesc {
     uint64_t n, m;
     uint64_t Bi, Bo;      // nominal chunk and window lengths (Bo % 64 == 0 if nouts > 1)
     uint32_t nchunks, nouts;
+    uint32_t cgroup;      // chunks per group (the last chunk group may be smaller)
     uint32_t tile_begin;  // first tile of this job in the launch's tile numbering
+    uint32_t group_begin; // first group of this job in the launch's group numbering
     uint32_t out_words;   // ceil(m / 64)
     uint32_t no_clear;    // 1: chunk-0 tiles do not clear their window (a tile
                           // re-run that XORs into an accumulated window)
@@ -35,14 +41,16 @@ struct JobTable {
     JobDesc one;
     const JobDesc* many;
     uint32_t njobs;       // 0: use `one`
-    uint32_t tile0;       // first tile of this launch (groups of tiles)
-    uint32_t ntiles;      // tiles in this launch
+    uint32_t tile0;       // first tile of this launch
+    uint32_t ntiles;      // tiles in this launch (whole groups)
+    uint32_t group0;      // first group of this launch
+    uint32_t ngroups;     // groups in this launch
     uint32_t clears;      // some job of `many` has a chunk-0 tile that clears its window
 };
 
-// Per-tile results of pass 2/3.
+// Per-group results of pass 2/3.
 struct TileMeta {
-    uint32_t popcnt;      // weight of the key chunk
+    uint32_t popcnt;      // weight of the group's key chunks
     uint32_t maxres;      // float bits of max |z - rint z|
     uint32_t maxabs;      // float bits of max |z|
     uint32_t badpar;      // outputs whose rounded value had the wrong parity
@@ -76,6 +84,7 @@ struct ClassCfg {
     int b1, b3;           // columns per workgroup in pass 1 / pass 3
     int r;                // points per thread
     size_t ws_extra = 0;  // workspace bytes per tile beyond its points (pass 1's bit planes)
+    bool sums = false;    // the row pass sums the products of a group (else cgroup = 1)
 };
 
 // Device pointers of a class's twiddle tables (element type matches prec).

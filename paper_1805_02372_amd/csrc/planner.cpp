@@ -71,10 +71,10 @@ bool class_geometry(int prec, int cls, ClassGeom* g) {
         // rows of the three-pass geometry of 2^k (its short lengths run as
         // one-kernel tiles, whose row is the whole length)
         const int n2log = std::max(k - 13, std::min(prec == PREC_FP64 ? 11 : 10, k / 2));
-        g->n1 = L >= (1ull << 20) ? 8192 : 1 << (k - n2log);
+        g->n1 = L >= (1ull << 20) ? 4096 : 1 << (k - n2log);
         g->n2 = (int)(L / (uint64_t)g->n1);
         g->b1 = prec == PREC_FP64 ? 4 : 8;
-        g->b3 = prec == PREC_FP64 ? 8 : 16;
+        g->b3 = prec == PREC_FP64 || g->n2 > 2048 ? 8 : 16;
         g->r = 4 * P;
         return true;
     }
@@ -87,14 +87,25 @@ bool class_geometry(int prec, int cls, ClassGeom* g) {
         g->b3 = 8;
         return true;
     }
-    if (logL >= 20) {  // wave-level classes: rows of 8192
-        const int n2 = 1 << (logL - 13);
+    if (logL >= 20) {  // wave-level classes
         const bool f32 = prec != PREC_FP64;
+        // rows of 4096: the row pass then has two workgroups per CU in FP32, and
+        // registers to spare in FP64.  FP32 2^24 keeps 8192 (its wave-level column
+        // passes take at most 2048 points), FP64 2^24 takes workgroup-wide ones
+        const int n1log = f32 && logL == 24 ? 13 : 12;
+        const int n2 = 1 << (logL - n1log);
+        if (n2 == 4096) {
+            g->n1 = 4096;
+            g->n2 = 4096;
+            g->b1 = 4;
+            g->b3 = 8;
+            return true;
+        }
         const int w = n2 > 1024 ? n2 / 1024 : 1, m = n2 > 1024 ? 1024 : n2;
         const int waves1 = (f32 && w > 1) ? 16 : 8;
         const int g3 = 1024 / (n2 / 2);
         const int waves3 = (f32 && g3 == 1) ? 16 : 8;
-        g->n1 = 8192;
+        g->n1 = 1 << n1log;
         g->n2 = n2;
         g->b1 = waves1 * (1024 / m) / w;
         g->b3 = waves3 * g3;
@@ -215,6 +226,7 @@ CostModel::CostModel() {
     for (int p = 0; p < 3; ++p)
         for (int id = 0; id < 64; ++id) {
             const uint64_t Lc = class_len(id);
+            chunk_s[p][id] = 0;
             if (Lc == 0) {
                 tile_s[p][id] = 1.0;
                 continue;
@@ -233,6 +245,11 @@ CostModel::CostModel() {
         }
 }
 
+double CostModel::chunk(int prec, int cls) const {
+    const double c = chunk_s[prec_index(prec)][cls];
+    return c > 0 ? c : 0.7 * tile(prec, cls);
+}
+void CostModel::set_chunk(int prec, int cls, double s) { chunk_s[prec_index(prec)][cls] = s; }
 double CostModel::tile(int prec, int cls) const { return tile_s[prec_index(prec)][cls]; }
 double CostModel::first(int prec, int cls) const { return first_s[prec_index(prec)][cls]; }
 void CostModel::set(int prec, int cls, double s) { tile_s[prec_index(prec)][cls] = s; }
@@ -242,7 +259,7 @@ static const char* prec_key(int prec) { return prec == PREC_FP32 ? "fp32" : prec
 
 // Minimal reader of the table pa_tune writes:
 //   {"launch": s, "direct": s, "direct_launch": s,
-//    "fp32": {"<L>": [tile_s, first_s], ...}, "fp64": {...}}
+//    "fp32": {"<L>": [tile_s, first_s], ...}, "fp64": {...}, "fp32_chunk": {"<L>": chunk_s, ...}}
 // (a plain number instead of the pair sets tile_s only).
 int load_tune_table(CostModel& cm, const char* path) {
     FILE* f = fopen(path, "r");
@@ -272,8 +289,24 @@ int load_tune_table(CostModel& cm, const char* path) {
         if (v >= 0 && v < 1e-2) cm.direct_launch_s = v;
     }
     for (int prec : {PREC_FP32, PREC_FP64, PREC_NTT}) {
+        // "<prec>_chunk": {"<L>": chunk_s, ...} (absent in older tables)
+        const size_t ca = text.find(std::string("\"") + prec_key(prec) + "_chunk\"");
+        if (ca != std::string::npos) {
+            const size_t o = text.find('{', ca), e = text.find('}', ca);
+            if (o == std::string::npos || e == std::string::npos || e < o) return -1;
+            const std::string body = text.substr(o + 1, e - o - 1);
+            for (int k = kMinClassId; k <= kMaxClassId; ++k) {
+                ClassGeom g;
+                if (!class_geometry(prec, k, &g)) continue;
+                const std::string key = "\"" + std::to_string(g.L) + "\":";
+                const size_t p = body.find(key);
+                if (p == std::string::npos) continue;
+                const double v = strtod(body.c_str() + p + key.size(), nullptr);
+                if (v > 0 && v < 10.0) cm.set_chunk(prec, k, v);
+            }
+        }
         const std::string tag = std::string("\"") + prec_key(prec) + "\"";
-        const size_t at = text.find(tag);
+        const size_t at = text.find(tag + ":");
         if (at == std::string::npos) continue;
         const size_t open = text.find('{', at), close = text.find('}', at);
         if (open == std::string::npos || close == std::string::npos || close < open) return -1;
@@ -337,6 +370,21 @@ bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostMode
            2.0 * (direct_cost(n, m, cm) - 1.1 * cm.direct_launch_s) < fft.cost - cm.first(fft.prec, fft.cls);
 }
 
+// Classes whose row pass sums the products of several chunks: those with
+// wave-level rows (from 2^20 points on).
+static bool class_sums(int prec, int cls) { return prec != PREC_NTT && class_len(cls) >= (1ull << 20); }
+
+// Chunks of one group: at most 64, in equal groups, and for FP32 no more than
+// keep the modeled error of the sum within the limit of groups.
+static uint64_t group_chunks(int prec, uint64_t L, uint64_t Bi, uint64_t nchunks) {
+    uint64_t most = 64;
+    if (prec == PREC_FP32) {
+        const double r = kGroupErrorLimit / error_bound(prec, L, Bi);
+        most = std::min<uint64_t>(most, (uint64_t)std::max(1.0, std::floor(r * r)));
+    }
+    return ceil_div(nchunks, ceil_div(nchunks, most));
+}
+
 bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out) {
     ClassGeom g;
     if (n == 0 || m == 0 || !class_geometry(prec, cls, &g)) return false;
@@ -348,6 +396,7 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
         const double cap = std::floor((kPlanErrorLimit / per) * (kPlanErrorLimit / per) - (double)L);
         if (cap < (double)bi_cap) bi_cap = (uint64_t)std::max(0.0, cap);
     }
+    const double tile = cm.tile(prec, cls), chunk = class_sums(prec, cls) ? cm.chunk(prec, cls) : tile;
     TilePlan best;
     bool found = false;
     const uint64_t max_outs = std::min<uint64_t>(ceil_div(m, 64), 1u << 14);
@@ -355,35 +404,38 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
     const uint64_t min_chunks = ceil_div(n, std::min<uint64_t>(L, bi_cap == 0 ? 1 : bi_cap));
     // fewer than ceil(m / L) windows cannot fit a window in L
     for (uint64_t w = std::max<uint64_t>(1, ceil_div(m, L)); w <= std::max<uint64_t>(1, max_outs); ++w) {
-        // every later candidate has >= w windows and >= min_chunks chunks
-        if (found && w * min_chunks >= best.tiles()) break;
+        // every later candidate has >= w windows of >= min_chunks chunks
+        if (found && (double)w * (tile + (double)(min_chunks - 1) * chunk) >= best.cost) break;
         uint64_t Bo = (w == 1) ? m : round_up64(ceil_div(m, w));
         if (Bo == last_bo) continue;
         last_bo = Bo;
         if (Bo > L) continue;
-        const uint64_t nouts = ceil_div(m, Bo);
-        uint64_t bi_max = std::min<uint64_t>(L - Bo + 1, bi_cap);
+        TilePlan p;
+        p.nouts = ceil_div(m, Bo);
+        const uint64_t bi_max = std::min<uint64_t>(L - Bo + 1, bi_cap);
         if (bi_max == 0) continue;
-        const uint64_t nchunks = ceil_div(n, bi_max);
-        const uint64_t Bi = ceil_div(n, nchunks);
-        const uint64_t tiles = nchunks * nouts;
-        if (!found || tiles < best.tiles()) {
+        p.nchunks = ceil_div(n, bi_max);
+        p.Bi = ceil_div(n, p.nchunks);
+        p.Bo = Bo;
+        p.cgroup = class_sums(prec, cls) ? group_chunks(prec, L, p.Bi, p.nchunks) : 1;
+        const double groups = (double)(ceil_div(p.nchunks, p.cgroup) * p.nouts);
+        p.cost = groups * tile + ((double)p.tiles() - groups) * chunk;
+        if (!found || p.cost < best.cost) {
             found = true;
-            best.prec = prec;
-            best.cls = cls;
-            best.L = L;
-            best.Bi = Bi;
-            best.Bo = Bo;
-            best.nchunks = nchunks;
-            best.nouts = nouts;
+            best = p;
         }
-        if (nouts == 1 && nchunks == 1) break;
+        if (best.nouts == 1 && best.nchunks == 1) break;
     }
     if (!found) return false;
-    best.bound = error_bound(prec, L, best.Bi);
-    best.rigorous = rigorous_bound(prec, L, best.Bi, best.Bo);
+    best.prec = prec;
+    best.cls = cls;
+    best.L = L;
+    // the errors of a group's summed products add up: about as independent
+    // noise in the model, in full in the worst case
+    best.bound = error_bound(prec, L, best.Bi) * std::sqrt((double)best.cgroup);
+    best.rigorous = rigorous_bound(prec, L, best.Bi, best.Bo) * (double)best.cgroup;
     if (best.bound > kPlanErrorLimit) return false;   // not reached by FP32 up to 2^24
-    best.cost = (double)best.tiles() * cm.tile(prec, cls) + cm.first(prec, cls);
+    best.cost += cm.first(prec, cls);
     *out = best;
     return true;
 }

@@ -32,20 +32,24 @@ int class_ids(int prec, int* ids, int cap_logL = 24);
 // A key of the environment settings above (plan caches depend on them).
 uint64_t class_filter_key();
 
-// Cost of a class's launches (seconds), by prec and class id: a launch of T
-// tiles costs first_s + T tile_s.  tile_s is the marginal cost of a tile on a
-// full device; first_s the rest of a one-tile launch (launch latency, ramp-up,
+// Cost of a class's launches (seconds), by prec and class id: a launch of G
+// groups with T tiles costs first_s + G tile_s + (T - G) chunk_s.  tile_s is the
+// marginal cost of a tile with its inverse on a full device, chunk_s that of a
+// further chunk whose product joins the same inverse; first_s the rest of a one-tile launch (launch latency, ramp-up,
 // and the part of the device one tile leaves idle).  Filled from tuning data
 // when present, else from the built-in model.
 struct CostModel {
     double tile_s[3][64];   // [0] FP32, [1] FP64, [2] NTT; index class id
     double first_s[3][64];  // extra cost of a launch (its first tile)
+    double chunk_s[3][64];  // marginal cost of a further chunk of a group (0: 0.7 tile_s)
     double launch_s;        // launch cost of a class without its own first_s
     double direct_s;        // direct GF(2) path: seconds per output per 32-bit key word
     double direct_launch_s; // direct GF(2) path: fixed cost of a job (its launches)
     CostModel();
     double tile(int prec, int cls) const;
     double first(int prec, int cls) const;
+    double chunk(int prec, int cls) const;
+    void set_chunk(int prec, int cls, double s);
     void set(int prec, int cls, double s);
     void set_first(int prec, int cls, double s);
 };
@@ -61,8 +65,9 @@ struct TilePlan {
     int prec = 0, cls = 0;
     uint64_t L = 0;        // FFT length of the class
     uint64_t Bi = 0, Bo = 0, nchunks = 0, nouts = 0;
+    uint64_t cgroup = 1;   // chunks whose products are summed before one inverse
     double bound = 0, cost = 0;
-    double rigorous = 0;   // worst-case rounding bound of a tile (any input bits)
+    double rigorous = 0;   // worst-case rounding bound of a group (any input bits)
     uint64_t tiles() const { return nchunks * nouts; }
 };
 
@@ -85,6 +90,11 @@ double error_kappa();
 // The admissible error for a floating-point plan before the a-posteriori
 // certificate (half the rounding margin of 0.5).
 constexpr double kPlanErrorLimit = 0.25;
+
+// The admissible modeled error of a group's sum of products (lower than a single
+// tile's: measured maxima reach 0.73 of the model, and the certificate rejects
+// 0.125).
+constexpr double kGroupErrorLimit = 0.15;
 
 // Modeled time of the direct GF(2) path for one job: a fixed cost and a cost per
 // output (in blocks of 256) and key word (ceil(n/32), rounded up to 4), plus 10%

@@ -183,7 +183,7 @@ void Ctx::serve_loop() {
                     dj[k] = DirectJob{batch[k]->seed, batch[k]->key, batch[k]->out, ns[k], ms[k], 0, 0, 0, 0};
                 pa_status s = ln.direct_batch(this, dj, &lane_stats[i]);
                 ln.jobs.clear();
-                ln.total_tiles = 0;
+                ln.total_groups = 0;
                 if (s == PA_OK && !ln.done && hipEventCreateWithFlags(&ln.done, hipEventDisableTiming) != hipSuccess)
                     s = PA_EDEVICE;
                 if (s == PA_OK && hipEventRecord(ln.done, ln.stream) != hipSuccess) s = PA_EDEVICE;

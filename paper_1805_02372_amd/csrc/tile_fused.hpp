@@ -157,7 +157,7 @@ template <typename T, int L>
 struct ClassImplF {
     static_assert(L <= (1 << fused_max_logL<T>()), "one-kernel tile length");
     static bool clears(const JobTable& jt) {
-        return jt.njobs == 0 ? (jt.one.nchunks > 1 && !jt.one.no_clear) : jt.clears != 0;
+        return jt.njobs == 0 ? (jt.one.nchunks > jt.one.cgroup && !jt.one.no_clear) : jt.clears != 0;
     }
     static int pass1(const JobTable& jt, void*, uint32_t*, TileMeta*, const Tables&, void* stream) {
         if (!clears(jt)) return 1;

@@ -43,20 +43,31 @@ static pa_status save_json(const CostModel& cm, const std::vector<int>& precs, c
             first = false;
         }
         fprintf(f, "}");
+        if (precs[i] == PREC_NTT) continue;
+        fprintf(f, ", \"%s_chunk\": {", prec_key(precs[i]));
+        first = true;
+        for (int k = kMinClassId; k <= kMaxClassId; ++k) {
+            ClassGeom g;
+            if (!class_geometry(precs[i], k, &g)) continue;
+            fprintf(f, "%s\"%llu\": %.9g", first ? "" : ", ", (unsigned long long)g.L, cm.chunk(precs[i], k));
+            first = false;
+        }
+        fprintf(f, "}");
     }
     fprintf(f, "}\n");
     return fclose(f) == 0 ? PA_OK : PA_EINVAL;
 }
 
-// Kernel time (s) of one launch of `count` identical one-tile jobs of class id k.
-static pa_status time_launch(Ctx* c, int prec, int k, const TilePlan& p, int count, uint64_t* dseed,
+// Kernel time (s) of one launch of `count` identical jobs of class id k, with n
+// key bits and half a tile of outputs each.
+static pa_status time_launch(Ctx* c, int prec, int k, const TilePlan& p, uint64_t n, int count, uint64_t* dseed,
                              uint64_t* dkey, uint64_t* douts, uint64_t out_words, int reps, double* best) {
     const uint64_t L = class_len(k);
     *best = 1e30;
     for (int r = 0; r <= reps; ++r) {  // the first run warms tables and workspace
         std::vector<JobDesc> jobs(count);
         for (int q = 0; q < count; ++q)
-            fill_job(&jobs[q], dseed, dkey, douts + q * out_words, L / 2, L / 2 + 1, p);
+            fill_job(&jobs[q], dseed, dkey, douts + q * out_words, n, L / 2 + 1, p);
         pa_stats ps{};
         pa_status st = c->main.launch(c, prec, k, jobs, true, true, &ps);
         if (st == PA_OK) st = c->main.finish(c, PA_TIMING | PA_NO_FALLBACK, &ps, nullptr);
@@ -87,7 +98,7 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
     constexpr int kMany = 4;   // tiles of the longer launch from 2^20 points on
     const uint64_t maxL = 1ull << 24;
     // synthetic job: n = L/2, m = L/2 + 1 fills one tile of class L exactly
-    const uint64_t words = (maxL + 64) / 64 + 2, out_words = maxL / 2 / 64 + 2;
+    const uint64_t words = (maxL + maxL / 2 + 64) / 64 + 2, out_words = maxL / 2 / 64 + 2;
     std::vector<uint64_t> host(2 * words);
     uint64_t s = 0x9E3779B97F4A7C15ull;
     for (uint64_t& w : host) w = xorshift(s);
@@ -118,8 +129,8 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
             double t1 = 0, tn = 0;
             const int many = L <= (1ull << 20) ? 4 * kMany : kMany;
             const uint64_t stride = L / 2 / 64 + 2;   // many * stride <= kMany * out_words
-            st = time_launch(c, prec, k, p, 1, dseed, dkey, douts, stride, reps, &t1);
-            if (st == PA_OK) st = time_launch(c, prec, k, p, many, dseed, dkey, douts, stride, reps, &tn);
+            st = time_launch(c, prec, k, p, L / 2, 1, dseed, dkey, douts, stride, reps, &t1);
+            if (st == PA_OK) st = time_launch(c, prec, k, p, L / 2, many, dseed, dkey, douts, stride, reps, &tn);
             if (st != PA_OK) {
                 buf.release(c);
                 return st;
@@ -127,6 +138,17 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
             if (t1 >= 1e30 || tn >= 1e30) continue;
             const double marginal = std::max((tn - t1) / (many - 1), 0.01 * t1);
             cm.set(prec, k, marginal);
+            // the same jobs with a second chunk summed into each inverse
+            TilePlan p2;
+            double t2 = 1e30;
+            if (plan_at_class(L, L / 2 + 1, prec, k, cm, &p2) && p2.nchunks == 2 && p2.nouts == 1 && p2.cgroup == 2) {
+                st = time_launch(c, prec, k, p2, L, many, dseed, dkey, douts, stride, reps, &t2);
+                if (st != PA_OK) {
+                    buf.release(c);
+                    return st;
+                }
+                if (t2 < 1e30) cm.set_chunk(prec, k, std::min(marginal, std::max((t2 - tn) / many, 0.2 * marginal)));
+            }
             cm.set_first(prec, k, std::max(t1 - marginal, 0.0));
             fixed.push_back(std::max(t1 - marginal, 0.0));
         }

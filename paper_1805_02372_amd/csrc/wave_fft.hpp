@@ -16,14 +16,6 @@
 
 namespace pa {
 
-// Returns p unchanged, but the compiler cannot see through it: loads through
-// the result cannot be hoisted above this point (keeps each stage's twiddle
-// loads next to their use instead of all of them live at once).
-template <typename P> __device__ __forceinline__ P opaque(P p) {
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
