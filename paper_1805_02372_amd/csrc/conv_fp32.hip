@@ -16,6 +16,12 @@ namespace pa {
     {ClassCfg{32, LOGL, N1, N2, ClassImpl2<float, N1, N2>::C1, ClassImpl2<float, N1, N2>::C3, 16,        \
               ClassImpl2<float, N1, N2>::kWsExtra, true},                                                      \
      &ClassImpl2<float, N1, N2>::pass1, &ClassImpl2<float, N1, N2>::pass2, &ClassImpl2<float, N1, N2>::pass3}
+#define PA_CLASS2S(LOGL, N1, N2) \
+    {ClassCfg{32, LOGL, N1, N2, ClassImpl2<float, N1, N2>::C1, ClassImpl2<float, N1, N2>::C3, 16,        \
+              ClassImpl2<float, N1, N2>::kWsExtra, true},                                                      \
+     &ClassImpl2<float, N1, N2>::pass1, &ClassImpl2<float, N1, N2>::pass2, &ClassImpl2<float, N1, N2>::pass3,  \
+     &ClassImpl2<float, N1, N2>::shared_pass1, &ClassImpl2<float, N1, N2>::shared_pass2,                       \
+     &ClassImpl2<float, N1, N2>::shared_pass3, &ClassImpl2<float, N1, N2>::shared_bytes}
 #define PA_FUSED(LOGL) \
     {ClassCfg{32, LOGL, 1 << LOGL, 1, 1 << LOGL, 1 << LOGL, 16}, &ClassImplF<float, 1 << LOGL>::pass1, \
      &ClassImplF<float, 1 << LOGL>::pass2, &ClassImplF<float, 1 << LOGL>::pass3}
@@ -30,9 +36,9 @@ static const ClassKernels kClasses32[] = {
     PA_CLASS(18, 512, 512),
     PA_CLASS(19, 1024, 512),
     PA_CLASS2(20, 4096, 256),
-    PA_CLASS2(21, 4096, 512),
-    PA_CLASS2(22, 4096, 1024),
-    PA_CLASS2(23, 4096, 2048),
+    PA_CLASS2S(21, 4096, 512),
+    PA_CLASS2S(22, 4096, 1024),
+    PA_CLASS2S(23, 4096, 2048),
     PA_CLASS2(24, 8192, 2048),
 };
 

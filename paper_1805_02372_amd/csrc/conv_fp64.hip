@@ -13,7 +13,8 @@ namespace pa {
     {ClassCfg{64, LOGL, N1, N2, 4, 8, 16}, &ClassImpl<double, N1, N2, 4, 8, 16, 16>::pass1, \
      &ClassImpl<double, N1, N2, 4, 8, 16, 16>::pass2, &ClassImpl<double, N1, N2, 4, 8, 16, 16>::pass3}
 #define PA_CLASS2(LOGL, N1, N2) \
-    {ClassCfg{64, LOGL, N1, N2, ClassImpl2<double, N1, N2>::C1, ClassImpl2<double, N1, N2>::C3, 16, 0, true}, \
+    {ClassCfg{64, LOGL, N1, N2, ClassImpl2<double, N1, N2>::C1, ClassImpl2<double, N1, N2>::C3, 16, \
+              ClassImpl2<double, N1, N2>::kWsExtra, true}, \
      &ClassImpl2<double, N1, N2>::pass1, &ClassImpl2<double, N1, N2>::pass2, &ClassImpl2<double, N1, N2>::pass3}
 #define PA_FUSED(LOGL) \
     {ClassCfg{64, LOGL, 1 << LOGL, 1, 1 << LOGL, 1 << LOGL, 16}, &ClassImplF<double, 1 << LOGL>::pass1, \

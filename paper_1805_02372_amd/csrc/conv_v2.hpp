@@ -2,11 +2,11 @@
 // the same three passes as conv_kernels.hpp (see there for the mathematics),
 // restructured around wave-level transforms (wave_fft.hpp):
 //
-//  * pass 1: the workgroup stages the key/seed bits of its C columns in LDS
-//    (one funnel-shifted word per row instead of one load per point), each
-//    wave transforms G whole columns (n2 <= 1024) or one half of a column
-//    after a radix-2 split (n2 = 2048), and an LDS transpose turns the
-//    column-major results into C-element row segments for the stores.
+//  * pass 1: a small kernel transposes the key and seed bits into bit planes
+//    (one word per lane and sequence), each wave transforms G whole columns
+//    (n2 <= 1024) or one half of a column after a radix-2 split (n2 = 2048),
+//    and an LDS transpose turns the column-major results into C-element row
+//    segments for the stores.
 //  * pass 2: a row of 8192 points is a radix-8 stage across the 8 waves
 //    (decimation in frequency, registers only) followed by one 1024-point
 //    transform per wave; the inverse runs the same steps in reverse.  Two
@@ -23,14 +23,14 @@
 namespace pa {
 
 template <typename T, int N2> struct P1Geom {
-    static constexpr int W = N2 > 1024 ? N2 / 1024 : 1;    // waves per column
+    static constexpr int H = N2 > 1024 ? N2 / 1024 : 1;    // halves of a column
+    static constexpr bool WGH = H == 2 && sizeof(T) == 4;  // each half in a workgroup of its own
     static constexpr int M = N2 > 1024 ? 1024 : N2;        // wave transform size
     static constexpr int G = 1024 / M;                     // columns per wave
-    static constexpr int WAVES = (sizeof(T) == 4 && W > 1) ? 16 : 8;
-    static constexpr int C = WAVES * G / W;                // columns per workgroup
+    static constexpr int WAVES = 8;
+    static constexpr int C = WAVES * G / (WGH ? 1 : H);    // columns per workgroup
     static constexpr int THREADS = WAVES * 64;
-    static_assert(W <= 2, "column length up to 2048");
-    static constexpr bool kPlanes = sizeof(T) == 4 && C == 8;   // bits from the planes of k2_bits
+    static_assert(H <= 2, "column length up to 2048");
     static_assert(C <= 64 && (C & (C - 1)) == 0, "column block");
 };
 
@@ -83,277 +83,310 @@ __device__ __forceinline__ uint32_t xcd_block() {
 }
 
 // ------------------------------------------------------------------ pass 1
-// Bit planes.  A pass-1 workgroup of 8 columns needs one byte of key bits and
-// one of seed bits from every row of the tile, rows 1 KB apart: read in place,
-// each byte costs a cache line on its way to the compute unit, and staging
-// them took a fifth of pass 1.  For the FP32 classes with 8 columns per
-// workgroup a small kernel first transposes them, coalesced, into two planes
-// per tile after the launch's tiles in the workspace: byte cb n2 + r of the
-// key plane holds the placed key bits at positions 8 cb + 8192 r .. + 7 (bit
-// q: position + q), the seed plane the seed bits there (zero from the window
-// end on).  Pass 1 then reads n2 contiguous bytes of each.
+// What a tile transforms: two bit sequences, the real and the imaginary part.
+// An ordinary tile has a key chunk and its seed slice; the tiles of a job with
+// shared spectra (SharedJob) have two key chunks or two seed slices.
+//
+// Position t (mod L) of a sequence holds source bit j0 + ((t + off) mod L) when
+// that index is below len: a key chunk (off = bi - 1: placed so that the kept
+// window starts at index 0) or a seed slice (off = 0).  Key bits are the values
+// 0 and 1, seed bits -1 and 1, and 0 from position len on.
+struct BitSeq {
+    const uint64_t* src;
+    uint64_t nw, j0;       // source words, first bit
+    uint32_t off, len;
+    bool seed;
+};
+struct TileBits {
+    BitSeq s[2];
+};
+__device__ __forceinline__ BitSeq key_seq(const JobDesc& jd, uint64_t j0, uint64_t bi) {
+    return BitSeq{jd.key, (jd.n + 63) >> 6, j0, bi ? (uint32_t)(bi - 1) : 0u, (uint32_t)bi, false};
+}
+__device__ __forceinline__ BitSeq seed_seq(const JobDesc& jd, uint64_t j0, uint64_t len) {
+    return BitSeq{jd.seed, (jd.n + jd.m - 1 + 63) >> 6, j0, 0u, (uint32_t)len, true};
+}
+// Tile lt of a shared-spectra launch: key packs (chunks 2 lt, 2 lt + 1 of the
+// group), then seed packs (slices b0 + 2 q, b0 + 2 q + 1).
+__device__ __forceinline__ TileBits shared_bits(const JobTable& jt, uint32_t lt) {
+    const JobDesc& jd = jt.one;
+    const SharedJob& sh = jt.shared;
+    TileBits r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (lt < sh.kpacks) {
+            const uint32_t c = 2 * lt + h;
+            uint64_t lo = 0, bi = 0;
+            if (c < sh.chunks) {
+                const uint64_t hi = jd.n - (uint64_t)(sh.chunk0 + c) * jd.Bi;
+                lo = hi > jd.Bi ? hi - jd.Bi : 0;
+                bi = hi - lo;
+            }
+            r.s[h] = key_seq(jd, lo, bi);
+        } else {
+            const uint64_t at = (uint64_t)(sh.chunk0 + 2 * (lt - sh.kpacks) + h) * jd.Bi, all = jd.n + jd.m - 1;
+            const uint64_t left = at < all ? all - at : 0, most = 2 * jd.Bi - 1;
+            r.s[h] = seed_seq(jd, left ? at : 0, left < most ? left : most);
+        }
+    }
+    return r;
+}
+__device__ __forceinline__ TileBits tile_bits(const JobDesc& jd, const TileGeo& g) {
+    TileBits r;
+    r.s[0] = key_seq(jd, g.j0, g.bi);
+    r.s[1] = seed_seq(jd, g.sigma, g.bi + g.bo - 1);
+    return r;
+}
+
+// Bit planes.  A lane of pass 1 takes rows j, j + NJ, j + 2 NJ, .. of one
+// column (NJ = N2 / 16 lanes per column, at most 64); read in place, each of its
+// bits is in another word, N1 bits apart.  k2_bits transposes the two sequences
+// of every tile into planes after the launch's tiles in the workspace: N2 bits
+// per column, as NJ words of N2 / NJ bits (16, or 32 for N2 = 2048); bit i of
+// word j of column t1 is position t1 + N1 (j + NJ i).  A lane of pass 1 then
+// loads one word of each plane, a wave consecutive ones.
 template <int N1, int N2> struct BitPlanes {
+    static constexpr int NJ = N2 >= 1024 ? 64 : N2 / 16, BITS = N2 / NJ;
+    static_assert(BITS == 16 || BITS == 32, "plane words");
+    using Word = std::conditional_t<BITS == 32, uint32_t, uint16_t>;
     static constexpr size_t kPlane = (size_t)N2 * (N1 / 8);
-    static constexpr size_t kTile = 2 * kPlane;   // key plane, then seed plane
+    static constexpr size_t kTile = 2 * kPlane;
     template <typename T>
-    __device__ static const uint8_t* key(const cx<T>* ws, uint32_t ntiles, uint32_t lt) {
+    __device__ static const uint8_t* base(const cx<T>* ws, uint32_t ntiles, uint32_t lt) {
         return reinterpret_cast<const uint8_t*>(ws + (size_t)ntiles * ((size_t)N1 * N2)) + (size_t)lt * kTile;
     }
 };
 
-// 8 x 8 byte transpose: byte c of x[q] moves to byte q of x[c].
-__device__ __forceinline__ void transpose8x8(uint64_t (&x)[8]) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint64_t a = x[q], b = x[q + 4];
-        x[q] = (a & 0xFFFFFFFFull) | (b << 32);
-        x[q + 4] = (a >> 32) | (b & 0xFFFFFFFF00000000ull);
-    }
-    constexpr uint64_t m16 = 0x0000FFFF0000FFFFull, m8 = 0x00FF00FF00FF00FFull;
-#pragma unroll
-    for (int q = 0; q < 8; q += (q & 1) ? 3 : 1) {   // q = 0, 1, 4, 5
-        const uint64_t a = x[q], b = x[q + 2];
-        x[q] = (a & m16) | ((b & m16) << 16);
-        x[q + 2] = ((a >> 16) & m16) | (b & ~m16);
-    }
-#pragma unroll
-    for (int q = 0; q < 8; q += 2) {
-        const uint64_t a = x[q], b = x[q + 1];
-        x[q] = (a & m8) | ((b & m8) << 8);
-        x[q + 1] = ((a >> 8) & m8) | (b & ~m8);
-    }
+// 64 bits of a sequence at positions p .. p + 63 (p a multiple of 64): the part
+// before the wrap to index 0, then the part after it.  Word indices are clamped
+// to the source and every load is unconditional, so that a lane issues all its
+// loads back to back.
+struct Seq64 {
+    uint64_t w1, w2;       // first words of the two parts
+    uint32_t s1, s2, c1, c2, fs;
+};
+__device__ __forceinline__ Seq64 seq64(const BitSeq& q, uint32_t L, uint32_t p) {
+    uint32_t u = p + q.off;
+    if (u >= L) u -= L;
+    Seq64 r;
+    r.fs = L - u < 64u ? L - u : 64u;
+    r.c1 = u < q.len ? (q.len - u < r.fs ? q.len - u : r.fs) : 0u;
+    r.c2 = q.len < 64u - r.fs ? q.len : 64u - r.fs;
+    const uint64_t b = q.j0 + u;
+    r.w1 = b >> 6;
+    r.s1 = (uint32_t)b & 63u;
+    r.w2 = q.j0 >> 6;
+    r.s2 = (uint32_t)q.j0 & 63u;
+    return r;
+}
+__device__ __forceinline__ uint64_t low_mask(uint32_t cnt) { return cnt >= 64u ? ~0ull : (1ull << cnt) - 1ull; }
+__device__ __forceinline__ uint64_t funnel64(uint64_t lo, uint64_t hi, uint32_t s) {
+    return (lo >> s) | ((hi << 1) << (63u - s));   // s = 0: hi drops out
 }
 
-// 64-bit extractions for k2_bits, split into the word loads and the shifts,
-// so that a thread issues all its loads back to back: both words of every
-// extraction are loaded (indices clamped to the array of nw words) and both
-// are used whatever the shift, so no load sits behind a branch.  Same results
-// as extract_bits / placed_key_bits<64>.
-struct Ext64 {
-    uint64_t w;     // first word
-    uint32_t s;     // bit offset in it
-    uint64_t mask;  // cnt low bits
-};
-__device__ __forceinline__ Ext64 ext64(uint64_t pos, uint32_t cnt) {
-    return Ext64{pos >> 6, (uint32_t)(pos & 63), cnt >= 64 ? ~0ull : ((1ull << (cnt & 63)) - 1ull)};
-}
-__device__ __forceinline__ void ext64_load(const uint64_t* __restrict__ a, uint64_t nw, const Ext64& e,
-                                           uint64_t& lo, uint64_t& hi) {
-    lo = a[e.w < nw ? e.w : nw - 1];
-    hi = a[e.w + 1 < nw ? e.w + 1 : nw - 1];
-}
-__device__ __forceinline__ uint64_t ext64_value(const Ext64& e, uint64_t lo, uint64_t hi) {
-    return ((lo >> e.s) | ((hi << 1) << (63 - e.s))) & e.mask;   // s = 0: hi drops out
-}
-// The two extractions of the placed key bits at positions s0 .. s0 + 63
-// (position t holds key bit j0 + ((t + bi - 1) mod L) when that index is < bi):
-// the positions before the wrap to u = 0, then those after it, shifted by fs.
-struct PlacedKey64 {
-    Ext64 e1, e2;
-    uint32_t fs;
-};
-__device__ __forceinline__ PlacedKey64 placed_key64(uint64_t j0, uint32_t bi, uint32_t L, uint32_t s0) {
-    uint32_t u0 = s0 + bi - 1;
-    if (u0 >= L) u0 -= L;
-    const uint32_t fs = u0 + 64 <= L ? 64u : L - u0;
-    const uint32_t c1 = u0 < bi ? (bi - u0 < fs ? bi - u0 : fs) : 0u;
-    const uint32_t c2 = fs < 64 ? (bi < 64 - fs ? bi : 64 - fs) : 0u;
-    return PlacedKey64{ext64(j0 + u0, c1), ext64(j0, c2), fs & 63u};   // c2 = 0 when fs = 64
+// 64 x 64 bit transpose across a wave: lane r holds row r (bit c: column c) and
+// gets column r (bit c: row c).
+__device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
+    constexpr uint64_t low[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0F0F0F0F0F0F0F0Full,
+                                 0x00FF00FF00FF00FFull, 0x0000FFFF0000FFFFull, 0x00000000FFFFFFFFull};
+#pragma unroll
+    for (int q = 5; q >= 0; --q) {
+        const int k = 1 << q;
+        const uint64_t y = __shfl_xor((unsigned long long)x, k);
+        x = (lane & k) ? ((x & ~low[q]) | ((y >> k) & low[q])) : ((x & low[q]) | ((y & low[q]) << k));
+    }
+    return x;
 }
 
-// Workgroup: 128 rows x 8 word columns (64 positions each) of one tile, both
-// planes, 256 threads.  Loads: 8 consecutive lanes take 8 consecutive words
-// of one row (64 contiguous bytes of key or seed), 4 rows per lane, every
-// load of a lane issued before the first wait.  The words go to LDS; then
-// each lane of one half of the workgroup (key plane, seed plane) reads the
-// word column of 8 consecutive rows, transposes the 8 x 8 bytes and stores
-// one 64-bit word (8 rows) per byte column, so that 16 consecutive lanes write
-// one whole 128-byte line.
-constexpr int kBitsRows = 128, kBitsCols = 8;
-// LDS slot of (row r, word w): bits 3..4 of r permute the rows within each
-// 256-byte bank span and bits 3..5 of r are XOR-ed into the word, so that both
-// the row-wise writes and the column-wise reads of 64 lanes touch every bank
-// pair at most twice.
-__device__ __forceinline__ int bits_slot(int r, int w) {
-    return (r ^ ((r >> 3) & 3)) * kBitsCols + (w ^ ((r >> 3) & 7));
-}
+// One wave: 64 rows (64 / BITS words j of every column, lane = (j, i)) by
+// kBitsCols groups of 64 columns of one plane.  Each lane reads consecutive
+// words of its row; a transpose turns them into 8 plane bytes per column.
+constexpr int kBitsCols = 4;
 template <int N1, int N2>
 __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict__ planes) {
-    constexpr int R = kBitsRows, WC = kBitsCols, RPL = R * WC / 256;   // rows per lane
-    constexpr int NRB = N2 / R, NWB = N1 / 64 / WC;
+    using Pl = BitPlanes<N1, N2>;
     constexpr uint32_t L = (uint32_t)N1 * N2;
-    static_assert(N2 % R == 0 && (N1 / 64) % WC == 0 && RPL == 4 && WC * 16 * 2 == 256, "workgroup block");
-    __shared__ uint64_t wbits[2][R * WC];   // key words, seed words
-    const uint32_t b = blockIdx.x;
-    const uint32_t lt = b / (NRB * NWB), rem = b % (NRB * NWB);
-    const uint32_t rb = rem / NWB, wb = rem % NWB;
-    const uint32_t t = jt.tile0 + lt;
-    const JobDesc jd = find_job(jt, t);
-    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
-    const uint32_t bi = (uint32_t)g.bi, win = (uint32_t)(g.bi + g.bo - 1);
-    const uint64_t nkw = (jd.n + 63) >> 6, nsw = (jd.n + jd.m - 1 + 63) >> 6;   // key and seed words
-    const int tid = threadIdx.x;
-    {
-        const int wl = tid & (WC - 1);
-        const uint32_t wc = wb * WC + (uint32_t)wl;
-        PlacedKey64 pk[RPL];
-        Ext64 se[RPL];
+    constexpr int NRC = N2 / 64, NCC = N1 / 64 / kBitsCols;   // row and column blocks of a plane
+    static_assert(NRC % 4 == 0 && N1 % (64 * kBitsCols) == 0, "blocks");
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint32_t rc = wave % NRC, cc = (wave / NRC) % NCC, pl = (wave / (NRC * NCC)) & 1u;
+    const uint32_t lt = wave / (2 * NRC * NCC);
+    TileBits tb;
+    if (jt.shared.kpacks) {
+        tb = shared_bits(jt, lt);
+    } else {
+        const JobDesc jd = find_job(jt, jt.tile0 + lt);
+        tb = tile_bits(jd, tile_geo(jd, jt.tile0 + lt - jd.tile_begin));
+    }
+    const BitSeq q = pl ? tb.s[1] : tb.s[0];
+    const uint32_t j = rc * (64 / Pl::BITS) + (uint32_t)(lane / Pl::BITS), i = (uint32_t)(lane % Pl::BITS);
+    const uint32_t p0 = cc * (64 * kBitsCols) + (uint32_t)N1 * (j + Pl::NJ * i);
+    uint64_t v[kBitsCols];
+    if (q.len == 0) {   // no such sequence (a pack of one)
 #pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            const int rl = tid / WC + (256 / WC) * q;
-            const uint32_t s0 = wc * 64 + (uint32_t)N1 * (rb * R + (uint32_t)rl);
-            pk[q] = placed_key64(g.j0, bi, L, s0);
-            const uint32_t nv = s0 < win ? ((win - s0) < 64u ? (win - s0) : 64u) : 0u;
-            se[q] = ext64(g.sigma + s0, nv);
+        for (int c = 0; c < kBitsCols; ++c) v[c] = 0;
+    } else {
+        Seq64 e[kBitsCols];
+        uint64_t a[kBitsCols], b[kBitsCols], d[kBitsCols], f[kBitsCols];
+        const uint64_t last = q.nw - 1;
+#pragma unroll
+        for (int c = 0; c < kBitsCols; ++c) {
+            e[c] = seq64(q, L, p0 + 64u * c);
+            a[c] = q.src[e[c].w1 < last ? e[c].w1 : last];
+            b[c] = q.src[e[c].w1 + 1 < last ? e[c].w1 + 1 : last];
+            d[c] = q.src[e[c].w2 < last ? e[c].w2 : last];
+            f[c] = q.src[e[c].w2 + 1 < last ? e[c].w2 + 1 : last];
         }
-        uint64_t kw[RPL][4], sw[RPL][2];
 #pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            ext64_load(jd.key, nkw, pk[q].e1, kw[q][0], kw[q][1]);
-            ext64_load(jd.key, nkw, pk[q].e2, kw[q][2], kw[q][3]);
-            ext64_load(jd.seed, nsw, se[q], sw[q][0], sw[q][1]);
-        }
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            const int sl = bits_slot(tid / WC + (256 / WC) * q, wl);
-            wbits[0][sl] = ext64_value(pk[q].e1, kw[q][0], kw[q][1]) |
-                           (ext64_value(pk[q].e2, kw[q][2], kw[q][3]) << pk[q].fs);
-            wbits[1][sl] = ext64_value(se[q], sw[q][0], sw[q][1]);
+        for (int c = 0; c < kBitsCols; ++c) {
+            const uint64_t x = funnel64(a[c], b[c], e[c].s1) & low_mask(e[c].c1);
+            const uint64_t y = funnel64(d[c], f[c], e[c].s2) & low_mask(e[c].c2);
+            v[c] = x | (e[c].fs < 64u ? y << e[c].fs : 0ull);
         }
     }
-    __syncthreads();
-    const int pl = tid >> 7, p = tid & 15, wl = (tid >> 4) & (WC - 1);   // plane, rows 8 p .. 8 p + 7, word
-    uint64_t x[8];
+    uint8_t* dst = planes + (size_t)lt * Pl::kTile + (size_t)pl * Pl::kPlane + (size_t)rc * 8;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = wbits[pl][bits_slot(8 * p + i, wl)];
-    transpose8x8(x);
-    uint8_t* dst = planes + (size_t)lt * BitPlanes<N1, N2>::kTile + (size_t)pl * BitPlanes<N1, N2>::kPlane +
-                   (size_t)((wb * WC + (uint32_t)wl) * 8) * N2 + rb * R + 8 * p;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) *reinterpret_cast<uint64_t*>(dst + (size_t)c * N2) = x[c];
+    for (int c = 0; c < kBitsCols; ++c)
+        *reinterpret_cast<uint64_t*>(dst + (size_t)(cc * (64 * kBitsCols) + 64 * c + lane) * (N2 / 8)) =
+            transpose64(v[c], lane);
 }
 
+// Values of bit i of a plane word: a key bit, or a seed bit before the mask of
+// the slice's end (seed_mask).
+template <typename T> __device__ __forceinline__ T key_value(uint32_t w, int i) { return (T)((w >> i) & 1u); }
+template <typename T> __device__ __forceinline__ T seed_value(uint32_t w, int i);
+template <> __device__ __forceinline__ float seed_value<float>(uint32_t w, int i) {
+    return __uint_as_float(((w << (31 - i)) & 0x80000000u) ^ 0xBF800000u);
+}
+template <> __device__ __forceinline__ double seed_value<double>(uint32_t w, int i) {
+    return __hiloint2double((int)(((w << (31 - i)) & 0x80000000u) ^ 0xBFF00000u), 0);
+}
+
+// One component of the column's input: element i from plane bit i, or for a
+// column of two halves e +- (e + 1024) (bits i and i + 16).  Seed rows i >= valid
+// of this lane lie past the slice: 0.
+template <typename T, int H, bool SEED, bool MASK>
+__device__ __forceinline__ void column_values(T (&x)[16], uint32_t w, uint32_t valid, bool minus) {
+    const T sign = minus ? T(-1) : T(1);
+    auto value = [&](int i) -> T {
+        const T a = SEED ? seed_value<T>(w, i) : key_value<T>(w, i);
+        return MASK && (uint32_t)i >= valid ? T(0) : a;
+    };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = H == 1 ? value(i) : value(i) + sign * value(i + 16);
+}
+template <typename T, int H>
+__device__ __forceinline__ void column_input(T (&x)[16], uint32_t w, bool seed, uint32_t valid, bool minus) {
+    if (!seed) column_values<T, H, false, false>(x, w, valid, minus);
+    else if (__any(valid < 16u * H)) column_values<T, H, true, true>(x, w, valid, minus);
+    else column_values<T, H, true, false>(x, w, valid, minus);
+}
+
+// Column pass: a workgroup of WAVES waves takes C columns; each wave transforms
+// G whole columns (N2 <= 1024) or one half of a column (N2 = 2048, a radix-2
+// split in decimation in frequency: half ka, outputs k2 = 2 e + ka, is the
+// 1024-point transform of z(e) + z(e + 1024), or of (z(e) - z(e + 1024))
+// w_2048^e).  The halves of a column are two waves of one workgroup in FP64 and
+// two workgroups in FP32 (the LDS of one half: two workgroups per CU).
 template <typename T, int N1, int N2>
 __global__ void __launch_bounds__((P1Geom<T, N2>::THREADS))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
          const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
          int fshift) {
     using Gm = P1Geom<T, N2>;
-    constexpr int C = Gm::C, G = Gm::G, W = Gm::W, M = Gm::M, NJ = M / 16;
+    using Pl = BitPlanes<N1, N2>;
+    constexpr int C = Gm::C, G = Gm::G, H = Gm::H, M = Gm::M, NJ = M / 16;
+    constexpr bool WGH = Gm::WGH;
     constexpr uint32_t L = (uint32_t)N1 * N2;
-    constexpr int NCB = N1 / C;
-    constexpr int SLOTS = (Gm::WAVES * kWaveSlots > N2 * C) ? Gm::WAVES * kWaveSlots : N2 * C;
-    static_assert(2 * N2 * sizeof(uint64_t) <= SLOTS * sizeof(cx<T>), "bit rows fit the LDS union");
+    constexpr int NCB = N1 / C, CG = WGH ? 1 : H;   // halves of a column in one workgroup
+    constexpr int ROWS = N2 / (WGH ? H : 1);        // rows this workgroup writes
+    constexpr int HALF = M * C + 8;                 // transposition tile of one half (the second off the first's banks)
+    constexpr int TILE = CG * HALF;
+    constexpr int SLOTS = (Gm::WAVES * kWaveSlots > TILE) ? Gm::WAVES * kWaveSlots : TILE;
     static_assert(G * 16 * sizeof(Root64) <= kWaveSlots * sizeof(cx<T>), "twiddle factors fit a wave region");
     __shared__ __align__(16) cx<T> lds[SLOTS];
     __shared__ __align__(16) cx<T> st[wfft_lds_entries(M)];
     __shared__ uint32_t wsum;
-    uint64_t* kbits = reinterpret_cast<uint64_t*>(lds);   // consumed before the wave regions are used
-    uint64_t* sbits = kbits + N2;
 
-    const uint32_t blk = xcd_block();
-    const uint32_t lt = blk / NCB;
-    const uint32_t cb = blk % NCB;
-    const uint32_t t = jt.tile0 + lt;
-    const JobDesc jd = find_job(jt, t);
-    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+    const uint32_t blk = xcd_block(), lb = WGH ? blk >> 1 : blk;
+    const uint32_t lt = lb / NCB, cb = lb % NCB;
     const int tid = threadIdx.x;
-    const uint32_t bi = (uint32_t)g.bi, win = (uint32_t)(g.bi + g.bo - 1);
-    if (tid == 0) wsum = 0;
-    clear_window(g, cb, NCB, tid, Gm::THREADS);
-    wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
-    __syncthreads();
-
-    // stage the bits of this workgroup's C columns: rows r = tid + q * THREADS
-    constexpr int RPT = (N2 + Gm::THREADS - 1) / Gm::THREADS;
-    uint32_t pc = 0;
-    uint64_t kb[RPT], sb[RPT];
-    constexpr bool kPlanes = Gm::kPlanes;
-    const uint8_t* kp = nullptr;
-    if constexpr (kPlanes) kp = BitPlanes<N1, N2>::key(ws, jt.ntiles, lt) + (size_t)cb * N2;
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-        const int r = tid + q * Gm::THREADS;
-        kb[q] = 0;
-        sb[q] = 0;
-        if (r < N2) {
-            if constexpr (kPlanes) {
-                kb[q] = kp[r];
-                sb[q] = kp[BitPlanes<N1, N2>::kPlane + r];
-            } else {
-                const uint32_t s0 = cb * C + (uint32_t)N1 * (uint32_t)r;
-                kb[q] = placed_key_bits<C>(jd.key, g.j0, bi, L, s0);
-                const uint32_t nv = s0 < win ? ((win - s0) < (uint32_t)C ? (win - s0) : (uint32_t)C) : 0u;
-                sb[q] = extract_bits(jd.seed, g.sigma + s0, nv);
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-        const int r = tid + q * Gm::THREADS;
-        if (r < N2) {
-            kbits[r] = kb[q];
-            sbits[r] = sb[q];
-            pc += (uint32_t)__popcll(kb[q]);
-        }
-    }
-    atomicAdd(&wsum, pc);
-    __syncthreads();
-
     const int wv = tid >> 6, l = tid & 63;
     int f, ka = 0, j, grp;
-    if constexpr (W == 1) {
+    if constexpr (H == 1) {
         grp = l / NJ;
         j = l % NJ;
         f = wv * G + grp;
     } else {
-        f = wv / W;
-        ka = wv % W;
+        f = WGH ? wv : wv / H;
+        ka = WGH ? (int)(blk & 1u) : wv % H;
         j = l;
         grp = 0;
     }
     const uint32_t t1 = cb * C + (uint32_t)f;
+    // this lane's bits of the two sequences
+    const typename Pl::Word* __restrict__ pw =
+        reinterpret_cast<const typename Pl::Word*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * Pl::NJ + j;
+    const uint32_t w0 = pw[0], w1 = pw[Pl::kPlane / sizeof(typename Pl::Word)];
+    uint32_t len[2];
+    bool seed[2];
+    if (jt.shared.kpacks) {
+        const TileBits tb = shared_bits(jt, lt);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) len[h] = tb.s[h].len, seed[h] = tb.s[h].seed;
+    } else {
+        const uint32_t t = jt.tile0 + lt;
+        const JobDesc jd = find_job(jt, t);
+        const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+        if (!WGH || !(blk & 1u)) clear_window(g, cb, NCB, tid, Gm::THREADS);
+        len[0] = 0;
+        seed[0] = false;
+        len[1] = (uint32_t)(g.bi + g.bo - 1);
+        seed[1] = true;
+    }
+    if (tid == 0) wsum = 0;
+    wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
+
     // Four-step twiddle w_L^{t1 k2} = base * c_i with
-    //   W = 1: k2 = j + NJ i,           base = w_L^{t1 j},          c_i = w_L^{NJ t1 i}
-    //   W = 2: k2 = 2 (j + 64 i) + ka,  base = w_L^{t1 (2 j + ka)}, c_i = w_L^{128 t1 i}
+    //   H = 1: k2 = j + NJ i,           base = w_L^{t1 j},          c_i = w_L^{NJ t1 i}
+    //   H = 2: k2 = 2 (j + 64 i) + ka,  base = w_L^{t1 (2 j + ka)}, c_i = w_L^{128 t1 i}
     // Each lane fetches its share of its group's 16 factors now (latency hidden
     // behind the transform); they are exchanged through LDS afterwards.
-    constexpr int LPG = W == 1 ? NJ : 64;            // lanes per transform group
+    constexpr int LPG = H == 1 ? NJ : 64;            // lanes per transform group
     constexpr int CPL = (16 + LPG - 1) / LPG;        // factors fetched per lane
-    constexpr uint32_t CSTEP = W == 1 ? (uint32_t)NJ : 128u;
-    const Root64 base = root64(fa64, fb64, fshift, W == 1 ? t1 * (uint32_t)j : t1 * (uint32_t)(2 * j + ka));
+    constexpr uint32_t CSTEP = H == 1 ? (uint32_t)NJ : 128u;
+    const Root64 base = root64(fa64, fb64, fshift, H == 1 ? t1 * (uint32_t)j : t1 * (uint32_t)(2 * j + ka));
     Root64 cf[CPL];
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
         const int i = j + q * LPG;
         cf[q] = root64(fa64, fb64, fshift, i < 16 ? CSTEP * t1 * (uint32_t)i : 0u);
     }
-    // bit f of row r from the 32-bit half holding it (unconditional reads, selects)
-    const uint32_t* __restrict__ kb32 = reinterpret_cast<const uint32_t*>(kbits) + (f >> 5);
-    const uint32_t* __restrict__ sb32 = reinterpret_cast<const uint32_t*>(sbits) + (f >> 5);
-    const uint32_t fs = (uint32_t)f & 31u;
-    auto z = [&](int r) -> cx<T> {
-        const uint32_t kw = kb32[2 * r], sw = sb32[2 * r];
-        const T xb = ((kw >> fs) & 1u) ? T(1) : T(0);
-        const T sv = ((sw >> fs) & 1u) ? T(1) : T(-1);
-        const T wb = (t1 + (uint32_t)N1 * (uint32_t)r < win) ? sv : T(0);
-        return cx<T>{xb, wb};
-    };
+    // rows j + NJ i of a sequence of len bits: those below rows = ceil((len - t1) / N1)
     cx<T> v[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int e = j + i * NJ;
-        if constexpr (W == 1) {
-            v[i] = z(e);
-        } else {
-            // radix-2 split of the 2048-point column: half ka, twiddle w_2048^{e ka}
-            const cx<T> a = z(e), b = z(e + 1024);
-            if (ka == 0) v[i] = a + b;
-            else v[i] = cmul(a - b, tw[e * (N1 / 2048)]);
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t rows = len[h] > t1 ? (len[h] - t1 + N1 - 1) / N1 : 0u;
+        const uint32_t valid = rows > (uint32_t)j ? (rows - (uint32_t)j + Pl::NJ - 1) / Pl::NJ : 0u;
+        T x[16];
+        column_input<T, H>(x, h ? w1 : w0, seed[h], valid, ka != 0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) (h ? v[i].im : v[i].re) = x[i];
+    }
+    if constexpr (H == 2) {
+        if (ka) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], tw[(j + i * NJ) * (N1 / N2)]);
         }
     }
-    __syncthreads();  // bits consumed; LDS becomes wave regions
-    cx<T>* reg = lds + wv * kWaveSlots + (W == 1 ? grp * (M + M / 16) : 0);
+    uint32_t pc = seed[0] ? 0u : (uint32_t)__popc(w0) + (seed[1] ? 0u : (uint32_t)__popc(w1));
+    if (ka) pc = 0;   // counted by the other half
+    __syncthreads();  // the stage tables and the zeroed sum are in place
+    if constexpr (!WGH) atomicAdd(&wsum, pc);
+    else if (!(blk & 1u)) atomicAdd(&wsum, pc);
+    cx<T>* reg = lds + wv * kWaveSlots + (H == 1 ? grp * (M + M / 16) : 0);
     wave_fft_lds<T, -1, M>(v, reg, j, st);
 
     // exchange the factors through this wave's own region (its transform is done)
@@ -368,157 +401,26 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], rounded<T>(mul64(base, cw[i])));
     __syncthreads();
-    // transpose through LDS for row-segment stores.  With W = 2 the rows
-    // k2 = 2 e + ka of each half go to a tile of their own (the second one 8
-    // slots further, off the first's banks), so that a wave writes
-    // consecutive rows e as in the W = 1 layout
-    constexpr int HALF = M * C + 8;
-    static_assert(W * HALF <= SLOTS, "transposition tiles fit the LDS union");
+    // transpose through LDS for row-segment stores, the halves of a column in
+    // tiles of their own so that a wave writes consecutive rows
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int e = j + i * NJ;
-        lds[ka * HALF + tslot<C>(e, f)] = v[i];
-    }
+    for (int i = 0; i < 16; ++i) lds[(WGH ? 0 : ka * HALF) + tslot<C>(j + i * NJ, f)] = v[i];
     __syncthreads();
-    cx<T>* __restrict__ Y = ws + (size_t)lt * L;
-    static_assert((N2 * C) % Gm::THREADS == 0, "store tile");
-    constexpr int SPT = N2 * C / Gm::THREADS;
+    cx<T>* __restrict__ Y = ws + (size_t)lt * L + cb * C;
+    static_assert((ROWS * C) % Gm::THREADS == 0, "store tile");
+    constexpr int SPT = ROWS * C / Gm::THREADS;
     cx<T> o[SPT];
 #pragma unroll
     for (int q = 0; q < SPT; ++q) {
-        const int idx = tid + q * Gm::THREADS, k2 = idx / C;
-        o[q] = lds[(k2 % W) * HALF + tslot<C>(k2 / W, idx % C)];
+        const int idx = tid + q * Gm::THREADS, r = idx / C;
+        o[q] = lds[(r % CG) * HALF + tslot<C>(r / CG, idx % C)];
     }
 #pragma unroll
     for (int q = 0; q < SPT; ++q) {
-        const int idx = tid + q * Gm::THREADS;
-        Y[(size_t)(idx / C) * N1 + cb * C + (idx % C)] = o[q];
+        const int idx = tid + q * Gm::THREADS, r = idx / C;
+        Y[(size_t)(WGH ? 2 * r + ka : r) * N1 + (idx % C)] = o[q];
     }
-    if (tid == 0) part[(size_t)lt * NCB + cb] = wsum;
-}
-
-// Pass 1 for FP32 columns of 2048 points, as two halves.  Half ka (outputs
-// k2 = 2 e + ka) is the 1024-point transform of z(e) + z(e + 1024) (ka = 0) or
-// (z(e) - z(e + 1024)) w_2048^e (ka = 1): a radix-2 split in decimation in
-// frequency.  A workgroup of eight waves takes one half of 8 columns (one
-// column per wave), so it needs the LDS of one half (the block's bits, then
-// the wave regions, then the transposition tile: 78 KB, two workgroups per
-// CU) and the registers of one 1024-point column; the two halves of a column
-// block read the same bit-plane bytes.
-struct P1hArgs {
-    JobDesc jd;
-    TileGeo g;
-    uint32_t lt, cb, ntiles;
-};
-
-template <typename T, int N1, int KA>
-__device__ __forceinline__ uint32_t pass1_half_body(const P1hArgs& A, cx<T>* __restrict__ ws, cx<T>* lds,
-                                                    const cx<T>* st, const cx<T>* __restrict__ tw,
-                                                    const cx<double>* __restrict__ fa64,
-                                                    const cx<double>* __restrict__ fb64, int fshift) {
-    constexpr int N2 = 2048, M = 1024, C = 8, THREADS = 512, NJ = M / 16;
-    constexpr uint32_t L = (uint32_t)N1 * N2;
-    const int tid = threadIdx.x, wv = tid >> 6, j = tid & 63;
-    const TileGeo& g = A.g;
-    const uint32_t bi = (uint32_t)g.bi, win = (uint32_t)(g.bi + g.bo - 1);
-    const int f = wv;   // this wave's column
-    const uint32_t t1 = A.cb * C + (uint32_t)f;
-    uint16_t* fld = reinterpret_cast<uint16_t*>(lds);   // per row: key bits (low byte), seed bits (high byte)
-    uint32_t pc = 0;
-    __syncthreads();   // the previous half's stores have read the LDS
-    const uint8_t* kp = BitPlanes<N1, N2>::key(ws, A.ntiles, A.lt) + (size_t)A.cb * N2;
-    for (int r = tid; r < N2; r += THREADS) {
-        const uint32_t kb = kp[r];
-        const uint32_t sb = kp[BitPlanes<N1, N2>::kPlane + r];
-        fld[r] = (uint16_t)(kb | (sb << 8));
-        pc += (uint32_t)__popc(kb);
-    }
-    __syncthreads();
-    // four-step twiddle w_L^{t1 k2}, k2 = 2 (j + 64 i) + KA: base w_L^{t1 (2 j + KA)}
-    // times c_i = w_L^{128 t1 i} (lane i < 16 fetches c_i; exchanged after the transform)
-    const Root64 base = root64(fa64, fb64, fshift, t1 * (uint32_t)(2 * j + KA));
-    const Root64 cf = root64(fa64, fb64, fshift, j < 16 ? 128u * t1 * (uint32_t)j : 0u);
-    auto z = [&](int r) -> cx<T> {
-        const uint32_t w = fld[r];
-        const T xb = ((w >> f) & 1u) ? T(1) : T(0);
-        const T sv = ((w >> (8 + f)) & 1u) ? T(1) : T(-1);
-        return cx<T>{xb, (t1 + (uint32_t)N1 * (uint32_t)r < win) ? sv : T(0)};
-    };
-    cx<T> v[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int e = j + i * NJ;
-        const cx<T> a = z(e), b = z(e + M);
-        if constexpr (KA == 0) v[i] = a + b;
-        else v[i] = cmul(a - b, tw[e * (N1 / N2)]);
-    }
-    __syncthreads();   // bits consumed; LDS becomes wave regions
-    cx<T>* reg = lds + wv * kWaveSlots;
-    wave_fft_lds<T, -1, M>(v, reg, j, st);
-    Root64* cw = reinterpret_cast<Root64*>(reg);
-    wave_sync();
-    if (j < 16) cw[j] = cf;
-    wave_sync();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], rounded<T>(mul64(base, cw[i])));
-    __syncthreads();
-    // transpose through LDS for row-segment stores (rows k2 = 2 e + KA)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) lds[tslot<C>(j + i * NJ, f)] = v[i];
-    __syncthreads();
-    cx<T>* __restrict__ Y = ws + (size_t)A.lt * L;
-    constexpr int SPT = M * C / THREADS;
-    cx<T> o[SPT];
-#pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-        const int idx = tid + q * THREADS;
-        o[q] = lds[tslot<C>(idx / C, idx % C)];
-    }
-#pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-        const int idx = tid + q * THREADS;
-        Y[(size_t)(2 * (idx / C) + KA) * N1 + A.cb * C + (idx % C)] = o[q];
-    }
-    return pc;
-}
-
-// Each half in a workgroup of its own: logical block 2 b + KA
-// takes half KA of column block b (the two read the same bit words, through
-// the L2 of one XCD).  Half 0 clears the window and reports the weight.
-template <typename T, int N1>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-k2_pass1s(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
-          const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
-          int fshift) {
-    constexpr int M = 1024, C = 8, THREADS = 512;
-    constexpr int NCB = N1 / C;
-    constexpr int SLOTS = 8 * kWaveSlots;
-    static_assert(M * C <= SLOTS && 2048 * (int)sizeof(uint16_t) <= SLOTS * (int)sizeof(cx<T>), "LDS union");
-    __shared__ __align__(16) cx<T> lds[SLOTS];
-    __shared__ __align__(16) cx<T> st[wfft_lds_entries(M)];
-    __shared__ uint32_t wsum;
-    const uint32_t blk = xcd_block();
-    const uint32_t lb = blk >> 1;
-    const bool second = (blk & 1u) != 0;
-    P1hArgs A;
-    A.lt = lb / NCB;
-    A.cb = lb % NCB;
-    A.ntiles = jt.ntiles;
-    const uint32_t t = jt.tile0 + A.lt;
-    A.jd = find_job(jt, t);
-    A.g = tile_geo(A.jd, t - A.jd.tile_begin);
-    const int tid = threadIdx.x;
-    if (tid == 0) wsum = 0;
-    if (!second) clear_window(A.g, A.cb, NCB, tid, THREADS);
-    wfft_load_lds<T, M>(st, stw, tid, THREADS);
-    if (second) {
-        (void)pass1_half_body<T, N1, 1>(A, ws, lds, st, tw, fa64, fb64, fshift);
-        return;
-    }
-    const uint32_t pc = pass1_half_body<T, N1, 0>(A, ws, lds, st, tw, fa64, fb64, fshift);
-    atomicAdd(&wsum, pc);
-    __syncthreads();
-    if (tid == 0) part[(size_t)A.lt * NCB + A.cb] = wsum;
+    if (tid == 0 && !(WGH && (blk & 1u))) part[(size_t)lt * NCB + cb] = wsum;
 }
 
 // ------------------------------------------------------------------ pass 2
@@ -822,6 +724,123 @@ k2_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part,
         row_unit<T, N1, N2, NCB1>(u, jt, ws, part, meta, S, R, wsum, fa64, fb64, fshift);
 }
 
+// ------------------------------------------------------------------ shared spectra
+// Jobs with several chunks and windows of equal length B = L / 2: chunk b and
+// window o meet seed slice b + o, so every chunk and slice is transformed once
+// (two to a tile, columns by pass 1, rows here) and the windows' spectra
+//     P_o = (1 / L) sum_b X_b S_{b+o}
+// are summed from the stored spectra.  Packing two chunks, or two slices,
+// separates sequences of equal size: the large low-frequency values of the
+// zero-padded chunks do not leak into the seeds' spectra.
+//
+// Forward rows in place: row k2 of a tile becomes Z[k2][p], p = w M + kb holding
+// frequency k1 = W kb + w, so the mirror of position p is N1 - 1 - p (row 0, whose
+// mirror is -k1 mod N1: M - p mod M within w = 0, else N1 + M - 1 - p).
+template <typename T, int N1, int N2>
+__global__ void __launch_bounds__((RowGeom<T, N1>::THREADS)) __attribute__((amdgpu_waves_per_eu(8)))
+k2_rows(JobTable jt, cx<T>* __restrict__ ws, const cx<T>* __restrict__ tw, const cx<T>* __restrict__ stw) {
+    using G = RowGeom<T, N1>;
+    __shared__ __align__(16) RowSmem<T, N1> S;
+    RowReg<T, N1> R;
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
+    row_setup<T, N1>(S, R, tw, stw, tid);
+    const uint32_t units = jt.ntiles * (uint32_t)N2;
+    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+        cx<T>* __restrict__ row = ws + (size_t)u * N1;   // tiles and rows are contiguous
+        cx<T> a[G::PT];
+        row_load<T, N1>(a, row, tid);
+        row_forward<T, N1>(a, S, R, tid);
+#pragma unroll
+        for (int i = 0; i < G::PT; ++i) row[wv * G::M + l + 64 * i] = a[i];
+    }
+}
+
+// Sums of the windows o0 .. o0 + NW - 1 (NW even, o0 even): a thread takes one
+// position of row k2 <= n2 / 2 and its mirror and walks the key packs, with the
+// NW + 2 slices that the windows meet sliding through registers.  Each spectrum
+// is read once per NW windows.  Bound by these reads.
+template <typename T, int N1, int N2, int NW>
+__global__ void __launch_bounds__(256)
+k2_mac(JobTable jt, const cx<T>* __restrict__ ws, cx<T>* __restrict__ win, uint32_t o0) {
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int M = RowGeom<T, N1>::M;
+    const uint32_t k2 = blockIdx.x / (N1 / 256), p = (blockIdx.x % (N1 / 256)) * 256 + threadIdx.x;   // k2 <= n2 / 2
+    const uint32_t km = k2 ? (uint32_t)N2 - k2 : 0u;
+    const uint32_t pm = k2 ? (uint32_t)N1 - 1u - p : (p < M ? (M - p) & (M - 1) : (uint32_t)(N1 + M - 1) - p);
+    const size_t at = (size_t)k2 * N1 + p, am = (size_t)km * N1 + pm;
+    const SharedJob sh = jt.shared;
+    const T quarter = T(0.25) / T(L);
+    // 2 X_a = z + conj m, 2 X_b = -i (z - conj m) of a pack
+    auto split = [&](uint32_t pack, cx<T>& xa, cx<T>& xb) {
+        const cx<T> z = ws[(size_t)pack * L + at], m = conj(ws[(size_t)pack * L + am]);
+        xa = z + m;
+        const cx<T> d = z - m;
+        xb = cx<T>{d.im, -d.re};
+    };
+    auto slices = [&](uint32_t q, cx<T>& sa, cx<T>& sb) {
+        if (q < sh.spacks) {
+            split(sh.kpacks + q, sa, sb);
+        } else {
+            sa = cx<T>{T(0), T(0)};
+            sb = sa;
+        }
+    };
+    cx<T> acc[NW], s[NW + 2];
+#pragma unroll
+    for (int o = 0; o < NW; ++o) acc[o] = cx<T>{T(0), T(0)};
+#pragma unroll
+    for (int o = 0; o < NW; o += 2) slices(o0 / 2 + o / 2, s[o], s[o + 1]);
+    for (uint32_t q = 0; q < sh.kpacks; ++q) {
+        cx<T> xa, xb;
+        split(q, xa, xb);
+        slices(q + (o0 + NW) / 2, s[NW], s[NW + 1]);
+#pragma unroll
+        for (int o = 0; o < NW; ++o) acc[o] = acc[o] + cmul(xa, s[o]) + cmul(xb, s[o + 1]);
+#pragma unroll
+        for (int o = 0; o < NW; ++o) s[o] = s[o + 2];
+    }
+#pragma unroll
+    for (int o = 0; o < NW; ++o)
+        if (o0 + o < jt.one.nouts) win[(size_t)(o0 + o) * L + at] = cx<T>{acc[o].re * quarter, acc[o].im * quarter};
+}
+
+// Inverse rows 0 .. n2 / 2 of every window, in place: from the order above to
+// rows of V (natural order) for pass 3; the unit of row 0 sets the certificate.
+template <typename T, int N1, int N2, int NCB1>
+__global__ void __launch_bounds__((RowGeom<T, N1>::THREADS))
+__attribute__((amdgpu_waves_per_eu(row_wgs_per_cu<T, N1>() * RowGeom<T, N1>::THREADS / 256)))
+k2_rows_inv(JobTable jt, cx<T>* __restrict__ win, const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
+            const cx<T>* __restrict__ tw, const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64,
+            const cx<double>* __restrict__ fb64, int fshift) {
+    using G = RowGeom<T, N1>;
+    constexpr uint32_t L = (uint32_t)N1 * N2, NR = N2 / 2 + 1;
+    __shared__ __align__(16) RowSmem<T, N1> S;
+    __shared__ uint32_t wsum;
+    RowReg<T, N1> R;
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
+    row_setup<T, N1>(S, R, tw, stw, tid);
+    const uint32_t units = jt.ngroups * NR;
+    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const uint32_t o = u / NR, k2 = u % NR;
+        cx<T>* __restrict__ row = win + (size_t)o * L + (size_t)k2 * N1;
+        cx<T> a[G::PT];
+#pragma unroll
+        for (int i = 0; i < G::PT; ++i) a[i] = row[wv * G::M + l + 64 * i];
+        row_inverse<T, N1>(a, S, R, tid);   // its barriers separate the loads from the stores below
+        row_store<T, N1>(row, a, k2, k2 == 0 || k2 == N2 / 2, tid, fa64, fb64, fshift);
+        if (k2 == 0) {
+            __syncthreads();
+            if (tid == 0) wsum = 0;
+            __syncthreads();
+            uint32_t sum = 0;
+            for (uint32_t c = tid; c < jt.shared.kpacks * NCB1; c += G::THREADS) sum += part[c];
+            atomicAdd(&wsum, sum);
+            __syncthreads();
+            if (tid == 0) meta[jt.group0 + o] = TileMeta{wsum, 0u, 0u, 0u};
+        }
+    }
+}
+
 // ------------------------------------------------------------------ pass 3
 // rint(z) mod 4 for an integral r (FP32: |r| < 2^31; FP64: |r| < 2^51)
 __device__ __forceinline__ uint32_t low2(float r) { return (uint32_t)(int)r & 3u; }
@@ -985,28 +1004,57 @@ struct ClassImpl2 {
     using G3 = P3Geom<T, N2>;
     static constexpr int C1 = G1::C, C3 = G3::C;
     // workspace bytes per tile beyond its points: the bit planes
-    static constexpr size_t kWsExtra = G1::kPlanes ? BitPlanes<N1, N2>::kTile : 0;
+    static constexpr size_t kWsExtra = BitPlanes<N1, N2>::kTile;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
-        dim3 grid(jt.ntiles * (N1 / C1)), block(G1::THREADS);
-        if constexpr (G1::kPlanes) {
-            uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
-            hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (N2 / kBitsRows) * (N1 / 64 / kBitsCols)), dim3(256),
-                               0, (hipStream_t)stream, jt, planes);
-        }
-        if constexpr (sizeof(T) == 4 && N2 == 2048) {
-            static_assert(C1 == 8, "eight columns per workgroup");
-            hipLaunchKernelGGL((k2_pass1s<T, N1>), dim3(2 * grid.x), dim3(512), 0, (hipStream_t)stream, jt, (cx<T>*)ws,
-                               part, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
-                               (const cx<double>*)tb.fb64, tb.fshift);
-        } else {
-            hipLaunchKernelGGL((k2_pass1<T, N1, N2>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws, part,
-                               (const cx<T>*)tb.tw, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
-                               (const cx<double>*)tb.fb64, tb.fshift);
-        }
+        uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
+        hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (2 * (N2 / 64) * (N1 / 64 / kBitsCols) / 4)), dim3(256), 0,
+                           (hipStream_t)stream, jt, planes);
+        hipLaunchKernelGGL((k2_pass1<T, N1, N2>), dim3(jt.ntiles * (N1 / C1) * (G1::WGH ? 2 : 1)), dim3(G1::THREADS), 0,
+                           (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
+                           (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     static int pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
         return launch_row_pass<T, N1, N2, N1 / C1>(jt, ws, part, meta, tb, stream);
+    }
+    // Shared spectra (FP32): `ws` holds the packs, then their planes, then the
+    // windows; the windows' column passes are pass3 on the windows.
+    static constexpr size_t shared_bytes(uint32_t packs, uint32_t windows) {
+        return (size_t)packs * ((size_t)N1 * N2 * sizeof(cx<T>) + kWsExtra) + (size_t)windows * N1 * N2 * sizeof(cx<T>);
+    }
+    static void* windows(const JobTable& jt, void* ws) {
+        return (uint8_t*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2 * sizeof(cx<T>) + kWsExtra);
+    }
+    static int shared_pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
+        return pass1(jt, ws, part, meta, tb, stream);
+    }
+    template <int NW>
+    static void mac(const JobTable& jt, void* ws, uint32_t o0, void* stream) {
+        hipLaunchKernelGGL((k2_mac<T, N1, N2, NW>), dim3((N2 / 2 + 1) * (N1 / 256)), dim3(256), 0, (hipStream_t)stream, jt,
+                           (const cx<T>*)ws, (cx<T>*)windows(jt, ws), o0);
+    }
+    static int shared_pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
+        hipStream_t s = (hipStream_t)stream;
+        const uint32_t wgs = (uint32_t)(row_pass_workgroups() * row_wgs_per_cu<T, N1>());
+        const uint32_t rows = jt.ntiles * N2, inv = jt.ngroups * (N2 / 2 + 1);
+        // one row at a time takes 64 registers: four workgroups per CU
+        hipLaunchKernelGGL((k2_rows<T, N1, N2>), dim3(rows < 2 * wgs ? rows : 2 * wgs), dim3(RowGeom<T, N1>::THREADS), 0, s, jt,
+                           (cx<T>*)ws, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw);
+        // eight windows at a time, the rest in the narrowest sum that holds them
+        uint32_t o0 = 0;
+        for (; o0 + 4 < jt.one.nouts; o0 += 8) mac<8>(jt, ws, o0, stream);
+        if (o0 + 2 < jt.one.nouts) mac<4>(jt, ws, o0, stream);
+        else if (o0 < jt.one.nouts) mac<2>(jt, ws, o0, stream);
+        hipLaunchKernelGGL((k2_rows_inv<T, N1, N2, N1 / C1>), dim3(inv < wgs ? inv : wgs), dim3(RowGeom<T, N1>::THREADS), 0,
+                           s, jt, (cx<T>*)windows(jt, ws), (const uint32_t*)part, meta, (const cx<T>*)tb.tw,
+                           (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    }
+    // `jt.one` describes the windows as one-chunk groups here
+    static int shared_pass3(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
+        JobTable w = jt;
+        w.tile0 = w.one.tile_begin = 0;
+        return pass3(w, windows(jt, ws), part, meta, tb, stream);
     }
     static int pass3(const JobTable& jt, void* ws, uint32_t*, TileMeta* meta, const Tables& tb, void* stream) {
         dim3 grid(jt.ngroups * (N1 / C3)), block(G3::THREADS);

@@ -240,7 +240,7 @@ bool Ctx::plan_cached(uint64_t n, uint64_t m, int policy, TilePlan* out) {
         std::lock_guard<std::mutex> lk(plan_mu);
         cm = cost;
     }
-    if (!plan_job(n, m, policy, cm, out)) return false;
+    if (!plan_job(n, m, policy, cm, out, 24, budget / 3)) return false;
     std::lock_guard<std::mutex> lk(plan_mu);
     if (plans.size() >= 256) plans.clear();
     plans[key] = *out;
@@ -372,6 +372,7 @@ void fill_job(JobDesc* jd, const uint64_t* seed, const uint64_t* key, uint64_t* 
     jd->nchunks = (uint32_t)p.nchunks;
     jd->nouts = (uint32_t)p.nouts;
     jd->cgroup = (uint32_t)p.cgroup;
+    jd->shared = p.shared ? 1u : 0u;
     jd->out_words = (uint32_t)words_of(m);
 }
 
@@ -402,6 +403,20 @@ struct Span {
     uint32_t tile, ntiles, group, ngroups;
 };
 
+// Three passes over the tiles and groups of a job table.
+static pa_status run_table(const launch_fn (&fns)[3], const JobTable (&jt)[3], Lane* ln, const Tables& tb, bool timing,
+                           uint64_t* launches) {
+    for (int p = 0; p < 3; ++p) {
+        hipEvent_t a = timing ? ln->timer.mark(ln->stream) : nullptr;
+        // 0: launched; 1: nothing to launch (one-kernel tiles); < 0: error
+        const int r = fns[p](jt[p], ln->ws.ptr, (uint32_t*)ln->part.ptr, (TileMeta*)ln->meta.ptr, tb, ln->stream);
+        if (r < 0) return PA_EDEVICE;
+        if (r == 0) *launches += 1;
+        if (timing) ln->timer.spans.push_back({p, {a, ln->timer.mark(ln->stream)}});
+    }
+    return PA_OK;
+}
+
 // The three passes over one span.
 static pa_status run_span(const ClassKernels* K, JobTable jt, const Span& sp, Lane* ln, const Tables& tb, bool timing,
                           uint64_t* launches) {
@@ -409,14 +424,36 @@ static pa_status run_span(const ClassKernels* K, JobTable jt, const Span& sp, La
     jt.ntiles = sp.ntiles;
     jt.group0 = sp.group;
     jt.ngroups = sp.ngroups;
-    const launch_fn fns[3] = {K->pass1, K->pass2, K->pass3};
-    for (int p = 0; p < 3; ++p) {
-        hipEvent_t a = timing ? ln->timer.mark(ln->stream) : nullptr;
-        // 0: launched; 1: nothing to launch (one-kernel tiles); < 0: error
-        const int r = fns[p](jt, ln->ws.ptr, (uint32_t*)ln->part.ptr, (TileMeta*)ln->meta.ptr, tb, ln->stream);
-        if (r < 0) return PA_EDEVICE;
-        if (r == 0) *launches += 1;
-        if (timing) ln->timer.spans.push_back({p, {a, ln->timer.mark(ln->stream)}});
+    return run_table({K->pass1, K->pass2, K->pass3}, {jt, jt, jt}, ln, tb, timing, launches);
+}
+
+static uint32_t shared_packs(const JobDesc& jd, uint32_t chunks) { return (chunks + 1) / 2 + (chunks + jd.nouts) / 2; }
+
+// A job with shared spectra, one chunk group after the other: several groups
+// XOR their windows into the cleared output.
+static pa_status run_shared(const ClassKernels* K, const JobDesc& jd, Lane* ln, const Tables& tb, bool timing,
+                            uint64_t* launches) {
+    const uint32_t groups = chunk_groups(jd);
+    if (groups > 1) {
+        if (launch_xor_words(jd.out, jd.out, words_of(jd.m), ln->stream)) return PA_EDEVICE;
+        *launches += 1;
+    }
+    for (uint32_t q = 0; q < groups; ++q) {
+        JobTable jt{};
+        jt.one = jd;
+        jt.shared.chunk0 = q * jd.cgroup;
+        jt.shared.chunks = std::min(jd.cgroup, jd.nchunks - q * jd.cgroup);
+        jt.shared.kpacks = (jt.shared.chunks + 1) / 2;
+        jt.shared.spacks = shared_packs(jd, jt.shared.chunks) - jt.shared.kpacks;
+        jt.ntiles = jt.shared.kpacks + jt.shared.spacks;
+        jt.group0 = jd.group_begin + q * jd.nouts;
+        jt.ngroups = jd.nouts;
+        JobTable win = jt;   // the windows as groups of one chunk, accumulated or not
+        win.one.cgroup = 1;
+        win.one.nchunks = groups > 1 ? 2 : 1;
+        win.one.group_begin = jt.group0;
+        const pa_status st = run_table({K->shared1, K->shared2, K->shared3}, {jt, jt, win}, ln, tb, timing, launches);
+        if (st != PA_OK) return st;
     }
     return PA_OK;
 }
@@ -429,7 +466,10 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     cls = cls_;
     const ClassCfg& cfg = K->cfg;
     uint32_t total = 0;
-    for (const JobDesc& jd : js) total += jd.nchunks * jd.nouts;
+    for (JobDesc& jd : js) {
+        if (jd.shared && (!K->shared_bytes || prec != PREC_FP32)) jd.shared = 0;
+        if (!jd.shared) total += jd.nchunks * jd.nouts;
+    }
     Tables tb;
     pa_status st = lane_tables(c, *this, prec, cls, &tb);
     if (st != PA_OK) return st;
@@ -445,21 +485,47 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     const size_t elt = cfg.prec == 64 ? 16 : 8;
     const size_t tile_bytes = (size_t)class_len(cfg.cls) * elt + cfg.ws_extra;
     const size_t part_bytes = (size_t)(cfg.n1 / cfg.b1) * sizeof(uint32_t);
+    uint64_t avail;   // workspace and partial sums together
+    if (ws.fixed) {
+        avail = ws.bytes;
+    } else {
+        const uint64_t u = c->used.load();
+        const uint64_t mine = ws.bytes + part.bytes;
+        avail = c->budget > u ? c->budget - u + mine : mine;
+        if (cap) avail = std::min<uint64_t>(avail, cap);
+    }
+    // a job with shared spectra: chunk groups as large as fit (those that the
+    // plan asks for, if possible); too little space for a few chunks: plain tiles
+    size_t sh_ws = 0, sh_part = 0;
+    for (JobDesc& jd : js) {
+        if (!jd.shared) continue;
+        auto bytes = [&](uint32_t cg) {
+            return K->shared_bytes(shared_packs(jd, cg), jd.nouts) + shared_packs(jd, cg) * part_bytes;
+        };
+        uint32_t cg = jd.cgroup, parts = chunk_groups(jd);
+        while (cg > 4 && (bytes(cg) > avail || (part.fixed && shared_packs(jd, cg) * part_bytes > part.bytes)))
+            cg = (jd.nchunks + parts) / (parts + 1), ++parts;
+        if (bytes(cg) > avail || (part.fixed && shared_packs(jd, cg) * part_bytes > part.bytes)) {
+            jd.shared = 0;
+            jd.cgroup = 1;
+            total += jd.nchunks * jd.nouts;
+            continue;
+        }
+        jd.cgroup = cg;
+        sh_ws = std::max(sh_ws, K->shared_bytes(shared_packs(jd, cg), jd.nouts));
+        sh_part = std::max(sh_part, shared_packs(jd, cg) * part_bytes);
+    }
     size_t G = total;
     if (ws.fixed) {   // a fixed workspace: as many tiles as it holds
         G = std::min<size_t>(G, std::min<size_t>(ws.bytes / tile_bytes, part.bytes / part_bytes));
-        if (G == 0) return PA_ESCRATCH;
-    } else if (ws.bytes < G * tile_bytes || part.bytes < G * part_bytes) {
-        const uint64_t u = c->used.load();
-        const uint64_t mine = ws.bytes + part.bytes;
-        uint64_t avail = c->budget > u ? c->budget - u + mine : mine;
-        if (cap) avail = std::min<uint64_t>(avail, cap);
+        if (G == 0 && total) return PA_ESCRATCH;
+    } else if (total && (ws.bytes < G * tile_bytes || part.bytes < G * part_bytes)) {
         G = std::max<size_t>(1, std::min<size_t>(G, avail / (tile_bytes + part_bytes)));
     }
     for (;;) {
-        st = ws.ensure(c, G * tile_bytes, stream);
-        if (st == PA_OK) st = part.ensure(c, G * part_bytes, stream);
-        if (st == PA_OK || G == 1) break;
+        st = ws.ensure(c, std::max(G * tile_bytes, sh_ws), stream);
+        if (st == PA_OK) st = part.ensure(c, std::max(G * part_bytes, sh_part), stream);
+        if (st == PA_OK || G <= 1) break;
         G = (G + 1) / 2;
     }
     if (st != PA_OK) return st;
@@ -473,6 +539,15 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     uint32_t tiles = 0, groups = 0;
     Span cur{0, 0, 0, 0};
     for (JobDesc& jd : js) {
+        if (jd.shared) {   // no tiles of its own here; its certificates lie between those of its neighbours
+            if (cur.ntiles) spans.push_back(cur);
+            jd.tile_begin = tiles;
+            jd.group_begin = groups;
+            groups += chunk_groups(jd) * jd.nouts;
+            cur = Span{tiles, 0, groups, 0};
+            stats->tiles += (uint64_t)jd.nchunks * jd.nouts;
+            continue;
+        }
         jd.cgroup = (uint32_t)std::max<size_t>(1, std::min<size_t>({(size_t)jd.cgroup, (size_t)jd.nchunks, G}));
         if (!cfg.sums) jd.cgroup = 1;
         jd.tile_begin = tiles;
@@ -491,7 +566,7 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
             }
         }
     }
-    spans.push_back(cur);
+    if (cur.ntiles) spans.push_back(cur);
     st = meta.ensure(c, (size_t)groups * sizeof(TileMeta), stream);
     if (st != PA_OK) return st;
 
@@ -511,6 +586,11 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     if (timing) timer.reset();
     for (const Span& sp : spans) {
         st = run_span(K, jt, sp, this, tb, timing, &stats->launches);
+        if (st != PA_OK) return st;
+    }
+    for (const JobDesc& jd : js) {
+        if (!jd.shared) continue;
+        st = run_shared(K, jd, this, tb, timing, &stats->launches);
         if (st != PA_OK) return st;
     }
     if (fetch_meta) {
@@ -582,6 +662,7 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
     // time (the chunks' partial hashes XOR into the window, Eq. 7).
     //  * Job of one chunk group: the failed group's chunks alone (its window is
     //    overwritten, or cleared by chunk 0 and XOR-ed into).
+    //  * Job with shared spectra: every chunk of the failed group's window.
     //  * Job that accumulates chunk groups: per failed group, the FP32 group
     //    again and then its FP64 chunks, all XOR-ing into the window without
     //    clearing it; the FP32 run is deterministic, so its bits cancel the
@@ -597,9 +678,9 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
     size_t most = 1;
     for (uint32_t t : failed) {
         const JobDesc& jd = jobs[job_of(t)];
-        if (jd.nchunks > jd.cgroup) most = std::max<size_t>(most, jd.cgroup);
+        if (!jd.shared && jd.nchunks > jd.cgroup) most = std::max<size_t>(most, jd.cgroup);
     }
-    st = ws.ensure(c, std::max<size_t>((size_t)class_len(cls) * 16,
+    st = ws.ensure(c, std::max<size_t>((size_t)class_len(cls) * 16 + K64->cfg.ws_extra,
                                        most * ((size_t)class_len(cls) * 8 + (K32 ? K32->cfg.ws_extra : 0))),
                    stream);
     if (st != PA_OK) return st;
@@ -607,6 +688,7 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
     st = part.ensure(c, part_words * sizeof(uint32_t), stream);
     if (st != PA_OK) return st;
     std::vector<uint8_t> rebuilt(jobs.size(), 0);
+    std::vector<uint32_t> windows_done;   // group numbers of the windows of jobs with shared spectra
     auto fetch_meta = [&](uint32_t first, uint32_t end, std::vector<TileMeta>* out) -> pa_status {
         out->resize(end - first);
         if (hipMemcpyAsync(out->data(), (TileMeta*)meta.ptr + first, (end - first) * sizeof(TileMeta),
@@ -621,7 +703,13 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         if (rebuilt[jx]) continue;
         const JobDesc& jd = jobs[jx];
         const uint32_t lg = t - jd.group_begin, q = lg / jd.nouts, o = lg % jd.nouts;
-        const uint32_t b0 = q * jd.cgroup, gs = std::min(jd.cgroup, jd.nchunks - b0);
+        uint32_t b0 = q * jd.cgroup, gs = std::min(jd.cgroup, jd.nchunks - b0);
+        if (jd.shared) {   // once per window, whichever groups failed
+            if (std::count(windows_done.begin(), windows_done.end(), jd.group_begin + o)) continue;
+            windows_done.push_back(jd.group_begin + o);
+            b0 = 0;
+            gs = jd.nchunks;
+        }
         JobTable jt{};
         jt.one = jd;
         jt.one.tile_begin = 0;
@@ -630,7 +718,7 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         st = meta.ensure(c, (size_t)jd.nchunks * jd.nouts * sizeof(TileMeta), stream);
         if (st != PA_OK) return st;
         bool whole = false;
-        if (jd.nchunks > jd.cgroup) {
+        if (!jd.shared && jd.nchunks > jd.cgroup) {
             jt.one.no_clear = 1;
             bool same = K32 != nullptr;
             if (same) {
@@ -740,7 +828,11 @@ void fill_plan_stats(pa_stats* s, const TilePlan& p) {
     s->bound = std::max(s->bound, p.bound);
     s->rigorous_bound = std::max(s->rigorous_bound, p.rigorous);
     if (p.prec == PREC_FP32 || p.prec == PREC_FP64) s->certified = PA_CERT_A_PRIORI;   // settled by set_certified
-    s->model_bytes += p.tiles() * (p.prec == PREC_FP64 ? 48ull : 24ull) * p.L;
+    // shared spectra: a pack is written, read and written (rows) and read (sums); a
+    // window's half spectrum is written and read twice
+    const uint64_t groups = (p.nchunks + p.cgroup - 1) / p.cgroup;
+    s->model_bytes += p.shared ? groups * (p.packs(p.cgroup) * 32 + p.nouts * 16) * p.L
+                               : p.tiles() * (p.prec == PREC_FP64 ? 48ull : 24ull) * p.L;
 }
 
 void set_certified(pa_stats* s, pa_status st) {
@@ -973,7 +1065,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
             }
         }
         if (!fidx.empty()) {
-            if (!plan_batch_groups(fns, fms, policy, cm, &groups, &fplans)) return PA_EINVAL;
+            if (!plan_batch_groups(fns, fms, policy, cm, &groups, &fplans, c->budget / 3)) return PA_EINVAL;
             for (BatchGroup& g : groups)
                 for (size_t& q : g.jobs) q = fidx[q];
         }

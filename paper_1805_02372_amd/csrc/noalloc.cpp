@@ -163,7 +163,7 @@ extern "C" pa_status pa_hash_noalloc(pa_ctx* ctx, const uint64_t* seed, uint64_t
         cm = c->cost;
     }
     TilePlan plan;
-    if (!plan_job(n, m, policy, cm, &plan, kCapLogL)) return PA_EINVAL;
+    if (!plan_job(n, m, policy, cm, &plan, kCapLogL, 0)) return PA_EINVAL;
     pa_stats st{};
     fill_plan_stats(&st, plan);
     pa_status s = PA_OK;

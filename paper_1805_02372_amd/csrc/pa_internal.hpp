@@ -31,8 +31,21 @@ struct JobDesc {
     uint32_t tile_begin;  // first tile of this job in the launch's tile numbering
     uint32_t group_begin; // first group of this job in the launch's group numbering
     uint32_t out_words;   // ceil(m / 64)
+    uint32_t shared;      // 1: shared spectra (Bi = Bo, see SharedJob)
     uint32_t no_clear;    // 1: chunk-0 tiles do not clear their window (a tile
                           // re-run that XORs into an accumulated window)
+};
+
+// One chunk group of a job with shared spectra (Bi = Bo = B, windows of B
+// outputs): seed slice j (bits [j B, j B + 2 B - 1)) serves every chunk b and
+// window o with b + o = j, so the chunks and the slices are transformed once
+// each, two to a tile ("pack"), and the windows' products are summed from the
+// stored spectra.
+struct SharedJob {
+    uint32_t kpacks;      // key packs (0: not a shared-spectra launch)
+    uint32_t spacks;      // seed packs
+    uint32_t chunk0;      // first chunk of the group
+    uint32_t chunks;      // chunks of the group
 };
 
 // Where the tiles of one launch come from: either one job passed by value or
@@ -45,6 +58,7 @@ struct JobTable {
     uint32_t ntiles;      // tiles in this launch (whole groups)
     uint32_t group0;      // first group of this launch
     uint32_t ngroups;     // groups in this launch
+    SharedJob shared;     // kpacks > 0: the tiles are the packs of one group of job `one`
     uint32_t clears;      // some job of `many` has a chunk-0 tile that clears its window
 };
 
@@ -109,6 +123,10 @@ typedef int (*launch_fn)(const JobTable& jt, void* ws, uint32_t* part, TileMeta*
 struct ClassKernels {
     ClassCfg cfg;
     launch_fn pass1, pass2, pass3;
+    // shared spectra (classes that have them): the passes, and the workspace
+    // bytes of a group
+    launch_fn shared1 = nullptr, shared2 = nullptr, shared3 = nullptr;
+    size_t (*shared_bytes)(uint32_t packs, uint32_t windows) = nullptr;
 };
 
 // Registered by the per-precision kernel objects.

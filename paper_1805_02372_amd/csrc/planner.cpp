@@ -374,6 +374,15 @@ bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostMode
 // wave-level rows (from 2^20 points on).
 static bool class_sums(int prec, int cls) { return prec != PREC_NTT && class_len(cls) >= (1ull << 20); }
 
+// Classes with shared spectra (ClassKernels::shared1).
+static bool class_shared(int prec, int cls) { return prec == PREC_FP32 && cls >= 21 && cls <= 23; }
+
+// Modeled error of one product of shared spectra: the noise term of error_bound
+// (the sequences of a pack are of equal size, so no box leaks into a seed).
+static double shared_error(int prec, uint64_t L, uint64_t Bi) {
+    return 6.0 * g_kappa * unit_roundoff(prec) * std::sqrt(std::log2((double)L) * ((double)Bi + (double)L));
+}
+
 // Chunks of one group: at most 64, in equal groups, and for FP32 no more than
 // keep the modeled error of the sum within the limit of groups.
 static uint64_t group_chunks(int prec, uint64_t L, uint64_t Bi, uint64_t nchunks) {
@@ -385,7 +394,44 @@ static uint64_t group_chunks(int prec, uint64_t L, uint64_t Bi, uint64_t nchunks
     return ceil_div(nchunks, ceil_div(nchunks, most));
 }
 
-bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out) {
+// The plan of job (n, m) with shared spectra at class `cls`: chunks and windows
+// of L / 2, the chunks in as many equal groups as the workspace and the error
+// model ask for.  Only jobs of several windows gain (each chunk meets several).
+static bool plan_shared(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, uint64_t shared_bytes,
+                        TilePlan* out) {
+    if (!class_shared(prec, cls)) return false;
+    TilePlan p;
+    p.prec = prec;
+    p.cls = cls;
+    p.L = class_len(cls);
+    p.shared = true;
+    p.Bi = p.Bo = p.L / 2;
+    p.nchunks = ceil_div(n, p.Bi);
+    p.nouts = ceil_div(m, p.Bo);
+    if (p.nouts < 2 || p.nchunks < 2 || p.tiles() > (1u << 20)) return false;
+    const uint64_t tile_bytes = 8 * p.L + p.L / 4;
+    const double err = shared_error(prec, p.L, p.Bi);
+    uint64_t groups = 1;
+    for (;; ++groups) {
+        p.cgroup = ceil_div(p.nchunks, groups);
+        p.bound = err * std::sqrt((double)p.cgroup);
+        if (p.bound <= kGroupErrorLimit && p.packs(p.cgroup) * tile_bytes + p.nouts * 8 * p.L <= shared_bytes) break;
+        if (p.cgroup <= 4) return false;   // little left to share
+    }
+    groups = ceil_div(p.nchunks, p.cgroup);
+    // per pack: a chunk's passes and the spectrum written once and read once per
+    // eight windows; per window and group: the rest of a tile and its sum, written and read
+    const double rate = 4.0e12, Ld = (double)p.L;
+    const double chunk = cm.chunk(prec, cls), rest = std::max(cm.tile(prec, cls) - chunk, 0.0);
+    const double packs = (double)(groups * p.packs(p.cgroup)), wins = (double)(groups * p.nouts);
+    p.cost = packs * (chunk + 8 * Ld * (1.0 + (double)ceil_div(p.nouts, 8)) / rate) + wins * (rest + 8 * Ld / rate);
+    p.rigorous = rigorous_bound(prec, p.L, p.Bi, p.Bo) * (double)p.cgroup;
+    *out = p;
+    return true;
+}
+
+bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out,
+                   uint64_t shared_bytes) {
     ClassGeom g;
     if (n == 0 || m == 0 || !class_geometry(prec, cls, &g)) return false;
     const uint64_t L = g.L;
@@ -435,12 +481,15 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
     best.bound = error_bound(prec, L, best.Bi) * std::sqrt((double)best.cgroup);
     best.rigorous = rigorous_bound(prec, L, best.Bi, best.Bo) * (double)best.cgroup;
     if (best.bound > kPlanErrorLimit) return false;   // not reached by FP32 up to 2^24
+    TilePlan sh;
+    if (shared_bytes && plan_shared(n, m, prec, cls, cm, shared_bytes, &sh) && sh.cost < best.cost) best = sh;
     best.cost += cm.first(prec, cls);
     *out = best;
     return true;
 }
 
-bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* out, int cap_logL) {
+bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* out, int cap_logL,
+              uint64_t shared_bytes) {
     if (n == 0 || m == 0) return false;
     const int prec = policy;
     int ids[kMaxClassId + 1];
@@ -450,7 +499,7 @@ bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan*
     // more than the noise of the measured costs (10%), so near-ties keep the
     // plan with fewer bytes.
     auto better = [](const TilePlan& p, const TilePlan& best) {
-        const double pts = (double)p.tiles() * (double)p.L, bpts = (double)best.tiles() * (double)best.L;
+        const double pts = p.points(), bpts = best.points();
         return pts <= bpts ? p.cost < best.cost : p.cost < 0.9 * best.cost;
     };
     if (prec == PREC_FP64 || prec == PREC_NTT) {
@@ -460,7 +509,7 @@ bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan*
         TilePlan best1;
         for (int q = 0; q < nid; ++q) {
             TilePlan p;
-            if (n + m - 1 > class_len(ids[q]) || !plan_at_class(n, m, prec, ids[q], cm, &p)) continue;
+            if (n + m - 1 > class_len(ids[q]) || !plan_at_class(n, m, prec, ids[q], cm, &p, shared_bytes)) continue;
             if (!one || better(p, best1)) {
                 best1 = p;
                 one = true;
@@ -475,7 +524,7 @@ bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan*
     TilePlan best;
     for (int q = 0; q < nid; ++q) {
         TilePlan p;
-        if (!plan_at_class(n, m, prec, ids[q], cm, &p)) continue;
+        if (!plan_at_class(n, m, prec, ids[q], cm, &p, shared_bytes)) continue;
         if (!found || better(p, best)) {
             best = p;
             found = true;
@@ -486,7 +535,8 @@ bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan*
 }
 
 bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy,
-                       const CostModel& cm, std::vector<BatchGroup>* groups, const std::vector<TilePlan>* own) {
+                       const CostModel& cm, std::vector<BatchGroup>* groups, const std::vector<TilePlan>* own,
+                       uint64_t shared_bytes) {
     if (ns.empty() || ns.size() != ms.size() || (own && own->size() != ns.size())) return false;
     // plans of job i at class id k, computed once: memo[i * NK + k], state 0
     // unknown, 1 found, -1 none
@@ -496,7 +546,7 @@ bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64
     auto at_class = [&](size_t i, int k, TilePlan* p) {
         if (k < 0 || k >= NK) return false;
         const size_t x = i * NK + (size_t)k;
-        if (!known[x]) known[x] = plan_at_class(ns[i], ms[i], policy, k, cm, &memo[x]) ? 1 : -1;
+        if (!known[x]) known[x] = plan_at_class(ns[i], ms[i], policy, k, cm, &memo[x], shared_bytes) ? 1 : -1;
         if (known[x] < 0) return false;
         *p = memo[x];
         return true;

@@ -66,9 +66,18 @@ struct TilePlan {
     uint64_t L = 0;        // FFT length of the class
     uint64_t Bi = 0, Bo = 0, nchunks = 0, nouts = 0;
     uint64_t cgroup = 1;   // chunks whose products are summed before one inverse
+    bool shared = false;   // spectra of chunks and seed slices shared by the windows (Bi = Bo = L / 2)
+    // tiles that a shared-spectra group of c chunks transforms, two sequences each
+    uint64_t packs(uint64_t c) const { return (c + 1) / 2 + (c + nouts) / 2; }
     double bound = 0, cost = 0;
     double rigorous = 0;   // worst-case rounding bound of a group (any input bits)
     uint64_t tiles() const { return nchunks * nouts; }
+    // points transformed (shared spectra: packs and windows)
+    double points() const {
+        if (!shared) return (double)tiles() * (double)L;
+        const uint64_t groups = (nchunks + cgroup - 1) / cgroup;
+        return (double)(groups * (packs(cgroup) + nouts)) * (double)L;
+    }
 };
 
 // Error model of one floating-point tile, a predicted maximum of the output
@@ -114,15 +123,23 @@ bool choose_direct(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, 
 // better.
 bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft);
 
+// Workspace that a shared-spectra plan may count on: what a serving lane of a
+// context with the default HBM budget has (a launch with less cuts the chunks
+// into smaller groups).
+constexpr uint64_t kSharedBytes = (8ull << 30) / 3;
+
 // Best (Bi, Bo) for job (n, m) at a fixed class; false if impossible.
-bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out);
+// `shared_bytes`: workspace for shared spectra (0: none).
+bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out,
+                   uint64_t shared_bytes = kSharedBytes);
 
 // Best plan over classes for one job.  policy: PREC_FP32 (segmented, bound
 // limited), PREC_FP64 and PREC_NTT (a single tile if one fits, else the
 // cheapest plan over the classes).  Among plans whose modeled costs differ by
 // less than 10% the one that moves fewer points wins.  Classes longer than
 // 2^cap_logL are not used.
-bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* out, int cap_logL = 24);
+bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* out, int cap_logL = 24,
+              uint64_t shared_bytes = kSharedBytes);
 
 // Jobs of a batch that share one FFT length class (one pipeline launch).
 struct BatchGroup {
@@ -139,7 +156,7 @@ struct BatchGroup {
 // known to the caller.
 bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy,
                        const CostModel& cm, std::vector<BatchGroup>* groups,
-                       const std::vector<TilePlan>* own = nullptr);
+                       const std::vector<TilePlan>* own = nullptr, uint64_t shared_bytes = kSharedBytes);
 
 // One class for a whole batch: minimises the summed cost of every job's tiles.
 bool plan_batch(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy,

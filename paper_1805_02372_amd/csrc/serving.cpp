@@ -65,7 +65,7 @@ static uint64_t request_bytes(Ctx* c, uint64_t n, uint64_t m, uint64_t* min_byte
     }
     *min_bytes = 8 * p.L;
     *cls = p.cls;
-    return p.tiles() * *min_bytes;
+    return p.shared ? (p.packs(p.cgroup) + p.nouts) * *min_bytes : p.tiles() * *min_bytes;
 }
 
 // Whether AUTO puts request (n, m) on the direct GF(2) path (short outputs).
@@ -212,7 +212,7 @@ void Ctx::serve_loop() {
             std::vector<TilePlan> plans(batch.size());
             pa_status s = PA_OK;
             for (size_t k = 0; k < batch.size() && s == PA_OK; ++k)
-                if (!plan_at_class(ns[k], ms[k], PREC_FP32, cls, cm, &plans[k])) s = PA_EINVAL;
+                if (!plan_at_class(ns[k], ms[k], PREC_FP32, cls, cm, &plans[k], budget / 3)) s = PA_EINVAL;
             std::vector<JobDesc> jobs(batch.size());
             if (s == PA_OK) {
                 for (size_t k = 0; k < batch.size(); ++k)
