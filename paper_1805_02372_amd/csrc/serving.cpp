@@ -91,7 +91,7 @@ void Ctx::serve_loop() {
         // completions
         for (size_t i = 0; i < lanes.size(); ++i) {
             if (!busy[i]) continue;
-            if (hipEventQuery(lanes[i].done) == hipErrorNotReady) {
+            if (!lanes[i].ended()) {
                 any_busy = true;
                 continue;
             }
@@ -184,6 +184,7 @@ void Ctx::serve_loop() {
                 pa_status s = ln.direct_batch(this, dj, &lane_stats[i]);
                 ln.jobs.clear();
                 ln.total_groups = 0;
+                ln.flagged = false;   // no certificates: an event marks the end
                 if (s == PA_OK && !ln.done && hipEventCreateWithFlags(&ln.done, hipEventDisableTiming) != hipSuccess)
                     s = PA_EDEVICE;
                 if (s == PA_OK && hipEventRecord(ln.done, ln.stream) != hipSuccess) s = PA_EDEVICE;
