@@ -30,11 +30,11 @@ static const ClassKernels kClasses32[] = {
     PA_FUSED(12),
     PA_FUSED(13),
     PA_CLASS(14, 128, 128),
-    PA_CLASS(15, 256, 128),
-    PA_CLASS(16, 256, 256),
-    PA_CLASS(17, 512, 256),
-    PA_CLASS(18, 512, 512),
-    PA_CLASS(19, 1024, 512),
+    PA_CLASS2(15, 512, 64),
+    PA_CLASS2(16, 512, 128),
+    PA_CLASS2(17, 512, 256),
+    PA_CLASS2(18, 512, 512),
+    PA_CLASS2(19, 512, 1024),
     PA_CLASS2(20, 4096, 256),
     PA_CLASS2S(21, 4096, 512),
     PA_CLASS2S(22, 4096, 1024),

@@ -1,4 +1,4 @@
-// Tile pipeline for the long FFT length classes (L = 8192 * n2, n2 = 128..2048):
+// Tile pipeline of the power-of-two FFT length classes from 2^15 on:
 // the same three passes as conv_kernels.hpp (see there for the mathematics),
 // restructured around wave-level transforms (wave_fft.hpp):
 //
@@ -22,37 +22,53 @@
 
 namespace pa {
 
-template <typename T, int N2> struct P1Geom {
+// Lengths below 2^20 are bound by latency (one tile fills a fraction of the
+// device), so their rows are 512 points, one wave each and without barriers, and
+// their column workgroups small.  Against workgroup-wide passes on 512 x 512 (64
+// column workgroups, rows of 1-2 waves with barriers): FP64 2^18, one tile,
+// passes 11.8 + 10.9 + 12.5 -> 10.0 + 7.6 + 7.8 us, call 41.4 -> 36.0 us; four
+// FP32 tiles of 2^19, 18.9 + 17.6 + 14.9 -> 22.4 + 17.0 + 9.4 us (summed, one
+// pass 3), call 62.7 -> 57.5 us.
+//
+// Column blocks.  A wave takes G columns (or one half of a column), a workgroup
+// as many waves, up to 8, as make row segments of 128 bytes (rows of 512, whose
+// launches seldom fill the device: 64 bytes, twice the workgroups).
+template <typename T, int N1> constexpr int column_target() { return (N1 >= 4096 ? 128 : 64) / (int)sizeof(cx<T>); }
+constexpr int column_waves(int target, int g) { return target <= g ? 1 : (target / g > 8 ? 8 : target / g); }
+
+template <typename T, int N1, int N2> struct P1Geom {
     static constexpr int H = N2 > 1024 ? N2 / 1024 : 1;    // halves of a column
     static constexpr bool WGH = H == 2 && sizeof(T) == 4;  // each half in a workgroup of its own
     static constexpr int M = N2 > 1024 ? 1024 : N2;        // wave transform size
     static constexpr int G = 1024 / M;                     // columns per wave
-    static constexpr int WAVES = 8;
+    static constexpr int WAVES = H == 2 ? 8 : column_waves(column_target<T, N1>(), G);
     static constexpr int C = WAVES * G / (WGH ? 1 : H);    // columns per workgroup
     static constexpr int THREADS = WAVES * 64;
+    static constexpr bool kPlanes = N1 >= 1024;            // bits from planes (else gathered)
     static_assert(H <= 2, "column length up to 2048");
     static_assert(C <= 64 && (C & (C - 1)) == 0, "column block");
 };
 
-template <typename T, int N2> struct P3Geom {
+template <typename T, int N1, int N2> struct P3Geom {
     static constexpr int M = N2 / 2;                       // Hermitian half
     static constexpr int G = 1024 / M;
-    static constexpr int WAVES = (sizeof(T) == 4 && G == 1) ? 16 : 8;   // >= 128 B row segments
+    static constexpr int CT = N1 >= 4096 ? 16 : 8;         // output groups of 8 bits and more
+    static constexpr int WAVES = (sizeof(T) == 4 && G == 1) ? 16 : column_waves(CT, G);
     static constexpr int C = WAVES * G;
     static constexpr int THREADS = WAVES * 64;
     static constexpr int CW = (C + 31) / 32;               // 32-bit words per output row
     static constexpr int SLOTS = (WAVES * kWaveSlots > M * C) ? WAVES * kWaveSlots : M * C;
     // LDS with the stage tables and Hermitian twiddles copied in (the twiddles
-    // share space with the output bit array) vs without; copy them only when
-    // the workgroups per CU (160 KB of LDS) stay the same.
+    // share space with the output bit array) vs without; copy them when a CU
+    // still holds its waves, or as many workgroups as without them.
+    static constexpr int WPE = sizeof(T) == 4 ? 4 : 2;     // waves per SIMD that the registers allow
     static constexpr size_t kBits = (size_t)WAVES * 64 * 4;   // 32 output bits per lane
     static constexpr size_t kHtw = (size_t)M * sizeof(cx<T>);
     static constexpr size_t kBase = (size_t)SLOTS * sizeof(cx<T>) + C * sizeof(T) + 64;
     static constexpr size_t kWithout = kBase + kBits;
     static constexpr size_t kWith = kBase + (kBits > kHtw ? kBits : kHtw) + wfft_lds_entries(M) * sizeof(cx<T>);
-    static constexpr bool LDS_TAB = kWith <= 163840 && (163840 / kWith) >= (163840 / kWithout);
-    // workgroups per CU that the LDS allows; registers are capped to match
-    static constexpr int MIN_WG = (163840 / (LDS_TAB ? kWith : kWithout)) >= 2 ? 2 : 1;
+    static constexpr bool LDS_TAB =
+        kWith <= 163840 && (kWith * (4 * WPE / WAVES) <= 180000 || (163840 / kWith) >= (163840 / kWithout));
 };
 
 // Transposition tile: row k2 of C elements, columns XOR-swizzled by the row.
@@ -207,7 +223,7 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
     using Pl = BitPlanes<N1, N2>;
     constexpr uint32_t L = (uint32_t)N1 * N2;
     constexpr int NRC = N2 / 64, NCC = N1 / 64 / kBitsCols;   // row and column blocks of a plane
-    static_assert(NRC % 4 == 0 && N1 % (64 * kBitsCols) == 0, "blocks");
+    static_assert((2 * NRC * NCC) % 4 == 0 && N1 % (64 * kBitsCols) == 0, "blocks");
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6);
     const uint32_t rc = wave % NRC, cc = (wave / NRC) % NCC, pl = (wave / (NRC * NCC)) & 1u;
@@ -252,6 +268,33 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
             transpose64(v[c], lane);
 }
 
+// The same word gathered by the lane itself: one 32-bit load per bit, all
+// issued before the first wait.  For the rows of 512: their pass 1 takes about
+// 10 us at 2^18 points in FP32 and FP64 alike, mostly latency, against the 5.5 us
+// that a launch of k2_bits takes at any short length.
+template <int N1, int N2>
+__device__ __forceinline__ uint32_t gather_bits(const BitSeq& q, uint32_t t1, uint32_t j) {
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int NJ = BitPlanes<N1, N2>::NJ;
+    static_assert(BitPlanes<N1, N2>::BITS == 16, "16 rows per lane");
+    const uint32_t* __restrict__ src = reinterpret_cast<const uint32_t*>(q.src) + (q.j0 >> 5);
+    const uint64_t left = 2 * q.nw - 1 - (q.j0 >> 5);
+    const uint32_t last = left < 0xFFFFFFFFull ? (uint32_t)left : 0xFFFFFFFFu, o = (uint32_t)q.j0 & 31u;
+    uint32_t u[16], w[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        uint32_t p = t1 + (uint32_t)N1 * (j + (uint32_t)(NJ * i)) + q.off;
+        if (p >= L) p -= L;
+        u[i] = p;
+        const uint32_t at = (p + o) >> 5;
+        w[i] = src[at < last ? at : last];
+    }
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) r |= (u[i] < q.len ? (w[i] >> ((u[i] + o) & 31u)) & 1u : 0u) << i;
+    return r;
+}
+
 // Values of bit i of a plane word: a key bit, or a seed bit before the mask of
 // the slice's end (seed_mask).
 template <typename T> __device__ __forceinline__ T key_value(uint32_t w, int i) { return (T)((w >> i) & 1u); }
@@ -290,12 +333,12 @@ __device__ __forceinline__ void column_input(T (&x)[16], uint32_t w, bool seed, 
 // w_2048^e).  The halves of a column are two waves of one workgroup in FP64 and
 // two workgroups in FP32 (the LDS of one half: two workgroups per CU).
 template <typename T, int N1, int N2>
-__global__ void __launch_bounds__((P1Geom<T, N2>::THREADS))
+__global__ void __launch_bounds__((P1Geom<T, N1, N2>::THREADS))
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
          const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
          int fshift) {
-    using Gm = P1Geom<T, N2>;
+    using Gm = P1Geom<T, N1, N2>;
     using Pl = BitPlanes<N1, N2>;
     constexpr int C = Gm::C, G = Gm::G, H = Gm::H, M = Gm::M, NJ = M / 16;
     constexpr bool WGH = Gm::WGH;
@@ -327,12 +370,16 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
     }
     const uint32_t t1 = cb * C + (uint32_t)f;
     // this lane's bits of the two sequences
-    const typename Pl::Word* __restrict__ pw =
-        reinterpret_cast<const typename Pl::Word*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * Pl::NJ + j;
-    const uint32_t w0 = pw[0], w1 = pw[Pl::kPlane / sizeof(typename Pl::Word)];
+    uint32_t w0, w1;
+    if constexpr (Gm::kPlanes) {
+        const typename Pl::Word* __restrict__ pw =
+            reinterpret_cast<const typename Pl::Word*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * Pl::NJ + j;
+        w0 = pw[0];
+        w1 = pw[Pl::kPlane / sizeof(typename Pl::Word)];
+    }
     uint32_t len[2];
     bool seed[2];
-    if (jt.shared.kpacks) {
+    if (Gm::kPlanes && jt.shared.kpacks) {
         const TileBits tb = shared_bits(jt, lt);
 #pragma unroll
         for (int h = 0; h < 2; ++h) len[h] = tb.s[h].len, seed[h] = tb.s[h].seed;
@@ -345,6 +392,11 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
         seed[0] = false;
         len[1] = (uint32_t)(g.bi + g.bo - 1);
         seed[1] = true;
+        if constexpr (!Gm::kPlanes) {
+            const TileBits tb = tile_bits(jd, g);
+            w0 = gather_bits<N1, N2>(tb.s[0], t1, (uint32_t)j);
+            w1 = gather_bits<N1, N2>(tb.s[1], t1, (uint32_t)j);
+        }
     }
     if (tid == 0) wsum = 0;
     wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
@@ -430,12 +482,13 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
 // wave; the inverse runs the same steps in reverse.  Two workgroup barriers per
 // row transform.  Rows of 4096 take 8 points per lane (8 x 8 x 8 x 8: a mirror
 // pair and the group's sum are 48 registers per lane in FP32, so that two
-// workgroups of 8 waves share a CU); rows of 8192 take 16 (8 x 4 x 16 x 16).
+// workgroups of 8 waves share a CU); rows of 8192 take 16 (8 x 4 x 16 x 16), rows
+// of 512 are one wave's (8 x 8 x 8, no barriers).
 template <typename T, int N1> struct RowGeom {
     static constexpr int PT = N1 >= 8192 ? 16 : 8;
     static constexpr int W = N1 / (64 * PT), M = 64 * PT, S = PT / W, THREADS = N1 / PT;
     static constexpr int SLOTS = M + M / (PT == 16 ? 16 : 8);   // LDS slots of a wave's region
-    static_assert(W == 8 && S * W == PT, "row geometry");
+    static_assert(W >= 1 && W <= 8 && S * W == PT, "row geometry");
     __device__ static __forceinline__ int slot(int e) { return PT == 16 ? e + (e >> 4) : e + (e >> 3); }
 };
 
@@ -457,23 +510,25 @@ template <typename T, int N1> struct RowSmem {
 // + ka - 1]; rows of 4096 also the last stage, w_512^{l r} at t3[r - 1].
 template <typename T, int N1> struct RowReg {
     using G = RowGeom<T, N1>;
-    cx<T> tw1[G::S * (G::W - 1)];
+    cx<T> tw1[G::W > 1 ? G::S * (G::W - 1) : 1];
     cx<T> t3[G::PT == 8 ? 7 : 1];
 };
 
-template <typename T, int N1>
+// tw: w_NT^e, NT = max(n1, n2)
+template <typename T, int N1, int N2>
 __device__ __forceinline__ void row_setup(RowSmem<T, N1>& S, RowReg<T, N1>& R, const cx<T>* __restrict__ tw,
                                           const cx<T>* __restrict__ stw, int tid) {
     using G = RowGeom<T, N1>;
+    constexpr int STEP = cmax<N1, N2>() / N1;
 #pragma unroll
     for (int s = 0; s < G::S; ++s)
 #pragma unroll
-        for (int ka = 1; ka < G::W; ++ka) R.tw1[s * (G::W - 1) + ka - 1] = tw[ka * (tid + G::THREADS * s)];
+        for (int ka = 1; ka < G::W; ++ka) R.tw1[s * (G::W - 1) + ka - 1] = tw[STEP * ka * (tid + G::THREADS * s)];
     if constexpr (G::PT == 8) {
         const int l = tid & 63;
 #pragma unroll
-        for (int r = 1; r < 8; ++r) R.t3[r - 1] = tw[l * r * (N1 / 512)];
-        if (tid < 56) S.st[tid] = tw[(tid & 7) * ((tid >> 3) + 1) * (N1 / 64)];
+        for (int r = 1; r < 8; ++r) R.t3[r - 1] = tw[STEP * l * r * (N1 / 512)];
+        if (tid < 56) S.st[tid] = tw[STEP * (tid & 7) * ((tid >> 3) + 1) * (N1 / 64)];
     } else {
         wfft_load_lds<T, 1024>(S.st, stw, tid, G::THREADS);
     }
@@ -534,6 +589,10 @@ __device__ __forceinline__ void row_forward(RowVec<T, N1>& a, RowSmem<T, N1>& S,
                                             int tid) {
     using G = RowGeom<T, N1>;
     const int wv = tid >> 6, l = tid & 63;
+    if constexpr (G::W == 1) {   // one wave: the loaded order is the transform's
+        row_wave_fft<T, N1, -1>(a, S.data, l, S, R);
+        return;
+    }
 #pragma unroll
     for (int s = 0; s < G::S; ++s) {
         dft<G::W, -1>(&a[s * G::W]);
@@ -561,6 +620,11 @@ __device__ __forceinline__ void row_inverse(RowVec<T, N1>& a, RowSmem<T, N1>& S,
     using G = RowGeom<T, N1>;
     const int wv = tid >> 6, l = tid & 63;
     cx<T>* reg = S.data + wv * G::SLOTS;
+    if constexpr (G::W == 1) {
+        wave_sync();
+        row_wave_fft<T, N1, +1>(a, reg, l, S, R);
+        return;
+    }
     __syncthreads();  // every wave is done with its region
     row_wave_fft<T, N1, +1>(a, reg, l, S, R);
     wave_sync();   // the wave's own region: no other wave uses it until the barrier below
@@ -586,7 +650,8 @@ __device__ __forceinline__ void row_mirror(RowVec<T, N1>& X, cx<T>* lds, int tid
     wave_sync();   // X was produced in the wave's own region, which no other wave touches
 #pragma unroll
     for (int i = 0; i < G::PT; ++i) lds[wv * G::SLOTS + G::slot(l) + G::slot(64) * i] = X[i];
-    __syncthreads();
+    if constexpr (G::W == 1) wave_sync();
+    else __syncthreads();
     const int sw = zero ? ((G::W - wv) & (G::W - 1)) : (G::W - 1 - wv);
 #pragma unroll
     for (int i = 0; i < G::PT; ++i) {
@@ -707,11 +772,13 @@ __device__ __forceinline__ void row_unit(uint32_t u, const JobTable& jt, cx<T>* 
     }
 }
 
-// Workgroups per CU: rows of 4096 in FP32 two (16 waves), else one.
-template <typename T, int N1> constexpr int row_wgs_per_cu() { return N1 == 4096 && sizeof(T) == 4 ? 2 : 1; }
+// Waves per SIMD: 4 in FP32 (two workgroups of rows of 4096 per CU), 2 in FP64
+// and for rows of 8192.
+template <typename T, int N1> constexpr int row_waves_per_eu() { return sizeof(T) == 4 && N1 <= 4096 ? 4 : 2; }
+template <typename T, int N1> constexpr int row_wgs_per_cu() { return row_waves_per_eu<T, N1>() * 4 / RowGeom<T, N1>::W; }
 template <typename T, int N1, int N2, int NCB1>
 __global__ void __launch_bounds__((RowGeom<T, N1>::THREADS))
-__attribute__((amdgpu_waves_per_eu(row_wgs_per_cu<T, N1>() * RowGeom<T, N1>::THREADS / 256)))
+__attribute__((amdgpu_waves_per_eu(row_waves_per_eu<T, N1>())))
 k2_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
          const cx<T>* __restrict__ tw, const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64,
          const cx<double>* __restrict__ fb64, int fshift) {
@@ -719,7 +786,7 @@ k2_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part,
     __shared__ uint32_t wsum;
     const uint32_t units = jt.ngroups * (uint32_t)(N2 / 2);
     RowReg<T, N1> R;
-    row_setup<T, N1>(S, R, tw, stw, threadIdx.x);
+    row_setup<T, N1, N2>(S, R, tw, stw, threadIdx.x);
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x)
         row_unit<T, N1, N2, NCB1>(u, jt, ws, part, meta, S, R, wsum, fa64, fb64, fshift);
 }
@@ -743,7 +810,7 @@ k2_rows(JobTable jt, cx<T>* __restrict__ ws, const cx<T>* __restrict__ tw, const
     __shared__ __align__(16) RowSmem<T, N1> S;
     RowReg<T, N1> R;
     const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
-    row_setup<T, N1>(S, R, tw, stw, tid);
+    row_setup<T, N1, N2>(S, R, tw, stw, tid);
     const uint32_t units = jt.ntiles * (uint32_t)N2;
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
         cx<T>* __restrict__ row = ws + (size_t)u * N1;   // tiles and rows are contiguous
@@ -808,7 +875,7 @@ k2_mac(JobTable jt, const cx<T>* __restrict__ ws, cx<T>* __restrict__ win, uint3
 // rows of V (natural order) for pass 3; the unit of row 0 sets the certificate.
 template <typename T, int N1, int N2, int NCB1>
 __global__ void __launch_bounds__((RowGeom<T, N1>::THREADS))
-__attribute__((amdgpu_waves_per_eu(row_wgs_per_cu<T, N1>() * RowGeom<T, N1>::THREADS / 256)))
+__attribute__((amdgpu_waves_per_eu(row_waves_per_eu<T, N1>())))
 k2_rows_inv(JobTable jt, cx<T>* __restrict__ win, const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
             const cx<T>* __restrict__ tw, const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64,
             const cx<double>* __restrict__ fb64, int fshift) {
@@ -818,7 +885,7 @@ k2_rows_inv(JobTable jt, cx<T>* __restrict__ win, const uint32_t* __restrict__ p
     __shared__ uint32_t wsum;
     RowReg<T, N1> R;
     const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
-    row_setup<T, N1>(S, R, tw, stw, tid);
+    row_setup<T, N1, N2>(S, R, tw, stw, tid);
     const uint32_t units = jt.ngroups * NR;
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
         const uint32_t o = u / NR, k2 = u % NR;
@@ -850,11 +917,11 @@ __device__ __forceinline__ uint32_t low2(double r) {
 }
 
 template <typename T, int N1, int N2>
-__global__ void __launch_bounds__((P3Geom<T, N2>::THREADS))
-__attribute__((amdgpu_waves_per_eu(P3Geom<T, N2>::MIN_WG * P3Geom<T, N2>::WAVES / 4)))
+__global__ void __launch_bounds__((P3Geom<T, N1, N2>::THREADS))
+__attribute__((amdgpu_waves_per_eu(P3Geom<T, N1, N2>::WPE)))
 k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta, const cx<T>* __restrict__ tw,
          const cx<T>* __restrict__ stw) {
-    using Gm = P3Geom<T, N2>;
+    using Gm = P3Geom<T, N1, N2>;
     constexpr int C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16, CW = Gm::CW;
     constexpr uint32_t L = (uint32_t)N1 * N2;
     constexpr int NCB = N1 / C;
@@ -894,7 +961,7 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
         if (tid < C) hrow[tid] = V[(size_t)M * N1 + cb * C + tid].re;   // H[n2/2], real
         if constexpr (LT) {
             wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
-            for (int k = tid; k < M; k += Gm::THREADS) U.htw[k] = tw[k * (N1 / N2)];
+            for (int k = tid; k < M; k += Gm::THREADS) U.htw[k] = tw[k * (cmax<N1, N2>() / N2)];
         }
 #pragma unroll
         for (int q = 0; q < LPT; ++q) {
@@ -921,7 +988,7 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
         } else {
             const cx<T> hm = conj(lds[tslot<C>(M - k, f)]);
             const cx<T> e = h + hm;
-            const cx<T> wk = LT ? U.htw[k] : tw[k * (N1 / N2)];
+            const cx<T> wk = LT ? U.htw[k] : tw[k * (cmax<N1, N2>() / N2)];
             const cx<T> o = cmulc(h - hm, wk);
             v[i] = cx<T>{e.re - o.im, e.im + o.re};
         }
@@ -1000,15 +1067,17 @@ int launch_row_pass(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta
 
 template <typename T, int N1, int N2>
 struct ClassImpl2 {
-    using G1 = P1Geom<T, N2>;
-    using G3 = P3Geom<T, N2>;
+    using G1 = P1Geom<T, N1, N2>;
+    using G3 = P3Geom<T, N1, N2>;
     static constexpr int C1 = G1::C, C3 = G3::C;
     // workspace bytes per tile beyond its points: the bit planes
-    static constexpr size_t kWsExtra = BitPlanes<N1, N2>::kTile;
+    static constexpr size_t kWsExtra = G1::kPlanes ? BitPlanes<N1, N2>::kTile : 0;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
-        uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
-        hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (2 * (N2 / 64) * (N1 / 64 / kBitsCols) / 4)), dim3(256), 0,
-                           (hipStream_t)stream, jt, planes);
+        if constexpr (G1::kPlanes) {
+            uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
+            hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (2 * (N2 / 64) * (N1 / 64 / kBitsCols) / 4)), dim3(256),
+                               0, (hipStream_t)stream, jt, planes);
+        }
         hipLaunchKernelGGL((k2_pass1<T, N1, N2>), dim3(jt.ntiles * (N1 / C1) * (G1::WGH ? 2 : 1)), dim3(G1::THREADS), 0,
                            (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
                            (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);

@@ -62,10 +62,9 @@ bool class_geometry(int prec, int cls, ClassGeom* g) {
     g->prec = prec;
     g->cls = cls;
     g->L = L;
-    g->r = 16;
     if (cls >= 32) {   // mixed-radix class L = P 2^k (FP32 and FP64 only)
         if (prec != PREC_FP32 && prec != PREC_FP64) return false;
-        // power-of-two rows: those of the class 2^k below 2^20, else 8192;
+        // power-of-two rows, 4096 points from 2^20 on;
         // the columns carry the factor P (radix-P stage, 4P points per thread)
         const int P = smooth_P(cls), k = smooth_k(cls);
         // rows of the three-pass geometry of 2^k (its short lengths run as
@@ -73,9 +72,6 @@ bool class_geometry(int prec, int cls, ClassGeom* g) {
         const int n2log = std::max(k - 13, std::min(prec == PREC_FP64 ? 11 : 10, k / 2));
         g->n1 = L >= (1ull << 20) ? 4096 : 1 << (k - n2log);
         g->n2 = (int)(L / (uint64_t)g->n1);
-        g->b1 = prec == PREC_FP64 ? 4 : 8;
-        g->b3 = prec == PREC_FP64 || g->n2 > 2048 ? 8 : 16;
-        g->r = 4 * P;
         return true;
     }
     const int logL = cls;
@@ -83,47 +79,29 @@ bool class_geometry(int prec, int cls, ClassGeom* g) {
         const int n2log = std::min(11, logL / 2);
         g->n2 = 1 << n2log;
         g->n1 = 1 << (logL - n2log);
-        g->b1 = 4;
-        g->b3 = 8;
         return true;
     }
-    if (logL >= 20) {  // wave-level classes
+    if (logL >= 15) {  // wave-level classes
         const bool f32 = prec != PREC_FP64;
         // rows of 4096: the row pass then has two workgroups per CU in FP32, and
         // registers to spare in FP64.  FP32 2^24 keeps 8192 (its wave-level column
         // passes take at most 2048 points), FP64 2^24 takes workgroup-wide ones
-        const int n1log = f32 && logL == 24 ? 13 : 12;
-        const int n2 = 1 << (logL - n1log);
-        if (n2 == 4096) {
-            g->n1 = 4096;
-            g->n2 = 4096;
-            g->b1 = 4;
-            g->b3 = 8;
-            return true;
-        }
-        const int w = n2 > 1024 ? n2 / 1024 : 1, m = n2 > 1024 ? 1024 : n2;
-        const int waves1 = (f32 && w > 1) ? 16 : 8;
-        const int g3 = 1024 / (n2 / 2);
-        const int waves3 = (f32 && g3 == 1) ? 16 : 8;
+        // (columns of 4096).  Below 2^20 a row is one wave's 512 points: many small
+        // workgroups, no barriers
+        const int n1log = logL < 20 ? 9 : f32 && logL == 24 ? 13 : 12;
         g->n1 = 1 << n1log;
-        g->n2 = n2;
-        g->b1 = waves1 * (1024 / m) / w;
-        g->b3 = waves3 * g3;
+        g->n2 = 1 << (logL - n1log);
         return true;
     }
     if (logL <= 13) {   // one-kernel tiles: the whole length in one workgroup
         g->n1 = 1 << logL;
         g->n2 = 1;
-        g->b1 = g->n1;
-        g->b3 = g->n1;
         return true;
     }
     int n2cap = prec == PREC_FP64 ? 11 : 10;
     int n2log = std::max(logL - 13, std::min(n2cap, logL / 2));
     g->n2 = 1 << n2log;
     g->n1 = 1 << (logL - n2log);
-    g->b1 = prec == PREC_FP64 ? 4 : 8;
-    g->b3 = prec == PREC_FP64 ? 8 : 16;
     return true;
 }
 
@@ -371,8 +349,10 @@ bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostMode
 }
 
 // Classes whose row pass sums the products of several chunks: those with
-// wave-level rows (from 2^20 points on).
-static bool class_sums(int prec, int cls) { return prec != PREC_NTT && class_len(cls) >= (1ull << 20); }
+// wave-level rows (powers of two from 2^15, mixed-radix lengths from 2^20 on).
+static bool class_sums(int prec, int cls) {
+    return prec != PREC_NTT && (cls < 32 ? cls >= 15 : class_len(cls) >= (1ull << 20));
+}
 
 // Classes with shared spectra (ClassKernels::shared1).
 static bool class_shared(int prec, int cls) { return prec == PREC_FP32 && cls >= 21 && cls <= 23; }

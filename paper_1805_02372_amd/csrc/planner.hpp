@@ -14,7 +14,7 @@ enum Prec { PREC_FP32 = 32, PREC_FP64 = 64, PREC_NTT = 1, PREC_DIRECT = 2 };
 struct ClassGeom {
     int prec, cls;        // precision, class id (pa_internal.hpp)
     uint64_t L;           // FFT length n1 * n2
-    int n1, n2, b1, b3, r;
+    int n1, n2;
 };
 
 // Geometry of class `cls` in the given precision; false if none.
