@@ -195,10 +195,9 @@ static pa_status stage_to_device(Ctx* c, Lane& ln, void* const* dst, const void*
     return PA_OK;
 }
 
-// Device outputs back to host memory through the pinned staging buffer
-// (synchronises the lane's stream).
-static pa_status stage_to_host(Ctx* c, Lane& ln, void* const* dst, const void* const* src, const size_t* bytes,
-                               int count) {
+// Device outputs back to host memory through the pinned staging buffer: the DMAs
+// behind what is on the lane's stream, then (synchronising it) the copies.
+static pa_status fetch_outputs(Lane& ln, const void* const* src, const size_t* bytes, int count) {
     size_t total = 0;
     for (int k = 0; k < count; ++k) total += (bytes[k] + 255) & ~(size_t)255;
     pa_status st = ln.io_host.ensure(total);
@@ -210,13 +209,23 @@ static pa_status stage_to_host(Ctx* c, Lane& ln, void* const* dst, const void* c
             return PA_EDEVICE;
         off += (bytes[k] + 255) & ~(size_t)255;
     }
+    return PA_OK;
+}
+
+static pa_status unstage_outputs(Ctx* c, Lane& ln, void* const* dst, const size_t* bytes, int count) {
     if (hipStreamSynchronize(ln.stream) != hipSuccess) return PA_EDEVICE;
-    off = 0;
+    size_t off = 0;
     for (int k = 0; k < count; ++k) {
         c->copier.copy(dst[k], (unsigned char*)ln.io_host.ptr + off, bytes[k]);
         off += (bytes[k] + 255) & ~(size_t)255;
     }
     return PA_OK;
+}
+
+static pa_status stage_to_host(Ctx* c, Lane& ln, void* const* dst, const void* const* src, const size_t* bytes,
+                               int count) {
+    const pa_status st = fetch_outputs(ln, src, bytes, count);
+    return st == PA_OK ? unstage_outputs(c, ln, dst, bytes, count) : st;
 }
 
 pa_status stage_in(Ctx* c, Lane& ln, void* const* dst, const void* const* src, const size_t* bytes, int count) {
@@ -980,6 +989,11 @@ pa_status pa_hash(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t m, con
     }
     const bool timing = flags & PA_TIMING;
     pa_status s = PA_OK;
+    // host output: its DMA is enqueued behind the kernels and ahead of the wait for
+    // the certificates; a fallback fetches it again
+    void* const hdst[1] = {out};
+    const void* const hsrc[1] = {dout};
+    const size_t hlen[1] = {ow * 8};
     CostModel cm;
     {
         std::lock_guard<std::mutex> pk(c->plan_mu);
@@ -993,6 +1007,7 @@ pa_status pa_hash(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t m, con
         st.window_bits = m;
         if (timing) ln.timer.reset();
         s = ln.direct(c, dseed, dkey, n, m, dout, timing, &st);
+        if (s == PA_OK && !dev) s = fetch_outputs(ln, hsrc, hlen, 1);
         const bool async = dev && (flags & PA_ASYNC) && !timing;
         if (s == PA_OK && !async && hipStreamSynchronize(ln.stream) != hipSuccess) s = PA_EDEVICE;
         if (s == PA_OK && timing) ln.timer.collect(st.ms_pass);
@@ -1004,14 +1019,12 @@ pa_status pa_hash(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t m, con
         // launch to finish.
         const bool async = dev && (flags & PA_ASYNC) && plan.rigorous < kRigorousLimit && !timing;
         s = ln.launch(c, plan.prec, plan.cls, jobs, timing, !async, &st);
+        if (s == PA_OK && !dev) s = fetch_outputs(ln, hsrc, hlen, 1);
         if (s == PA_OK && !async) s = ln.finish(c, flags, &st, nullptr);
+        if (s == PA_OK && !dev && st.fallback_tiles) s = fetch_outputs(ln, hsrc, hlen, 1);
     }
-    if (s == PA_OK && !dev) {
-        void* dsts[1] = {out};
-        const void* srcs[1] = {dout};
-        const size_t lens[1] = {ow * 8};
-        s = stage_to_host(c, ln, dsts, srcs, lens, 1);
-    }
+    if (s == PA_OK && !dev) s = unstage_outputs(c, ln, hdst, hlen, 1);
+    else if (!dev) (void)hipStreamSynchronize(ln.stream);   // the staging buffer is free for the next call
     set_certified(&st, s);
     c->last = st;
     return s;

@@ -133,13 +133,21 @@ struct Lane {
     pa_status direct_batch(Ctx* c, std::vector<DirectJob>& js, pa_stats* stats);
 };
 
-// GPU resources of a block stream (pa_stream_*): its lane, a copy stream and
-// two staging slots (device buffer, pinned host image, events).  A closed
-// stream's resources stay with the context for the next stream.
+// GPU resources of a block stream (pa_stream_*): two lanes on one GPU stream
+// (two blocks in flight, one behind the other), a copy stream and two staging
+// slots (device buffer, pinned host image, events).  The lanes have certificates
+// and an output each and one workspace, which the stream's order lets them take
+// in turn.  A closed stream's resources stay with the context for the next stream.
 struct StreamRes {
-    Lane ln;
+    Lane ln[2];
     hipStream_t copy = nullptr;
-    DevBuf part, in[2];
+    DevBuf part[2], in[2];
+    // Lane b, holding the workspace.
+    Lane& lane(int b) {
+        if (ln[b ^ 1].ws.ptr) std::swap(ln[b].ws, ln[b ^ 1].ws);
+        if (ln[b ^ 1].part.ptr) std::swap(ln[b].part, ln[b ^ 1].part);
+        return ln[b];
+    }
     HostBuf pin[2];
     hipEvent_t staged[2] = {}, used[2] = {};
     void release(Ctx* c);

@@ -6,11 +6,11 @@
 //
 // Blocks from host memory are pipelined over two staging slots: a feed copies
 // its block into pinned memory and starts the DMA on a copy stream while the
-// previous block's kernels still run, then checks the previous block's
-// certificate (FP64 fallback as in pa_hash), merges it and enqueues its own
-// block behind its DMA.  The last block is checked by the next call on the
-// stream (feed, state, resume or close).  The stream has its own lane (GPU
-// stream and workspace), so it runs beside the context's other calls.
+// previous block's kernels still run, enqueues its own block behind them and its
+// DMA, then checks the previous block's certificate (FP64 fallback as in
+// pa_hash) and merges it.  The last block is checked by the next call on the
+// stream (feed, state, resume or close).  The stream has its own GPU stream and
+// workspace, so it runs beside the context's other calls.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -28,75 +28,121 @@ struct pa_stream {
     uint32_t flags = 0;
     uint64_t fed = 0;
     DevBuf acc;                     // the accumulator
-    StreamRes* r = nullptr;         // lane, copy stream, staging slots
+    StreamRes* r = nullptr;         // lanes, copy stream, staging slots
     int slot = 0;                   // slot of the next host block
-    // the block in flight: its kernels enqueued, its certificate not yet read
-    bool pending = false, pending_fft = false;
-    uint64_t pending_len = 0;
+    // the block in flight: its kernels enqueued on lane `lane`, its certificate
+    // not yet read
+    struct Block {
+        bool live = false, fft = false;
+        uint64_t len = 0;
+        int lane = 0;
+    } pending;
+    bool ahead = true;              // a block may be enqueued before the last one is checked
+    hipStream_t stream() const { return r->ln[0].stream; }
 };
 
 static uint64_t nwords(uint64_t bits) { return (bits + 63) >> 6; }
 
-// Settle the block in flight: wait for it, check its certificate (FP64
-// fallback of failed tiles) and merge it into the accumulator.  On an error
-// the block is dropped (accumulator and fed count unchanged).
-static pa_status drain(pa_stream* s) {
-    if (!s->pending) return PA_OK;
-    s->pending = false;
-    if (s->pending_fft) {
+// Settle a block: wait for it, check its certificate (FP64 fallback of failed
+// tiles) and merge it into the accumulator.  On an error the block is dropped
+// (accumulator and fed count unchanged).
+static pa_status settle(pa_stream* s, const pa_stream::Block& b) {
+    if (!b.live) return PA_OK;
+    if (b.fft) {
         pa_stats st{};
-        const pa_status r = s->r->ln.finish(s->c, s->flags & PA_NO_FALLBACK, &st, nullptr);
+        const pa_status r = s->r->lane(b.lane).finish(s->c, s->flags & PA_NO_FALLBACK, &st, nullptr);
         if (r != PA_OK) return r;
-        if (launch_xor_words((uint64_t*)s->acc.ptr, (const uint64_t*)s->r->part.ptr, nwords(s->m), s->r->ln.stream))
+        if (launch_xor_words((uint64_t*)s->acc.ptr, (const uint64_t*)s->r->part[b.lane].ptr, nwords(s->m), s->stream()))
             return PA_EDEVICE;
     }
-    s->fed += s->pending_len;
+    s->fed += b.len;
     return PA_OK;
 }
 
-// Enqueue the partial hash of one block (device pointers) into `part` on the
-// stream's lane; a direct-product block is merged at once (it has no
-// certificate), an FFT block when drained.
+static pa_status drain(pa_stream* s) {
+    const pa_stream::Block b = s->pending;
+    s->pending.live = false;
+    return settle(s, b);
+}
+
+// Enqueue the partial hash of an FFT block on a lane.
+static pa_status launch_fft(pa_stream* s, int lane, const uint64_t* dseed, const uint64_t* dkey, uint64_t len,
+                            const TilePlan& plan) {
+    pa_stats st{};
+    std::vector<JobDesc> jobs(1);
+    fill_job(&jobs[0], dseed, dkey, (uint64_t*)s->r->part[lane].ptr, len, s->m, plan);
+    return s->r->lane(lane).launch(s->c, plan.prec, plan.cls, jobs, false, true, &st);
+}
+
+// Enqueue the partial hash of one block (device pointers) and settle the block
+// before it; a direct-product block is merged at once (it has no certificate),
+// an FFT block when settled.  The previous block's error is returned, and this
+// block is dropped.  An FFT block is enqueued before the previous one is checked,
+// so that the device goes from one to the next without waiting for the host (8
+// blocks of 16 Mbit, m = 10^6: 1.73 -> 1.54 ms); where the memory of a
+// second output is not there, after it.
 static pa_status launch_block(pa_stream* s, const uint64_t* dseed, const uint64_t* dkey, uint64_t len) {
     Ctx* c = s->c;
     const uint64_t m = s->m;
     const int policy = policy_of(s->flags);
     TilePlan plan;
-    if (!c->plan_cached(len, m, policy, &plan)) return PA_EINVAL;
     CostModel cm;
+    const bool planned = c->plan_cached(len, m, policy, &plan);
     {
         std::lock_guard<std::mutex> pk(c->plan_mu);
         cm = c->cost;
     }
-    pa_stats st{};
-    uint64_t* out = (uint64_t*)s->r->part.ptr;
-    if (choose_direct(s->flags, len, m, cm, plan)) {
-        pa_status r = s->r->ln.direct(c, dseed, dkey, len, m, out, false, &st);
-        if (r != PA_OK) return r;
-        if (launch_xor_words((uint64_t*)s->acc.ptr, out, nwords(m), s->r->ln.stream)) return PA_EDEVICE;
-        s->pending_fft = false;
-    } else {
-        std::vector<JobDesc> jobs(1);
-        fill_job(&jobs[0], dseed, dkey, out, len, m, plan);
-        pa_status r = s->r->ln.launch(c, plan.prec, plan.cls, jobs, false, true, &st);
-        if (r != PA_OK) return r;
-        s->pending_fft = true;
+    const bool direct = planned && choose_direct(s->flags, len, m, cm, plan);
+    if (planned && !direct && s->pending.live && s->pending.fft && s->ahead) {
+        const int b = s->pending.lane ^ 1;
+        if (s->r->part[b].ensure(c, nwords(m) * 8, s->stream()) == PA_OK &&
+            launch_fft(s, b, dseed, dkey, len, plan) == PA_OK) {
+            const pa_status st = drain(s);
+            if (st != PA_OK) {
+                (void)hipStreamSynchronize(s->stream());   // the dropped block's certificates are written
+                return st;
+            }
+            s->pending = {true, true, len, b};
+            return PA_OK;
+        }
+        (void)hipStreamSynchronize(s->stream());   // whatever part of it was enqueued
+        s->ahead = false;
     }
-    s->pending = true;
-    s->pending_len = len;
+    const int b = s->pending.lane;
+    pa_status st = drain(s);
+    if (st != PA_OK) return st;
+    if (!planned) return PA_EINVAL;
+    if (!s->ahead) s->r->part[b ^ 1].release(c);
+    if (direct) {
+        pa_stats stats{};
+        uint64_t* out = (uint64_t*)s->r->part[b].ptr;
+        st = s->r->lane(b).direct(c, dseed, dkey, len, m, out, false, &stats);
+        if (st != PA_OK) return st;
+        if (launch_xor_words((uint64_t*)s->acc.ptr, out, nwords(m), s->stream())) return PA_EDEVICE;
+    } else {
+        st = launch_fft(s, b, dseed, dkey, len, plan);
+        if (st == PA_ENOMEM && s->ahead) {   // the second output's memory
+            s->ahead = false;
+            s->r->part[b ^ 1].release(c);
+            st = launch_fft(s, b, dseed, dkey, len, plan);
+        }
+        if (st != PA_OK) return st;
+    }
+    s->pending = {true, !direct, len, b};
     return PA_OK;
 }
 
 namespace pa {
 void StreamRes::release(Ctx* c) {
-    if (ln.stream) (void)hipStreamSynchronize(ln.stream);
+    if (ln[0].stream) (void)hipStreamSynchronize(ln[0].stream);
     if (copy) (void)hipStreamSynchronize(copy);
-    part.release(c);
     for (int b = 0; b < 2; ++b) {
+        part[b].release(c);
         in[b].release(c);
         pin[b].release();
     }
-    ln.release(c);   // synchronises its stream (the frees above were queued on it)
+    ln[1].release(c);
+    ln[0].release(c);   // synchronises its stream (the frees above were queued on it) and destroys it
     if (copy) {
         (void)hipStreamSynchronize(copy);
         (void)hipStreamDestroy(copy);
@@ -123,17 +169,18 @@ static pa_status take_res(Ctx* c, uint64_t m, StreamRes** out) {
     pa_status st = PA_OK;
     if (!r) {
         r = new StreamRes();
-        if (hipStreamCreateWithFlags(&r->ln.stream, hipStreamNonBlocking) != hipSuccess) st = PA_EDEVICE;
-        r->ln.own_stream = r->ln.stream != nullptr;
+        if (hipStreamCreateWithFlags(&r->ln[0].stream, hipStreamNonBlocking) != hipSuccess) st = PA_EDEVICE;
+        r->ln[0].own_stream = r->ln[0].stream != nullptr;
+        r->ln[1].stream = r->ln[0].stream;
         if (st == PA_OK && hipStreamCreateWithFlags(&r->copy, hipStreamNonBlocking) != hipSuccess) st = PA_EDEVICE;
         for (int b = 0; b < 2 && st == PA_OK; ++b)
             if (hipEventCreateWithFlags(&r->staged[b], hipEventDisableTiming) != hipSuccess ||
                 hipEventCreateWithFlags(&r->used[b], hipEventDisableTiming) != hipSuccess ||
                 hipEventRecord(r->staged[b], r->copy) != hipSuccess ||   // waits on them find them recorded
-                hipEventRecord(r->used[b], r->ln.stream) != hipSuccess)
+                hipEventRecord(r->used[b], r->ln[0].stream) != hipSuccess)
                 st = PA_EDEVICE;
     }
-    if (st == PA_OK) st = r->part.ensure(c, nwords(m) * 8, r->ln.stream);
+    if (st == PA_OK) st = r->part[0].ensure(c, nwords(m) * 8, r->ln[0].stream);
     if (st != PA_OK) {
         r->release(c);
         delete r;
@@ -148,11 +195,12 @@ static void free_stream(pa_stream* s) {
     Ctx* c = s->c;
     (void)hipSetDevice(c->device);
     if (s->r) {
-        (void)hipStreamSynchronize(s->r->ln.stream);
+        (void)hipStreamSynchronize(s->stream());
         (void)hipStreamSynchronize(s->r->copy);
     }
     s->acc.release(c);
     if (s->r) {
+        s->r->part[1].release(c);
         bool kept = false;
         {
             std::lock_guard<std::mutex> lk(c->stream_mu);
@@ -183,12 +231,12 @@ pa_status pa_stream_open(pa_ctx* ctx, uint64_t n, uint64_t m, uint32_t flags, pa
     s->m = m;
     s->flags = flags;
     pa_status st = take_res(c, m, &s->r);
-    if (st == PA_OK) st = s->acc.ensure(c, nwords(m) * 8, s->r->ln.stream);
+    if (st == PA_OK) st = s->acc.ensure(c, nwords(m) * 8, s->stream());
     // x ^ x = 0: clear the accumulator with the XOR kernel itself
     if (st == PA_OK &&
-        launch_xor_words((uint64_t*)s->acc.ptr, (const uint64_t*)s->acc.ptr, nwords(m), s->r->ln.stream))
+        launch_xor_words((uint64_t*)s->acc.ptr, (const uint64_t*)s->acc.ptr, nwords(m), s->stream()))
         st = PA_EDEVICE;
-    if (st == PA_OK && hipStreamSynchronize(s->r->ln.stream) != hipSuccess) st = PA_EDEVICE;
+    if (st == PA_OK && hipStreamSynchronize(s->stream()) != hipSuccess) st = PA_EDEVICE;
     if (st != PA_OK) {
         free_stream(s);
         return st;
@@ -206,7 +254,7 @@ pa_status pa_stream_feed(pa_stream* s, const uint64_t* key_block, uint64_t lo, u
     if (s->flags & PA_DEVICE_PTRS) {   // the caller's buffers, read before the call returns
         pa_status st = launch_block(s, seed_block, key_block, len);
         if (st == PA_OK) st = drain(s);
-        if (hipStreamSynchronize(s->r->ln.stream) != hipSuccess && st == PA_OK) st = PA_EDEVICE;
+        if (hipStreamSynchronize(s->stream()) != hipSuccess && st == PA_OK) st = PA_EDEVICE;
         return st;
     }
     // Stage the block in slot b while the previous block runs: the slot's
@@ -223,20 +271,22 @@ pa_status pa_stream_feed(pa_stream* s, const uint64_t* key_block, uint64_t lo, u
     }
     if (st != PA_OK) return st;
     unsigned char* h = (unsigned char*)s->r->pin[b].ptr;
+    unsigned char* d = (unsigned char*)s->r->in[b].ptr;
     c->copier.copy(h, seed_block, sbytes);
-    c->copier.copy(h + off, key_block, kbytes);
     if (hipStreamWaitEvent(s->r->copy, s->r->used[b], 0) != hipSuccess ||
-        hipMemcpyAsync(s->r->in[b].ptr, h, off + kbytes, hipMemcpyHostToDevice, s->r->copy) != hipSuccess ||
+        hipMemcpyAsync(d, h, sbytes, hipMemcpyHostToDevice, s->r->copy) != hipSuccess)
+        return PA_EDEVICE;
+    c->copier.copy(h + off, key_block, kbytes);   // while the seed's DMA runs
+    if (hipMemcpyAsync(d + off, h + off, kbytes, hipMemcpyHostToDevice, s->r->copy) != hipSuccess ||
         hipEventRecord(s->r->staged[b], s->r->copy) != hipSuccess)
         return PA_EDEVICE;
-    // the previous block: certificate, fallback, merge; its error is this call's
-    st = drain(s);
-    if (st != PA_OK) return st;
-    if (hipStreamWaitEvent(s->r->ln.stream, s->r->staged[b], 0) != hipSuccess) return PA_EDEVICE;
+    // this block behind the previous one, then the previous block's certificate,
+    // fallback and merge; its error is this call's
+    if (hipStreamWaitEvent(s->stream(), s->r->staged[b], 0) != hipSuccess) return PA_EDEVICE;
     const uint64_t* dseed = (const uint64_t*)s->r->in[b].ptr;
-    const uint64_t* dkey = (const uint64_t*)((const unsigned char*)s->r->in[b].ptr + off);
+    const uint64_t* dkey = (const uint64_t*)(d + off);
     st = launch_block(s, dseed, dkey, len);
-    if (hipEventRecord(s->r->used[b], s->r->ln.stream) != hipSuccess && st == PA_OK) st = PA_EDEVICE;
+    if (hipEventRecord(s->r->used[b], s->stream()) != hipSuccess && st == PA_OK) st = PA_EDEVICE;
     s->slot ^= 1;
     return st;
 }
@@ -250,8 +300,8 @@ pa_status pa_stream_state(pa_stream* s, uint64_t* acc, uint64_t* fed_bits) {
     if (fed_bits) *fed_bits = s->fed;
     if (!acc) return PA_OK;
     const hipMemcpyKind kind = (s->flags & PA_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (hipMemcpyAsync(acc, s->acc.ptr, nwords(s->m) * 8, kind, s->r->ln.stream) != hipSuccess ||
-        hipStreamSynchronize(s->r->ln.stream) != hipSuccess)
+    if (hipMemcpyAsync(acc, s->acc.ptr, nwords(s->m) * 8, kind, s->stream()) != hipSuccess ||
+        hipStreamSynchronize(s->stream()) != hipSuccess)
         return PA_EDEVICE;
     return PA_OK;
 }
@@ -262,8 +312,8 @@ pa_status pa_stream_resume(pa_stream* s, const uint64_t* acc, uint64_t fed_bits)
     if (hipSetDevice(c->device) != hipSuccess) return PA_EDEVICE;
     (void)drain(s);   // a block in flight is replaced with the rest of the state
     const hipMemcpyKind kind = (s->flags & PA_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    if (hipMemcpyAsync(s->acc.ptr, acc, nwords(s->m) * 8, kind, s->r->ln.stream) != hipSuccess ||
-        hipStreamSynchronize(s->r->ln.stream) != hipSuccess)
+    if (hipMemcpyAsync(s->acc.ptr, acc, nwords(s->m) * 8, kind, s->stream()) != hipSuccess ||
+        hipStreamSynchronize(s->stream()) != hipSuccess)
         return PA_EDEVICE;
     s->fed = fed_bits;
     return PA_OK;

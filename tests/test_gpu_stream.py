@@ -195,3 +195,35 @@ def test_stream_block_error_reported_by_next_call(pa, ctx, monkeypatch):
     out = np.zeros(synth.words_for(m), np.uint64)
     assert pa.pa_stream_close(s, out) == pa.PA_OK
     assert np.array_equal(synth.bits_to_array(out, m), np.full(m, par, np.uint8))
+
+
+def test_stream_blocks_ahead_within_budget(pa, monkeypatch):
+    """Blocks of one tile enqueued behind one another while the budget holds a
+    second output (125 KB), one at a time where it does not: budgets in steps of
+    16 KB give the same hash from the first that holds the stream on."""
+    monkeypatch.setenv("PA_ONLY_LEN", str(1 << 20))
+    rng = np.random.default_rng(69)
+    n, m = 200_000, 1_000_000
+    p = synth.random_problem(rng, n, m)
+    blocks = _blocks(n, [40_000, 80_000, 120_000, 160_000])
+    idx = np.unique(rng.integers(0, m, 500)).astype(np.uint64)
+    ref = oracle.hash_select(p.seed, n, m, p.key, idx)
+    ok = []
+    for budget in range(8_900_000, 9_700_000, 16_384):
+        c = pa.pa_create(0, budget, None)
+        st, s = pa.pa_stream_open(c, n, m, pa.PA_PREC_FP32_SEG)
+        assert st == pa.PA_OK
+        for lo, length in blocks:
+            st = _feed(pa, s, p, lo, length)
+            if st != pa.PA_OK:
+                break
+        assert st in (pa.PA_OK, pa.PA_ENOMEM), pa.pa_strerror(st)
+        ok.append(st == pa.PA_OK)
+        out = np.zeros(synth.words_for(m), np.uint64)
+        assert pa.pa_stream_close(s, out) == (pa.PA_OK if ok[-1] else pa.PA_EINVAL)
+        pa.pa_destroy(c)
+        if ok[-1]:
+            assert np.array_equal(synth.bits_to_array(out, m)[idx.astype(np.int64)], ref), budget
+    first = ok.index(True)
+    print(f"{first} budgets refused, {len(ok) - first} accepted")
+    assert first > 0 and all(ok[first:])
