@@ -33,9 +33,12 @@ static const ClassKernels kClasses64[] = {
     PA_CLASS2(21, 4096, 512),
     PA_CLASS2(22, 4096, 1024),
     PA_CLASS2(23, 4096, 2048),
-    // columns of 4096 points: workgroup-wide Stockham passes, split exchange
-    {ClassCfg{64, 24, 4096, 4096, 4, 8, 16, 0, true}, &ClassImplS<double, 4096, 4, 8, 16>::pass1,
-     &ClassImplS<double, 4096, 4, 8, 16>::pass2, &ClassImplS<double, 4096, 4, 8, 16>::pass3},
+    // columns of 4096 points: split columns in pass 1, a workgroup-wide Stockham
+    // pass 3 with the split exchange
+    {ClassCfg{64, 24, 4096, 4096, ClassImplS<double, 4096, 8, 16>::C1, 8, 16, ClassImplS<double, 4096, 8, 16>::kWsExtra,
+              true},
+     &ClassImplS<double, 4096, 8, 16>::pass1, &ClassImplS<double, 4096, 8, 16>::pass2,
+     &ClassImplS<double, 4096, 8, 16>::pass3},
 };
 
 const ClassKernels* class_kernels64(int cls) {

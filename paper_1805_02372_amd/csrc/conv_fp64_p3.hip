@@ -4,8 +4,8 @@
 // Rows n1 are a power of two: those of the class 2^k below 2^20
 // (workgroup-wide Stockham row pass, 16 points per thread), else 4096 (the
 // wave-level row pass of conv_v2.hpp).  Columns n2 = L / n1 carry the factor
-// 3: workgroup-wide Stockham column passes with a radix-3 stage, 12 points
-// per thread (conv_kernels.hpp).
+// 3: a split in pass 1 from 2^20 on (conv_v2.hpp), else workgroup-wide Stockham
+// column passes with a radix-3 stage, 12 or 24 points per thread (conv_kernels.hpp).
 #include "conv_kernels.hpp"
 #include "conv_v2.hpp"
 
@@ -14,9 +14,11 @@ namespace pa {
 #define PA_SMOOTH(K, N1, N2, RR, RC)                                                                   \
     {ClassCfg{64, smooth_id(3, K), N1, N2, 4, 8, RC}, &ClassImpl<double, N1, N2, 4, 8, RR, RC, true>::pass1, \
      &ClassImpl<double, N1, N2, 4, 8, RR, RC, true>::pass2, &ClassImpl<double, N1, N2, 4, 8, RR, RC, true>::pass3}
-#define PA_SMOOTH_LONG(K, N2, RC, B3)                                                                   \
-    {ClassCfg{64, smooth_id(3, K), 4096, N2, 4, B3, RC, 0, true}, &ClassImplS<double, N2, 4, B3, RC>::pass1,         \
-     &ClassImplS<double, N2, 4, B3, RC>::pass2, &ClassImplS<double, N2, 4, B3, RC>::pass3}
+#define PA_SMOOTH_LONG(K, N2, RC, B3)                                                                     \
+    {ClassCfg{64, smooth_id(3, K), 4096, N2, ClassImplS<double, N2, B3, RC>::C1, B3, RC,                      \
+              ClassImplS<double, N2, B3, RC>::kWsExtra, true},                                               \
+     &ClassImplS<double, N2, B3, RC>::pass1, &ClassImplS<double, N2, B3, RC>::pass2,                              \
+     &ClassImplS<double, N2, B3, RC>::pass3}
 
 static const ClassKernels kClasses[] = {
     PA_SMOOTH(13, 128, 192, 16, 12),  // L = 24,576

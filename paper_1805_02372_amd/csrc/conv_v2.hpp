@@ -160,12 +160,27 @@ __device__ __forceinline__ TileBits tile_bits(const JobDesc& jd, const TileGeo& 
 // of every tile into planes after the launch's tiles in the workspace: N2 bits
 // per column, as NJ words of N2 / NJ bits (16, or 32 for N2 = 2048); bit i of
 // word j of column t1 is position t1 + N1 (j + NJ i).  A lane of pass 1 then
-// loads one word of each plane, a wave consecutive ones.
+// loads one word of each plane, a wave consecutive ones.  Split columns (P M rows,
+// P = 3, 4, 5, 7) are P transforms of M points on the bits of rows e, e + M, ..:
+// NJ = M / 16, and a lane's word has a field of FW (4 or 8) bits for each of its
+// 16 points, bit FW i + q being row j + NJ i + M q.
+constexpr int column_parts(int n2) { return odd_part(n2) > 1 ? odd_part(n2) : n2 > 2048 ? 4 : 1; }
 template <int N1, int N2> struct BitPlanes {
-    static constexpr int NJ = N2 >= 1024 ? 64 : N2 / 16, BITS = N2 / NJ;
-    static_assert(BITS == 16 || BITS == 32, "plane words");
-    using Word = std::conditional_t<BITS == 32, uint32_t, uint16_t>;
-    static constexpr size_t kPlane = (size_t)N2 * (N1 / 8);
+    static constexpr int P = column_parts(N2), M = N2 / P, FW = P == 1 ? 1 : P <= 4 ? 4 : 8;
+    static constexpr int NJ = M >= 1024 ? 64 : M / 16, BITS = M * FW / NJ;   // bits of a lane
+    static_assert(P == 1 ? BITS == 16 || BITS == 32 : BITS == 16 * FW, "plane words");
+    struct alignas(BITS / 8) Wide {
+        uint32_t w[BITS > 32 ? BITS / 32 : 1];
+    };
+    using Word = std::conditional_t<BITS == 16, uint16_t, std::conditional_t<BITS == 32, uint32_t, Wide>>;
+    static constexpr size_t kColumn = (size_t)M * FW / 8, kPlane = kColumn * N1;
+    // row of bit b of a column's plane bytes (N2 where the bit stands for none)
+    __device__ static __forceinline__ uint32_t row(uint32_t b) {
+        const uint32_t j = b / BITS, r = b % BITS;
+        if constexpr (P == 1) return j + NJ * r;
+        const uint32_t q = r % FW;
+        return q < (uint32_t)P ? j + NJ * (r / FW) + M * q : N2;
+    }
     static constexpr size_t kTile = 2 * kPlane;
     template <typename T>
     __device__ static const uint8_t* base(const cx<T>* ws, uint32_t ntiles, uint32_t lt) {
@@ -173,59 +188,90 @@ template <int N1, int N2> struct BitPlanes {
     }
 };
 
-// 64 bits of a sequence at positions p .. p + 63 (p a multiple of 64): the part
-// before the wrap to index 0, then the part after it.  Word indices are clamped
-// to the source and every load is unconditional, so that a lane issues all its
-// loads back to back.
-struct Seq64 {
-    uint64_t w1, w2;       // first words of the two parts
-    uint32_t s1, s2, c1, c2, fs;
+// 64 bits of a sequence at positions p .. p + 63 (p a multiple of 64), LSB first:
+// the part before the wrap to index 0, then (rarely) the part after it.  32-bit
+// words throughout: on gfx950 a 64-bit shift whose amount is in the last VGPR of
+// the wave's allocation takes a wrong amount now and then, when another wave is
+// resident, and the compiler does not avoid that register.
+struct alignas(8) Bits64 {
+    uint32_t lo, hi;
 };
-__device__ __forceinline__ Seq64 seq64(const BitSeq& q, uint32_t L, uint32_t p) {
-    uint32_t u = p + q.off;
-    if (u >= L) u -= L;
+__device__ __forceinline__ uint32_t low_mask32(int cnt) { return cnt >= 32 ? ~0u : cnt > 0 ? (1u << cnt) - 1u : 0u; }
+__device__ __forceinline__ Bits64 low_bits(Bits64 x, int cnt) {
+    return Bits64{x.lo & low_mask32(cnt), x.hi & low_mask32(cnt - 32)};
+}
+// A lane's loads of one group of 64: three words from word `at` on, clamped to
+// the source, unconditional, so that a lane issues all its loads back to back.
+struct Seq64 {
+    uint32_t w[3], s;      // words, shift
+    uint32_t u;            // index of the first bit
+};
+__device__ __forceinline__ Seq64 seq64(const BitSeq& q, const uint32_t* src, uint32_t last, uint32_t L, uint32_t p) {
     Seq64 r;
-    r.fs = L - u < 64u ? L - u : 64u;
-    r.c1 = u < q.len ? (q.len - u < r.fs ? q.len - u : r.fs) : 0u;
-    r.c2 = q.len < 64u - r.fs ? q.len : 64u - r.fs;
-    const uint64_t b = q.j0 + u;
-    r.w1 = b >> 6;
-    r.s1 = (uint32_t)b & 63u;
-    r.w2 = q.j0 >> 6;
-    r.s2 = (uint32_t)q.j0 & 63u;
+    r.u = p + q.off;
+    if (r.u >= L) r.u -= L;
+    const uint32_t b = r.u + ((uint32_t)q.j0 & 31u), at = b >> 5;
+    r.s = b & 31u;
+#pragma unroll
+    for (uint32_t k = 0; k < 3; ++k) r.w[k] = src[at + k < last ? at + k : last];
     return r;
 }
-__device__ __forceinline__ uint64_t low_mask(uint32_t cnt) { return cnt >= 64u ? ~0ull : (1ull << cnt) - 1ull; }
-__device__ __forceinline__ uint64_t funnel64(uint64_t lo, uint64_t hi, uint32_t s) {
-    return (lo >> s) | ((hi << 1) << (63u - s));   // s = 0: hi drops out
+__device__ __forceinline__ Bits64 funnel(const uint32_t (&w)[3], uint32_t s) {
+    return Bits64{__builtin_amdgcn_alignbit(w[1], w[0], s), __builtin_amdgcn_alignbit(w[2], w[1], s)};
+}
+__device__ __forceinline__ Bits64 shift_left(Bits64 x, uint32_t s) {   // 0 < s < 64
+    if (s >= 32u) return Bits64{0u, x.lo << (s - 32u)};
+    return Bits64{x.lo << s, __builtin_amdgcn_alignbit(x.hi, x.lo, 32u - s)};
 }
 
+// Value of lane l ^ k (k a power of two below 32).
+template <int K> __device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    if constexpr (K == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);         // quad_perm 1 0 3 2
+    else if constexpr (K == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true);    // quad_perm 2 3 0 1
+    else if constexpr (K == 4)   // l ^ 7, then l ^ 3
+        return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (K == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, true);   // rotate a row by 8
+    else return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x401F);                                     // xor 16
+}
+// One step of a bit transpose: lanes l and l ^ K exchange the bits c with
+// (c ^ l) & K set.
+template <int K> __device__ __forceinline__ uint32_t transpose_step(uint32_t x, int lane) {
+    constexpr uint32_t low = K == 1 ? 0x55555555u : K == 2 ? 0x33333333u : K == 4 ? 0x0F0F0F0Fu : K == 8 ? 0x00FF00FFu : 0xFFFFu;
+    const uint32_t y = lane_xor<K>(x);
+    const bool up = (lane & K) != 0;
+    const uint32_t keep = up ? ~low : low, moved = __builtin_amdgcn_alignbit(y, y, up ? K : 32 - K);   // rotated by K
+    return (x & keep) | (moved & ~keep);
+}
 // 64 x 64 bit transpose across a wave: lane r holds row r (bit c: column c) and
 // gets column r (bit c: row c).
-__device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
-    constexpr uint64_t low[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0F0F0F0F0F0F0F0Full,
-                                 0x00FF00FF00FF00FFull, 0x0000FFFF0000FFFFull, 0x00000000FFFFFFFFull};
-#pragma unroll
-    for (int q = 5; q >= 0; --q) {
-        const int k = 1 << q;
-        const uint64_t y = __shfl_xor((unsigned long long)x, k);
-        x = (lane & k) ? ((x & ~low[q]) | ((y >> k) & low[q])) : ((x & low[q]) | ((y & low[q]) << k));
-    }
-    return x;
+__device__ __forceinline__ Bits64 transpose64(Bits64 x, int lane) {
+    // lanes l and l ^ 32: the upper half's low words for the lower half's high words
+    const bool up = lane >= 32;
+    const uint32_t got = __shfl_xor(up ? x.lo : x.hi, 32);
+    if (up) x.lo = got;
+    else x.hi = got;
+    auto half = [&](uint32_t w) {
+        w = transpose_step<16>(w, lane);
+        w = transpose_step<8>(w, lane);
+        w = transpose_step<4>(w, lane);
+        w = transpose_step<2>(w, lane);
+        return transpose_step<1>(w, lane);
+    };
+    return Bits64{half(x.lo), half(x.hi)};
 }
 
-// One wave: 64 rows (64 / BITS words j of every column, lane = (j, i)) by
-// kBitsCols groups of 64 columns of one plane.  Each lane reads consecutive
-// words of its row; a transpose turns them into 8 plane bytes per column.
+// One wave: 64 plane bits of every column (a lane each) by kBitsCols groups of 64
+// columns of one plane.  Each lane reads consecutive words of its bit's row; a
+// transpose turns them into 8 plane bytes per column.
 constexpr int kBitsCols = 4;
 template <int N1, int N2>
 __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict__ planes) {
     using Pl = BitPlanes<N1, N2>;
     constexpr uint32_t L = (uint32_t)N1 * N2;
-    constexpr int NRC = N2 / 64, NCC = N1 / 64 / kBitsCols;   // row and column blocks of a plane
+    constexpr int NRC = (int)Pl::kColumn / 8, NCC = N1 / 64 / kBitsCols;   // row and column blocks of a plane
     static_assert((2 * NRC * NCC) % 4 == 0 && N1 % (64 * kBitsCols) == 0, "blocks");
     const int lane = threadIdx.x & 63;
-    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint32_t wave = xcd_block() * 4 + (threadIdx.x >> 6);   // neighbours share lines on both sides
     const uint32_t rc = wave % NRC, cc = (wave / NRC) % NCC, pl = (wave / (NRC * NCC)) & 1u;
     const uint32_t lt = wave / (2 * NRC * NCC);
     TileBits tb;
@@ -236,35 +282,37 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
         tb = tile_bits(jd, tile_geo(jd, jt.tile0 + lt - jd.tile_begin));
     }
     const BitSeq q = pl ? tb.s[1] : tb.s[0];
-    const uint32_t j = rc * (64 / Pl::BITS) + (uint32_t)(lane / Pl::BITS), i = (uint32_t)(lane % Pl::BITS);
-    const uint32_t p0 = cc * (64 * kBitsCols) + (uint32_t)N1 * (j + Pl::NJ * i);
-    uint64_t v[kBitsCols];
+    const uint32_t row = Pl::row(rc * 64 + lane), p0 = cc * (64 * kBitsCols) + (uint32_t)N1 * row;
+    Bits64 v[kBitsCols];
     if (q.len == 0) {   // no such sequence (a pack of one)
 #pragma unroll
-        for (int c = 0; c < kBitsCols; ++c) v[c] = 0;
+        for (int c = 0; c < kBitsCols; ++c) v[c] = Bits64{0, 0};
     } else {
+        const uint32_t* __restrict__ src = reinterpret_cast<const uint32_t*>(q.src) + (q.j0 >> 5);
+        const uint64_t left = 2 * q.nw - 1 - (q.j0 >> 5);
+        const uint32_t last = left < 0xFFFFFFFFull ? (uint32_t)left : 0xFFFFFFFFu;
         Seq64 e[kBitsCols];
-        uint64_t a[kBitsCols], b[kBitsCols], d[kBitsCols], f[kBitsCols];
-        const uint64_t last = q.nw - 1;
+#pragma unroll
+        for (int c = 0; c < kBitsCols; ++c) e[c] = seq64(q, src, last, L, p0 + 64u * c);
 #pragma unroll
         for (int c = 0; c < kBitsCols; ++c) {
-            e[c] = seq64(q, L, p0 + 64u * c);
-            a[c] = q.src[e[c].w1 < last ? e[c].w1 : last];
-            b[c] = q.src[e[c].w1 + 1 < last ? e[c].w1 + 1 : last];
-            d[c] = q.src[e[c].w2 < last ? e[c].w2 : last];
-            f[c] = q.src[e[c].w2 + 1 < last ? e[c].w2 + 1 : last];
-        }
-#pragma unroll
-        for (int c = 0; c < kBitsCols; ++c) {
-            const uint64_t x = funnel64(a[c], b[c], e[c].s1) & low_mask(e[c].c1);
-            const uint64_t y = funnel64(d[c], f[c], e[c].s2) & low_mask(e[c].c2);
-            v[c] = x | (e[c].fs < 64u ? y << e[c].fs : 0ull);
+            const uint32_t fs = L - e[c].u;   // bits before the wrap
+            const int left_u = (int)q.len - (int)e[c].u;
+            v[c] = low_bits(funnel(e[c].w, e[c].s), left_u < (int)fs ? left_u : (int)fs);
+            if (fs < 64u) {
+                const uint32_t h[3] = {src[0], src[1 < last ? 1 : last], src[2 < last ? 2 : last]};
+                const uint32_t cnt = 64u - fs < q.len ? 64u - fs : q.len;
+                const Bits64 y = shift_left(low_bits(funnel(h, (uint32_t)q.j0 & 31u), (int)cnt), fs);
+                v[c].lo |= y.lo;
+                v[c].hi |= y.hi;
+            }
+            if (Pl::P > 1 && row >= (uint32_t)N2) v[c] = Bits64{0, 0};
         }
     }
     uint8_t* dst = planes + (size_t)lt * Pl::kTile + (size_t)pl * Pl::kPlane + (size_t)rc * 8;
 #pragma unroll
     for (int c = 0; c < kBitsCols; ++c)
-        *reinterpret_cast<uint64_t*>(dst + (size_t)(cc * (64 * kBitsCols) + 64 * c + lane) * (N2 / 8)) =
+        *reinterpret_cast<Bits64*>(dst + (size_t)(cc * (64 * kBitsCols) + 64 * c + lane) * Pl::kColumn) =
             transpose64(v[c], lane);
 }
 
@@ -473,6 +521,136 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
         Y[(size_t)(WGH ? 2 * r + ka : r) * N1 + (idx % C)] = o[q];
     }
     if (tid == 0 && !(WGH && (blk & 1u))) part[(size_t)lt * NCB + cb] = wsum;
+}
+
+// Column pass of the mixed-radix classes and of FP64 2^24: columns of N2 = P M rows
+// (P = 3, 4, 5, 7) by a radix-P split in decimation in frequency.  The outputs k2 = P k + h are the
+// M-point transform of
+//   w_N2^{h e} sum_q z(e + M q) w_P^{h q},
+// and a workgroup makes them for one h and C columns, a wave transforming G
+// columns in registers as in k2_pass1.  The sums need no arithmetic: the inputs
+// are bits, so that P of them index a table of 2^P sums in LDS (of the roots in
+// FP64, rounded once), one lookup for the key and one for the seed, whose signs
+// +-1 within the slice are twice the sum of its bits less that of its rows.
+// Against a workgroup-wide transform of whole columns (one workgroup of 8 waves
+// per CU, 122 KB of LDS, bits staged through LDS, barriers at each stage): FP64
+// L = 7 2^21, 162 -> 85 us with k2_bits (2.8 TB/s written); FP64 2^24, 171 -> 122
+// us; FP32 L = 5 2^20 in groups of four tiles, 8.8 -> 5.2 ns per 1000 points with
+// the row pass.
+template <typename T, int N2> struct PSplitGeom {
+    static constexpr int N1 = 4096, P = column_parts(N2), M = N2 / P, G = 1024 / M;
+    static constexpr int WAVES = column_waves(column_target<T, N1>(), G);
+    static constexpr int C = WAVES * G, THREADS = WAVES * 64;
+    static_assert(P > 1 && P < 8 && M >= 64 && M <= 1024 && C <= 64 && (C & (C - 1)) == 0, "column block");
+};
+template <typename T, int N2>
+__global__ void __launch_bounds__((PSplitGeom<T, N2>::THREADS))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k2_pass1_split(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw2,
+             const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
+             int fshift) {
+    using Gm = PSplitGeom<T, N2>;
+    constexpr int N1 = Gm::N1, P = Gm::P, C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16;
+    using Pl = BitPlanes<N1, N2>;
+    static_assert(Pl::NJ == NJ && Pl::M == M, "plane words");
+    constexpr uint32_t L = (uint32_t)N1 * N2, ALL = (1u << P) - 1u;
+    constexpr int NCB = N1 / C;
+    constexpr int SLOTS = (Gm::WAVES * kWaveSlots > M * C) ? Gm::WAVES * kWaveSlots : M * C;
+    __shared__ __align__(16) cx<T> lds[SLOTS];
+    __shared__ __align__(16) cx<T> st[wfft_lds_entries(M)];
+    __shared__ __align__(16) cx<T> sums[1 << P];
+    __shared__ uint32_t wsum;
+
+    const uint32_t blk = xcd_block(), h = blk % P, lb = blk / P;   // the P workgroups of a column block share its bits
+    const uint32_t lt = lb / NCB, cb = lb % NCB;
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, grp = l / NJ, j = l % NJ, f = wv * G + grp;
+    const uint32_t t1 = cb * C + (uint32_t)f;
+    const typename Pl::Word* __restrict__ pw =
+        reinterpret_cast<const typename Pl::Word*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * NJ + j;
+    const typename Pl::Word kw = pw[0], sw = pw[Pl::kPlane / sizeof(typename Pl::Word)];
+    const uint32_t t = jt.tile0 + lt;
+    const JobDesc jd = find_job(jt, t);
+    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+    if (h == 0) clear_window(g, cb, NCB, tid, Gm::THREADS);
+    if (tid == 0) wsum = 0;
+    wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
+    // sums of w_P^{h q} over the bits q of the index
+    for (uint32_t x = tid; x <= ALL; x += Gm::THREADS) {
+        Root64 a{0, 0};
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const Root64 r = root64(fa64, fb64, fshift, (h * q) % P * (L / P));
+            if ((x >> q) & 1u) a = Root64{a.re + r.re, a.im + r.im};
+        }
+        if (h && x == ALL) a = Root64{0, 0};
+        sums[x] = rounded<T>(a);
+    }
+    // four-step twiddle w_L^{t1 k2} = base * c_i with k2 = P (j + NJ i) + h,
+    // base = w_L^{t1 (P j + h)}, c_i = w_L^{P NJ t1 i} (as in k2_pass1)
+    constexpr int CPL = (16 + NJ - 1) / NJ;
+    const Root64 base = root64(fa64, fb64, fshift, t1 * (uint32_t)(P * j + h));
+    Root64 cf[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+        const int i = j + q * NJ;
+        cf[q] = root64(fa64, fb64, fshift, i < 16 ? (uint32_t)(P * NJ) * t1 * (uint32_t)i : 0u);
+    }
+    cx<T> tw[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tw[i] = tw2[h * (uint32_t)(j + i * NJ)];
+    // rows of the slice in this column; of the P rows of element e, the first q0, and
+    // one more when e < e0
+    const uint32_t win = (uint32_t)(g.bi + g.bo - 1), rows = win > t1 ? (win - t1 + N1 - 1) / N1 : 0u;
+    const uint32_t q0 = rows / M, e0 = rows % M;
+    __syncthreads();  // the tables and the zeroed sum are in place
+    const cx<T> in0 = sums[(1u << q0) - 1u], in1 = sums[((1u << (q0 + 1)) - 1u) & ALL];
+    constexpr uint32_t FM = (1u << Pl::FW) - 1u;
+    constexpr int PER = 32 / Pl::FW;   // fields per 32-bit word
+    cx<T> v[16];
+    uint32_t pc = 0;
+#pragma unroll
+    for (int i = 0; i < Pl::BITS / 32; ++i) pc += (uint32_t)__popc(kw.w[i]);
+    if (h == 0) atomicAdd(&wsum, pc);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const cx<T> a = sums[(kw.w[i / PER] >> (Pl::FW * (i % PER))) & FM], b = sums[(sw.w[i / PER] >> (Pl::FW * (i % PER))) & FM];
+        const cx<T> in = (uint32_t)(j + i * NJ) < e0 ? in1 : in0;
+        const cx<T> s = cx<T>{T(2) * b.re - in.re, T(2) * b.im - in.im};
+        v[i] = cmul(cx<T>{a.re - s.im, a.im + s.re}, tw[i]);   // key + i seed
+    }
+    cx<T>* reg = lds + wv * kWaveSlots + grp * (M + M / 16);
+    wave_fft_lds<T, -1, M>(v, reg, j, st);
+
+    // exchange the factors through this wave's own region (its transform is done)
+    static_assert(G * 16 * sizeof(Root64) <= kWaveSlots * sizeof(cx<T>), "twiddle factors fit a wave region");
+    Root64* cw = reinterpret_cast<Root64*>(lds + wv * kWaveSlots) + grp * 16;
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+        const int i = j + q * NJ;
+        if (i < 16) cw[i] = cf[q];
+    }
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], rounded<T>(mul64(base, cw[i])));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lds[tslot<C>(j + i * NJ, f)] = v[i];   // transposed for row-segment stores
+    __syncthreads();
+    cx<T>* __restrict__ Y = ws + (size_t)lt * L + cb * C;
+    static_assert(M * C == Gm::THREADS * 16, "store tile");
+    cx<T> o[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int idx = tid + q * Gm::THREADS;
+        o[q] = lds[tslot<C>(idx / C, idx % C)];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int idx = tid + q * Gm::THREADS;
+        Y[(size_t)(P * (idx / C) + h) * N1 + (idx % C)] = o[q];
+    }
+    if (tid == 0 && h == 0) part[(size_t)lt * NCB + cb] = wsum;
 }
 
 // ------------------------------------------------------------------ pass 2
@@ -1065,6 +1243,11 @@ int launch_row_pass(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+template <int N1, int N2> void launch_bits(const JobTable& jt, uint8_t* planes, void* stream) {
+    constexpr int waves = 2 * ((int)BitPlanes<N1, N2>::kColumn / 8) * (N1 / 64 / kBitsCols);   // of a tile
+    hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (waves / 4)), dim3(256), 0, (hipStream_t)stream, jt, planes);
+}
+
 template <typename T, int N1, int N2>
 struct ClassImpl2 {
     using G1 = P1Geom<T, N1, N2>;
@@ -1075,8 +1258,7 @@ struct ClassImpl2 {
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
         if constexpr (G1::kPlanes) {
             uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
-            hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (2 * (N2 / 64) * (N1 / 64 / kBitsCols) / 4)), dim3(256),
-                               0, (hipStream_t)stream, jt, planes);
+            launch_bits<N1, N2>(jt, planes, stream);
         }
         hipLaunchKernelGGL((k2_pass1<T, N1, N2>), dim3(jt.ntiles * (N1 / C1) * (G1::WGH ? 2 : 1)), dim3(G1::THREADS), 0,
                            (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
@@ -1133,17 +1315,21 @@ struct ClassImpl2 {
     }
 };
 
-// Mixed-radix classes with rows of 4096 (L = 4096 n2, n2 = P 2^b): the
-// wave-level row pass above (it does not depend on how n2 factors) between
-// the workgroup-wide Stockham column passes of conv_kernels.hpp, whose columns
-// carry the radix-P stage (RC points per thread).
-template <typename T, int N2, int B1, int B3, int RC>
+// Classes with rows of 4096 and split columns (L = 4096 n2, n2 = P 2^b): the
+// wave-level column and row passes above, and the workgroup-wide Stockham pass 3
+// of conv_kernels.hpp, whose columns carry the radix-P stage (RC points per
+// thread).
+template <typename T, int N2, int B3, int RC>
 struct ClassImplS {
-    static constexpr int N1 = 4096, NCB1 = N1 / B1;
+    using G1 = PSplitGeom<T, N2>;
+    static constexpr int N1 = G1::N1, C1 = G1::C, NCB1 = N1 / C1;
+    static constexpr size_t kWsExtra = BitPlanes<N1, N2>::kTile;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
-        dim3 grid(jt.ntiles * NCB1), block(B1 * (N2 / RC));
-        hipLaunchKernelGGL((k_pass1<T, N1, N2, B1, RC, N2>), grid, block, 0, (hipStream_t)stream, jt, (cx<T>*)ws,
-                           part, (const cx<T>*)tb.tw2, (const cx<T>*)tb.fa, (const cx<T>*)tb.fb, tb.fshift);
+        uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
+        launch_bits<N1, N2>(jt, planes, stream);
+        hipLaunchKernelGGL((k2_pass1_split<T, N2>), dim3(jt.ntiles * NCB1 * G1::P), dim3(G1::THREADS), 0,
+                           (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.tw2, (const cx<T>*)tb.stw,
+                           (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     static int pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {

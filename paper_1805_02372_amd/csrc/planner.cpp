@@ -345,7 +345,7 @@ bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostMode
     const uint32_t p = flags & PA_PREC_MASK;
     if (p == PA_PREC_DIRECT) return true;
     return p == PA_PREC_AUTO &&
-           2.0 * (direct_cost(n, m, cm) - 1.1 * cm.direct_launch_s) < fft.cost - cm.first(fft.prec, fft.cls);
+           2.5 * (direct_cost(n, m, cm) - 1.1 * cm.direct_launch_s) < fft.cost - cm.first(fft.prec, fft.cls);
 }
 
 // Classes whose row pass sums the products of several chunks: those with
@@ -431,7 +431,7 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
     // fewer than ceil(m / L) windows cannot fit a window in L
     for (uint64_t w = std::max<uint64_t>(1, ceil_div(m, L)); w <= std::max<uint64_t>(1, max_outs); ++w) {
         // every later candidate has >= w windows of >= min_chunks chunks
-        if (found && (double)w * (tile + (double)(min_chunks - 1) * chunk) >= best.cost) break;
+        if (found && (double)w * (tile + (double)(min_chunks - 1) * chunk) >= 1.03 * best.cost) break;
         uint64_t Bo = (w == 1) ? m : round_up64(ceil_div(m, w));
         if (Bo == last_bo) continue;
         last_bo = Bo;
@@ -446,7 +446,8 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
         p.cgroup = class_sums(prec, cls) ? group_chunks(prec, L, p.Bi, p.nchunks) : 1;
         const double groups = (double)(ceil_div(p.nchunks, p.cgroup) * p.nouts);
         p.cost = groups * tile + ((double)p.tiles() - groups) * chunk;
-        if (!found || p.cost < best.cost) {
+        // a tie within the noise of the measured costs goes to fewer tiles (less workspace)
+        if (!found || p.cost < (p.tiles() < best.tiles() ? 1.03 : 1.0) * best.cost) {
             found = true;
             best = p;
         }

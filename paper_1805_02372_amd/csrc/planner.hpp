@@ -118,9 +118,12 @@ bool choose_direct(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, 
 
 // The same for a job of a batch or a serving launch, where both paths share
 // their launches with other jobs: the costs beyond the launches are compared.
-// The direct path has to be modeled twice as fast: a class's marginal tile cost
-// is measured with 16 tiles per launch, and larger launches fill the device
-// better.
+// The direct path has to be modeled 2.5 times as fast: its cost per output and
+// key word is that of long keys, and short ones take 1.7 to 2 times as long,
+// while a class's marginal tile cost is measured with 16 tiles per launch, and
+// larger launches fill the device better (256 jobs of 100,000 -> 50,000 bits:
+// 2.55 us per job direct, modeled 1.5, and 2.73 us on FP32 tiles, modeled 2.8;
+// 30,000 -> 10,000: 0.55 and 0.64).
 bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft);
 
 // Workspace that a shared-spectra plan may count on: what a serving lane of a
