@@ -36,17 +36,13 @@ namespace pa {
 template <typename T, int N1> constexpr int column_target() { return (N1 >= 4096 ? 128 : 64) / (int)sizeof(cx<T>); }
 constexpr int column_waves(int target, int g) { return target <= g ? 1 : (target / g > 8 ? 8 : target / g); }
 
+// Rows of 512: a column is one transform.
 template <typename T, int N1, int N2> struct P1Geom {
-    static constexpr int H = N2 > 1024 ? N2 / 1024 : 1;    // halves of a column
-    static constexpr bool WGH = H == 2 && sizeof(T) == 4;  // each half in a workgroup of its own
-    static constexpr int M = N2 > 1024 ? 1024 : N2;        // wave transform size
-    static constexpr int G = 1024 / M;                     // columns per wave
-    static constexpr int WAVES = H == 2 ? 8 : column_waves(column_target<T, N1>(), G);
-    static constexpr int C = WAVES * G / (WGH ? 1 : H);    // columns per workgroup
+    static constexpr int P = 1, M = N2, G = 1024 / M;      // columns per wave
+    static constexpr int WAVES = column_waves(column_target<T, N1>(), G);
+    static constexpr int C = WAVES * G;                    // columns per workgroup
     static constexpr int THREADS = WAVES * 64;
-    static constexpr bool kPlanes = N1 >= 1024;            // bits from planes (else gathered)
-    static_assert(H <= 2, "column length up to 2048");
-    static_assert(C <= 64 && (C & (C - 1)) == 0, "column block");
+    static_assert(M <= 1024 && C <= 64 && (C & (C - 1)) == 0, "column block");
 };
 
 template <typename T, int N1, int N2> struct P3Geom {
@@ -154,32 +150,27 @@ __device__ __forceinline__ TileBits tile_bits(const JobDesc& jd, const TileGeo& 
     return r;
 }
 
-// Bit planes.  A lane of pass 1 takes rows j, j + NJ, j + 2 NJ, .. of one
-// column (NJ = N2 / 16 lanes per column, at most 64); read in place, each of its
-// bits is in another word, N1 bits apart.  k2_bits transposes the two sequences
-// of every tile into planes after the launch's tiles in the workspace: N2 bits
-// per column, as NJ words of N2 / NJ bits (16, or 32 for N2 = 2048); bit i of
-// word j of column t1 is position t1 + N1 (j + NJ i).  A lane of pass 1 then
-// loads one word of each plane, a wave consecutive ones.  Split columns (P M rows,
-// P = 3, 4, 5, 7) are P transforms of M points on the bits of rows e, e + M, ..:
-// NJ = M / 16, and a lane's word has a field of FW (4 or 8) bits for each of its
-// 16 points, bit FW i + q being row j + NJ i + M q.
-constexpr int column_parts(int n2) { return odd_part(n2) > 1 ? odd_part(n2) : n2 > 2048 ? 4 : 1; }
+// Bit planes.  Columns of N2 = P M rows are split into P transforms of M points
+// (k2_pass1_split), on the bits of rows e, e + M, .. together, and a lane has
+// points e = j + NJ i (i < 16, NJ = M / 16 lanes per column); read in place, each
+// of its bits is in another word, N1 bits apart.  k2_bits transposes the two
+// sequences of every tile into planes after the launch's tiles in the workspace:
+// per column NJ words of 16 fields of FW (4 or 8) bits, bit FW i + q of word j of
+// column t1 being position t1 + N1 (j + NJ i + M q).  A lane of pass 1 then loads
+// one word of each plane, a wave consecutive ones.
+// P = 4 or 8 leaves M = 64 .. 256 (512 at 4096), two radix stages for the wave.
+constexpr int column_parts(int n2) { return odd_part(n2) > 1 ? odd_part(n2) : n2 == 2048 ? 8 : 4; }
 template <int N1, int N2> struct BitPlanes {
-    static constexpr int P = column_parts(N2), M = N2 / P, FW = P == 1 ? 1 : P <= 4 ? 4 : 8;
-    static constexpr int NJ = M >= 1024 ? 64 : M / 16, BITS = M * FW / NJ;   // bits of a lane
-    static_assert(P == 1 ? BITS == 16 || BITS == 32 : BITS == 16 * FW, "plane words");
-    struct alignas(BITS / 8) Wide {
-        uint32_t w[BITS > 32 ? BITS / 32 : 1];
+    static constexpr int P = column_parts(N2), M = N2 / P, FW = P <= 4 ? 4 : 8;
+    static constexpr int NJ = M / 16, BITS = 16 * FW;   // bits of a lane
+    struct alignas(BITS / 8) Word {
+        uint32_t w[BITS / 32];
     };
-    using Word = std::conditional_t<BITS == 16, uint16_t, std::conditional_t<BITS == 32, uint32_t, Wide>>;
     static constexpr size_t kColumn = (size_t)M * FW / 8, kPlane = kColumn * N1;
     // row of bit b of a column's plane bytes (N2 where the bit stands for none)
     __device__ static __forceinline__ uint32_t row(uint32_t b) {
-        const uint32_t j = b / BITS, r = b % BITS;
-        if constexpr (P == 1) return j + NJ * r;
-        const uint32_t q = r % FW;
-        return q < (uint32_t)P ? j + NJ * (r / FW) + M * q : N2;
+        const uint32_t j = b / BITS, r = b % BITS, q = r % FW;
+        return P == FW || q < (uint32_t)P ? j + NJ * (r / FW) + M * q : N2;
     }
     static constexpr size_t kTile = 2 * kPlane;
     template <typename T>
@@ -306,7 +297,7 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
                 v[c].lo |= y.lo;
                 v[c].hi |= y.hi;
             }
-            if (Pl::P > 1 && row >= (uint32_t)N2) v[c] = Bits64{0, 0};
+            if (Pl::P != Pl::FW && row >= (uint32_t)N2) v[c] = Bits64{0, 0};
         }
     }
     uint8_t* dst = planes + (size_t)lt * Pl::kTile + (size_t)pl * Pl::kPlane + (size_t)rc * 8;
@@ -316,15 +307,15 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
             transpose64(v[c], lane);
 }
 
-// The same word gathered by the lane itself: one 32-bit load per bit, all
+// Bits of rows j + NJ i of column t1 (bit i) gathered by the lane itself: one 32-bit
+// load per bit, all
 // issued before the first wait.  For the rows of 512: their pass 1 takes about
 // 10 us at 2^18 points in FP32 and FP64 alike, mostly latency, against the 5.5 us
 // that a launch of k2_bits takes at any short length.
 template <int N1, int N2>
 __device__ __forceinline__ uint32_t gather_bits(const BitSeq& q, uint32_t t1, uint32_t j) {
     constexpr uint32_t L = (uint32_t)N1 * N2;
-    constexpr int NJ = BitPlanes<N1, N2>::NJ;
-    static_assert(BitPlanes<N1, N2>::BITS == 16, "16 rows per lane");
+    constexpr int NJ = N2 / 16;   // 16 rows per lane
     const uint32_t* __restrict__ src = reinterpret_cast<const uint32_t*>(q.src) + (q.j0 >> 5);
     const uint64_t left = 2 * q.nw - 1 - (q.j0 >> 5);
     const uint32_t last = left < 0xFFFFFFFFull ? (uint32_t)left : 0xFFFFFFFFu, o = (uint32_t)q.j0 & 31u;
@@ -343,8 +334,75 @@ __device__ __forceinline__ uint32_t gather_bits(const BitSeq& q, uint32_t t1, ui
     return r;
 }
 
-// Values of bit i of a plane word: a key bit, or a seed bit before the mask of
-// the slice's end (seed_mask).
+// What the column passes share.  LDS: the wave regions, used again as the
+// transposition tile, and the stage tables.
+template <typename T, typename Gm> struct ColumnSmem {
+    static constexpr int SLOTS = (Gm::WAVES * kWaveSlots > Gm::M * Gm::C) ? Gm::WAVES * kWaveSlots : Gm::M * Gm::C;
+    static_assert(Gm::G * 16 * sizeof(Root64) <= kWaveSlots * sizeof(cx<T>), "twiddle factors fit a wave region");
+    alignas(16) cx<T> lds[SLOTS];
+    alignas(16) cx<T> st[wfft_lds_entries(Gm::M)];
+};
+// Four-step twiddle w_L^{t1 k2}, k2 = P (j + NJ i) + h, as base * c_i with base =
+// w_L^{t1 (P j + h)} and c_i = w_L^{P NJ t1 i}.  Each lane fetches its share of its
+// column's 16 factors before the transform (latency hidden behind it); they are
+// exchanged through LDS afterwards.
+template <int NJ, int P> struct ColumnRoots {
+    static constexpr int CPL = (16 + NJ - 1) / NJ;   // factors fetched per lane
+    Root64 base, c[CPL];
+    __device__ __forceinline__ ColumnRoots(uint32_t t1, uint32_t j, uint32_t h, const cx<double>* __restrict__ fa64,
+                                           const cx<double>* __restrict__ fb64, int fshift) {
+        base = root64(fa64, fb64, fshift, t1 * (P * j + h));
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+            const uint32_t i = j + q * NJ;
+            c[q] = root64(fa64, fb64, fshift, i < 16 ? (uint32_t)(P * NJ) * t1 * i : 0u);
+        }
+    }
+};
+// The M-point transform of a lane's column and the twiddles.
+template <typename T, typename Gm, typename Roots>
+__device__ __forceinline__ void column_transform(cx<T> (&v)[16], ColumnSmem<T, Gm>& S, const Roots& roots, int wv, int grp,
+                                                 int j) {
+    constexpr int M = Gm::M, NJ = M / 16;
+    wave_fft_lds<T, -1, M>(v, S.lds + wv * kWaveSlots + grp * (M + M / 16), j, S.st);
+    // exchange the factors through this wave's own region (its transform is done)
+    Root64* cw = reinterpret_cast<Root64*>(S.lds + wv * kWaveSlots) + grp * 16;
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < Roots::CPL; ++q) {
+        const int i = j + q * NJ;
+        if (i < 16) cw[i] = roots.c[q];
+    }
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], rounded<T>(mul64(roots.base, cw[i])));
+}
+// Rows P k + h of the workgroup's columns, transposed through LDS for row-segment
+// stores.
+template <typename T, typename Gm, int N1>
+__device__ __forceinline__ void column_store(const cx<T> (&v)[16], ColumnSmem<T, Gm>& S, int tid, int f, int j, uint32_t h,
+                                             cx<T>* __restrict__ Y) {
+    constexpr int C = Gm::C, NJ = Gm::M / 16;
+    static_assert(Gm::M * C == Gm::THREADS * 16, "store tile");
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S.lds[tslot<C>(j + i * NJ, f)] = v[i];
+    __syncthreads();
+    cx<T> o[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int idx = tid + q * Gm::THREADS;
+        o[q] = S.lds[tslot<C>(idx / C, idx % C)];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int idx = tid + q * Gm::THREADS;
+        Y[(size_t)((uint32_t)Gm::P * (uint32_t)(idx / C) + h) * N1 + (idx % C)] = o[q];
+    }
+}
+
+// Values of bit i of a lane's word: a key bit, or a seed bit before the mask of the
+// slice's end.
 template <typename T> __device__ __forceinline__ T key_value(uint32_t w, int i) { return (T)((w >> i) & 1u); }
 template <typename T> __device__ __forceinline__ T seed_value(uint32_t w, int i);
 template <> __device__ __forceinline__ float seed_value<float>(uint32_t w, int i) {
@@ -354,210 +412,95 @@ template <> __device__ __forceinline__ double seed_value<double>(uint32_t w, int
     return __hiloint2double((int)(((w << (31 - i)) & 0x80000000u) ^ 0xBFF00000u), 0);
 }
 
-// One component of the column's input: element i from plane bit i, or for a
-// column of two halves e +- (e + 1024) (bits i and i + 16).  Seed rows i >= valid
+// One component of the column's input: element i from bit i.  Seed rows i >= valid
 // of this lane lie past the slice: 0.
-template <typename T, int H, bool SEED, bool MASK>
-__device__ __forceinline__ void column_values(T (&x)[16], uint32_t w, uint32_t valid, bool minus) {
-    const T sign = minus ? T(-1) : T(1);
-    auto value = [&](int i) -> T {
-        const T a = SEED ? seed_value<T>(w, i) : key_value<T>(w, i);
-        return MASK && (uint32_t)i >= valid ? T(0) : a;
-    };
+template <typename T, bool SEED, bool MASK>
+__device__ __forceinline__ void column_values(T (&x)[16], uint32_t w, uint32_t valid) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = H == 1 ? value(i) : value(i) + sign * value(i + 16);
-}
-template <typename T, int H>
-__device__ __forceinline__ void column_input(T (&x)[16], uint32_t w, bool seed, uint32_t valid, bool minus) {
-    if (!seed) column_values<T, H, false, false>(x, w, valid, minus);
-    else if (__any(valid < 16u * H)) column_values<T, H, true, true>(x, w, valid, minus);
-    else column_values<T, H, true, false>(x, w, valid, minus);
+    for (int i = 0; i < 16; ++i) {
+        const T a = SEED ? seed_value<T>(w, i) : key_value<T>(w, i);
+        x[i] = MASK && (uint32_t)i >= valid ? T(0) : a;
+    }
 }
 
-// Column pass: a workgroup of WAVES waves takes C columns; each wave transforms
-// G whole columns (N2 <= 1024) or one half of a column (N2 = 2048, a radix-2
-// split in decimation in frequency: half ka, outputs k2 = 2 e + ka, is the
-// 1024-point transform of z(e) + z(e + 1024), or of (z(e) - z(e + 1024))
-// w_2048^e).  The halves of a column are two waves of one workgroup in FP64 and
-// two workgroups in FP32 (the LDS of one half: two workgroups per CU).
+// Column pass of the rows of 512: a workgroup of WAVES waves takes C columns, each
+// wave transforming G of them in registers.
 template <typename T, int N1, int N2>
 __global__ void __launch_bounds__((P1Geom<T, N1, N2>::THREADS))
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
-         const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
-         int fshift) {
+k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ stw,
+         const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64, int fshift) {
     using Gm = P1Geom<T, N1, N2>;
-    using Pl = BitPlanes<N1, N2>;
-    constexpr int C = Gm::C, G = Gm::G, H = Gm::H, M = Gm::M, NJ = M / 16;
-    constexpr bool WGH = Gm::WGH;
-    constexpr uint32_t L = (uint32_t)N1 * N2;
-    constexpr int NCB = N1 / C, CG = WGH ? 1 : H;   // halves of a column in one workgroup
-    constexpr int ROWS = N2 / (WGH ? H : 1);        // rows this workgroup writes
-    constexpr int HALF = M * C + 8;                 // transposition tile of one half (the second off the first's banks)
-    constexpr int TILE = CG * HALF;
-    constexpr int SLOTS = (Gm::WAVES * kWaveSlots > TILE) ? Gm::WAVES * kWaveSlots : TILE;
-    static_assert(G * 16 * sizeof(Root64) <= kWaveSlots * sizeof(cx<T>), "twiddle factors fit a wave region");
-    __shared__ __align__(16) cx<T> lds[SLOTS];
-    __shared__ __align__(16) cx<T> st[wfft_lds_entries(M)];
+    constexpr int C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16;
+    constexpr int NCB = N1 / C;
+    __shared__ ColumnSmem<T, Gm> S;
     __shared__ uint32_t wsum;
 
-    const uint32_t blk = xcd_block(), lb = WGH ? blk >> 1 : blk;
-    const uint32_t lt = lb / NCB, cb = lb % NCB;
-    const int tid = threadIdx.x;
-    const int wv = tid >> 6, l = tid & 63;
-    int f, ka = 0, j, grp;
-    if constexpr (H == 1) {
-        grp = l / NJ;
-        j = l % NJ;
-        f = wv * G + grp;
-    } else {
-        f = WGH ? wv : wv / H;
-        ka = WGH ? (int)(blk & 1u) : wv % H;
-        j = l;
-        grp = 0;
-    }
-    const uint32_t t1 = cb * C + (uint32_t)f;
-    // this lane's bits of the two sequences
-    uint32_t w0, w1;
-    if constexpr (Gm::kPlanes) {
-        const typename Pl::Word* __restrict__ pw =
-            reinterpret_cast<const typename Pl::Word*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * Pl::NJ + j;
-        w0 = pw[0];
-        w1 = pw[Pl::kPlane / sizeof(typename Pl::Word)];
-    }
-    uint32_t len[2];
-    bool seed[2];
-    if (Gm::kPlanes && jt.shared.kpacks) {
-        const TileBits tb = shared_bits(jt, lt);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) len[h] = tb.s[h].len, seed[h] = tb.s[h].seed;
-    } else {
-        const uint32_t t = jt.tile0 + lt;
-        const JobDesc jd = find_job(jt, t);
-        const TileGeo g = tile_geo(jd, t - jd.tile_begin);
-        if (!WGH || !(blk & 1u)) clear_window(g, cb, NCB, tid, Gm::THREADS);
-        len[0] = 0;
-        seed[0] = false;
-        len[1] = (uint32_t)(g.bi + g.bo - 1);
-        seed[1] = true;
-        if constexpr (!Gm::kPlanes) {
-            const TileBits tb = tile_bits(jd, g);
-            w0 = gather_bits<N1, N2>(tb.s[0], t1, (uint32_t)j);
-            w1 = gather_bits<N1, N2>(tb.s[1], t1, (uint32_t)j);
-        }
-    }
+    const uint32_t blk = xcd_block(), lt = blk / NCB, cb = blk % NCB;
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, grp = l / NJ, j = l % NJ, f = wv * G + grp;
+    const uint32_t t1 = cb * C + (uint32_t)f, t = jt.tile0 + lt;
+    const JobDesc jd = find_job(jt, t);
+    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+    const TileBits tb = tile_bits(jd, g);
+    clear_window(g, cb, NCB, tid, Gm::THREADS);
+    const uint32_t kw = gather_bits<N1, N2>(tb.s[0], t1, (uint32_t)j), sw = gather_bits<N1, N2>(tb.s[1], t1, (uint32_t)j);
     if (tid == 0) wsum = 0;
-    wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
-
-    // Four-step twiddle w_L^{t1 k2} = base * c_i with
-    //   H = 1: k2 = j + NJ i,           base = w_L^{t1 j},          c_i = w_L^{NJ t1 i}
-    //   H = 2: k2 = 2 (j + 64 i) + ka,  base = w_L^{t1 (2 j + ka)}, c_i = w_L^{128 t1 i}
-    // Each lane fetches its share of its group's 16 factors now (latency hidden
-    // behind the transform); they are exchanged through LDS afterwards.
-    constexpr int LPG = H == 1 ? NJ : 64;            // lanes per transform group
-    constexpr int CPL = (16 + LPG - 1) / LPG;        // factors fetched per lane
-    constexpr uint32_t CSTEP = H == 1 ? (uint32_t)NJ : 128u;
-    const Root64 base = root64(fa64, fb64, fshift, H == 1 ? t1 * (uint32_t)j : t1 * (uint32_t)(2 * j + ka));
-    Root64 cf[CPL];
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-        const int i = j + q * LPG;
-        cf[q] = root64(fa64, fb64, fshift, i < 16 ? CSTEP * t1 * (uint32_t)i : 0u);
-    }
-    // rows j + NJ i of a sequence of len bits: those below rows = ceil((len - t1) / N1)
+    wfft_load_lds<T, M>(S.st, stw, tid, Gm::THREADS);
+    const ColumnRoots<NJ, 1> roots(t1, (uint32_t)j, 0, fa64, fb64, fshift);
+    // rows j + NJ i of the slice: those below rows = ceil((len - t1) / N1)
+    const uint32_t win = tb.s[1].len, rows = win > t1 ? (win - t1 + N1 - 1) / N1 : 0u;
+    const uint32_t valid = rows > (uint32_t)j ? (rows - (uint32_t)j + NJ - 1) / NJ : 0u;
+    T x[16], w[16];
+    column_values<T, false, false>(x, kw, 16);
+    if (__any(valid < 16u)) column_values<T, true, true>(w, sw, valid);
+    else column_values<T, true, false>(w, sw, 16);
     cx<T> v[16];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t rows = len[h] > t1 ? (len[h] - t1 + N1 - 1) / N1 : 0u;
-        const uint32_t valid = rows > (uint32_t)j ? (rows - (uint32_t)j + Pl::NJ - 1) / Pl::NJ : 0u;
-        T x[16];
-        column_input<T, H>(x, h ? w1 : w0, seed[h], valid, ka != 0);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) (h ? v[i].im : v[i].re) = x[i];
-    }
-    if constexpr (H == 2) {
-        if (ka) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], tw[(j + i * NJ) * (N1 / N2)]);
-        }
-    }
-    uint32_t pc = seed[0] ? 0u : (uint32_t)__popc(w0) + (seed[1] ? 0u : (uint32_t)__popc(w1));
-    if (ka) pc = 0;   // counted by the other half
+    for (int i = 0; i < 16; ++i) v[i] = cx<T>{x[i], w[i]};
     __syncthreads();  // the stage tables and the zeroed sum are in place
-    if constexpr (!WGH) atomicAdd(&wsum, pc);
-    else if (!(blk & 1u)) atomicAdd(&wsum, pc);
-    cx<T>* reg = lds + wv * kWaveSlots + (H == 1 ? grp * (M + M / 16) : 0);
-    wave_fft_lds<T, -1, M>(v, reg, j, st);
-
-    // exchange the factors through this wave's own region (its transform is done)
-    Root64* cw = reinterpret_cast<Root64*>(lds + wv * kWaveSlots) + grp * 16;
-    wave_sync();
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-        const int i = j + q * LPG;
-        if (i < 16) cw[i] = cf[q];
-    }
-    wave_sync();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], rounded<T>(mul64(base, cw[i])));
-    __syncthreads();
-    // transpose through LDS for row-segment stores, the halves of a column in
-    // tiles of their own so that a wave writes consecutive rows
-#pragma unroll
-    for (int i = 0; i < 16; ++i) lds[(WGH ? 0 : ka * HALF) + tslot<C>(j + i * NJ, f)] = v[i];
-    __syncthreads();
-    cx<T>* __restrict__ Y = ws + (size_t)lt * L + cb * C;
-    static_assert((ROWS * C) % Gm::THREADS == 0, "store tile");
-    constexpr int SPT = ROWS * C / Gm::THREADS;
-    cx<T> o[SPT];
-#pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-        const int idx = tid + q * Gm::THREADS, r = idx / C;
-        o[q] = lds[(r % CG) * HALF + tslot<C>(r / CG, idx % C)];
-    }
-#pragma unroll
-    for (int q = 0; q < SPT; ++q) {
-        const int idx = tid + q * Gm::THREADS, r = idx / C;
-        Y[(size_t)(WGH ? 2 * r + ka : r) * N1 + (idx % C)] = o[q];
-    }
-    if (tid == 0 && !(WGH && (blk & 1u))) part[(size_t)lt * NCB + cb] = wsum;
+    atomicAdd(&wsum, (uint32_t)__popc(kw));
+    column_transform<T, Gm>(v, S, roots, wv, grp, j);
+    column_store<T, Gm, N1>(v, S, tid, f, j, 0, ws + (size_t)lt * N1 * N2 + cb * C);
+    if (tid == 0) part[(size_t)lt * NCB + cb] = wsum;
 }
 
-// Column pass of the mixed-radix classes and of FP64 2^24: columns of N2 = P M rows
-// (P = 3, 4, 5, 7) by a radix-P split in decimation in frequency.  The outputs k2 = P k + h are the
-// M-point transform of
+// Column pass of the rows of 4096 and 8192: columns of N2 = P M rows by a radix-P
+// split in decimation in frequency.  The outputs k2 = P k + h are the M-point
+// transform of
 //   w_N2^{h e} sum_q z(e + M q) w_P^{h q},
 // and a workgroup makes them for one h and C columns, a wave transforming G
-// columns in registers as in k2_pass1.  The sums need no arithmetic: the inputs
-// are bits, so that P of them index a table of 2^P sums in LDS (of the roots in
-// FP64, rounded once), one lookup for the key and one for the seed, whose signs
-// +-1 within the slice are twice the sum of its bits less that of its rows.
+// columns in registers.  The sums need no arithmetic: the inputs are bits, so that
+// P of them index a table of 2^P sums in LDS (of the roots in FP64, rounded once),
+// one lookup per sequence; the signs +-1 of a seed are twice the sum of its bits
+// less that of its rows.
 // Against a workgroup-wide transform of whole columns (one workgroup of 8 waves
 // per CU, 122 KB of LDS, bits staged through LDS, barriers at each stage): FP64
 // L = 7 2^21, 162 -> 85 us with k2_bits (2.8 TB/s written); FP64 2^24, 171 -> 122
 // us; FP32 L = 5 2^20 in groups of four tiles, 8.8 -> 5.2 ns per 1000 points with
-// the row pass.
-template <typename T, int N2> struct PSplitGeom {
-    static constexpr int N1 = 4096, P = column_parts(N2), M = N2 / P, G = 1024 / M;
+// the row pass.  Against whole (or halved) columns a wave with the bits as inputs,
+// powers of two: two FP32 tiles of 2^23, 55.6 -> 51.0 us; FP64 2^22 in fives, 130 ->
+// 106 us.  Now bound by vector instructions (1,180 for 1024 FP32 points, 130 of
+// them the FP64 products of the four-step twiddles: about 3/4 of the time).
+template <typename T, int N1_, int N2> struct PSplitGeom {
+    static constexpr int N1 = N1_, P = column_parts(N2), M = N2 / P, G = 1024 / M;
     static constexpr int WAVES = column_waves(column_target<T, N1>(), G);
     static constexpr int C = WAVES * G, THREADS = WAVES * 64;
-    static_assert(P > 1 && P < 8 && M >= 64 && M <= 1024 && C <= 64 && (C & (C - 1)) == 0, "column block");
+    static_assert(P > 1 && P <= 8 && M >= 64 && M <= 1024 && C <= 64 && (C & (C - 1)) == 0, "column block");
 };
-template <typename T, int N2>
-__global__ void __launch_bounds__((PSplitGeom<T, N2>::THREADS))
+// tw: w_NT^e.  SHARED: the tiles are packs of two chunks or two slices, else of a
+// chunk and its slice (one kernel for both took 20 registers more, and spilled).
+template <typename T, int N1, int N2, int NT, bool SHARED>
+__global__ void __launch_bounds__((PSplitGeom<T, N1, N2>::THREADS))
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-k2_pass1_split(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw2,
-             const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
-             int fshift) {
-    using Gm = PSplitGeom<T, N2>;
-    constexpr int N1 = Gm::N1, P = Gm::P, C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16;
+k2_pass1_split(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ tw,
+               const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
+               int fshift) {
+    using Gm = PSplitGeom<T, N1, N2>;
+    constexpr int P = Gm::P, C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16;
     using Pl = BitPlanes<N1, N2>;
-    static_assert(Pl::NJ == NJ && Pl::M == M, "plane words");
     constexpr uint32_t L = (uint32_t)N1 * N2, ALL = (1u << P) - 1u;
     constexpr int NCB = N1 / C;
-    constexpr int SLOTS = (Gm::WAVES * kWaveSlots > M * C) ? Gm::WAVES * kWaveSlots : M * C;
-    __shared__ __align__(16) cx<T> lds[SLOTS];
-    __shared__ __align__(16) cx<T> st[wfft_lds_entries(M)];
+    __shared__ ColumnSmem<T, Gm> S;
     __shared__ __align__(16) cx<T> sums[1 << P];
     __shared__ uint32_t wsum;
 
@@ -567,13 +510,22 @@ k2_pass1_split(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part,
     const uint32_t t1 = cb * C + (uint32_t)f;
     const typename Pl::Word* __restrict__ pw =
         reinterpret_cast<const typename Pl::Word*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * NJ + j;
-    const typename Pl::Word kw = pw[0], sw = pw[Pl::kPlane / sizeof(typename Pl::Word)];
-    const uint32_t t = jt.tile0 + lt;
-    const JobDesc jd = find_job(jt, t);
-    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
-    if (h == 0) clear_window(g, cb, NCB, tid, Gm::THREADS);
+    const typename Pl::Word bits[2] = {pw[0], pw[Pl::kPlane / sizeof(typename Pl::Word)]};
+    uint32_t len[2] = {0, 0};
+    const bool seeds = SHARED && lt >= jt.shared.kpacks;   // both sequences are slices
+    if constexpr (SHARED) {
+        const TileBits tb = shared_bits(jt, lt);
+        len[0] = tb.s[0].len;
+        len[1] = tb.s[1].len;
+    } else {
+        const uint32_t t = jt.tile0 + lt;
+        const JobDesc jd = find_job(jt, t);
+        const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+        if (h == 0) clear_window(g, cb, NCB, tid, Gm::THREADS);
+        len[1] = (uint32_t)(g.bi + g.bo - 1);
+    }
     if (tid == 0) wsum = 0;
-    wfft_load_lds<T, M>(st, stw, tid, Gm::THREADS);
+    wfft_load_lds<T, M>(S.st, stw, tid, Gm::THREADS);
     // sums of w_P^{h q} over the bits q of the index
     for (uint32_t x = tid; x <= ALL; x += Gm::THREADS) {
         Root64 a{0, 0};
@@ -585,71 +537,48 @@ k2_pass1_split(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part,
         if (h && x == ALL) a = Root64{0, 0};
         sums[x] = rounded<T>(a);
     }
-    // four-step twiddle w_L^{t1 k2} = base * c_i with k2 = P (j + NJ i) + h,
-    // base = w_L^{t1 (P j + h)}, c_i = w_L^{P NJ t1 i} (as in k2_pass1)
-    constexpr int CPL = (16 + NJ - 1) / NJ;
-    const Root64 base = root64(fa64, fb64, fshift, t1 * (uint32_t)(P * j + h));
-    Root64 cf[CPL];
+    const ColumnRoots<NJ, P> roots(t1, (uint32_t)j, h, fa64, fb64, fshift);
+    cx<T> r[16];
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-        const int i = j + q * NJ;
-        cf[q] = root64(fa64, fb64, fshift, i < 16 ? (uint32_t)(P * NJ) * t1 * (uint32_t)i : 0u);
-    }
-    cx<T> tw[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) tw[i] = tw2[h * (uint32_t)(j + i * NJ)];
-    // rows of the slice in this column; of the P rows of element e, the first q0, and
-    // one more when e < e0
-    const uint32_t win = (uint32_t)(g.bi + g.bo - 1), rows = win > t1 ? (win - t1 + N1 - 1) / N1 : 0u;
-    const uint32_t q0 = rows / M, e0 = rows % M;
+    for (int i = 0; i < 16; ++i) r[i] = tw[h * (uint32_t)(j + i * NJ) * (uint32_t)(NT / N2)];
     __syncthreads();  // the tables and the zeroed sum are in place
-    const cx<T> in0 = sums[(1u << q0) - 1u], in1 = sums[((1u << (q0 + 1)) - 1u) & ALL];
     constexpr uint32_t FM = (1u << Pl::FW) - 1u;
     constexpr int PER = 32 / Pl::FW;   // fields per 32-bit word
-    cx<T> v[16];
-    uint32_t pc = 0;
+    // rows of a slice in this column; of the P rows of element e, the first q0, and
+    // one more when e < e0.  A key's rows add nothing
+    cx<T> in0[2], in1[2];
+    uint32_t e0[2], pc = 0;
 #pragma unroll
-    for (int i = 0; i < Pl::BITS / 32; ++i) pc += (uint32_t)__popc(kw.w[i]);
-    if (h == 0) atomicAdd(&wsum, pc);
+    for (int s = SHARED ? 0 : 1; s < 2; ++s) {
+        const uint32_t rows = (!SHARED || seeds) && len[s] > t1 ? (len[s] - t1 + N1 - 1) / N1 : 0u, q0 = rows / M;
+        e0[s] = rows % M;
+        in0[s] = sums[(1u << q0) - 1u];
+        in1[s] = sums[((1u << (q0 + 1)) - 1u) & ALL];
+    }
+    const T scale = !SHARED || seeds ? T(2) : T(1);
+#pragma unroll
+    for (int i = 0; i < Pl::BITS / 32; ++i)
+        pc += (uint32_t)__popc(bits[0].w[i]) + (SHARED ? (uint32_t)__popc(bits[1].w[i]) : 0u);
+    if (h == 0 && !seeds) atomicAdd(&wsum, pc);
+    cx<T> v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const cx<T> a = sums[(kw.w[i / PER] >> (Pl::FW * (i % PER))) & FM], b = sums[(sw.w[i / PER] >> (Pl::FW * (i % PER))) & FM];
-        const cx<T> in = (uint32_t)(j + i * NJ) < e0 ? in1 : in0;
-        const cx<T> s = cx<T>{T(2) * b.re - in.re, T(2) * b.im - in.im};
-        v[i] = cmul(cx<T>{a.re - s.im, a.im + s.re}, tw[i]);   // key + i seed
+        cx<T> x[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const cx<T> a = sums[(bits[s].w[i / PER] >> (Pl::FW * (i % PER))) & FM];
+            if (!SHARED && s == 0) {
+                x[s] = a;
+            } else {
+                const cx<T> in = (uint32_t)(j + i * NJ) < e0[s] ? in1[s] : in0[s];
+                x[s] = cx<T>{scale * a.re - in.re, scale * a.im - in.im};
+            }
+        }
+        v[i] = cmul(cx<T>{x[0].re - x[1].im, x[0].im + x[1].re}, r[i]);   // first + i second
+        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few lookups in flight, not all (registers)
     }
-    cx<T>* reg = lds + wv * kWaveSlots + grp * (M + M / 16);
-    wave_fft_lds<T, -1, M>(v, reg, j, st);
-
-    // exchange the factors through this wave's own region (its transform is done)
-    static_assert(G * 16 * sizeof(Root64) <= kWaveSlots * sizeof(cx<T>), "twiddle factors fit a wave region");
-    Root64* cw = reinterpret_cast<Root64*>(lds + wv * kWaveSlots) + grp * 16;
-    wave_sync();
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-        const int i = j + q * NJ;
-        if (i < 16) cw[i] = cf[q];
-    }
-    wave_sync();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = cmul(v[i], rounded<T>(mul64(base, cw[i])));
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) lds[tslot<C>(j + i * NJ, f)] = v[i];   // transposed for row-segment stores
-    __syncthreads();
-    cx<T>* __restrict__ Y = ws + (size_t)lt * L + cb * C;
-    static_assert(M * C == Gm::THREADS * 16, "store tile");
-    cx<T> o[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int idx = tid + q * Gm::THREADS;
-        o[q] = lds[tslot<C>(idx / C, idx % C)];
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int idx = tid + q * Gm::THREADS;
-        Y[(size_t)(P * (idx / C) + h) * N1 + (idx % C)] = o[q];
-    }
+    column_transform<T, Gm>(v, S, roots, wv, grp, j);
+    column_store<T, Gm, N1>(v, S, tid, f, j, h, ws + (size_t)lt * L + cb * C);
     if (tid == 0 && h == 0) part[(size_t)lt * NCB + cb] = wsum;
 }
 
@@ -1248,21 +1177,34 @@ template <int N1, int N2> void launch_bits(const JobTable& jt, uint8_t* planes, 
     hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (waves / 4)), dim3(256), 0, (hipStream_t)stream, jt, planes);
 }
 
+// Pass 1 of the rows of 4096 and 8192: the bit planes, then the split columns.
+template <typename T, int N1, int N2, int NT, bool SHARED = false>
+int launch_split(const JobTable& jt, void* ws, uint32_t* part, const void* tw, const Tables& tb, void* stream) {
+    using G = PSplitGeom<T, N1, N2>;
+    uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
+    launch_bits<N1, N2>(jt, planes, stream);
+    hipLaunchKernelGGL((k2_pass1_split<T, N1, N2, NT, SHARED>), dim3(jt.ntiles * (N1 / G::C) * G::P), dim3(G::THREADS), 0,
+                       (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tw, (const cx<T>*)tb.stw,
+                       (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 template <typename T, int N1, int N2>
 struct ClassImpl2 {
-    using G1 = P1Geom<T, N1, N2>;
+    static constexpr bool kSplit = N1 >= 1024;
+    using G1 = std::conditional_t<kSplit, PSplitGeom<T, N1, kSplit ? N2 : 256>, P1Geom<T, N1, kSplit ? 256 : N2>>;
     using G3 = P3Geom<T, N1, N2>;
     static constexpr int C1 = G1::C, C3 = G3::C;
     // workspace bytes per tile beyond its points: the bit planes
-    static constexpr size_t kWsExtra = G1::kPlanes ? BitPlanes<N1, N2>::kTile : 0;
+    static constexpr size_t kWsExtra = kSplit ? BitPlanes<N1, kSplit ? N2 : 256>::kTile : 0;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
-        if constexpr (G1::kPlanes) {
-            uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
-            launch_bits<N1, N2>(jt, planes, stream);
+        if constexpr (kSplit) {
+            return launch_split<T, N1, N2, cmax<N1, N2>()>(jt, ws, part, tb.tw, tb, stream);
+        } else {
+            hipLaunchKernelGGL((k2_pass1<T, N1, N2>), dim3(jt.ntiles * (N1 / C1)), dim3(G1::THREADS), 0, (hipStream_t)stream,
+                               jt, (cx<T>*)ws, part, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
+                               (const cx<double>*)tb.fb64, tb.fshift);
         }
-        hipLaunchKernelGGL((k2_pass1<T, N1, N2>), dim3(jt.ntiles * (N1 / C1) * (G1::WGH ? 2 : 1)), dim3(G1::THREADS), 0,
-                           (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
-                           (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     static int pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
@@ -1276,8 +1218,8 @@ struct ClassImpl2 {
     static void* windows(const JobTable& jt, void* ws) {
         return (uint8_t*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2 * sizeof(cx<T>) + kWsExtra);
     }
-    static int shared_pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
-        return pass1(jt, ws, part, meta, tb, stream);
+    static int shared_pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
+        return launch_split<T, N1, N2, cmax<N1, N2>(), true>(jt, ws, part, tb.tw, tb, stream);
     }
     template <int NW>
     static void mac(const JobTable& jt, void* ws, uint32_t o0, void* stream) {
@@ -1321,16 +1263,10 @@ struct ClassImpl2 {
 // thread).
 template <typename T, int N2, int B3, int RC>
 struct ClassImplS {
-    using G1 = PSplitGeom<T, N2>;
-    static constexpr int N1 = G1::N1, C1 = G1::C, NCB1 = N1 / C1;
+    static constexpr int N1 = 4096, C1 = PSplitGeom<T, N1, N2>::C, NCB1 = N1 / C1;
     static constexpr size_t kWsExtra = BitPlanes<N1, N2>::kTile;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
-        uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
-        launch_bits<N1, N2>(jt, planes, stream);
-        hipLaunchKernelGGL((k2_pass1_split<T, N2>), dim3(jt.ntiles * NCB1 * G1::P), dim3(G1::THREADS), 0,
-                           (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.tw2, (const cx<T>*)tb.stw,
-                           (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
-        return hipGetLastError() == hipSuccess ? 0 : -1;
+        return launch_split<T, N1, N2, N2>(jt, ws, part, tb.tw2, tb, stream);
     }
     static int pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
         return launch_row_pass<T, N1, N2, NCB1>(jt, ws, part, meta, tb, stream);
