@@ -307,31 +307,33 @@ __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict_
             transpose64(v[c], lane);
 }
 
-// Bits of rows j + NJ i of column t1 (bit i) gathered by the lane itself: one 32-bit
-// load per bit, all
-// issued before the first wait.  For the rows of 512: their pass 1 takes about
-// 10 us at 2^18 points in FP32 and FP64 alike, mostly latency, against the 5.5 us
-// that a launch of k2_bits takes at any short length.
-template <int N1, int N2>
-__device__ __forceinline__ uint32_t gather_bits(const BitSeq& q, uint32_t t1, uint32_t j) {
-    constexpr uint32_t L = (uint32_t)N1 * N2;
-    constexpr int NJ = N2 / 16;   // 16 rows per lane
-    const uint32_t* __restrict__ src = reinterpret_cast<const uint32_t*>(q.src) + (q.j0 >> 5);
-    const uint64_t left = 2 * q.nw - 1 - (q.j0 >> 5);
-    const uint32_t last = left < 0xFFFFFFFFull ? (uint32_t)left : 0xFFFFFFFFu, o = (uint32_t)q.j0 & 31u;
-    uint32_t u[16], w[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        uint32_t p = t1 + (uint32_t)N1 * (j + (uint32_t)(NJ * i)) + q.off;
-        if (p >= L) p -= L;
-        u[i] = p;
-        const uint32_t at = (p + o) >> 5;
-        w[i] = src[at < last ? at : last];
-    }
-    uint32_t r = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) r |= (u[i] < q.len ? (w[i] >> ((u[i] + o) & 31u)) & 1u : 0u) << i;
+// C (at most 16) bits of a sequence at position p, a multiple of C: two words, and
+// in the rare case of a wrap to index 0 the sequence's first.
+struct FieldLoad {
+    uint32_t w[2], s, u;
+};
+__device__ __forceinline__ FieldLoad field_load(const BitSeq& q, const uint32_t* src, uint32_t last, uint32_t L, uint32_t p) {
+    FieldLoad r;
+    r.u = p + q.off;
+    if (r.u >= L) r.u -= L;
+    const uint32_t b = r.u + ((uint32_t)q.j0 & 31u), at = b >> 5;
+    r.s = b & 31u;
+    r.w[0] = src[at < last ? at : last];
+    r.w[1] = src[at + 1 < last ? at + 1 : last];
     return r;
+}
+template <int C>
+__device__ __forceinline__ uint32_t field_bits(const BitSeq& q, const uint32_t* src, uint32_t last, uint32_t L,
+                                               const FieldLoad& e) {
+    const uint32_t fs = L - e.u;   // bits before the wrap
+    const int left = (int)q.len - (int)e.u, cnt = left < (int)fs ? left : (int)fs;
+    uint32_t x = __builtin_amdgcn_alignbit(e.w[1], e.w[0], e.s) & low_mask32(cnt < C ? cnt : C);
+    if (fs < (uint32_t)C) {
+        const uint32_t head = __builtin_amdgcn_alignbit(src[1 < last ? 1 : last], src[0], (uint32_t)q.j0 & 31u);
+        const uint32_t most = C - fs < q.len ? C - fs : q.len;
+        x |= (head & low_mask32((int)most)) << fs;
+    }
+    return x;
 }
 
 // What the column passes share.  LDS: the wave regions, used again as the
@@ -401,30 +403,22 @@ __device__ __forceinline__ void column_store(const cx<T> (&v)[16], ColumnSmem<T,
     }
 }
 
-// Values of bit i of a lane's word: a key bit, or a seed bit before the mask of the
-// slice's end.
-template <typename T> __device__ __forceinline__ T key_value(uint32_t w, int i) { return (T)((w >> i) & 1u); }
-template <typename T> __device__ __forceinline__ T seed_value(uint32_t w, int i);
-template <> __device__ __forceinline__ float seed_value<float>(uint32_t w, int i) {
-    return __uint_as_float(((w << (31 - i)) & 0x80000000u) ^ 0xBF800000u);
+// -1 or 1 for a seed bit (in bit 31).
+template <typename T> __device__ __forceinline__ T sign_value(uint32_t top);
+template <> __device__ __forceinline__ float sign_value<float>(uint32_t top) {
+    return __uint_as_float((top & 0x80000000u) ^ 0xBF800000u);
 }
-template <> __device__ __forceinline__ double seed_value<double>(uint32_t w, int i) {
-    return __hiloint2double((int)(((w << (31 - i)) & 0x80000000u) ^ 0xBFF00000u), 0);
-}
-
-// One component of the column's input: element i from bit i.  Seed rows i >= valid
-// of this lane lie past the slice: 0.
-template <typename T, bool SEED, bool MASK>
-__device__ __forceinline__ void column_values(T (&x)[16], uint32_t w, uint32_t valid) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const T a = SEED ? seed_value<T>(w, i) : key_value<T>(w, i);
-        x[i] = MASK && (uint32_t)i >= valid ? T(0) : a;
-    }
+template <> __device__ __forceinline__ double sign_value<double>(uint32_t top) {
+    return __hiloint2double((int)((top & 0x80000000u) ^ 0xBFF00000u), 0);
 }
 
 // Column pass of the rows of 512: a workgroup of WAVES waves takes C columns, each
-// wave transforming G of them in registers.
+// wave transforming G of them in registers.  The bits are staged through LDS, per
+// row the C key bits and the C seed bits in one word: a thread loads a row or a few
+// (all their words in flight at once).  Each lane fetching its own 16 rows instead
+// took four times the requests, every one to another line, and bound the pass in
+// launches of many tiles: FP32 2^19, 48 tiles and more 10.6 -> 3.0 ns per 1000
+// points, four tiles 22.4 -> 19.3 us.
 template <typename T, int N1, int N2>
 __global__ void __launch_bounds__((P1Geom<T, N1, N2>::THREADS))
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
@@ -432,7 +426,10 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
          const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64, int fshift) {
     using Gm = P1Geom<T, N1, N2>;
     constexpr int C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16;
-    constexpr int NCB = N1 / C;
+    constexpr int NCB = N1 / C, ROWS = N2 / Gm::THREADS;   // rows staged by a thread
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    static_assert(C <= 16 && ROWS * Gm::THREADS == N2, "staged fields");
+    static_assert(sizeof(cx<T>) * Gm::WAVES * kWaveSlots >= sizeof(uint32_t) * N2, "staged fields fit the wave regions");
     __shared__ ColumnSmem<T, Gm> S;
     __shared__ uint32_t wsum;
 
@@ -442,23 +439,41 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
     const JobDesc jd = find_job(jt, t);
     const TileGeo g = tile_geo(jd, t - jd.tile_begin);
     const TileBits tb = tile_bits(jd, g);
+    const uint32_t* src[2];
+    uint32_t last[2];
+    FieldLoad e[ROWS][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        src[s] = reinterpret_cast<const uint32_t*>(tb.s[s].src) + (tb.s[s].j0 >> 5);
+        const uint64_t left = 2 * tb.s[s].nw - 1 - (tb.s[s].j0 >> 5);
+        last[s] = left < 0xFFFFFFFFull ? (uint32_t)left : 0xFFFFFFFFu;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            e[r][s] = field_load(tb.s[s], src[s], last[s], L, cb * C + (uint32_t)N1 * (uint32_t)(tid + r * Gm::THREADS));
+    }
     clear_window(g, cb, NCB, tid, Gm::THREADS);
-    const uint32_t kw = gather_bits<N1, N2>(tb.s[0], t1, (uint32_t)j), sw = gather_bits<N1, N2>(tb.s[1], t1, (uint32_t)j);
     if (tid == 0) wsum = 0;
     wfft_load_lds<T, M>(S.st, stw, tid, Gm::THREADS);
     const ColumnRoots<NJ, 1> roots(t1, (uint32_t)j, 0, fa64, fb64, fshift);
-    // rows j + NJ i of the slice: those below rows = ceil((len - t1) / N1)
+    uint32_t* fld = reinterpret_cast<uint32_t*>(S.lds);
+    uint32_t pc = 0;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const uint32_t kb = field_bits<C>(tb.s[0], src[0], last[0], L, e[r][0]);
+        fld[tid + r * Gm::THREADS] = kb | field_bits<C>(tb.s[1], src[1], last[1], L, e[r][1]) << 16;
+        pc += (uint32_t)__popc(kb);
+    }
+    __syncthreads();  // the fields, the stage tables and the zeroed sum are in place
+    atomicAdd(&wsum, pc);
+    // rows of the slice in this column: ceil((len - t1) / N1)
     const uint32_t win = tb.s[1].len, rows = win > t1 ? (win - t1 + N1 - 1) / N1 : 0u;
-    const uint32_t valid = rows > (uint32_t)j ? (rows - (uint32_t)j + NJ - 1) / NJ : 0u;
-    T x[16], w[16];
-    column_values<T, false, false>(x, kw, 16);
-    if (__any(valid < 16u)) column_values<T, true, true>(w, sw, valid);
-    else column_values<T, true, false>(w, sw, 16);
     cx<T> v[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = cx<T>{x[i], w[i]};
-    __syncthreads();  // the stage tables and the zeroed sum are in place
-    atomicAdd(&wsum, (uint32_t)__popc(kw));
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t row = (uint32_t)(j + i * NJ), w = fld[row] >> f;
+        v[i] = cx<T>{(T)(w & 1u), row < rows ? sign_value<T>(w << 15) : T(0)};
+    }
+    __syncthreads();  // the wave regions are free
     column_transform<T, Gm>(v, S, roots, wv, grp, j);
     column_store<T, Gm, N1>(v, S, tid, f, j, 0, ws + (size_t)lt * N1 * N2 + cb * C);
     if (tid == 0) part[(size_t)lt * NCB + cb] = wsum;
@@ -879,6 +894,101 @@ __device__ __forceinline__ void row_unit(uint32_t u, const JobTable& jt, cx<T>* 
     }
 }
 
+// The row pass of the rows of 512 in launches that leave the device idle: a unit is
+// a team of 2 Q waves, Q chunks at a time, the two rows of a pair in parallel.  Row
+// n2 - pr comes mirrored through LDS; the first wave adds the Q partial sums and
+// inverts.  Against one wave per unit: four summed FP32 tiles of 2^19, 18.6 -> 11.7
+// us (call 53.4 -> 46.2); 48 of 2^17, 49 -> 20; one FP64 tile of 2^18, 9.5 -> 8.0.
+template <typename T, int N1, int N2, int NCB1, int Q>
+__global__ void __launch_bounds__(128 * Q)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k2_pass2_team(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part, TileMeta* __restrict__ meta,
+              const cx<T>* __restrict__ tw, const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64,
+              const cx<double>* __restrict__ fb64, int fshift) {
+    using G = RowGeom<T, N1>;
+    static_assert(G::W == 1, "one wave per row");
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int NP = N2 / 2, PT = G::PT;
+    __shared__ __align__(16) RowSmem<T, N1> S[2 * Q];
+    __shared__ uint32_t wsum;
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, side = wv & 1, q = wv >> 1;
+    const uint32_t u = blockIdx.x;
+    const T quarter = T(0.25) / T(L);
+    RowReg<T, N1> R;
+    row_setup<T, N1, N2>(S[wv], R, tw, stw, l);
+    const uint32_t npairs = jt.ngroups * (uint32_t)(NP - 1);
+    const bool pair = u < npairs;
+    const uint32_t gl = pair ? u / (uint32_t)(NP - 1) : u - npairs;
+    const uint32_t pr = pair ? 1u + u % (uint32_t)(NP - 1) : 0u;
+    const JobDesc jd = find_group_job(jt, jt.group0 + gl);
+    uint32_t first, gs;
+    (void)group_geo(jd, jt.group0 + gl - jd.group_begin, &first, &gs);
+    const uint32_t lt = jd.tile_begin + first - jt.tile0;
+    cx<T>* __restrict__ Y = ws + (size_t)lt * L;
+    // pair: rows pr and n2 - pr; else rows 0 and n2/2, their own mirrors, with real V
+    const uint32_t row = pair ? (side ? (uint32_t)N2 - pr : pr) : (side ? (uint32_t)NP : 0u);
+    if (!pair) {   // weight of the group's chunks; reset the certificate
+        if (tid == 0) wsum = 0;
+        __syncthreads();
+        uint32_t sum = 0;
+        for (uint32_t c = tid; c < gs * NCB1; c += 128 * Q) sum += part[(size_t)lt * NCB1 + c];
+        atomicAdd(&wsum, sum);
+        __syncthreads();
+        if (tid == 0) meta[jt.group0 + gl] = TileMeta{wsum, 0u, 0u, 0u};
+    }
+    cx<T> acc[PT];
+#pragma unroll
+    for (int i = 0; i < PT; ++i) acc[i] = cx<T>{T(0), T(0)};
+    for (uint32_t c0 = 0; c0 < gs; c0 += Q) {   // the same trips for every wave: barriers inside
+        const uint32_t c = c0 + (uint32_t)q;
+        const bool active = c < gs;
+        cx<T> A[PT], B[PT];
+        if (active) {
+            row_load<T, N1>(A, Y + (size_t)c * L + (size_t)row * N1, l);
+            row_forward<T, N1>(A, S[wv], R, l);
+        }
+        if (pair) {
+            if (active && side) {
+                wave_sync();
+#pragma unroll
+                for (int i = 0; i < PT; ++i) S[wv].data[G::slot(l) + G::slot(64) * i] = A[i];
+            }
+            __syncthreads();
+            if (active && !side) {
+#pragma unroll
+                for (int i = 0; i < PT; ++i) B[i] = S[wv + 1].data[G::slot(G::M - 1 - l - 64 * i)];
+#pragma unroll
+                for (int i = 0; i < PT; ++i) acc[i] = acc[i] + spectrum_product(A[i], B[i], quarter);
+            }
+            __syncthreads();
+        } else if (active) {
+#pragma unroll
+            for (int i = 0; i < PT; ++i) B[i] = A[i];
+            row_mirror<T, N1>(B, S[wv].data, l, side == 0);
+#pragma unroll
+            for (int i = 0; i < PT; ++i) acc[i] = acc[i] + spectrum_product(A[i], B[i], quarter);
+        }
+    }
+    const bool holds = !pair || side == 0;
+    if constexpr (Q > 1) {
+        if (holds && q > 0) {
+            wave_sync();
+#pragma unroll
+            for (int i = 0; i < PT; ++i) S[wv].data[G::slot(l) + G::slot(64) * i] = acc[i];
+        }
+        __syncthreads();
+        if (holds && q == 0)
+#pragma unroll
+            for (int k = 1; k < Q; ++k)
+#pragma unroll
+                for (int i = 0; i < PT; ++i) acc[i] = acc[i] + S[wv + 2 * k].data[G::slot(l) + G::slot(64) * i];
+    }
+    if (holds && q == 0) {
+        row_inverse<T, N1>(acc, S[wv], R, l);
+        row_store<T, N1>(Y + (size_t)row * N1, acc, row, !pair, l, fa64, fb64, fshift);
+    }
+}
+
 // Waves per SIMD: 4 in FP32 (two workgroups of rows of 4096 per CU), 2 in FP64
 // and for rows of 8192.
 template <typename T, int N1> constexpr int row_waves_per_eu() { return sizeof(T) == 4 && N1 <= 4096 ? 4 : 2; }
@@ -1161,10 +1271,26 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
 // Compute units of the current device.
 int row_pass_workgroups();
 
+template <typename T, int N1, int N2, int NCB1, int Q>
+int launch_team(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
+    hipLaunchKernelGGL((k2_pass2_team<T, N1, N2, NCB1, Q>), dim3(jt.ngroups * (N2 / 2)), dim3(128 * Q), 0,
+                       (hipStream_t)stream, jt, (cx<T>*)ws, (const uint32_t*)part, meta, (const cx<T>*)tb.tw,
+                       (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 template <typename T, int N1, int N2, int NCB1>
 int launch_row_pass(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
     const uint32_t units = jt.ngroups * (N2 / 2);
     const uint32_t wgs = (uint32_t)(row_pass_workgroups() * row_wgs_per_cu<T, N1>());
+    if constexpr (RowGeom<T, N1>::W == 1) {
+        // teams as large as the chunks of a group give work to, while the device holds
+        // all their waves at once (wgs is its waves here)
+        const uint32_t chunks = (jt.ntiles + jt.ngroups - 1) / jt.ngroups;
+        if (chunks > 2 && units * 8 <= wgs) return launch_team<T, N1, N2, NCB1, 4>(jt, ws, part, meta, tb, stream);
+        if (chunks > 1 && units * 4 <= wgs) return launch_team<T, N1, N2, NCB1, 2>(jt, ws, part, meta, tb, stream);
+        if (units * 2 <= wgs) return launch_team<T, N1, N2, NCB1, 1>(jt, ws, part, meta, tb, stream);
+    }
     hipLaunchKernelGGL((k2_pass2<T, N1, N2, NCB1>), dim3(units < wgs ? units : wgs),
                        dim3(RowGeom<T, N1>::THREADS), 0,
                        (hipStream_t)stream, jt, (cx<T>*)ws, (const uint32_t*)part, meta, (const cx<T>*)tb.tw,

@@ -37,6 +37,8 @@ def test_short_class(pa, ctx, prec, logL, monkeypatch):
               (2 * L + 31, L // 2 + 1), (5 * L - 64, L // 3)]    # chunks in one window
     if logL < 18:
         shapes.append((L + 77, 2 * L + 129))                     # chunks and windows
+    if logL == 15:
+        shapes.append((L // 3, 100 * L))                         # more rows than the device has waves
     for n, m in shapes:
         plan = pa.pa_plan_query(n, m, flags)
         assert plan["fft_len"] == L, plan
