@@ -52,6 +52,14 @@ __device__ __forceinline__ JobDesc find_group_job(const JobTable& jt, uint32_t g
     return jt.many[lo];
 }
 
+// XCD-aware workgroup order: the hardware deals consecutive workgroups to the
+// 8 XCDs in turn; remap so that each XCD gets a contiguous range of logical
+// blocks (neighbouring column blocks of pass 1 share bit words in its L2).
+__device__ __forceinline__ uint32_t xcd_block() {
+    const uint32_t b = blockIdx.x, n = gridDim.x;
+    return (n & 7u) ? b : (b & 7u) * (n >> 3) + (b >> 3);
+}
+
 struct TileGeo {
     uint64_t j0, bi, i0, bo, sigma;
     uint64_t* dst;        // output words of this tile's window (bit 0 = output i0)
@@ -378,8 +386,8 @@ k_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta, 
     __shared__ cx<T> lds[XSPLIT ? (lds_slots<N2h, B>() + 1) / 2 : lds_slots<N2h, B>()];
     __shared__ uint32_t s_res, s_abs, s_bad;
 
-    const uint32_t t = jt.group0 + blockIdx.x / NCB;   // group
-    const uint32_t cb = blockIdx.x % NCB;
+    const uint32_t blk = xcd_block(), t = jt.group0 + blk / NCB;   // group
+    const uint32_t cb = blk % NCB;
     const JobDesc jd = find_group_job(jt, t);
     uint32_t first, gs;
     const TileGeo g = group_geo(jd, t - jd.group_begin, &first, &gs);

@@ -86,14 +86,6 @@ __device__ __forceinline__ Root64 root64(const cx<double>* __restrict__ fa64, co
 }
 template <typename T> __device__ __forceinline__ cx<T> rounded(Root64 w) { return cx<T>{(T)w.re, (T)w.im}; }
 
-// XCD-aware workgroup order: the hardware deals consecutive workgroups to the
-// 8 XCDs in turn; remap so that each XCD gets a contiguous range of logical
-// blocks (neighbouring column blocks of pass 1 share bit words in its L2).
-__device__ __forceinline__ uint32_t xcd_block() {
-    const uint32_t b = blockIdx.x, n = gridDim.x;
-    return (n & 7u) ? b : (b & 7u) * (n >> 3) + (b >> 3);
-}
-
 // ------------------------------------------------------------------ pass 1
 // What a tile transforms: two bit sequences, the real and the imaginary part.
 // An ordinary tile has a key chunk and its seed slice; the tiles of a job with
@@ -1157,8 +1149,8 @@ k2_pass3(JobTable jt, const cx<T>* __restrict__ ws, TileMeta* __restrict__ meta,
     __shared__ T hrow[C];
     __shared__ uint32_t s_res, s_abs, s_bad;
 
-    const uint32_t t = jt.group0 + blockIdx.x / NCB;   // group
-    const uint32_t cb = blockIdx.x % NCB;
+    const uint32_t blk = xcd_block(), t = jt.group0 + blk / NCB;   // group; neighbours write to the same lines
+    const uint32_t cb = blk % NCB;
     const JobDesc jd = find_group_job(jt, t);
     uint32_t first, gs;
     const TileGeo g = group_geo(jd, t - jd.group_begin, &first, &gs);
