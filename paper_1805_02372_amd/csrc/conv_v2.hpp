@@ -628,6 +628,21 @@ template <typename T, int N1> struct RowReg {
     cx<T> t3[G::PT == 8 ? 7 : 1];
 };
 
+// The same twiddles in LDS (kernels whose registers are taken): a lane reads its own
+// entries, 512 or 64 apart.
+template <typename T, int N1> struct RowTwiddles {
+    using G = RowGeom<T, N1>;
+    cx<T> tw1[G::S * (G::W - 1) * G::THREADS], t3[7 * 64];
+};
+template <typename T, int STRIDE> struct LdsLane {
+    const cx<T>* p;
+    __device__ __forceinline__ cx<T> operator[](int i) const { return p[i * STRIDE]; }
+};
+template <typename T, int N1> struct RowLds {
+    LdsLane<T, RowGeom<T, N1>::THREADS> tw1;
+    LdsLane<T, 64> t3;
+};
+
 // tw: w_NT^e, NT = max(n1, n2)
 template <typename T, int N1, int N2>
 __device__ __forceinline__ void row_setup(RowSmem<T, N1>& S, RowReg<T, N1>& R, const cx<T>* __restrict__ tw,
@@ -652,9 +667,9 @@ __device__ __forceinline__ void row_setup(RowSmem<T, N1>& S, RowReg<T, N1>& R, c
 // Transform of M points by one wave, register i holding element l + 64 i before
 // and after; `reg` is the wave's own LDS region.  512 points: three Stockham
 // stages of radix 8 (wave_fft.hpp holds the 1024-point transform).
-template <typename T, int N1, int DIR>
+template <typename T, int N1, int DIR, typename Reg>
 __device__ __forceinline__ void row_wave_fft(RowVec<T, N1>& v, cx<T>* __restrict__ reg, int l,
-                                             const RowSmem<T, N1>& S, const RowReg<T, N1>& R) {
+                                             const RowSmem<T, N1>& S, const Reg& R) {
     if constexpr (RowGeom<T, N1>::PT == 16) {
         wave_fft_lds<T, DIR, 1024>(v, reg, l, S.st);
     } else {
@@ -698,8 +713,8 @@ __device__ __forceinline__ void row_load(RowVec<T, N1>& a, const cx<T>* __restri
 
 // Forward transform of a row loaded by row_load: lane l of wave w ends with
 // X[W k_b + w] in register i, k_b = l + 64 i.
-template <typename T, int N1>
-__device__ __forceinline__ void row_forward(RowVec<T, N1>& a, RowSmem<T, N1>& S, const RowReg<T, N1>& R,
+template <typename T, int N1, typename Reg>
+__device__ __forceinline__ void row_forward(RowVec<T, N1>& a, RowSmem<T, N1>& S, const Reg& R,
                                             int tid) {
     using G = RowGeom<T, N1>;
     const int wv = tid >> 6, l = tid & 63;
@@ -728,8 +743,8 @@ __device__ __forceinline__ void row_forward(RowVec<T, N1>& a, RowSmem<T, N1>& S,
 
 // Inverse transform of a row held as P[W k_b + w] (register i, k_b = l + 64 i);
 // ends with a[t_b + M t_a] in a[s W + t_a], t_b = tid + THREADS s.
-template <typename T, int N1>
-__device__ __forceinline__ void row_inverse(RowVec<T, N1>& a, RowSmem<T, N1>& S, const RowReg<T, N1>& R,
+template <typename T, int N1, typename Reg>
+__device__ __forceinline__ void row_inverse(RowVec<T, N1>& a, RowSmem<T, N1>& S, const Reg& R,
                                             int tid) {
     using G = RowGeom<T, N1>;
     const int wv = tid >> 6, l = tid & 63;
@@ -1005,11 +1020,145 @@ k2_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part,
 // window o meet seed slice b + o, so every chunk and slice is transformed once
 // (two to a tile, columns by pass 1, rows here) and the windows' spectra
 //     P_o = (1 / L) sum_b X_b S_{b+o}
-// are summed from the stored spectra.  Packing two chunks, or two slices,
-// separates sequences of equal size: the large low-frequency values of the
-// zero-padded chunks do not leak into the seeds' spectra.
+// are sums over the packs' spectra.  Packing two chunks, or two slices, separates
+// sequences of equal size: the large low-frequency values of the zero-padded
+// chunks do not leak into the seeds' spectra.
 //
-// Forward rows in place: row k2 of a tile becomes Z[k2][p], p = w M + kb holding
+// Jobs of up to four windows: a workgroup takes one pair of mirror rows (unit 0: the
+// self rows 0 and n2/2 one after the other) through every pack, walks the key packs
+// with the slices that the windows meet sliding through registers, and inverts the
+// windows' sums; no spectrum goes to memory.  The unit of row 0 sets the
+// certificates.
+//
+// 64 registers of sums and 64 of slices beside the two rows of a pack leave two
+// waves per SIMD (one workgroup per CU; the twiddles are in LDS), so the next row
+// is loaded while one is transformed.  Bound by the latency of a row's steps: 3.5
+// us per row and CU, 2.4 TB/s.  33 packs of 2^23, four windows: 936 us, against
+// 1,620 us for the three kernels below on as many points; per further four windows
+// the rows would be transformed again, while the sums below take 510 us per eight.
+// Two rows at a time need registers that are not there (1,550 us with the spills).
+constexpr int kSharedWins = 4;
+template <typename T, int N1, int N2, int NCB1>
+__global__ void __launch_bounds__((RowGeom<T, N1>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
+k2_shared_rows(JobTable jt, const cx<T>* __restrict__ ws, cx<T>* __restrict__ win, const uint32_t* __restrict__ part,
+               TileMeta* __restrict__ meta, const cx<T>* __restrict__ tw,
+               const cx<T>* __restrict__ stw, const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64,
+               int fshift) {
+    using G = RowGeom<T, N1>;
+    constexpr uint32_t L = (uint32_t)N1 * N2;
+    constexpr int NP = N2 / 2, PT = G::PT;
+    static_assert(kSharedWins == 4, "four slices in registers");
+    __shared__ __align__(16) RowSmem<T, N1> S;
+    __shared__ uint32_t wsum;
+    __shared__ RowTwiddles<T, N1> X;
+    const int tid = threadIdx.x;
+    {
+        RowReg<T, N1> r;
+        row_setup<T, N1, N2>(S, r, tw, stw, tid);
+#pragma unroll
+        for (int i = 0; i < G::S * (G::W - 1); ++i) X.tw1[i * G::THREADS + tid] = r.tw1[i];
+        if (tid < 64)
+#pragma unroll
+            for (int i = 0; i < 7; ++i) X.t3[i * 64 + tid] = r.t3[i];
+    }
+    const RowLds<T, N1> R{{X.tw1 + tid}, {X.t3 + (tid & 63)}};
+    const SharedJob sh = jt.shared;
+    const T quarter = T(0.25) / T(L);
+    const uint32_t nw = jt.one.nouts;   // at most kSharedWins
+    for (uint32_t u = blockIdx.x; u < (uint32_t)NP; u += gridDim.x) {
+        const bool pair = u > 0;
+        if (!pair) {
+            __syncthreads();
+            if (tid == 0) wsum = 0;
+            __syncthreads();
+            uint32_t sum = 0;
+            for (uint32_t c = tid; c < sh.kpacks * NCB1; c += G::THREADS) sum += part[c];
+            atomicAdd(&wsum, sum);
+            __syncthreads();
+            if (tid < (int)nw) meta[jt.group0 + tid] = TileMeta{wsum, 0u, 0u, 0u};
+        }
+#pragma nounroll
+        for (int v = 0; v < (pair ? 1 : 2); ++v) {
+            const uint32_t row = pair ? u : v ? (uint32_t)NP : 0u;
+            const cx<T>* __restrict__ ra = ws + (size_t)row * N1;
+            const cx<T>* __restrict__ rb = ws + (size_t)(N2 - u) * N1;
+            cx<T> raw[PT];   // the next row, in flight
+            row_load<T, N1>(raw, ra + (size_t)sh.kpacks * L, tid);
+            // 2 X_a = z + conj m, 2 X_b = -i (z - conj m) of the pack whose first row is
+            // in flight; `next` comes after it
+            auto split = [&](uint32_t pack, uint32_t next, cx<T> (&xa)[PT], cx<T> (&xb)[PT]) {
+#pragma unroll
+                for (int i = 0; i < PT; ++i) xa[i] = raw[i];
+                row_load<T, N1>(raw, pair ? rb + (size_t)pack * L : ra + (size_t)next * L, tid);
+                row_forward<T, N1>(xa, S, R, tid);
+                if (pair) {
+#pragma unroll
+                    for (int i = 0; i < PT; ++i) xb[i] = raw[i];
+                    row_load<T, N1>(raw, ra + (size_t)next * L, tid);
+                    row_forward<T, N1>(xb, S, R, tid);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < PT; ++i) xb[i] = xa[i];
+                }
+                row_mirror<T, N1>(xb, S.data, tid, !pair && v == 0);
+#pragma unroll
+                for (int i = 0; i < PT; ++i) {
+                    const cx<T> m = conj(xb[i]), d = xa[i] - m;
+                    xa[i] = xa[i] + m;
+                    xb[i] = cx<T>{d.im, -d.re};
+                }
+            };
+            // the slices of seed pack q; past the last pack zero, and pack `next` (in
+            // flight) stays the next one
+            auto slices = [&](uint32_t q, uint32_t next, cx<T> (&sa)[PT], cx<T> (&sb)[PT]) {
+                if (q < sh.spacks) {
+                    split(sh.kpacks + q, next, sa, sb);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < PT; ++i) sa[i] = sb[i] = cx<T>{T(0), T(0)};
+                }
+            };
+            // pack that follows: seed pack q, or `other` where there is none
+            auto seed_or = [&](uint32_t q, uint32_t other) { return q < sh.spacks ? sh.kpacks + q : other; };
+            cx<T> acc[kSharedWins][PT], s0[PT], s1[PT], s2[PT], s3[PT];
+#pragma unroll
+            for (int o = 0; o < kSharedWins; ++o)
+#pragma unroll
+                for (int i = 0; i < PT; ++i) acc[o][i] = cx<T>{T(0), T(0)};
+            slices(0, seed_or(1, 0), s0, s1);
+            slices(1, 0, s2, s3);
+#pragma nounroll
+            for (uint32_t q = 0; q < sh.kpacks; ++q) {
+                const uint32_t sq = q + kSharedWins / 2, after = q + 1 < sh.kpacks ? q + 1 : 0;
+                cx<T> xa[PT], xb[PT];
+                split(q, seed_or(sq, after), xa, xb);
+#pragma unroll
+                for (int i = 0; i < PT; ++i) {
+                    acc[0][i] = acc[0][i] + cmul(xa[i], s0[i]) + cmul(xb[i], s1[i]);
+                    acc[1][i] = acc[1][i] + cmul(xa[i], s1[i]) + cmul(xb[i], s2[i]);
+                    acc[2][i] = acc[2][i] + cmul(xa[i], s2[i]) + cmul(xb[i], s3[i]);
+                    acc[3][i] = acc[3][i] + cmul(xa[i], s3[i]);
+                    s0[i] = s2[i];
+                    s1[i] = s3[i];
+                }
+                slices(sq, after, s2, s3);
+#pragma unroll
+                for (int i = 0; i < PT; ++i) acc[3][i] = acc[3][i] + cmul(xb[i], s2[i]);
+            }
+#pragma unroll
+            for (int o = 0; o < kSharedWins; ++o) {
+                if ((uint32_t)o >= nw) break;
+#pragma unroll
+                for (int i = 0; i < PT; ++i) acc[o][i] = cx<T>{acc[o][i].re * quarter, acc[o][i].im * quarter};
+                row_inverse<T, N1>(acc[o], S, R, tid);
+                row_store<T, N1>(win + (size_t)o * L + (size_t)row * N1, acc[o], row, !pair, tid, fa64, fb64, fshift);
+            }
+        }
+    }
+}
+
+// Jobs of more windows: forward rows, sums and inverse rows by three kernels, the
+// spectra in memory.  Forward rows in place: row k2 of a tile becomes Z[k2][p], p = w M + kb holding
 // frequency k1 = W kb + w, so the mirror of position p is N1 - 1 - p (row 0, whose
 // mirror is -k1 mod N1: M - p mod M within w = 0, else N1 + M - 1 - p).
 template <typename T, int N1, int N2>
@@ -1346,6 +1495,14 @@ struct ClassImpl2 {
     }
     static int shared_pass2(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta, const Tables& tb, void* stream) {
         hipStream_t s = (hipStream_t)stream;
+        if (jt.one.nouts <= kSharedWins) {
+            const uint32_t cus = (uint32_t)row_pass_workgroups(), units = N2 / 2;
+            hipLaunchKernelGGL((k2_shared_rows<T, N1, N2, N1 / C1>), dim3(units < cus ? units : cus),
+                               dim3(RowGeom<T, N1>::THREADS), 0, s, jt, (const cx<T>*)ws, (cx<T>*)windows(jt, ws),
+                               (const uint32_t*)part, meta, (const cx<T>*)tb.tw, (const cx<T>*)tb.stw,
+                               (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        }
         const uint32_t wgs = (uint32_t)(row_pass_workgroups() * row_wgs_per_cu<T, N1>());
         const uint32_t rows = jt.ntiles * N2, inv = jt.ngroups * (N2 / 2 + 1);
         // one row at a time takes 64 registers: four workgroups per CU

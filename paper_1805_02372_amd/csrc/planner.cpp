@@ -399,12 +399,15 @@ static bool plan_shared(uint64_t n, uint64_t m, int prec, int cls, const CostMod
         if (p.cgroup <= 4) return false;   // little left to share
     }
     groups = ceil_div(p.nchunks, p.cgroup);
-    // per pack: a chunk's passes and the spectrum written once and read once per
-    // eight windows; per window and group: the rest of a tile and its sum, written and read
+    // up to four windows: a chunk's passes and the sums beside them (52 us per pack of
+    // 2^23, where a chunk takes 45).  More: per pack a chunk's passes and the spectrum
+    // written once and read once per eight windows; per window and group the rest of a
+    // tile and its sum, written and read
     const double rate = 4.0e12, Ld = (double)p.L;
     const double chunk = cm.chunk(prec, cls), rest = std::max(cm.tile(prec, cls) - chunk, 0.0);
     const double packs = (double)(groups * p.packs(p.cgroup)), wins = (double)(groups * p.nouts);
-    p.cost = packs * (chunk + 8 * Ld * (1.0 + (double)ceil_div(p.nouts, 8)) / rate) + wins * (rest + 8 * Ld / rate);
+    if (p.nouts <= 4) p.cost = packs * 1.15 * chunk + wins * rest;
+    else p.cost = packs * (chunk + 8 * Ld * (1.0 + (double)ceil_div(p.nouts, 8)) / rate) + wins * (rest + 8 * Ld / rate);
     p.rigorous = rigorous_bound(prec, p.L, p.Bi, p.Bo) * (double)p.cgroup;
     *out = p;
     return true;

@@ -49,9 +49,10 @@ def _check(pa, ctx, p, s, k, y, rng):
     assert np.array_equal(synth.bits_to_array(y, p.m)[idx.astype(np.int64)], oracle.hash_select(p.seed, p.n, p.m, p.key, idx))
 
 
-# windows 3, 4, 5, 6 and 9 (sums of 4, 8 and 8 + 2 windows at a time), chunk
-# counts odd and even, last chunks and windows short, full and ragged
-SHAPES = [(20 * B + 5, 3 * B - 17), (7 * B + 7, 4 * B), (4 * B, 4 * B + 64), (6 * B + 7, 5 * B + 5),
+# windows 2, 3, 4 (sums in the row pass), 5, 6 and 9 (sums of 8 and 8 + 2 stored
+# windows at a time), chunk counts odd and even, last chunks and windows short, full
+# and ragged
+SHAPES = [(9 * B + 3, 2 * B - 1), (2 * B, B + 1), (20 * B + 5, 3 * B - 17), (7 * B + 7, 4 * B), (4 * B, 4 * B + 64), (6 * B + 7, 5 * B + 5),
           (3 * B + 12345, 8 * B + 999_001)]
 
 
