@@ -52,7 +52,7 @@ def _check(pa, ctx, p, s, k, y, rng):
 # windows 2, 3, 4 (sums in the row pass), 5, 6 and 9 (sums of 8 and 8 + 2 stored
 # windows at a time), chunk counts odd and even, last chunks and windows short, full
 # and ragged
-SHAPES = [(9 * B + 3, 2 * B - 1), (2 * B, B + 1), (20 * B + 5, 3 * B - 17), (7 * B + 7, 4 * B), (4 * B, 4 * B + 64), (6 * B + 7, 5 * B + 5),
+SHAPES = [(9 * B + 3, 2 * B - 1), (12 * B, 2 * B), (20 * B + 5, 3 * B - 17), (7 * B + 7, 4 * B), (4 * B, 4 * B + 64), (6 * B + 7, 5 * B + 5),
           (3 * B + 12345, 8 * B + 999_001)]
 
 
