@@ -269,8 +269,9 @@ typedef struct {
     double max_abs;           /* max |z| over all outputs                     */
     double bound;             /* predicted max error of the plan              */
     double ms_pass[4];        /* PA_TIMING: summed kernel ms of pass 1, 2, 3; [3] is 0
-                                 (key chunks are XOR-merged inside pass 3).
-                                 Direct path: [0] key reversal, [1] product */
+                                 (key chunks are summed in pass 2 and XOR-merged
+                                 inside pass 3).  Direct path: [0] clearing of the
+                                 output, [1] product */
     uint64_t model_bytes;     /* algorithmic HBM bytes of the FFT passes (direct
                                  path: seed, key and output once)             */
     uint64_t launches;        /* kernel launches                              */
@@ -303,13 +304,16 @@ const char* pa_strerror(pa_status status);
  * the precisions selected by flags (PA_PREC_AUTO: FP32 and FP64; otherwise the
  * one named), with `reps` timed runs each on synthetic bits, and use the
  * results in this context's planner.  Each class runs one launch with one tile
- * and one with four: the marginal cost per tile goes to the class and the
- * remainder (median over classes) to the per-launch cost.  With PA_PREC_AUTO
+ * and one with 4 (16 up to 2^20 points): the marginal cost per tile and the rest of
+ * the first go to the class, the median of the latter to the per-launch cost.
+ * Classes that sum the products of several key chunks also run the jobs with a
+ * second chunk each, for the cost of a further chunk.  With PA_PREC_AUTO
  * or PA_PREC_DIRECT it also times the direct GF(2) path at two output lengths
  * and takes the slope as its cost per output and key word (PA_PREC_DIRECT
  * times only that).  If path is not NULL the table is also written there as
- * JSON ({"launch": seconds, "direct": seconds, "fp32": {"12": seconds, ...},
- * ...}).  Synchronous; PA_EDEVICE on a HIP error, PA_EINVAL for
+ * JSON ({"launch": seconds, "direct": seconds, "fp32": {"4096": [tile, first],
+ * ...}, "fp32_chunk": {"4096": seconds, ...}, ...}; a table without the chunk
+ * sections loads too).  Synchronous; PA_EDEVICE on a HIP error, PA_EINVAL for
  * a file that cannot be written. */
 pa_status pa_tune(pa_ctx* ctx, uint32_t flags, int reps, const char* path);
 

@@ -1,8 +1,7 @@
 // FFT length classes for FP64 tiles.  2^12 .. 2^13: one kernel per tile, the
-// whole length in one workgroup (tile_fused.hpp).  2^14 .. 2^19: L = n1 * n2
-// with n2 = 2^max(logL-13, min(11, logL/2)), workgroup-wide Stockham stages
-// (conv_kernels.hpp).  2^20 .. 2^24: n1 = 4096, wave-level
-// transforms (conv_v2.hpp; the columns of 2^24 workgroup-wide).
+// whole length in one workgroup (tile_fused.hpp).  2^14: 128 x 128, workgroup-wide
+// Stockham stages (conv_kernels.hpp).  2^15 .. 2^19: n1 = 512; 2^20 .. 2^24: n1 =
+// 4096; wave-level transforms (conv_v2.hpp; pass 3 of 2^24 workgroup-wide).
 #include "conv_kernels.hpp"
 #include "conv_v2.hpp"
 #include "tile_fused.hpp"

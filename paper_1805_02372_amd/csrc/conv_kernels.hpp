@@ -1,5 +1,6 @@
 // The Toeplitz-hash tile pipeline as three HIP kernels with workgroup-wide
-// Stockham transforms (the short length classes).
+// Stockham transforms (2^14 and the mixed-radix classes below 2^20; pass 3 also of
+// the mixed-radix classes above and of FP64 2^24).
 //
 // A tile convolves a seed slice w (bi+bo-1 bits, encoded +-1) with a key
 // chunk x (bi bits, encoded 0/1) circularly over L = n1*n2 >= bi+bo-1 points

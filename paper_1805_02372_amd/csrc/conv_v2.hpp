@@ -1,19 +1,22 @@
-// Tile pipeline of the power-of-two FFT length classes from 2^15 on:
-// the same three passes as conv_kernels.hpp (see there for the mathematics),
-// restructured around wave-level transforms (wave_fft.hpp):
+// Tile pipeline of the power-of-two FFT length classes from 2^15 on and of the
+// mixed-radix ones from 2^20 on: the same three passes as conv_kernels.hpp (see
+// there for the mathematics), restructured around wave-level transforms
+// (wave_fft.hpp):
 //
-//  * pass 1: a small kernel transposes the key and seed bits into bit planes
-//    (one word per lane and sequence), each wave transforms G whole columns
-//    (n2 <= 1024) or one half of a column after a radix-2 split (n2 = 2048),
-//    and an LDS transpose turns the column-major results into C-element row
-//    segments for the stores.
-//  * pass 2: a row of 8192 points is a radix-8 stage across the 8 waves
-//    (decimation in frequency, registers only) followed by one 1024-point
-//    transform per wave; the inverse runs the same steps in reverse.  Two
-//    workgroup barriers per row transform.
-//  * pass 3: C columns are read as C-element row segments, transposed in
-//    LDS, each wave inverts G columns, output bits are OR-ed into an LDS bit
-//    array and stored as C-bit groups.
+//  * pass 1, rows of 4096 and 8192: a small kernel transposes the key and seed bits
+//    into bit planes, and the columns are split into 3 to 8 parts whose first radix
+//    level is looked up from the bits; each wave transforms G columns of a part in
+//    registers.  Rows of 512: the bits are staged through LDS and each wave
+//    transforms G whole columns.  An LDS transpose turns the column-major results
+//    into C-element row segments for the stores.
+//  * pass 2: a row of 4096 points is a radix-8 stage across the 8 waves
+//    (decimation in frequency, registers only) followed by one 512-point transform
+//    per wave; the inverse runs the same steps in reverse.  Two workgroup barriers
+//    per row transform.  The products of a group's chunks are summed before the
+//    inverse.  Rows of 512 are one wave's.
+//  * pass 3: C columns are read as C-element row segments, transposed in LDS, each
+//    wave inverts G columns, the output bits are gathered in an LDS array and stored
+//    as C-bit groups.
 #pragma once
 #include <type_traits>
 
