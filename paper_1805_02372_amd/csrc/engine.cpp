@@ -879,7 +879,9 @@ void fill_plan_stats(pa_stats* s, const TilePlan& p) {
     // shared spectra: a pack is written, read and written (rows) and read (sums); a
     // window's half spectrum is written and read twice
     const uint64_t groups = (p.nchunks + p.cgroup - 1) / p.cgroup;
-    s->model_bytes += p.shared ? groups * (p.packs(p.cgroup) * 32 + p.nouts * 16) * p.L
+    // up to four windows: a pack is written and read, a window's half written and read
+    const uint64_t pb = p.nouts > 4 ? 32 : 16, wb = p.nouts > 4 ? 16 : 8;
+    s->model_bytes += p.shared ? groups * (p.packs(p.cgroup) * pb + p.nouts * wb) * p.L
                                : p.tiles() * (p.prec == PREC_FP64 ? 48ull : 24ull) * p.L;
 }
 
@@ -893,6 +895,13 @@ void set_certified(pa_stats* s, pa_status st) {
 }  // namespace pa
 
 // ================================================================ C ABI
+
+namespace pa {
+bool smaller_plan(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* plan) {
+    const int cap = ceil_log2(plan->L) - 1;
+    return cap >= kMinLogL && plan_job(n, m, policy, cm, plan, cap, 0);
+}
+}  // namespace pa
 
 extern "C" {
 
@@ -1012,13 +1021,19 @@ pa_status pa_hash(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t m, con
         if (s == PA_OK && !async && hipStreamSynchronize(ln.stream) != hipSuccess) s = PA_EDEVICE;
         if (s == PA_OK && timing) ln.timer.collect(st.ms_pass);
     } else {
-        std::vector<JobDesc> jobs(1);
-        fill_job(&jobs[0], dseed, dkey, dout, n, m, plan);
         // Only an a-priori certified plan (worst-case bound below 0.5, or
         // NTT) may skip the certificate read-back; kernel timing needs the
         // launch to finish.
-        const bool async = dev && (flags & PA_ASYNC) && plan.rigorous < kRigorousLimit && !timing;
-        s = ln.launch(c, plan.prec, plan.cls, jobs, timing, !async, &st);
+        bool async = false;
+        for (;;) {
+            async = dev && (flags & PA_ASYNC) && plan.rigorous < kRigorousLimit && !timing;
+            std::vector<JobDesc> jobs(1);
+            fill_job(&jobs[0], dseed, dkey, dout, n, m, plan);
+            s = ln.launch(c, plan.prec, plan.cls, jobs, timing, !async, &st);
+            if (s != PA_ENOMEM || !smaller_plan(n, m, policy, cm, &plan)) break;
+            st = pa_stats{};
+            fill_plan_stats(&st, plan);
+        }
         if (s == PA_OK && !dev) s = fetch_outputs(ln, hsrc, hlen, 1);
         if (s == PA_OK && !async) s = ln.finish(c, flags, &st, nullptr);
         if (s == PA_OK && !dev && st.fallback_tiles) s = fetch_outputs(ln, hsrc, hlen, 1);

@@ -229,6 +229,9 @@ void fill_plan_stats(pa_stats* s, const TilePlan& p);
 void set_certified(pa_stats* s, pa_status st);
 void fill_job(JobDesc* jd, const uint64_t* seed, const uint64_t* key, uint64_t* out, uint64_t n, uint64_t m,
               const TilePlan& p);
+// Replace a plan whose single tile does not fit the budget by one over shorter
+// classes; false if there is none.
+bool smaller_plan(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* plan);
 double now_seconds();
 // Host buffers to device memory on a lane's stream through its pinned staging
 // buffer (copied in by the context's copy pool, then one DMA each); the lane's

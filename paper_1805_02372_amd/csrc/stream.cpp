@@ -126,6 +126,7 @@ static pa_status launch_block(pa_stream* s, const uint64_t* dseed, const uint64_
             s->r->part[b ^ 1].release(c);
             st = launch_fft(s, b, dseed, dkey, len, plan);
         }
+        while (st == PA_ENOMEM && smaller_plan(len, m, policy, cm, &plan)) st = launch_fft(s, b, dseed, dkey, len, plan);
         if (st != PA_OK) return st;
     }
     s->pending = {true, !direct, len, b};

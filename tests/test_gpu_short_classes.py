@@ -51,3 +51,26 @@ def test_short_class(pa, ctx, prec, logL, monkeypatch):
         assert s["fft_len"] == L and s["n1"] * s["n2"] == L and s["fallback_tiles"] == 0, s
         assert s["max_residual"] < (1e-6 if prec == "fp64" else 0.25), s   # 1/4: the certificate's own limit
         _check(p, y, plan["window_bits"], rng, what)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_budget_below_the_planned_tile(pa, prec):
+    """A budget that does not hold one tile of the planned class: the job runs on
+    shorter classes."""
+    from gpu_util import gpu_hash
+    flags = pa.PA_PREC_FP32_SEG if prec == "fp32" else pa.PA_PREC_FP64
+    n, m = 400_000, 60_001
+    rng = np.random.default_rng(23)
+    p = synth.random_problem(rng, n, m)
+    tile = pa.pa_plan_query(n, m, flags)["fft_len"] * (8 if prec == "fp32" else 16)
+    seen = set()
+    for budget in (4 * tile, tile + tile // 8, tile - 4096, tile // 2):
+        c = pa.pa_create(0, budget, None)
+        st, y = gpu_hash(pa, c, p.seed, n, m, p.key, flags)
+        assert st == pa.PA_OK, (budget, pa.pa_strerror(st))
+        s = pa.pa_last_stats(c)
+        assert s["tiles"] >= 1 and s["fft_len"] * (8 if prec == "fp32" else 16) <= budget, (budget, s)
+        seen.add(s["fft_len"])
+        _check(p, y, s["window_bits"], rng, f"{prec} budget {budget}")
+        pa.pa_destroy(c)
+    assert len(seen) > 1, seen
