@@ -96,6 +96,13 @@ __device__ __forceinline__ v8i mm_expand_b(uint32_t w) {
     return v8i{(int)((w << 2) & 0x44444444u), (int)(w & 0x22222222u), (int)((w >> 2) & 0x11111111u),
                (int)((w >> 3) & 0x11111111u), 0, 0, 0, 0};
 }
+// The nibbles a half word after those of a, b being the next word's.
+__device__ __forceinline__ v8i mm_half(v8i a, v8i b) {
+    v8i h{};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) h[q] = (int)__builtin_amdgcn_alignbit((uint32_t)b[q], (uint32_t)a[q], 16);
+    return h;
+}
 
 // Workgroup (x, y) of a job: outputs [1024 NB x, + 1024 NB) over words
 // [kc y, + kc) of the p axis (p < n + 64 (16 NB - 1)), kc = 32 seg.  `merge`:
@@ -151,25 +158,38 @@ k_direct_mm(DirectJob one, const DirectJob* __restrict__ many, uint32_t njobs, u
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-    uint32_t s0 = S[q0], s1 = S[q0 + 1];
-#pragma unroll 2
-    for (uint32_t h = 0; h < seg; ++h) {
-        const uint32_t s2 = S[q0 + h + 2];
+    // Row 16 a + r of a step are the 32 seed bits from bit 16 a + r of its word on:
+    // for a = 0 and 2 the nibbles of this and the next word at shift r, for a = 1
+    // and 3 the same a half word further (16 bits are whole nibbles).  Two of the
+    // four are the next step's, so a step expands one word and shifts it once.
+    uint32_t s2 = S[q0 + 2];
+    v8i e0 = mm_expand_a(__builtin_amdgcn_alignbit(S[q0 + 1], S[q0], r));
+    v8i e1 = mm_expand_a(__builtin_amdgcn_alignbit(s2, S[q0 + 1], r));
+    v8i e2, h0 = mm_half(e0, e1), h1;
+    // a step from (a, ha, b): its fourth row hb and the word c after b
+    auto step = [&](uint32_t h, const v8i& a, const v8i& ha, const v8i& b, v8i& hb, v8i& c) {
+        const uint32_t s3 = S[q0 + h + 3];
+        c = mm_expand_a(__builtin_amdgcn_alignbit(s3, s2, r));
+        s2 = s3;
+        hb = mm_half(b, c);
+        const v8i A[4] = {a, ha, b, hb};
         v8i B[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) B[b] = mm_expand_b(xs[(int)h - 32 * b]);
+        for (int k = 0; k < NB; ++k) B[k] = mm_expand_b(xs[(int)h - 32 * k]);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            // row 16 a + r: the 32 seed bits from bit 16 a + r of (s0, s1, s2)
-            const uint32_t w = a < 2 ? __builtin_amdgcn_alignbit(s1, s0, 16 * a + r)
-                                     : __builtin_amdgcn_alignbit(s2, s1, 16 * (a - 2) + r);
-            const v8i A = mm_expand_a(w);
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B[b], acc[a][b], 4, 4, 0, 0, 0, 0);
-        }
-        s0 = s1;
-        s1 = s2;
+            for (int k = 0; k < NB; ++k)
+                acc[q][k] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[q], B[k], acc[q][k], 4, 4, 0, 0, 0, 0);
+    };
+    // seg is odd: one step, then pairs
+    step(0, e0, h0, e1, h1, e2);
+    for (uint32_t h = 1; h + 1 < seg; h += 2) {
+        step(h, e1, h1, e2, h0, e0);
+        step(h + 1, e2, h0, e0, h1, e1);
+        const v8i t = e1;   // (word, half, next word) = (e0, h1, e1)
+        e1 = e0;
+        e2 = t;
     }
     // lane (r, g) holds rows 16 a + 4 g + v of column 16 b + r: the parities of
     // one column are the 64 bits of one output word
@@ -276,13 +296,13 @@ constexpr uint64_t kSlabX = 1ull << 20, kSlabY = 1ull << 15;
 constexpr uint64_t kMmBatchWgs = 1ull << 24;
 
 // Column blocks of a tile: 1024 NB outputs.  A step of 128 key bits takes
-// about 120, 144 and 256 cycles of a SIMD at NB = 1, 2, 4 (operand preparation
-// bounds the first two, the matrix cores the last).
+// about 92, 128 and 256 cycles of a SIMD at NB = 1, 2, 4 (operand preparation
+// bounds the first, the matrix cores the others).
 static int mm_blocks(uint64_t m) {
     int best = 1;
     double cost = 1e300;
     for (int nb : {1, 2, 4}) {
-        const double c = (double)cdiv(m, 1024 * nb) * (nb == 1 ? 120.0 : nb == 2 ? 144.0 : 256.0);
+        const double c = (double)cdiv(m, 1024 * nb) * (nb == 1 ? 92.0 : nb == 2 ? 128.0 : 256.0);
         if (c < cost) cost = c, best = nb;
     }
     return best;
