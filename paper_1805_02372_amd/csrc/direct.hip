@@ -68,15 +68,17 @@ k_direct_prep(const uint64_t* __restrict__ key, uint64_t n, uint32_t* __restrict
 // as four masks: bits 0, 4, .. / 1, 5, .. / 2, 6, .. / 3, 7, .. of the word in
 // place are nibbles of value 0.5, 1 and 2 in A, matched by 2, 1 and 0.5 in B, so
 // that every product of set bits is 1.  Expanding a word costs 5 (A) or 7 (B)
-// operations beside A's funnel shift, no table.  The four K groups of each
+// operations beside A's funnel shift, no table; the four row blocks of A share
+// their words (k_direct_mm).  The four K groups of each
 // wave walk their own consecutive words, so a lane loads one new seed word and
 // NB key words per step.
 //
 // Bound by the matrix cores for NB = 4 (16 products of 16 cycles per step beside
-// 48 vector operations of 4) and by the vector operations that prepare a step
-// for NB = 1 (30, and 4 products).  Measured on MI355X: n = 12,345,679, m = 1000
-// 10 us (the word-parallel kernel before it, one output per lane: 55 us); n =
-// 10^6, m = 200,000 3.1e15 bit products per second (2.2e14 before).
+// 44 vector operations of 4) and by the vector operations that prepare a step
+// for NB = 1 (23, and 4 products; 32 with every row block expanded by itself: call
+// 26.9 -> 26.0 us at n = 12,345,679, m = 1000).  Measured on MI355X, that job 10-13
+// us (the word-parallel kernel before it, one output per lane: 55 us); n = 10^6, m =
+// 200,000 3.1e15 bit products per second (2.2e14 before).
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
