@@ -1454,10 +1454,12 @@ int launch_row_pass(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta
     if constexpr (RowGeom<T, N1>::W == 1) {
         // teams as large as the chunks of a group give work to, while the device holds
         // all their waves at once (wgs is its waves here)
-        const uint32_t chunks = (jt.ntiles + jt.ngroups - 1) / jt.ngroups;
-        if (chunks > 2 && units * 8 <= wgs) return launch_team<T, N1, N2, NCB1, 4>(jt, ws, part, meta, tb, stream);
-        if (chunks > 1 && units * 4 <= wgs) return launch_team<T, N1, N2, NCB1, 2>(jt, ws, part, meta, tb, stream);
-        if (units * 2 <= wgs) return launch_team<T, N1, N2, NCB1, 1>(jt, ws, part, meta, tb, stream);
+        // (and a repeat as large as the first run's, whose order of summation it needs)
+        const uint32_t groups = jt.as_groups ? jt.as_groups : jt.ngroups, waves = groups * (N2 / 2);
+        const uint32_t chunks = ((jt.as_groups ? jt.as_tiles : jt.ntiles) + groups - 1) / groups;
+        if (chunks > 2 && waves * 8 <= wgs) return launch_team<T, N1, N2, NCB1, 4>(jt, ws, part, meta, tb, stream);
+        if (chunks > 1 && waves * 4 <= wgs) return launch_team<T, N1, N2, NCB1, 2>(jt, ws, part, meta, tb, stream);
+        if (waves * 2 <= wgs) return launch_team<T, N1, N2, NCB1, 1>(jt, ws, part, meta, tb, stream);
     }
     hipLaunchKernelGGL((k2_pass2<T, N1, N2, NCB1>), dim3(units < wgs ? units : wgs),
                        dim3(RowGeom<T, N1>::THREADS), 0,

@@ -409,11 +409,6 @@ void Lane::release(Ctx* c) {
 
 static uint32_t chunk_groups(const JobDesc& jd) { return (jd.nchunks + jd.cgroup - 1) / jd.cgroup; }
 
-// A run of whole groups: tiles [tile, tile + ntiles), groups [group, group + ngroups).
-struct Span {
-    uint32_t tile, ntiles, group, ngroups;
-};
-
 // Three passes over the tiles and groups of a job table.
 static pa_status run_table(const launch_fn (&fns)[3], const JobTable (&jt)[3], Lane* ln, const Tables& tb, bool timing,
                            uint64_t* launches) {
@@ -546,7 +541,7 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     // job the chunk groups come in order, so a window is cleared (pass 1 of its
     // chunk-0 tile) before any group XORs into it, also when the tiles are split
     // over several launches.
-    std::vector<Span> spans;
+    spans.clear();
     uint32_t tiles = 0, groups = 0;
     Span cur{0, 0, 0, 0};
     for (JobDesc& jd : js) {
@@ -713,10 +708,12 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
     //  * Job with shared spectra: every chunk of the failed group's window.
     //  * Job that accumulates chunk groups: per failed group, the FP32 group
     //    again and then its FP64 chunks, all XOR-ing into the window without
-    //    clearing it; the FP32 run is deterministic, so its bits cancel the
-    //    first run's.  If the repeat's certificate is not bit-identical to the
-    //    first run's, the whole job is rebuilt in FP64 instead (its windows
-    //    cleared and rebuilt).
+    //    clearing it; the repeat runs the kernels of the first run, with the same
+    //    order of summation, so its bits cancel the first run's.  (Equal
+    //    certificates do not show that by themselves: above 2^24 an FP32 value has
+    //    no residual.)  Certificates that differ would mean that the inputs have
+    //    changed; the whole job is then rebuilt in FP64 (its windows cleared and
+    //    rebuilt).
     const ClassKernels* K32 = class_kernels(PREC_FP32, cls);
     Tables tb, tb32;
     pa_status st = lane_tables(c, *this, PREC_FP64, cls, &tb);
@@ -771,6 +768,11 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
             bool same = K32 != nullptr;
             if (same) {
                 const Span sp{q * jd.nouts * jd.cgroup + o * gs, gs, lg, 1};
+                for (const Span& first : spans)
+                    if (t - first.group < first.ngroups) {
+                        jt.as_tiles = first.ntiles;
+                        jt.as_groups = first.ngroups;
+                    }
                 st = run_span(K32, jt, sp, this, tb32, false, &stats->launches);
                 if (st != PA_OK) return st;
                 std::vector<TileMeta> again;
@@ -787,6 +789,7 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         }
         // FP64: a tile is a group of its own, numbered chunk b, window o -> b nouts + o
         jt.one.cgroup = 1;
+        jt.as_tiles = jt.as_groups = 0;
         std::vector<uint32_t> again;
         for (uint32_t b = whole ? 0u : b0; b < (whole ? jd.nchunks : b0 + gs); ++b)
             for (uint32_t w = whole ? 0u : o; w < (whole ? jd.nouts : o + 1); ++w) again.push_back(b * jd.nouts + w);

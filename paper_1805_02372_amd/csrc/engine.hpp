@@ -87,6 +87,11 @@ struct PassTimer {
 };
 
 // A stream with its own workspace: runs one plan at a time.
+// A run of whole groups: tiles [tile, tile + ntiles), groups [group, group + ngroups).
+struct Span {
+    uint32_t tile, ntiles, group, ngroups;
+};
+
 struct Lane {
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -108,6 +113,7 @@ struct Lane {
     int prec = 0, cls = 0;
     uint32_t total_groups = 0;
     std::vector<JobDesc> jobs;
+    std::vector<Span> spans;   // its launches of tiles, in order
     hipEvent_t done = nullptr;
 
     void release(Ctx* c);

@@ -58,6 +58,9 @@ struct JobTable {
     uint32_t ntiles;      // tiles in this launch (whole groups)
     uint32_t group0;      // first group of this launch
     uint32_t ngroups;     // groups in this launch
+    // The repeat of a group takes the row kernel that a launch of so many tiles and
+    // groups takes, the first run's (0: this launch's own numbers)
+    uint32_t as_tiles, as_groups;
     SharedJob shared;     // kpacks > 0: the tiles are the packs of one group of job `one`
     uint32_t clears;      // some job of `many` has a chunk-0 tile that clears its window
 };
