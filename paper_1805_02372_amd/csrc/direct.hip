@@ -294,8 +294,9 @@ uint64_t direct_key_words(uint64_t n) { return cdiv(cdiv(n, 32), 4) * 4; }
 
 // Grid slabs: at most 2^20 workgroups along x and 2^15 along y per launch.
 constexpr uint64_t kSlabX = 1ull << 20, kSlabY = 1ull << 15;
-// Workgroups of one batched launch.
-constexpr uint64_t kMmBatchWgs = 1ull << 24;
+// Workgroups of one batched launch, at most: a launch counts the work-items along a
+// dimension in 32 bits, and drops those beyond without an error.
+constexpr uint64_t kMmBatchWgs = 0xFFFFFFFFull / kMmThreads;
 
 // Column blocks of a tile: 1024 NB outputs.  A step of 128 key bits takes
 // about 92, 128 and 256 cycles of a SIMD at NB = 1, 2, 4 (operand preparation
