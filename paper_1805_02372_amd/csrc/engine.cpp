@@ -725,12 +725,15 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         const JobDesc& jd = jobs[job_of(t)];
         if (!jd.shared && jd.nchunks > jd.cgroup) most = std::max<size_t>(most, jd.cgroup);
     }
-    st = ws.ensure(c, std::max<size_t>((size_t)class_len(cls) * 16 + K64->cfg.ws_extra,
-                                       most * ((size_t)class_len(cls) * 8 + (K32 ? K32->cfg.ws_extra : 0))),
-                   stream);
-    if (st != PA_OK) return st;
+    st = ws.ensure(c, std::max<size_t>(tile_bytes(PREC_FP64, cls), most * tile_bytes(PREC_FP32, cls)), stream);
     const size_t part_words = std::max<size_t>(K64->cfg.n1 / K64->cfg.b1, K32 ? most * (K32->cfg.n1 / K32->cfg.b1) : 0);
-    st = part.ensure(c, part_words * sizeof(uint32_t), stream);
+    if (st == PA_OK) st = part.ensure(c, part_words * sizeof(uint32_t), stream);
+    if (st == PA_ENOMEM) {
+        std::vector<size_t> which;
+        for (uint32_t t : failed)
+            if (which.empty() || which.back() != job_of(t)) which.push_back(job_of(t));
+        return rebuild_shorter(c, flags, which, stats, per_job);
+    }
     if (st != PA_OK) return st;
     std::vector<uint8_t> rebuilt(jobs.size(), 0);
     std::vector<uint32_t> windows_done;   // group numbers of the windows of jobs with shared spectra
@@ -809,6 +812,39 @@ pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_s
         stats->tiles += again.size();
     }
     if (hipStreamSynchronize(stream) != hipSuccess) return PA_EDEVICE;
+    return result;
+}
+
+// Jobs of the finished launch again in FP64 and on shorter classes, where the
+// budget does not hold one FP64 tile of their class.
+pa_status Lane::rebuild_shorter(Ctx* c, uint32_t flags, const std::vector<size_t>& which, pa_stats* stats,
+                                std::vector<pa_status>* per_job) {
+    const std::vector<JobDesc> js = jobs;   // the launches below take the lane's place
+    const uint64_t len = class_len(cls);
+    CostModel cm;
+    {
+        std::lock_guard<std::mutex> pk(c->plan_mu);
+        cm = c->cost;
+    }
+    pa_status result = PA_OK;
+    for (size_t jx : which) {
+        const JobDesc& jd = js[jx];
+        TilePlan p;
+        p.L = len;
+        pa_status st = PA_ENOMEM;
+        while (st == PA_ENOMEM && smaller_plan(jd.n, jd.m, PREC_FP64, cm, &p)) {
+            std::vector<JobDesc> one(1);
+            fill_job(&one[0], jd.seed, jd.key, jd.out, jd.n, jd.m, p);
+            st = launch(c, PREC_FP64, p.cls, one, false, true, stats);
+        }
+        if (st == PA_OK) st = finish(c, flags & ~PA_TIMING, stats, nullptr);
+        if (st != PA_OK && st != PA_EPRECISION) return st;
+        stats->fallback_tiles += p.tiles();
+        if (st == PA_EPRECISION) {
+            result = st;
+            if (per_job) (*per_job)[jx] = st;
+        }
+    }
     return result;
 }
 
@@ -903,6 +939,17 @@ namespace pa {
 bool smaller_plan(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* plan) {
     const int cap = ceil_log2(plan->L) - 1;
     return cap >= kMinLogL && plan_job(n, m, policy, cm, plan, cap, 0);
+}
+
+bool smaller_plans(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy, const CostModel& cm,
+                   int* cls, std::vector<TilePlan>* plans) {
+    const int cap = ceil_log2(class_len(*cls)) - 1;
+    return cap >= kMinLogL && plan_batch(ns, ms, policy, cm, cls, plans, cap, 0);
+}
+
+uint64_t tile_bytes(int prec, int cls) {
+    const ClassKernels* K = class_kernels(prec, cls);
+    return class_len(cls) * (prec == PREC_FP64 ? 16 : 8) + (K ? K->cfg.ws_extra : 0);
 }
 }  // namespace pa
 
@@ -1143,16 +1190,6 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         if (c->batch_plans.size() >= 16) c->batch_plans.clear();
         c->batch_plans[std::move(bkey)] = Ctx::BatchPlan{is_direct, groups};
     }
-    std::vector<const TilePlan*> plan_of(count, nullptr);
-    pa_stats st{};
-    for (const BatchGroup& g : groups)   // ascending classes: the stats name the largest
-        for (size_t q = 0; q < g.jobs.size(); ++q) {
-            plan_of[g.jobs[q]] = &g.plans[q];
-            fill_plan_stats(&st, g.plans[q]);
-        }
-    st.chunk_bits = 0;   // differ per job
-    st.window_bits = 0;
-
     const bool dev = flags & PA_DEVICE_PTRS;
     std::vector<JobDesc> all(count);
     std::vector<uint64_t> out_off(count, 0);
@@ -1183,15 +1220,12 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
             out_off[i] = off + sw + kw;
             off += sw + kw + ow;
         }
-        if (is_direct[i]) {   // pointers only
-            all[i].seed = dseed;
-            all[i].key = dkey;
-            all[i].out = dout;
-            all[i].n = j.n;
-            all[i].m = j.m;
-        } else {
-            fill_job(&all[i], dseed, dkey, dout, j.n, j.m, *plan_of[i]);
-        }
+        // (the plans of the FFT jobs with their group's launch)
+        all[i].seed = dseed;
+        all[i].key = dkey;
+        all[i].out = dout;
+        all[i].n = j.n;
+        all[i].m = j.m;
     }
     if (!dev) {
         const pa_status ss = stage_to_device(c, ln, sdst.data(), ssrc.data(), slen.data(), (int)sdst.size());
@@ -1237,10 +1271,37 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
     while (true) {
         for (size_t k = 0; k < lanes.size() && !stop && !queue.empty(); ++k) {
             if (on_lane[k] >= 0) continue;
-            const BatchGroup& g = groups[queue.front()];
-            std::vector<JobDesc> jobs(g.jobs.size());
-            for (size_t q = 0; q < g.jobs.size(); ++q) jobs[q] = all[g.jobs[q]];
-            const pa_status ls = lanes[k]->launch(c, g.plans[0].prec, g.cls, jobs, flags & PA_TIMING, true, &lst[k]);
+            BatchGroup& g = groups[queue.front()];
+            pa_status ls;
+            for (bool freed = false;; freed = true) {
+                std::vector<JobDesc> jobs(g.jobs.size());
+                for (size_t q = 0; q < g.jobs.size(); ++q) {
+                    const JobDesc& a = all[g.jobs[q]];
+                    fill_job(&jobs[q], a.seed, a.key, a.out, a.n, a.m, g.plans[q]);
+                }
+                const pa_stats before = lst[k];
+                ls = lanes[k]->launch(c, g.plans[0].prec, g.cls, jobs, flags & PA_TIMING, true, &lst[k]);
+                if (ls != PA_ENOMEM) break;
+                lst[k] = before;
+                (void)hipStreamSynchronize(lanes[k]->stream);   // what was enqueued reads the lane's buffers
+                if (!fifo.empty()) break;
+                // nothing in flight: the memory that the other lanes keep, then shorter classes
+                if (!freed) {
+                    for (Lane* other : lanes)
+                        if (other != lanes[k]) {
+                            other->ws.release(c);
+                            other->part.release(c);
+                        }
+                } else {
+                    std::vector<uint64_t> gn, gm;
+                    for (size_t q : g.jobs) {
+                        gn.push_back(ns[q]);
+                        gm.push_back(ms[q]);
+                    }
+                    if (!smaller_plans(gn, gm, policy, cm, &g.cls, &g.plans)) break;
+                }
+            }
+            if (ls == PA_ENOMEM && !fifo.empty()) break;   // again when the group in flight has ended
             if (ls != PA_OK) {
                 for (size_t q = 0; q < g.jobs.size(); ++q) status[g.jobs[q]] = ls;
                 s = ls;
@@ -1266,6 +1327,13 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
     }
     if (ndirect && hipStreamSynchronize(ln.stream) != hipSuccess && s == PA_OK) s = PA_EDEVICE;
     lst.push_back(dst);
+    pa_stats st{};
+    std::stable_sort(groups.begin(), groups.end(),   // the stats name the largest class
+                     [](const BatchGroup& a, const BatchGroup& b) { return class_len(a.cls) < class_len(b.cls); });
+    for (const BatchGroup& g : groups)
+        for (const TilePlan& p : g.plans) fill_plan_stats(&st, p);
+    st.chunk_bits = 0;   // differ per job
+    st.window_bits = 0;
     st.direct_jobs = dst.direct_jobs;
     if (ndirect == count) st.prec = PA_PREC_DIRECT;
     for (const pa_stats& x : lst) {

@@ -122,6 +122,9 @@ struct Lane {
     bool ended();
     hipError_t wait();
 
+    pa_status rebuild_shorter(Ctx* c, uint32_t flags, const std::vector<size_t>& which, pa_stats* stats,
+                              std::vector<pa_status>* per_job);
+
     // Enqueue every tile of `jobs` (planned at precision prec, class cls); sets
     // tile_begin.  With `fetch_meta` the tile
     // certificates are copied to meta_host behind the kernels.
@@ -238,6 +241,11 @@ void fill_job(JobDesc* jd, const uint64_t* seed, const uint64_t* key, uint64_t* 
 // Replace a plan whose single tile does not fit the budget by one over shorter
 // classes; false if there is none.
 bool smaller_plan(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* plan);
+// The same for jobs of one launch: `cls` and their plans.
+bool smaller_plans(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy, const CostModel& cm,
+                   int* cls, std::vector<TilePlan>* plans);
+// Workspace bytes of one tile of a class (its points and bit planes).
+uint64_t tile_bytes(int prec, int cls);
 double now_seconds();
 // Host buffers to device memory on a lane's stream through its pinned staging
 // buffer (copied in by the context's copy pool, then one DMA each); the lane's

@@ -593,19 +593,19 @@ bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64
 }
 
 bool plan_batch(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy,
-                const CostModel& cm, int* cls_out, std::vector<TilePlan>* plans) {
+                const CostModel& cm, int* cls_out, std::vector<TilePlan>* plans, int cap_logL, uint64_t shared_bytes) {
     if (ns.empty() || ns.size() != ms.size()) return false;
     bool found = false;
     double best_cost = 0;
     std::vector<TilePlan> tmp(ns.size());
     int ids[kMaxClassId + 1];
-    const int nid = class_ids(policy, ids);
+    const int nid = class_ids(policy, ids, cap_logL);
     for (int q = 0; q < nid; ++q) {
         const int k = ids[q];
         double cost = cm.first(policy, k);
         bool ok = true;
         for (size_t i = 0; i < ns.size() && ok; ++i) {
-            ok = plan_at_class(ns[i], ms[i], policy, k, cm, &tmp[i]);
+            ok = plan_at_class(ns[i], ms[i], policy, k, cm, &tmp[i], shared_bytes);
             if (ok) cost += tmp[i].cost - cm.first(policy, k);
         }
         if (!ok) continue;

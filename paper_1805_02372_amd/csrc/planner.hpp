@@ -161,8 +161,10 @@ bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64
                        const CostModel& cm, std::vector<BatchGroup>* groups,
                        const std::vector<TilePlan>* own = nullptr, uint64_t shared_bytes = kSharedBytes);
 
-// One class for a whole batch: minimises the summed cost of every job's tiles.
+// One class for a whole batch, of at most 2^cap_logL points: minimises the summed
+// cost of every job's tiles.
 bool plan_batch(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms, int policy,
-                const CostModel& cm, int* cls, std::vector<TilePlan>* plans);
+                const CostModel& cm, int* cls, std::vector<TilePlan>* plans, int cap_logL = 24,
+                uint64_t shared_bytes = kSharedBytes);
 
 }  // namespace pa

@@ -52,10 +52,10 @@ void Ctx::serving_release() {
     pending.clear();
 }
 
-// Tile-workspace bytes of a request at its own best FP32 plan (all tiles
-// resident at once; a launch runs fewer at a time if the budget is short).
-// Workspace bytes of a request's cheapest FP32 plan (all tiles resident) and
-// of one of its tiles; the plan's length class goes to *cls.
+// Workspace bytes of a request's cheapest FP32 plan (all tiles resident; a launch
+// runs fewer at a time if the budget is short) and of one of its tiles; the plan's
+// length class goes to *cls.  Classes of which the budget does not hold one tile
+// are passed by.
 static uint64_t request_bytes(Ctx* c, uint64_t n, uint64_t m, uint64_t* min_bytes, int* cls) {
     TilePlan p;
     if (!c->plan_cached(n, m, PREC_FP32, &p)) {
@@ -63,7 +63,13 @@ static uint64_t request_bytes(Ctx* c, uint64_t n, uint64_t m, uint64_t* min_byte
         *cls = 0;
         return ~0ull;
     }
-    *min_bytes = 8 * p.L;
+    CostModel cm;
+    {
+        std::lock_guard<std::mutex> pl(c->plan_mu);
+        cm = c->cost;
+    }
+    while (tile_bytes(PREC_FP32, p.cls) > c->budget && smaller_plan(n, m, PREC_FP32, cm, &p)) {}
+    *min_bytes = tile_bytes(PREC_FP32, p.cls);
     *cls = p.cls;
     return p.shared ? (p.packs(p.cgroup) + p.nouts) * *min_bytes : p.tiles() * *min_bytes;
 }
@@ -204,7 +210,7 @@ void Ctx::serve_loop() {
                 }
                 continue;
             }
-            const int cls = cls0;
+            int cls = cls0;
             CostModel cm;
             {
                 std::lock_guard<std::mutex> pl(plan_mu);
@@ -214,14 +220,18 @@ void Ctx::serve_loop() {
             pa_status s = PA_OK;
             for (size_t k = 0; k < batch.size() && s == PA_OK; ++k)
                 if (!plan_at_class(ns[k], ms[k], PREC_FP32, cls, cm, &plans[k], budget / 3)) s = PA_EINVAL;
-            std::vector<JobDesc> jobs(batch.size());
-            if (s == PA_OK) {
+            while (s == PA_OK) {
+                std::vector<JobDesc> jobs(batch.size());
                 for (size_t k = 0; k < batch.size(); ++k)
                     fill_job(&jobs[k], batch[k]->seed, batch[k]->key, batch[k]->out,
                              batch[k]->n, batch[k]->m, plans[k]);
                 lane_stats[i] = pa_stats{};
                 for (const TilePlan& tp : plans) fill_plan_stats(&lane_stats[i], tp);
                 s = lanes[i].launch(this, PREC_FP32, cls, jobs, false, true, &lane_stats[i]);
+                if (s != PA_ENOMEM) break;
+                // the memory is with the other lanes and calls: a shorter class
+                (void)hipStreamSynchronize(lanes[i].stream);   // what was enqueued reads the lane's buffers
+                if (smaller_plans(ns, ms, PREC_FP32, cm, &cls, &plans)) s = PA_OK;
             }
             lk.lock();
             if (s != PA_OK) {

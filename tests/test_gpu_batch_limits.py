@@ -41,3 +41,113 @@ def test_direct_batch_beyond_one_grid(pa):
             del outs
     finally:
         pa.pa_destroy(c)
+
+
+# One FP32 tile of this shape's planned class (3 2^20 points and their bit planes)
+# is more than 24 MiB; 2^21 points fit.
+TIGHT = (3_664_349, 1_086_326)
+
+
+def _direct(pa, ctx, s, k, n, m):
+    from gpu_util import empty_dev, from_dev
+    import torch
+    out = empty_dev(synth.words_for(m))
+    assert pa.pa_hash(ctx, s, n, m, k, out, pa.PA_PREC_DIRECT) == pa.PA_OK
+    torch.cuda.synchronize()
+    return from_dev(out)[:synth.words_for(m)]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "ntt"])
+@pytest.mark.parametrize("others", [[], [(300_000, 70_001), (1_500_000, 150_000), TIGHT]])
+def test_batch_budget_below_the_planned_tile(pa, prec, others):
+    """A budget that does not hold one tile of a group's class: its jobs run on
+    shorter classes.  With several groups, one that finds the memory taken waits
+    for the group beside it."""
+    from gpu_util import to_dev, from_dev, empty_dev, describe
+    import torch
+    flags = {"fp32": pa.PA_PREC_FP32_SEG, "fp64": pa.PA_PREC_FP64, "ntt": pa.PA_PREC_NTT}[prec]
+    rng = np.random.default_rng(24)
+    budget = 24 << 20
+    assert pa.pa_plan_query(*TIGHT, pa.PA_PREC_FP32_SEG)["fft_len"] * 8 >= budget
+    c = pa.pa_create(0, budget, None)
+    try:
+        jobs = []
+        for n, m in [TIGHT] + others:
+            p = synth.random_problem(rng, n, m)
+            jobs.append((to_dev(p.seed), to_dev(p.key), empty_dev(synth.words_for(m)), n, m))
+        for _ in range(2):   # again with the workspaces that the first call left
+            print(f"batch of {len(jobs)}, {prec}", flush=True)
+            st, per = pa.pa_hash_batch(c, jobs, flags)
+            torch.cuda.synchronize()
+            assert st == pa.PA_OK and per == [pa.PA_OK] * len(jobs), (pa.pa_strerror(st), per)
+            s = pa.pa_last_stats(c)
+            assert s["tiles"] >= len(jobs) and s["fallback_tiles"] == 0 and s["model_bytes"] > 0, s
+            for js, jk, jo, n, m in jobs:
+                a, b = from_dev(jo)[:synth.words_for(m)], _direct(pa, c, js, jk, n, m)
+                assert np.array_equal(a, b), describe(a, b, m)
+                jo.fill_(-1)
+            torch.cuda.synchronize()
+    finally:
+        pa.pa_destroy(c)
+
+
+def test_serving_budget_below_the_planned_tile(pa):
+    """The same for requests: admitted at a class whose tile fits the budget, and
+    run on a shorter one where the launch does not find the memory."""
+    from gpu_util import to_dev, from_dev, empty_dev, describe
+    import torch
+    n, m = TIGHT
+    rng = np.random.default_rng(25)
+    c = pa.pa_create(0, 24 << 20, None)
+    try:
+        seed = synth.gen_bits(rng, n + m - 1)
+        ds = to_dev(seed)
+        sid = pa.pa_seed_register(c, ds, n + m - 1)
+        keys = [to_dev(synth.gen_bits(rng, n)) for _ in range(5)]
+        outs = [empty_dev(synth.words_for(m)) for _ in keys]
+        tickets = []
+        for k, o in zip(keys, outs):
+            st, t = pa.pa_submit(c, sid, n, m, k, o)
+            assert st == pa.PA_OK, pa.pa_strerror(st)
+            tickets.append(t)
+        got = [pa.pa_wait(c, t) for t in tickets]
+        torch.cuda.synchronize()
+        assert got == [pa.PA_OK] * len(keys), [pa.pa_strerror(x) for x in got]
+        assert pa.pa_serve_stats(c)["tiles"] >= len(keys)
+        for k, o in zip(keys, outs):
+            a, b = from_dev(o)[:synth.words_for(m)], _direct(pa, c, ds, k, n, m)
+            assert np.array_equal(a, b), describe(a, b, m)
+    finally:
+        pa.pa_destroy(c)
+
+
+@pytest.mark.parametrize("call", ["hash", "batch"])
+def test_fallback_budget_below_one_fp64_tile(pa, call):
+    """A budget that holds the FP32 tiles but not one FP64 tile of their class:
+    the failed job is rebuilt in FP64 on shorter classes.  All ones: every output
+    is n mod 2."""
+    from gpu_util import to_dev, from_dev, empty_dev
+    import torch
+    n, m = TIGHT
+    rng = np.random.default_rng(26)
+    c = pa.pa_create(0, 40 << 20, None)
+    try:
+        s, k = to_dev(synth.pattern_bits("ones", n + m - 1)), to_dev(synth.pattern_bits("ones", n))
+        o = empty_dev(synth.words_for(m))
+        p = synth.random_problem(rng, 200_000, 50_000)
+        o2 = empty_dev(synth.words_for(p.m))
+        if call == "hash":
+            assert pa.pa_hash(c, s, n, m, k, o, pa.PA_PREC_FP32_SEG) == pa.PA_OK
+        else:
+            st, per = pa.pa_hash_batch(c, [(s, k, o, n, m), (to_dev(p.seed), to_dev(p.key), o2, p.n, p.m)],
+                                       pa.PA_PREC_FP32_SEG)
+            assert st == pa.PA_OK and per == [pa.PA_OK] * 2
+        torch.cuda.synchronize()
+        stats = pa.pa_last_stats(c)
+        assert stats["fallback_tiles"] > 0, stats
+        assert np.array_equal(synth.bits_to_array(from_dev(o), m), np.full(m, n & 1, np.uint8)), stats
+        if call == "batch":
+            assert np.array_equal(from_dev(o2)[:synth.words_for(p.m)], oracle.hash_words(p.seed, p.n, p.m, p.key))
+        assert pa.pa_hash(c, s, n, m, k, o, pa.PA_PREC_FP32_SEG | pa.PA_NO_FALLBACK) == pa.PA_EPRECISION
+    finally:
+        pa.pa_destroy(c)
