@@ -164,13 +164,25 @@ static double box_leak_rms(int prec, uint64_t Lc, uint64_t Bi) {
     return unit_roundoff(prec) * std::sqrt(s4) / L;
 }
 
-double error_bound(int prec, uint64_t Lc, uint64_t Bi) {
-    if (prec == PREC_NTT) return 0.0;
-    // the noise term: the packed transform carries the seed's norm sqrt(L)
-    // beside the chunk's sqrt(Bi), so even a one-bit chunk sees u sqrt(L log L)
+// The noise term: the packed transform carries the seed's norm sqrt(L) beside
+// the chunk's sqrt(Bi), so even a one-bit chunk sees u sqrt(L log L).
+static double noise_error(int prec, uint64_t Lc, uint64_t Bi) {
     const double L = (double)Lc;
-    return 6.0 * g_kappa * unit_roundoff(prec) * std::sqrt(std::log2(L) * ((double)Bi + L)) +
-           5.0 * box_leak_rms(prec, Lc, Bi);
+    return 6.0 * g_kappa * unit_roundoff(prec) * std::sqrt(std::log2(L) * ((double)Bi + L));
+}
+static double leak_error(int prec, uint64_t L, uint64_t Bi) { return 5.0 * box_leak_rms(prec, L, Bi); }
+
+double error_bound(int prec, uint64_t Lc, uint64_t Bi) {
+    return prec == PREC_NTT ? 0.0 : noise_error(prec, Lc, Bi) + leak_error(prec, Lc, Bi);
+}
+
+// The same for the sum of the products of c chunks: the noise is independent from
+// chunk to chunk, but the low-frequency error is not.  Every chunk has about the
+// same box spectrum, so its roots' rounding leaves about the same wave, and the
+// waves add in full: measured maxima grow as a sqrt(c) + b c, with b 0.22 to 0.35
+// of the low-frequency term from 2^15 to 2^23.
+static double group_error(int prec, uint64_t L, uint64_t Bi, uint64_t c) {
+    return prec == PREC_NTT ? 0.0 : noise_error(prec, L, Bi) * std::sqrt((double)c) + leak_error(prec, L, Bi) * (double)c;
 }
 
 // Worst-case bound of Percival's form (Math. Comp. 72, 2003): an FFT
@@ -360,7 +372,7 @@ static bool class_shared(int prec, int cls) { return prec == PREC_FP32 && cls >=
 // Modeled error of one product of shared spectra: the noise term of error_bound
 // (the sequences of a pack are of equal size, so no box leaks into a seed).
 static double shared_error(int prec, uint64_t L, uint64_t Bi) {
-    return 6.0 * g_kappa * unit_roundoff(prec) * std::sqrt(std::log2((double)L) * ((double)Bi + (double)L));
+    return noise_error(prec, L, Bi);
 }
 
 // Chunks of one group: at most 64, in equal groups, and for FP32 no more than
@@ -368,7 +380,9 @@ static double shared_error(int prec, uint64_t L, uint64_t Bi) {
 static uint64_t group_chunks(int prec, uint64_t L, uint64_t Bi, uint64_t nchunks) {
     uint64_t most = 64;
     if (prec == PREC_FP32) {
-        const double r = kGroupErrorLimit / error_bound(prec, L, Bi);
+        // the largest c with noise sqrt(c) + leak c within the limit
+        const double noise = noise_error(prec, L, Bi), leak = leak_error(prec, L, Bi);
+        const double r = 2 * kGroupErrorLimit / (noise + std::sqrt(noise * noise + 4 * leak * kGroupErrorLimit));
         most = std::min<uint64_t>(most, (uint64_t)std::max(1.0, std::floor(r * r)));
     }
     return ceil_div(nchunks, ceil_div(nchunks, most));
@@ -460,9 +474,8 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
     best.prec = prec;
     best.cls = cls;
     best.L = L;
-    // the errors of a group's summed products add up: about as independent
-    // noise in the model, in full in the worst case
-    best.bound = error_bound(prec, L, best.Bi) * std::sqrt((double)best.cgroup);
+    // the errors of a group's summed products add up, in the worst case in full
+    best.bound = group_error(prec, L, best.Bi, best.cgroup);
     best.rigorous = rigorous_bound(prec, L, best.Bi, best.Bo) * (double)best.cgroup;
     if (best.bound > kPlanErrorLimit) return false;   // not reached by FP32 up to 2^24
     TilePlan sh;

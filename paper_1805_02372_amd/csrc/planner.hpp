@@ -100,10 +100,11 @@ double error_kappa();
 // certificate (half the rounding margin of 0.5).
 constexpr double kPlanErrorLimit = 0.25;
 
-// The admissible modeled error of a group's sum of products (lower than a single
-// tile's: measured maxima reach 0.73 of the model, and the certificate rejects
-// 0.125).
-constexpr double kGroupErrorLimit = 0.15;
+// The admissible modeled error of a group's sum of products: about that of the
+// longest single tile (0.19 at 2^24).  Over 230 shapes of random bits the largest
+// residual of such groups was 0.07 (0.21 to 0.46 of the model, the largest groups
+// up to 0.41), against the 0.125 that the certificate rejects.
+constexpr double kGroupErrorLimit = 0.2;
 
 // Modeled time of the direct GF(2) path for one job: a fixed cost and a cost per
 // output (in blocks of 256) and key word (ceil(n/32), rounded up to 4), plus 10%
