@@ -197,14 +197,15 @@ static double group_error(int prec, uint64_t L, uint64_t Bi, uint64_t c) {
 // two levels (3k+2), and the two sequences share one transform, so
 // ||a|| ||b|| is replaced by (||x|| + ||w||)^2 with ||x|| <= sqrt(Bi) (0/1
 // chunk) and ||w|| = sqrt(Bi+Bo-1) (+-1 seed slice).  It holds for every
-// input bit pattern.
-double rigorous_bound(int prec, uint64_t L, uint64_t Bi, uint64_t Bo) {
+// input bit pattern.  A group of c chunks adds c products of these norms before
+// the inverse: c - 1 additions, each with a relative error of at most u.
+double rigorous_bound(int prec, uint64_t L, uint64_t Bi, uint64_t Bo, uint64_t c) {
     if (prec == PREC_NTT || prec == PREC_DIRECT) return 0.0;
     const int levels = ceil_log2(L) + ((L & (L - 1)) ? 1 : 0);
     const double u = unit_roundoff(prec), lv = 3.0 * levels + 2.0, beta = 2.0 * u;
-    const double g = lv * std::log1p(u) + (lv + 1) * std::log1p(u * std::sqrt(5.0)) + lv * std::log1p(beta);
+    const double g = (lv + (double)(c - 1)) * std::log1p(u) + (lv + 1) * std::log1p(u * std::sqrt(5.0)) + lv * std::log1p(beta);
     const double norms = std::sqrt((double)Bi) + std::sqrt((double)(Bi + Bo - 1));
-    return norms * norms * std::expm1(g);
+    return (double)c * norms * norms * std::expm1(g);
 }
 
 CostModel::CostModel() {
@@ -422,7 +423,7 @@ static bool plan_shared(uint64_t n, uint64_t m, int prec, int cls, const CostMod
     const double packs = (double)(groups * p.packs(p.cgroup)), wins = (double)(groups * p.nouts);
     if (p.nouts <= 4) p.cost = packs * 1.15 * chunk + wins * rest;
     else p.cost = packs * (chunk + 8 * Ld * (1.0 + (double)ceil_div(p.nouts, 8)) / rate) + wins * (rest + 8 * Ld / rate);
-    p.rigorous = rigorous_bound(prec, p.L, p.Bi, p.Bo) * (double)p.cgroup;
+    p.rigorous = rigorous_bound(prec, p.L, p.Bi, p.Bo, p.cgroup);
     *out = p;
     return true;
 }
@@ -476,7 +477,7 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
     best.L = L;
     // the errors of a group's summed products add up, in the worst case in full
     best.bound = group_error(prec, L, best.Bi, best.cgroup);
-    best.rigorous = rigorous_bound(prec, L, best.Bi, best.Bo) * (double)best.cgroup;
+    best.rigorous = rigorous_bound(prec, L, best.Bi, best.Bo, best.cgroup);
     if (best.bound > kPlanErrorLimit) return false;   // not reached by FP32 up to 2^24
     TilePlan sh;
     if (shared_bytes && plan_shared(n, m, prec, cls, cm, shared_bytes, &sh) && sh.cost < best.cost) best = sh;

@@ -89,9 +89,10 @@ struct TilePlan {
 double error_bound(int prec, uint64_t L, uint64_t Bi);
 // Worst-case (a-priori) bound of a tile's max error for any input bits:
 // (||x|| + ||w||)^2 times the relative error growth of the forward FFT,
-// product and inverse FFT, with ||x|| <= sqrt(Bi), ||w|| = sqrt(Bi+Bo-1).  A
-// tile whose bound is below 0.5 rounds to the exact integers.
-double rigorous_bound(int prec, uint64_t L, uint64_t Bi, uint64_t Bo);
+// product and inverse FFT, with ||x|| <= sqrt(Bi), ||w|| = sqrt(Bi+Bo-1); of a
+// group of c chunks, c times that with the rounding of the sum.  A tile or group
+// whose bound is below 0.5 rounds to the exact integers.
+double rigorous_bound(int prec, uint64_t L, uint64_t Bi, uint64_t Bo, uint64_t c = 1);
 constexpr double kRigorousLimit = 0.5;
 void set_error_kappa(double kappa);
 double error_kappa();
