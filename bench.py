@@ -57,21 +57,26 @@ def kernel_source_digest() -> str:
 def launch_bytes(st: dict, n: int, m: int) -> list[float]:
     """Algorithmic HBM bytes of one launch of each pass over all tiles of a
     job (e = 8 for FP32, 16 for FP64; L the FFT length; T tiles = C chunks x
-    W windows):
+    W windows; G groups of chunks, whose products share one inverse: one, in the
+    classes that sum them, for the few chunks of a single job here, else C):
       pass 1: reads each tile's key chunk and seed slice, writes the complex
-              array (and clears the output when C > 1):
+              array (and clears the output when G > 1):
               e L T + (2 W n + C m) / 8 [+ m / 8]
-      pass 2: reads the array, writes half of it: 1.5 e L T
-      pass 3: reads the half, writes (C = 1) or XORs in (C > 1) each tile's
-              output window: 0.5 e L T + C m / 8
-    The fourth entry (the former merge) is 0: chunks are XOR-accumulated."""
+      pass 2: reads the array, writes half a tile per group and window:
+              e L T + 0.5 e L G W
+      pass 3: reads the halves, writes (G = 1) or XORs in (G > 1) each group's
+              output window: 0.5 e L G W + G m / 8
+    The fourth entry (the former merge) is 0: groups are XOR-accumulated."""
     e = 16 if st["prec"] == 0x20 else 8
     L = float(st["fft_len"])
     C = -(-n // st["chunk_bits"])
     W = -(-m // st["window_bits"])
     T = C * W
-    clear = m / 8 if C > 1 else 0.0
-    return [e * L * T + (2 * W * n + C * m) / 8 + clear, 1.5 * e * L * T, 0.5 * e * L * T + C * m / 8, 0.0]
+    pow2 = st["fft_len"] & (st["fft_len"] - 1) == 0
+    G = 1 if st["prec"] != 0x30 and st["fft_len"] >= (1 << 15 if pow2 else 1 << 20) else C
+    clear = m / 8 if G > 1 else 0.0
+    return [e * L * T + (2 * W * n + C * m) / 8 + clear, e * L * T + 0.5 * e * L * G * W,
+            0.5 * e * L * G * W + G * m / 8, 0.0]
 
 
 def run_single(pa, ctx, torch, prob, flags, steps, warmup):
@@ -598,9 +603,9 @@ def main():
         "roofline_valu": valu,
         "pipeline": {
             "kernel_ms": [round(x, 5) for x in head["kernel_ms"]],
-            "model_bytes": st["model_bytes"],
-            "model_GBs": round(st["model_bytes"] / (pipeline_ms * 1e-3) / 1e9, 1),
-            "model_frac": round(st["model_bytes"] / (pipeline_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+            "model_bytes": round(sum(pb)),
+            "model_GBs": round(sum(pb) / (pipeline_ms * 1e-3) / 1e9, 1),
+            "model_frac": round(sum(pb) / (pipeline_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
         },
         "latency_ms": {"p50": round(float(np.percentile(head["lat"], 50)) * 1e3, 4),
                        "p99": round(float(np.percentile(head["lat"], 99)) * 1e3, 4)},

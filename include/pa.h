@@ -272,8 +272,11 @@ typedef struct {
                                  (key chunks are summed in pass 2 and XOR-merged
                                  inside pass 3).  Direct path: [0] clearing of the
                                  output, [1] product */
-    uint64_t model_bytes;     /* algorithmic HBM bytes of the FFT passes (direct
-                                 path: seed, key and output once)             */
+    uint64_t model_bytes;     /* HBM bytes of three FFT passes per tile: 24 L
+                                 (FP64 48 L), also where summed chunks share an
+                                 inverse and move less; shared spectra: of their
+                                 packs and windows (direct path: seed, key and
+                                 output once)                                 */
     uint64_t launches;        /* kernel launches                              */
     uint64_t direct_jobs;     /* jobs that ran on the direct path (prec is
                                  PA_PREC_DIRECT when all of them did)         */
