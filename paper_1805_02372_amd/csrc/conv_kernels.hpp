@@ -173,14 +173,14 @@ template <int A, int B> constexpr int cmax() { return A > B ? A : B; }
 
 // ------------------------------------------------------------------ pass 1
 // NT2: length of the root table tw of the column transforms (a multiple of N2).
-// Column passes take the split exchange where their complex buffer does not
-// fit the LDS (columns of 2560 to 3584 points), and in FP64 also where it would
-// leave room for one workgroup per compute unit; the registers of the latter
-// are budgeted for two workgroups (no spills).  FP32 column workgroups of eight
-// and more waves would then get 128 registers or fewer and spill: measured
-// slower.
+// FP64 column passes take the split exchange where their complex buffer would
+// leave room for one workgroup per compute unit or for none, and registers for
+// two workgroups where the scalar buffers of two fit (no spills), else for one
+// (FP64 2^24, pass 3: 16 waves of 128 registers, 88 more spilled to 336 bytes of
+// scratch per lane).  FP32 column workgroups of eight and more waves would get 128
+// registers or fewer and spill: measured slower.
 template <typename T, int N, int F> constexpr bool column_split() {
-    return (size_t)lds_slots<N, F>() * sizeof(cx<T>) > 150000 || (split_exchange<T, N, F>() && sizeof(T) == 8);
+    return split_exchange<T, N, F>() && sizeof(T) == 8;
 }
 template <typename T, int N, int F, int THREADS> constexpr int column_waves_per_eu() {
     constexpr int wgs = (size_t)lds_slots<N, F>() * sizeof(T) > 81920 ? 1 : 2;

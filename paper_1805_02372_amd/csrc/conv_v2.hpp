@@ -153,7 +153,8 @@ __device__ __forceinline__ TileBits tile_bits(const JobDesc& jd, const TileGeo& 
 // per column NJ words of 16 fields of FW (4 or 8) bits, bit FW i + q of word j of
 // column t1 being position t1 + N1 (j + NJ i + M q).  A lane of pass 1 then loads
 // one word of each plane, a wave consecutive ones.
-// P = 4 or 8 leaves M = 64 .. 256 (512 at 4096), two radix stages for the wave.
+// P = 4 or 8 leaves M = 64 .. 256, two radix stages for the wave (n2 = 4096, FP64
+// 2^24: P = 4 and M = 1024, three stages).
 constexpr int column_parts(int n2) { return odd_part(n2) > 1 ? odd_part(n2) : n2 == 2048 ? 8 : 4; }
 template <int N1, int N2> struct BitPlanes {
     static constexpr int P = column_parts(N2), M = N2 / P, FW = P <= 4 ? 4 : 8;
@@ -623,7 +624,7 @@ k2_pass1_split(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part,
 // wave; the inverse runs the same steps in reverse.  Two workgroup barriers per
 // row transform.  Rows of 4096 take 8 points per lane (8 x 8 x 8 x 8: a mirror
 // pair and the group's sum are 48 registers per lane in FP32, so that two
-// workgroups of 8 waves share a CU); rows of 8192 take 16 (8 x 4 x 16 x 16), rows
+// workgroups of 8 waves share a CU, at 128 registers with 17 to 22 spilled); rows of 8192 take 16 (8 x 4 x 16 x 16), rows
 // of 512 are one wave's (8 x 8 x 8, no barriers).
 template <typename T, int N1> struct RowGeom {
     static constexpr int PT = N1 >= 8192 ? 16 : 8;
@@ -1063,7 +1064,9 @@ k2_pass2(JobTable jt, cx<T>* __restrict__ ws, const uint32_t* __restrict__ part,
 // us per row and CU, 2.4 TB/s.  33 packs of 2^23, four windows: 936 us, against
 // 1,620 us for the three kernels below on as many points; per further four windows
 // the rows would be transformed again, while the sums below take 510 us per eight.
-// Two rows at a time need registers that are not there (1,550 us with the spills).
+// All 256 registers are taken and 30 more spilled (124 bytes of scratch per lane, two
+// or three of them reloaded per key pack); two rows at a time: 1,550 us with the
+// spills.
 constexpr int kSharedWins = 4;
 template <typename T, int N1, int N2, int NCB1>
 __global__ void __launch_bounds__((RowGeom<T, N1>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))

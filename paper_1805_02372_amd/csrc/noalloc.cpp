@@ -168,6 +168,7 @@ extern "C" pa_status pa_hash_noalloc(pa_ctx* ctx, const uint64_t* seed, uint64_t
     fill_plan_stats(&st, plan);
     pa_status s = PA_OK;
     if (choose_direct(flags, n, m, cm, plan)) {
+        // (the product itself needs no scratch: the limit of this entry on direct keys)
         if (direct_key_words(n) * 4 > kWsBytes) return PA_ESCRATCH;
         st = pa_stats{};
         st.prec = PA_PREC_DIRECT;

@@ -152,7 +152,7 @@ void Ctx::serve_loop() {
                 int cls = 0;
                 uint64_t b;
                 if (request_direct(this, r->n, r->m)) {
-                    b = bmin = ((r->n + 127) / 128) * 16;   // its key
+                    b = bmin = ((r->n + 127) / 128) * 16;   // its key's bytes: a measure of its work
                 } else {
                     b = request_bytes(this, r->n, r->m, &bmin, &cls);
                 }
