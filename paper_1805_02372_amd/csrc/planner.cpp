@@ -376,16 +376,24 @@ static double shared_error(int prec, uint64_t L, uint64_t Bi) {
     return noise_error(prec, L, Bi);
 }
 
-// Chunks of one group: at most 64, in equal groups, and for FP32 no more than
-// keep the modeled error of the sum within the limit of groups.
-static uint64_t group_chunks(int prec, uint64_t L, uint64_t Bi, uint64_t nchunks) {
-    uint64_t most = 64;
-    if (prec == PREC_FP32) {
-        // the largest c with noise sqrt(c) + leak c within the limit
-        const double noise = noise_error(prec, L, Bi), leak = leak_error(prec, L, Bi);
-        const double r = 2 * kGroupErrorLimit / (noise + std::sqrt(noise * noise + 4 * leak * kGroupErrorLimit));
-        most = std::min<uint64_t>(most, (uint64_t)std::max(1.0, std::floor(r * r)));
-    }
+// Chunks of one group: at most kMaxGroup, in equal groups, and for FP32 no more
+// than keep the modeled error of the sum within the limit of groups.
+constexpr uint64_t kMaxGroup = 64;
+// The largest c with noise sqrt(c) + leak c within the limit.
+static uint64_t most_chunks(double noise, double leak) {
+    const double r = 2 * kGroupErrorLimit / (noise + std::sqrt(noise * noise + 4 * leak * kGroupErrorLimit));
+    return std::min<uint64_t>(kMaxGroup, (uint64_t)std::max(1.0, std::floor(r * r)));
+}
+// Chunks that make one group whatever their length: the noise at Bi = L, and each
+// |X_k| at most L / (2 pi k) (1% for the sines and the rounding).  kMaxGroup up to
+// 2^17, so that the scan of a class's windows seldom asks the model.
+static uint64_t any_chunks(int prec, uint64_t L) {
+    if (prec != PREC_FP32) return kMaxGroup;
+    return most_chunks(1.01 * noise_error(prec, L, L), 1.01 * 5.0 * unit_roundoff(prec) * (double)L * std::sqrt(2 * 1.0824) / (4 * M_PI * M_PI));
+}
+static uint64_t group_chunks(int prec, uint64_t L, uint64_t Bi, uint64_t nchunks, uint64_t any) {
+    if (nchunks <= any) return nchunks;
+    const uint64_t most = any < kMaxGroup ? most_chunks(noise_error(prec, L, Bi), leak_error(prec, L, Bi)) : kMaxGroup;
     return ceil_div(nchunks, ceil_div(nchunks, most));
 }
 
@@ -440,16 +448,25 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
         const double cap = std::floor((kPlanErrorLimit / per) * (kPlanErrorLimit / per) - (double)L);
         if (cap < (double)bi_cap) bi_cap = (uint64_t)std::max(0.0, cap);
     }
-    const double tile = cm.tile(prec, cls), chunk = class_sums(prec, cls) ? cm.chunk(prec, cls) : tile;
+    const bool sums = class_sums(prec, cls);
+    const uint64_t any = sums ? any_chunks(prec, L) : 1;
+    const double tile = cm.tile(prec, cls), chunk = sums ? cm.chunk(prec, cls) : tile;
     TilePlan best;
     bool found = false;
     const uint64_t max_outs = std::min<uint64_t>(ceil_div(m, 64), 1u << 14);
     uint64_t last_bo = 0;
     const uint64_t min_chunks = ceil_div(n, std::min<uint64_t>(L, bi_cap == 0 ? 1 : bi_cap));
     // fewer than ceil(m / L) windows cannot fit a window in L
+    const double per_tile = (tile + (double)(kMaxGroup - 1) * chunk) / (double)kMaxGroup;   // in the largest groups
     for (uint64_t w = std::max<uint64_t>(1, ceil_div(m, L)); w <= std::max<uint64_t>(1, max_outs); ++w) {
         // every later candidate has >= w windows of >= min_chunks chunks
         if (found && (double)w * (tile + (double)(min_chunks - 1) * chunk) >= 1.03 * best.cost) break;
+        // and >= w n / (L + 1 - m / w) tiles, which grows with w from w = 2 m / (L + 1)
+        // on, in >= w groups of at most kMaxGroup
+        const double room = (double)(L + 1) - (double)m / (double)w, tiles = (double)w * (double)n / room;
+        if (found && chunk <= tile && 2 * room >= (double)(L + 1) &&
+            (1 - 1e-9) * std::max((double)w * (tile - chunk) + tiles * chunk, tiles * per_tile) >= 1.03 * best.cost)
+            break;
         uint64_t Bo = (w == 1) ? m : round_up64(ceil_div(m, w));
         if (Bo == last_bo) continue;
         last_bo = Bo;
@@ -459,15 +476,22 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
         const uint64_t bi_max = std::min<uint64_t>(L - Bo + 1, bi_cap);
         if (bi_max == 0) continue;
         p.nchunks = ceil_div(n, bi_max);
-        p.Bi = ceil_div(n, p.nchunks);
         p.Bo = Bo;
-        p.cgroup = class_sums(prec, cls) ? group_chunks(prec, L, p.Bi, p.nchunks) : 1;
-        const double groups = (double)(ceil_div(p.nchunks, p.cgroup) * p.nouts);
-        p.cost = groups * tile + ((double)p.tiles() - groups) * chunk;
         // a tie within the noise of the measured costs goes to fewer tiles (less workspace)
-        if (!found || p.cost < (p.tiles() < best.tiles() ? 1.03 : 1.0) * best.cost) {
-            found = true;
-            best = p;
+        const double limit = found ? (p.tiles() < best.tiles() ? 1.03 : 1.0) * best.cost : HUGE_VAL;
+        auto cost = [&](uint64_t cgroup) {
+            const double groups = (double)(ceil_div(p.nchunks, cgroup) * p.nouts);
+            return groups * tile + ((double)p.tiles() - groups) * chunk;
+        };
+        // (the error model, the dearest step here, only where the largest groups would win)
+        if (!sums || chunk > tile || cost(kMaxGroup) < limit) {
+            p.Bi = ceil_div(n, p.nchunks);
+            p.cgroup = sums ? group_chunks(prec, L, p.Bi, p.nchunks, any) : 1;
+            p.cost = cost(p.cgroup);
+            if (p.cost < limit) {
+                found = true;
+                best = p;
+            }
         }
         if (best.nouts == 1 && best.nchunks == 1) break;
     }
