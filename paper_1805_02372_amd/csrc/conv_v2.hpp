@@ -6,8 +6,8 @@
 //  * pass 1, rows of 4096 and 8192: a small kernel transposes the key and seed bits
 //    into bit planes, and the columns are split into 3 to 8 parts whose first radix
 //    level is looked up from the bits; each wave transforms G columns of a part in
-//    registers.  Rows of 512: the bits are staged through LDS and each wave
-//    transforms G whole columns.  An LDS transpose turns the column-major results
+//    registers (FP32 2^20 and 2^21: G whole columns, with the bits as inputs).  Rows
+//    of 512: the bits are staged through LDS and each wave transforms G whole columns.  An LDS transpose turns the column-major results
 //    into C-element row segments for the stores.
 //  * pass 2: a row of 4096 points is a radix-8 stage across the 8 waves
 //    (decimation in frequency, registers only) followed by one 512-point transform
@@ -39,7 +39,7 @@ namespace pa {
 template <typename T, int N1> constexpr int column_target() { return (N1 >= 4096 ? 128 : 64) / (int)sizeof(cx<T>); }
 constexpr int column_waves(int target, int g) { return target <= g ? 1 : (target / g > 8 ? 8 : target / g); }
 
-// Rows of 512: a column is one transform.
+// Whole columns: a column is one transform.
 template <typename T, int N1, int N2> struct P1Geom {
     static constexpr int P = 1, M = N2, G = 1024 / M;      // columns per wave
     static constexpr int WAVES = column_waves(column_target<T, N1>(), G);
@@ -155,13 +155,15 @@ __device__ __forceinline__ TileBits tile_bits(const JobDesc& jd, const TileGeo& 
 // one word of each plane, a wave consecutive ones.
 // P = 4 or 8 leaves M = 64 .. 256, two radix stages for the wave (n2 = 4096, FP64
 // 2^24: P = 4 and M = 1024, three stages).
+// Whole columns (P = 1, M = N2, k2_pass1_whole): a lane's 16 points are 16 bits.
 constexpr int column_parts(int n2) { return odd_part(n2) > 1 ? odd_part(n2) : n2 == 2048 ? 8 : 4; }
-template <int N1, int N2> struct BitPlanes {
-    static constexpr int P = column_parts(N2), M = N2 / P, FW = P <= 4 ? 4 : 8;
+template <int N1, int N2, int P_ = column_parts(N2)> struct BitPlanes {
+    static constexpr int P = P_, M = N2 / P, FW = P == 1 ? 1 : P <= 4 ? 4 : 8;
     static constexpr int NJ = M / 16, BITS = 16 * FW;   // bits of a lane
-    struct alignas(BITS / 8) Word {
-        uint32_t w[BITS / 32];
+    struct alignas(BITS / 8) Wide {
+        uint32_t w[BITS < 32 ? 1 : BITS / 32];
     };
+    using Word = std::conditional_t<BITS == 16, uint16_t, Wide>;
     static constexpr size_t kColumn = (size_t)M * FW / 8, kPlane = kColumn * N1;
     // row of bit b of a column's plane bytes (N2 where the bit stands for none)
     __device__ static __forceinline__ uint32_t row(uint32_t b) {
@@ -254,9 +256,9 @@ __device__ __forceinline__ Bits64 transpose64(Bits64 x, int lane) {
 // instead of three per column group (calls: c3 125.7 -> 124.3 us, 128 Mbit 1.821 ->
 // 1.798 ms, eight stream blocks 1.546 -> 1.511 ms).
 constexpr int kBitsCols = 4;
-template <int N1, int N2>
+template <int N1, int N2, int P>
 __global__ void __launch_bounds__(256) k2_bits(JobTable jt, uint8_t* __restrict__ planes) {
-    using Pl = BitPlanes<N1, N2>;
+    using Pl = BitPlanes<N1, N2, P>;
     constexpr uint32_t L = (uint32_t)N1 * N2;
     constexpr int NRC = (int)Pl::kColumn / 8, NCC = N1 / 64 / kBitsCols;   // row and column blocks of a plane
     static_assert((2 * NRC * NCC) % 4 == 0 && N1 % (64 * kBitsCols) == 0, "blocks");
@@ -494,6 +496,55 @@ k2_pass1(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const
         v[i] = cx<T>{(T)(w & 1u), row < rows ? sign_value<T>(w << 15) : T(0)};
     }
     __syncthreads();  // the wave regions are free
+    column_transform<T, Gm>(v, S, roots, wv, grp, j);
+    column_store<T, Gm, N1>(v, S, tid, f, j, 0, ws + (size_t)lt * N1 * N2 + cb * C);
+    if (tid == 0) part[(size_t)lt * NCB + cb] = wsum;
+}
+
+// Column pass of FP32 2^20 and 2^21 (rows of 4096, columns of 256 and 512): whole
+// columns from the bit planes, a wave transforming G of them in registers.  The
+// transforms are short enough that the split below only adds to them: its lookups,
+// a product per point for the split's twiddles and as many workgroups again for each
+// part.  Against the split columns, per tile: 2^20 in launches of 128 tiles 3.4 ->
+// 2.3 us, one tile 18.3 -> 15.0; 2^21 of 64 tiles 6.6 -> 4.7, one 24.0 -> 21.2; 2^22, whose
+// columns of 1024 take three stages, 11.5 us split and 12.3 whole.
+template <typename T, int N1, int N2>
+__global__ void __launch_bounds__((P1Geom<T, N1, N2>::THREADS))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k2_pass1_whole(JobTable jt, cx<T>* __restrict__ ws, uint32_t* __restrict__ part, const cx<T>* __restrict__ stw,
+               const cx<double>* __restrict__ fa64, const cx<double>* __restrict__ fb64, int fshift) {
+    using Gm = P1Geom<T, N1, N2>;
+    using Pl = BitPlanes<N1, N2, 1>;
+    constexpr int C = Gm::C, G = Gm::G, M = Gm::M, NJ = M / 16;
+    constexpr int NCB = N1 / C;
+    __shared__ ColumnSmem<T, Gm> S;
+    __shared__ uint32_t wsum;
+
+    const uint32_t blk = xcd_block(), lt = blk / NCB, cb = blk % NCB;
+    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, grp = l / NJ, j = l % NJ, f = wv * G + grp;
+    const uint32_t t1 = cb * C + (uint32_t)f, t = jt.tile0 + lt;
+    const uint16_t* __restrict__ pw =
+        reinterpret_cast<const uint16_t*>(Pl::base(ws, jt.ntiles, lt)) + (size_t)t1 * NJ + j;
+    const uint32_t key = pw[0], seed = pw[Pl::kPlane / sizeof(uint16_t)];
+    const JobDesc jd = find_job(jt, t);
+    const TileGeo g = tile_geo(jd, t - jd.tile_begin);
+    clear_window(g, cb, NCB, tid, Gm::THREADS);
+    if (tid == 0) wsum = 0;
+    wfft_load_lds<T, M>(S.st, stw, tid, Gm::THREADS);
+    const ColumnRoots<NJ, 1> roots(t1, (uint32_t)j, 0, fa64, fb64, fshift);
+    // rows of the slice in this column; of this lane's rows j + NJ i the first `valid`
+    const uint32_t len = (uint32_t)(g.bi + g.bo - 1), rows = len > t1 ? (len - t1 + N1 - 1) / N1 : 0u;
+    const uint32_t valid = rows > (uint32_t)j ? (rows - (uint32_t)j + NJ - 1) / NJ : 0u;
+    cx<T> v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = cx<T>{(T)((key >> i) & 1u), sign_value<T>(seed << (31 - i))};
+    if (__any(valid < 16u)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if ((uint32_t)i >= valid) v[i].im = T(0);
+    }
+    __syncthreads();  // the stage tables and the zeroed sum are in place
+    atomicAdd(&wsum, (uint32_t)__popc(key));
     column_transform<T, Gm>(v, S, roots, wv, grp, j);
     column_store<T, Gm, N1>(v, S, tid, f, j, 0, ws + (size_t)lt * N1 * N2 + cb * C);
     if (tid == 0) part[(size_t)lt * NCB + cb] = wsum;
@@ -1471,9 +1522,9 @@ int launch_row_pass(const JobTable& jt, void* ws, uint32_t* part, TileMeta* meta
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <int N1, int N2> void launch_bits(const JobTable& jt, uint8_t* planes, void* stream) {
-    constexpr int waves = 2 * ((int)BitPlanes<N1, N2>::kColumn / 8) * (N1 / 64 / kBitsCols);   // of a tile
-    hipLaunchKernelGGL((k2_bits<N1, N2>), dim3(jt.ntiles * (waves / 4)), dim3(256), 0, (hipStream_t)stream, jt, planes);
+template <int N1, int N2, int P> void launch_bits(const JobTable& jt, uint8_t* planes, void* stream) {
+    constexpr int waves = 2 * ((int)BitPlanes<N1, N2, P>::kColumn / 8) * (N1 / 64 / kBitsCols);   // of a tile
+    hipLaunchKernelGGL((k2_bits<N1, N2, P>), dim3(jt.ntiles * (waves / 4)), dim3(256), 0, (hipStream_t)stream, jt, planes);
 }
 
 // Pass 1 of the rows of 4096 and 8192: the bit planes, then the split columns.
@@ -1481,7 +1532,7 @@ template <typename T, int N1, int N2, int NT, bool SHARED = false>
 int launch_split(const JobTable& jt, void* ws, uint32_t* part, const void* tw, const Tables& tb, void* stream) {
     using G = PSplitGeom<T, N1, N2>;
     uint8_t* planes = reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2));
-    launch_bits<N1, N2>(jt, planes, stream);
+    launch_bits<N1, N2, G::P>(jt, planes, stream);
     hipLaunchKernelGGL((k2_pass1_split<T, N1, N2, NT, SHARED>), dim3(jt.ntiles * (N1 / G::C) * G::P), dim3(G::THREADS), 0,
                        (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tw, (const cx<T>*)tb.stw,
                        (const cx<double>*)tb.fa64, (const cx<double>*)tb.fb64, tb.fshift);
@@ -1490,15 +1541,22 @@ int launch_split(const JobTable& jt, void* ws, uint32_t* part, const void* tw, c
 
 template <typename T, int N1, int N2>
 struct ClassImpl2 {
-    static constexpr bool kSplit = N1 >= 1024;
+    // bit planes; whole columns from them where the columns are short (k2_pass1_whole)
+    static constexpr bool kPlanes = N1 >= 1024, kWhole = sizeof(T) == 4 && N2 <= 512, kSplit = kPlanes && !kWhole;
     using G1 = std::conditional_t<kSplit, PSplitGeom<T, N1, kSplit ? N2 : 256>, P1Geom<T, N1, kSplit ? 256 : N2>>;
     using G3 = P3Geom<T, N1, N2>;
     static constexpr int C1 = G1::C, C3 = G3::C;
     // workspace bytes per tile beyond its points: the bit planes
-    static constexpr size_t kWsExtra = kSplit ? BitPlanes<N1, kSplit ? N2 : 256>::kTile : 0;
+    static constexpr size_t kWsExtra = kPlanes ? BitPlanes<N1, kPlanes ? N2 : 256>::kTile : 0;
     static int pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
         if constexpr (kSplit) {
             return launch_split<T, N1, N2, cmax<N1, N2>()>(jt, ws, part, tb.tw, tb, stream);
+        } else if constexpr (kPlanes) {
+            static_assert(BitPlanes<N1, N2, 1>::kTile == kWsExtra, "planes of either form");
+            launch_bits<N1, N2, 1>(jt, reinterpret_cast<uint8_t*>((cx<T>*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2)), stream);
+            hipLaunchKernelGGL((k2_pass1_whole<T, N1, N2>), dim3(jt.ntiles * (N1 / C1)), dim3(G1::THREADS), 0,
+                               (hipStream_t)stream, jt, (cx<T>*)ws, part, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
+                               (const cx<double>*)tb.fb64, tb.fshift);
         } else {
             hipLaunchKernelGGL((k2_pass1<T, N1, N2>), dim3(jt.ntiles * (N1 / C1)), dim3(G1::THREADS), 0, (hipStream_t)stream,
                                jt, (cx<T>*)ws, part, (const cx<T>*)tb.stw, (const cx<double>*)tb.fa64,
@@ -1518,6 +1576,7 @@ struct ClassImpl2 {
         return (uint8_t*)ws + (size_t)jt.ntiles * ((size_t)N1 * N2 * sizeof(cx<T>) + kWsExtra);
     }
     static int shared_pass1(const JobTable& jt, void* ws, uint32_t* part, TileMeta*, const Tables& tb, void* stream) {
+        static_assert(PSplitGeom<T, N1, N2>::C == C1, "partial weights of the packs");
         return launch_split<T, N1, N2, cmax<N1, N2>(), true>(jt, ws, part, tb.tw, tb, stream);
     }
     template <int NW>
