@@ -306,17 +306,19 @@ const char* pa_strerror(pa_status status);
  * 3, step 2: the planner picks block and batch sizes from measured costs) for
  * the precisions selected by flags (PA_PREC_AUTO: FP32 and FP64; otherwise the
  * one named), with `reps` timed runs each on synthetic bits, and use the
- * results in this context's planner.  Each class runs one launch with one tile
- * and one with 4 (16 up to 2^20 points): the marginal cost per tile and the rest of
- * the first go to the class, the median of the latter to the per-launch cost.
- * Classes that sum the products of several key chunks also run the jobs with a
- * second chunk each, for the cost of a further chunk.  With PA_PREC_AUTO
+ * results in this context's planner.  Each class runs launches of one tile, of 4 and
+ * of 4 to 256 (2^25 points): the marginal costs per tile of the few and of the many
+ * and the rest of the first go to the class, the median of the latter to the
+ * per-launch cost.  Classes that sum the products of several key chunks also run
+ * the many with a second chunk each, and one job of 8 and one of 24 chunks, for the
+ * costs of a further chunk.  With PA_PREC_AUTO
  * or PA_PREC_DIRECT it also times the direct GF(2) path at two output lengths
  * and takes the slope as its cost per output and key word (PA_PREC_DIRECT
  * times only that).  If path is not NULL the table is also written there as
  * JSON ({"launch": seconds, "direct": seconds, "fp32": {"4096": [tile, first],
- * ...}, "fp32_chunk": {"4096": seconds, ...}, ...}; a table without the chunk
- * sections loads too).  Synchronous; PA_EDEVICE on a HIP error, PA_EINVAL for
+ * ...}, "fp32_few": {"4096": seconds, ...}, and likewise "fp32_chunk",
+ * "fp32_chunk_alone" and "fp32_chunk_run", ...}; a table without these sections
+ * loads too).  Synchronous; PA_EDEVICE on a HIP error, PA_EINVAL for
  * a file that cannot be written. */
 pa_status pa_tune(pa_ctx* ctx, uint32_t flags, int reps, const char* path);
 

@@ -1173,7 +1173,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         for (uint64_t i = 0; i < count; ++i) {
             TilePlan p;
             if (!c->plan_cached(ns[i], ms[i], policy, &p)) return PA_EINVAL;
-            is_direct[i] = choose_direct_shared(flags, ns[i], ms[i], cm, p);
+            is_direct[i] = choose_direct_shared(flags, ns[i], ms[i], cm, p, count);
             if (!is_direct[i]) {
                 fidx.push_back(i);
                 fns.push_back(ns[i]);

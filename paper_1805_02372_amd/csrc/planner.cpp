@@ -217,7 +217,7 @@ CostModel::CostModel() {
     for (int p = 0; p < 3; ++p)
         for (int id = 0; id < 64; ++id) {
             const uint64_t Lc = class_len(id);
-            chunk_s[p][id] = 0;
+            chunk_s[p][id] = alone_s[p][id] = run_s[p][id] = few_s[p][id] = 0;
             if (Lc == 0) {
                 tile_s[p][id] = 1.0;
                 continue;
@@ -241,6 +241,27 @@ double CostModel::chunk(int prec, int cls) const {
     return c > 0 ? c : 0.7 * tile(prec, cls);
 }
 void CostModel::set_chunk(int prec, int cls, double s) { chunk_s[prec_index(prec)][cls] = s; }
+double CostModel::tile_of(int prec, int cls, uint64_t groups) const {
+    return std::max(tile(prec, cls), few_s[prec_index(prec)][cls] * 12.0 / (double)std::max<uint64_t>(groups, 12));
+}
+double CostModel::alone(int prec, int cls) const {
+    const double a = alone_s[prec_index(prec)][cls];
+    return a > 0 ? a : chunk(prec, cls);
+}
+double CostModel::run(int prec, int cls) const {
+    const double r = run_s[prec_index(prec)][cls];
+    return r > 0 ? r : alone(prec, cls);
+}
+double CostModel::chunk_of(int prec, int cls, uint64_t groups, uint64_t chunks, uint64_t tiles) const {
+    const double cached = 240e6, bytes = (double)tiles * (double)class_len(cls) * (prec == PREC_FP64 ? 16 : 8);
+    const double base = bytes > cached ? chunk(prec, cls) : least_chunk(prec, cls);
+    double a = alone(prec, cls);
+    if (chunks > 8) a = (7 * a + (double)(chunks - 8) * run(prec, cls)) / (double)(chunks - 1);
+    return base + std::max(a - base, 0.0) / (double)groups;
+}
+void CostModel::set_run(int prec, int cls, double s) { run_s[prec_index(prec)][cls] = s; }
+void CostModel::set_few(int prec, int cls, double s) { few_s[prec_index(prec)][cls] = s; }
+void CostModel::set_alone(int prec, int cls, double s) { alone_s[prec_index(prec)][cls] = s; }
 double CostModel::tile(int prec, int cls) const { return tile_s[prec_index(prec)][cls]; }
 double CostModel::first(int prec, int cls) const { return first_s[prec_index(prec)][cls]; }
 void CostModel::set(int prec, int cls, double s) { tile_s[prec_index(prec)][cls] = s; }
@@ -250,7 +271,9 @@ static const char* prec_key(int prec) { return prec == PREC_FP32 ? "fp32" : prec
 
 // Minimal reader of the table pa_tune writes:
 //   {"launch": s, "direct": s, "direct_launch": s,
-//    "fp32": {"<L>": [tile_s, first_s], ...}, "fp64": {...}, "fp32_chunk": {"<L>": chunk_s, ...}}
+//    "fp32": {"<L>": [tile_s, first_s], ...}, "fp64": {...}, "fp32_few": {"<L>": few_s, ...},
+//    "fp32_chunk": {"<L>": chunk_s, ...}, "fp32_chunk_alone": {"<L>": alone_s, ...},
+//    "fp32_chunk_run": {"<L>": run_s, ...}}
 // (a plain number instead of the pair sets tile_s only).
 int load_tune_table(CostModel& cm, const char* path) {
     FILE* f = fopen(path, "r");
@@ -280,9 +303,17 @@ int load_tune_table(CostModel& cm, const char* path) {
         if (v >= 0 && v < 1e-2) cm.direct_launch_s = v;
     }
     for (int prec : {PREC_FP32, PREC_FP64, PREC_NTT}) {
-        // "<prec>_chunk": {"<L>": chunk_s, ...} (absent in older tables)
-        const size_t ca = text.find(std::string("\"") + prec_key(prec) + "_chunk\"");
-        if (ca != std::string::npos) {
+        // "<prec>_few", "<prec>_chunk", "<prec>_chunk_alone", "<prec>_chunk_run":
+        // {"<L>": seconds, ...} (absent in older tables)
+        struct Section {
+            const char* kind;
+            void (CostModel::*set)(int, int, double);
+        };
+        for (const Section& sec : {Section{"_few", &CostModel::set_few}, Section{"_chunk", &CostModel::set_chunk},
+                                   Section{"_chunk_alone", &CostModel::set_alone},
+                                   Section{"_chunk_run", &CostModel::set_run}}) {
+            const size_t ca = text.find(std::string("\"") + prec_key(prec) + sec.kind + "\"");
+            if (ca == std::string::npos) continue;
             const size_t o = text.find('{', ca), e = text.find('}', ca);
             if (o == std::string::npos || e == std::string::npos || e < o) return -1;
             const std::string body = text.substr(o + 1, e - o - 1);
@@ -293,7 +324,7 @@ int load_tune_table(CostModel& cm, const char* path) {
                 const size_t p = body.find(key);
                 if (p == std::string::npos) continue;
                 const double v = strtod(body.c_str() + p + key.size(), nullptr);
-                if (v > 0 && v < 10.0) cm.set_chunk(prec, k, v);
+                if (v > 0 && v < 10.0) (cm.*sec.set)(prec, k, v);
             }
         }
         const std::string tag = std::string("\"") + prec_key(prec) + "\"";
@@ -354,11 +385,13 @@ bool choose_direct(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, 
     return p == PA_PREC_AUTO && direct_cost(n, m, cm) < fft.cost;
 }
 
-bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft) {
+bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft, uint64_t jobs) {
     const uint32_t p = flags & PA_PREC_MASK;
     if (p == PA_PREC_DIRECT) return true;
-    return p == PA_PREC_AUTO &&
-           2.5 * (direct_cost(n, m, cm) - 1.1 * cm.direct_launch_s) < fft.cost - cm.first(fft.prec, fft.cls);
+    if (p != PA_PREC_AUTO) return false;
+    TilePlan beside;
+    if (!plan_at_class(n, m, fft.prec, fft.cls, cm, &beside, 0, jobs)) beside = fft;
+    return kDirectShared * (direct_cost(n, m, cm) - 1.1 * cm.direct_launch_s) < beside.cost - cm.first(fft.prec, fft.cls);
 }
 
 // Classes whose row pass sums the products of several chunks: those with
@@ -422,22 +455,19 @@ static bool plan_shared(uint64_t n, uint64_t m, int prec, int cls, const CostMod
         if (p.cgroup <= 4) return false;   // little left to share
     }
     groups = ceil_div(p.nchunks, p.cgroup);
-    // up to four windows: a chunk's passes and the sums beside them (52 us per pack of
-    // 2^23, where a chunk takes 45).  More: per pack a chunk's passes and the spectrum
-    // written once and read once per eight windows; per window and group the rest of a
-    // tile and its sum, written and read
-    const double rate = 4.0e12, Ld = (double)p.L;
-    const double chunk = cm.chunk(prec, cls), rest = std::max(cm.tile(prec, cls) - chunk, 0.0);
-    const double packs = (double)(groups * p.packs(p.cgroup)), wins = (double)(groups * p.nouts);
-    if (p.nouts <= 4) p.cost = packs * 1.15 * chunk + wins * rest;
-    else p.cost = packs * (chunk + 8 * Ld * (1.0 + (double)ceil_div(p.nouts, 8)) / rate) + wins * (rest + 8 * Ld / rate);
+    // Measured per 1000 points (2^21 to 2^23; 6, 16 and 40 chunks, 2 to 16 windows): a
+    // pack takes 6.1 to 7.1 ns up to four windows, with more 8.0 to 8.7 ns up to eight
+    // and 9.6 to 10.6 up to sixteen (its spectrum is read once per eight), a
+    // window's inverse and columns 1.5 to 1.9 ns.
+    const double pack = p.nouts <= 4 ? 6.3e-12 : 6.6e-12 + 1.65e-12 * (double)ceil_div(p.nouts, 8);
+    p.cost = (double)p.L * (double)groups * ((double)p.packs(p.cgroup) * pack + (double)p.nouts * 1.9e-12);
     p.rigorous = rigorous_bound(prec, p.L, p.Bi, p.Bo, p.cgroup);
     *out = p;
     return true;
 }
 
 bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out,
-                   uint64_t shared_bytes) {
+                   uint64_t shared_bytes, uint64_t jobs) {
     ClassGeom g;
     if (n == 0 || m == 0 || !class_geometry(prec, cls, &g)) return false;
     const uint64_t L = g.L;
@@ -450,7 +480,7 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
     }
     const bool sums = class_sums(prec, cls);
     const uint64_t any = sums ? any_chunks(prec, L) : 1;
-    const double tile = cm.tile(prec, cls), chunk = sums ? cm.chunk(prec, cls) : tile;
+    const double tile = cm.tile(prec, cls), chunk = sums ? cm.least_chunk(prec, cls) : tile;
     TilePlan best;
     bool found = false;
     const uint64_t max_outs = std::min<uint64_t>(ceil_div(m, 64), 1u << 14);
@@ -479,15 +509,16 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
         p.Bo = Bo;
         // a tie within the noise of the measured costs goes to fewer tiles (less workspace)
         const double limit = found ? (p.tiles() < best.tiles() ? 1.03 : 1.0) * best.cost : HUGE_VAL;
-        auto cost = [&](uint64_t cgroup) {
-            const double groups = (double)(ceil_div(p.nchunks, cgroup) * p.nouts);
-            return groups * tile + ((double)p.tiles() - groups) * chunk;
-        };
+        auto groups_of = [&](uint64_t cgroup) { return ceil_div(p.nchunks, cgroup) * p.nouts; };
+        const double least = (double)groups_of(kMaxGroup) * tile + (double)(p.tiles() - groups_of(kMaxGroup)) * chunk;
         // (the error model, the dearest step here, only where the largest groups would win)
-        if (!sums || chunk > tile || cost(kMaxGroup) < limit) {
+        if (!sums || chunk > tile || least < limit) {
             p.Bi = ceil_div(n, p.nchunks);
             p.cgroup = sums ? group_chunks(prec, L, p.Bi, p.nchunks, any) : 1;
-            p.cost = cost(p.cgroup);
+            const uint64_t groups = groups_of(p.cgroup);
+            p.cost = (double)groups * cm.tile_of(prec, cls, groups * jobs);
+            if (p.cgroup > 1)
+                p.cost += (double)(p.tiles() - groups) * cm.chunk_of(prec, cls, groups * jobs, p.cgroup, p.tiles() * jobs);
             if (p.cost < limit) {
                 found = true;
                 best = p;
@@ -518,22 +549,22 @@ bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan*
     const int nid = class_ids(prec, ids, cap_logL);
     // Classes come in increasing length.  A plan that moves more points (tiles
     // x L) replaces the best so far only when its modeled cost is lower by
-    // more than the noise of the measured costs (10%), so near-ties keep the
+    // more than the noise of the measured costs (2%), so near-ties keep the
     // plan with fewer bytes.
     auto better = [](const TilePlan& p, const TilePlan& best) {
         const double pts = p.points(), bpts = best.points();
-        return pts <= bpts ? p.cost < best.cost : p.cost < 0.9 * best.cost;
+        return pts <= bpts ? p.cost < best.cost : p.cost < 0.98 * best.cost;
     };
     if (prec == PREC_FP64 || prec == PREC_NTT) {
         // one tile: the shortest class that holds the whole product, unless a
         // longer class is cheaper by more than the noise of a tile's measured time,
-        // which its cost is (3%; FP64 2^21 takes 71 us, 5 2^18 75 us)
+        // which its cost is (1%)
         bool one = false;
         TilePlan best1;
         for (int q = 0; q < nid; ++q) {
             TilePlan p;
             if (n + m - 1 > class_len(ids[q]) || !plan_at_class(n, m, prec, ids[q], cm, &p, shared_bytes)) continue;
-            if (!one || p.cost < (p.points() > best1.points() ? 0.97 : 1.0) * best1.cost) {
+            if (!one || p.cost < (p.points() > best1.points() ? 0.99 : 1.0) * best1.cost) {
                 best1 = p;
                 one = true;
             }
@@ -569,7 +600,7 @@ bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64
     auto at_class = [&](size_t i, int k, TilePlan* p) {
         if (k < 0 || k >= NK) return false;
         const size_t x = i * NK + (size_t)k;
-        if (!known[x]) known[x] = plan_at_class(ns[i], ms[i], policy, k, cm, &memo[x], shared_bytes) ? 1 : -1;
+        if (!known[x]) known[x] = plan_at_class(ns[i], ms[i], policy, k, cm, &memo[x], shared_bytes, ns.size()) ? 1 : -1;
         if (known[x] < 0) return false;
         *p = memo[x];
         return true;
@@ -579,6 +610,8 @@ bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64
         TilePlan p;
         if (own) p = (*own)[i];
         else if (!plan_job(ns[i], ms[i], policy, cm, &p)) return false;
+        TilePlan beside;   // among the other jobs' groups its further chunks may cost less
+        if (at_class(i, p.cls, &beside)) p = beside;
         BatchGroup& g = by_class[p.cls];
         g.cls = p.cls;
         g.jobs.push_back(i);
@@ -643,7 +676,7 @@ bool plan_batch(const std::vector<uint64_t>& ns, const std::vector<uint64_t>& ms
         double cost = cm.first(policy, k);
         bool ok = true;
         for (size_t i = 0; i < ns.size() && ok; ++i) {
-            ok = plan_at_class(ns[i], ms[i], policy, k, cm, &tmp[i], shared_bytes);
+            ok = plan_at_class(ns[i], ms[i], policy, k, cm, &tmp[i], shared_bytes, ns.size());
             if (ok) cost += tmp[i].cost - cm.first(policy, k);
         }
         if (!ok) continue;

@@ -2,6 +2,7 @@
 // rounding-error model that bounds them.  Pure host code.
 #pragma once
 #include <cstddef>
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -33,15 +34,30 @@ int class_ids(int prec, int* ids, int cap_logL = 24);
 uint64_t class_filter_key();
 
 // Cost of a class's launches (seconds), by prec and class id: a launch of G
-// groups with T tiles costs first_s + G tile_s + (T - G) chunk_s.  tile_s is the
-// marginal cost of a tile with its inverse on a full device, chunk_s that of a
-// further chunk whose product joins the same inverse; first_s the rest of a one-tile launch (launch latency, ramp-up,
-// and the part of the device one tile leaves idle).  Filled from tuning data
-// when present, else from the built-in model.
+// groups with T tiles costs first_s + G tile + (T - G) chunk.  tile is the cost of
+// a tile with its inverse, chunk that of a further chunk whose product joins the
+// same inverse; first_s the rest of a one-tile launch (launch latency, ramp-up, and
+// the part of the device one tile leaves idle).  Both have two measured ends:
+// tile_s and chunk_s on a full device, few_s per tile of four and alone_s per
+// further chunk, up to the eighth, of a launch's only group, whose chunks follow
+// one another through the row pass (run_s beyond the eighth).  In between, the few
+// groups of a launch share what they leave idle: max(tile_s, few_s) up to 12 groups
+// and max(tile_s, 12 few_s / G) beyond (FP32 2^19: a tile takes 5.5 us of 4, 4.0 of 16
+// and 3.3 of 64; 2^17 2.4, 1.7 and 0.9); of the further chunks of G groups one costs
+// alone_s and the others chunk_s each, or the least of the three where the tiles
+// stay in the last-level cache (256 MB; 2^15, 30 chunks: 0.7 us per chunk of one group, 0.84
+// per pair of two, 0.9 per four of four; 2^19: a further chunk takes 2.9 us up to the
+// eighth, 1.6 to 2.0 up to the sixtieth, and 2.8 with 64 groups).  With one cost each, measured with 16 tiles, batches of 64 and more
+// jobs of 0.8 to 1.4 Mbit took 2^19 where 2^20 and 2^21 are up to 1.9 times as fast, and
+// single keys took more chunks in a shorter class than paid, by up to 36%.  Filled
+// from tuning data when present, else from the built-in model.
 struct CostModel {
     double tile_s[3][64];   // [0] FP32, [1] FP64, [2] NTT; index class id
+    double few_s[3][64];    // (0: tile_s)
     double first_s[3][64];  // extra cost of a launch (its first tile)
-    double chunk_s[3][64];  // marginal cost of a further chunk of a group (0: 0.7 tile_s)
+    double chunk_s[3][64];  // (0: 0.7 tile_s)
+    double alone_s[3][64];  // (0: chunk_s)
+    double run_s[3][64];    // (0: alone_s)
     double launch_s;        // launch cost of a class without its own first_s
     double direct_s;        // direct GF(2) path: seconds per output per 32-bit key word
     double direct_launch_s; // direct GF(2) path: fixed cost of a job (its launches)
@@ -49,7 +65,16 @@ struct CostModel {
     double tile(int prec, int cls) const;
     double first(int prec, int cls) const;
     double chunk(int prec, int cls) const;
+    // in a launch of `groups` groups, of `chunks` chunks and `tiles` tiles altogether
+    double tile_of(int prec, int cls, uint64_t groups) const;
+    double chunk_of(int prec, int cls, uint64_t groups, uint64_t chunks, uint64_t tiles) const;
+    double alone(int prec, int cls) const;
+    double run(int prec, int cls) const;
+    double least_chunk(int prec, int cls) const { return std::min({alone(prec, cls), run(prec, cls), chunk(prec, cls)}); }
     void set_chunk(int prec, int cls, double s);
+    void set_few(int prec, int cls, double s);
+    void set_alone(int prec, int cls, double s);
+    void set_run(int prec, int cls, double s);
     void set(int prec, int cls, double s);
     void set_first(int prec, int cls, double s);
 };
@@ -118,15 +143,13 @@ double direct_cost(uint64_t n, uint64_t m, const CostModel& cm);
 // cheaper than the FFT plan `fft`.
 bool choose_direct(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft);
 
-// The same for a job of a batch or a serving launch, where both paths share
-// their launches with other jobs: the costs beyond the launches are compared.
-// The direct path has to be modeled 2.5 times as fast: its cost per output and
-// key word is that of long keys, and short ones take 1.7 to 2 times as long,
-// while a class's marginal tile cost is measured with 16 tiles per launch, and
-// larger launches fill the device better (256 jobs of 100,000 -> 50,000 bits:
-// 2.55 us per job direct, modeled 1.5, and 2.73 us on FP32 tiles, modeled 2.8;
-// 30,000 -> 10,000: 0.55 and 0.64).
-bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft);
+// The same for a job of a batch or a serving launch of about `jobs` jobs, where both
+// paths share their launches with other jobs: the costs beyond the launches are
+// compared, the FFT plan's in that company.  The direct path has to be modeled 1.1
+// times as fast: on 258 batches of 1 to 256 jobs of random sizes that choice took
+// 0.6 to 1.1% longer than the faster path, 1.3 to 2.4% at 1.3, and 4 to 6% at 2.5.
+constexpr double kDirectShared = 1.1;
+bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostModel& cm, const TilePlan& fft, uint64_t jobs);
 
 // Workspace that a shared-spectra plan may count on: what a serving lane of a
 // context with the default HBM budget has (a launch with less cuts the chunks
@@ -134,9 +157,10 @@ bool choose_direct_shared(uint32_t flags, uint64_t n, uint64_t m, const CostMode
 constexpr uint64_t kSharedBytes = (8ull << 30) / 3;
 
 // Best (Bi, Bo) for job (n, m) at a fixed class; false if impossible.
-// `shared_bytes`: workspace for shared spectra (0: none).
+// `shared_bytes`: workspace for shared spectra (0: none); `jobs`: about as many
+// share the launch.
 bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& cm, TilePlan* out,
-                   uint64_t shared_bytes = kSharedBytes);
+                   uint64_t shared_bytes = kSharedBytes, uint64_t jobs = 1);
 
 // Best plan over classes for one job.  policy: PREC_FP32 (segmented, bound
 // limited), PREC_FP64 and PREC_NTT (a single tile if one fits, else the

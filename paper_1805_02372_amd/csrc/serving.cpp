@@ -74,7 +74,8 @@ static uint64_t request_bytes(Ctx* c, uint64_t n, uint64_t m, uint64_t* min_byte
     return p.shared ? (p.packs(p.cgroup) + p.nouts) * *min_bytes : p.tiles() * *min_bytes;
 }
 
-// Whether AUTO puts request (n, m) on the direct GF(2) path (short outputs).
+// Whether AUTO puts request (n, m) on the direct GF(2) path (short outputs), among
+// as many requests as a burst of small ones brings to a launch.
 static bool request_direct(Ctx* c, uint64_t n, uint64_t m) {
     TilePlan p;
     if (!c->plan_cached(n, m, PREC_FP32, &p)) return false;
@@ -83,7 +84,7 @@ static bool request_direct(Ctx* c, uint64_t n, uint64_t m) {
         std::lock_guard<std::mutex> pl(c->plan_mu);
         cm = c->cost;
     }
-    return choose_direct_shared(PA_PREC_AUTO, n, m, cm, p);
+    return choose_direct_shared(PA_PREC_AUTO, n, m, cm, p, 64);
 }
 
 void Ctx::serve_loop() {
@@ -219,7 +220,7 @@ void Ctx::serve_loop() {
             std::vector<TilePlan> plans(batch.size());
             pa_status s = PA_OK;
             for (size_t k = 0; k < batch.size() && s == PA_OK; ++k)
-                if (!plan_at_class(ns[k], ms[k], PREC_FP32, cls, cm, &plans[k], budget / 3)) s = PA_EINVAL;
+                if (!plan_at_class(ns[k], ms[k], PREC_FP32, cls, cm, &plans[k], budget / 3, batch.size())) s = PA_EINVAL;
             while (s == PA_OK) {
                 std::vector<JobDesc> jobs(batch.size());
                 for (size_t k = 0; k < batch.size(); ++k)

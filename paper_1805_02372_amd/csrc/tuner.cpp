@@ -43,20 +43,29 @@ static pa_status save_json(const CostModel& cm, const std::vector<int>& precs, c
             first = false;
         }
         fprintf(f, "}");
-        if (precs[i] == PREC_NTT) continue;
-        fprintf(f, ", \"%s_chunk\": {", prec_key(precs[i]));
-        first = true;
-        for (int k = kMinClassId; k <= kMaxClassId; ++k) {
-            ClassGeom g;
-            if (!class_geometry(precs[i], k, &g)) continue;
-            fprintf(f, "%s\"%llu\": %.9g", first ? "" : ", ", (unsigned long long)g.L, cm.chunk(precs[i], k));
-            first = false;
+        for (const char* kind : {"few", "chunk", "chunk_alone", "chunk_run"}) {
+            if (precs[i] == PREC_NTT && strcmp(kind, "few")) continue;
+            fprintf(f, ", \"%s_%s\": {", prec_key(precs[i]), kind);
+            first = true;
+            for (int k = kMinClassId; k <= kMaxClassId; ++k) {
+                ClassGeom g;
+                if (!class_geometry(precs[i], k, &g)) continue;
+                fprintf(f, "%s\"%llu\": %.9g", first ? "" : ", ", (unsigned long long)g.L,
+                        !strcmp(kind, "few")           ? cm.tile_of(precs[i], k, 1)
+                        : !strcmp(kind, "chunk")       ? cm.chunk(precs[i], k)
+                        : !strcmp(kind, "chunk_alone") ? cm.alone(precs[i], k)
+                                                       : cm.run(precs[i], k));
+                first = false;
+            }
+            fprintf(f, "}");
         }
-        fprintf(f, "}");
     }
     fprintf(f, "}\n");
     return fclose(f) == 0 ? PA_OK : PA_EINVAL;
 }
+
+// Bits that the tiles of one job hold, at most: eight of 2^24 points.
+constexpr uint64_t kTuneBits = 8ull << 24;
 
 // Kernel time (s) of one launch of `count` identical jobs of class id k, with n
 // key bits and half a tile of outputs each.
@@ -78,12 +87,26 @@ static pa_status time_launch(Ctx* c, int prec, int k, const TilePlan& p, uint64_
     return PA_OK;
 }
 
-// Per class: kernel time of one launch with 1 tile (T1) and with N tiles (TN, N =
-// 4, or 16 up to 2^20 points, where 4 tiles still leave the device idle); the
-// marginal tile cost (TN - T1) / (N - 1) goes to the class's tile_s, the rest of
-// T1 (ramp-up and tail of the launch, and what one tile leaves of the device
-// idle) to its first_s; the median of the latter is the launch cost of the
-// direct path.
+// The same of one job whose `chunks` chunks make one group (1e30: none at this class).
+static pa_status time_group(Ctx* c, int prec, int k, const CostModel& cm, uint64_t chunks, uint64_t* dseed, uint64_t* dkey,
+                            uint64_t* douts, uint64_t out_words, int reps, double* best) {
+    const uint64_t L = class_len(k);
+    TilePlan p;
+    *best = 1e30;
+    if (chunks * L > kTuneBits || !plan_at_class(chunks * L / 2, L / 2 + 1, prec, k, cm, &p, 0) || p.nchunks != chunks ||
+        p.nouts != 1 || p.cgroup != chunks)
+        return PA_OK;
+    return time_launch(c, prec, k, p, chunks * L / 2, 1, dseed, dkey, douts, out_words, reps, best);
+}
+
+// Per class: kernel time of one launch with 1 tile (T1), with 4 (T4) and with N
+// tiles (TN), N as many as make 2^25 points, 4 to 256.  The marginal cost of a tile
+// on a full device, (TN - T1) / (N - 1), goes to the class's tile_s, that of the
+// first few, (T4 - T1) / 3, to its few_s, and the rest of T1 (ramp-up and tail of
+// the launch, and what one tile leaves of the device idle) to its first_s; the
+// median of the latter is the launch cost of the direct path.  With 16 tiles for N,
+// up to 2^20 points, and 4 above, tile_s came out up to twice as large (FP32 2^15: 0.45
+// us, 0.24 per tile in a batch of 256 jobs).
 pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
     std::vector<int> precs;
     switch (flags & PA_PREC_MASK) {
@@ -95,15 +118,15 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
         default: return PA_EINVAL;
     }
     if (reps < 1) reps = 1;
-    constexpr int kMany = 4;   // tiles of the longer launch from 2^20 points on
+    constexpr int kFew = 4;
     const uint64_t maxL = 1ull << 24;
     // synthetic job: n = L/2, m = L/2 + 1 fills one tile of class L exactly
-    const uint64_t words = (maxL + maxL / 2 + 64) / 64 + 2, out_words = maxL / 2 / 64 + 2;
+    const uint64_t words = (kTuneBits / 2 + maxL / 2 + 64) / 64 + 2, out_words = maxL / 2 / 64 + 2;
     std::vector<uint64_t> host(2 * words);
     uint64_t s = 0x9E3779B97F4A7C15ull;
     for (uint64_t& w : host) w = xorshift(s);
     DevBuf buf;
-    pa_status st = buf.ensure(c, (2 * words + kMany * out_words) * 8);
+    pa_status st = buf.ensure(c, (2 * words + kFew * out_words) * 8);
     if (st != PA_OK) return st;
     uint64_t* dseed = (uint64_t*)buf.ptr;
     uint64_t* dkey = dseed + words;
@@ -126,18 +149,21 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
             const uint64_t L = class_len(k);
             TilePlan p;
             if (!plan_at_class(L / 2, L / 2 + 1, prec, k, cm, &p) || p.tiles() != 1) continue;
-            double t1 = 0, tn = 0;
-            const int many = L <= (1ull << 20) ? 4 * kMany : kMany;
-            const uint64_t stride = L / 2 / 64 + 2;   // many * stride <= kMany * out_words
+            double t1 = 0, t4 = 0, tn = 0;
+            const int many = (int)std::min<uint64_t>(std::max<uint64_t>((1ull << 25) / L, kFew), 256);
+            const uint64_t stride = L / 2 / 64 + 2;   // many * stride <= kFew * out_words
             st = time_launch(c, prec, k, p, L / 2, 1, dseed, dkey, douts, stride, reps, &t1);
-            if (st == PA_OK) st = time_launch(c, prec, k, p, L / 2, many, dseed, dkey, douts, stride, reps, &tn);
+            if (st == PA_OK) st = time_launch(c, prec, k, p, L / 2, kFew, dseed, dkey, douts, stride, reps, &t4);
+            tn = t4;
+            if (st == PA_OK && many > kFew) st = time_launch(c, prec, k, p, L / 2, many, dseed, dkey, douts, stride, reps, &tn);
             if (st != PA_OK) {
                 buf.release(c);
                 return st;
             }
-            if (t1 >= 1e30 || tn >= 1e30) continue;
-            const double marginal = std::max((tn - t1) / (many - 1), 0.01 * t1);
+            if (t1 >= 1e30 || t4 >= 1e30 || tn >= 1e30) continue;
+            const double marginal = std::max((tn - t1) / (many - 1), 0.002 * t1);
             cm.set(prec, k, marginal);
+            cm.set_few(prec, k, std::max((t4 - t1) / (kFew - 1), 0.0));
             // the same jobs with a second chunk summed into each inverse
             TilePlan p2;
             double t2 = 1e30;
@@ -149,7 +175,25 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
                 }
                 if (t2 < 1e30) cm.set_chunk(prec, k, std::min(marginal, std::max((t2 - tn) / many, 0.2 * marginal)));
             }
-            cm.set_first(prec, k, std::max(t1 - marginal, 0.0));
+            cm.set_alone(prec, k, 0);
+            cm.set_run(prec, k, 0);
+            // and one job with as many chunks summed as its group takes, up to eight,
+            // and with 24
+            double ta = 1e30, tr = 1e30;
+            for (uint64_t chunks : {8, 4, 2}) {
+                st = time_group(c, prec, k, cm, chunks, dseed, dkey, douts, stride, reps, &ta);
+                if (st == PA_OK && ta < 1e30 && chunks == 8)
+                    st = time_group(c, prec, k, cm, 24, dseed, dkey, douts, stride, reps, &tr);
+                if (st != PA_OK) {
+                    buf.release(c);
+                    return st;
+                }
+                if (ta >= 1e30) continue;
+                cm.set_alone(prec, k, std::max((ta - t1) / (double)(chunks - 1), 0.0));
+                if (tr < 1e30) cm.set_run(prec, k, std::max((tr - ta) / 16, 0.1 * marginal));
+                break;
+            }
+            cm.set_first(prec, k, std::max(t1 - cm.tile_of(prec, k, 1), 0.0));
             fixed.push_back(std::max(t1 - marginal, 0.0));
         }
     }

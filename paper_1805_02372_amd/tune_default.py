@@ -3,8 +3,8 @@
 Usage (on an MI355X): python -m paper_1805_02372_amd.tune_default [out.json]
 
 Runs pa_tune for FP32, FP64 and the direct path (PA_PREC_AUTO) and for the
-NTT, each class timed with one-tile and four-tile launches, and writes one
-table in pa_tune's format.  Contexts load it as their starting cost model
+NTT, each class timed in launches of one tile, of four and of as many as fill the
+device, 40 times each, and writes one table in pa_tune's format.  Contexts load it as their starting cost model
 (tune_mi355x.json next to libpa.so); pa_tune or PA_TUNE_CACHE replace it.
 """
 from __future__ import annotations
@@ -18,7 +18,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_OUT = os.path.join(HERE, "tune_mi355x.json")
 
 
-def main(out: str = DEFAULT_OUT, reps: int = 5) -> dict:
+def main(out: str = DEFAULT_OUT, reps: int = 40) -> dict:
     from paper_1805_02372_amd import pa
     os.environ["PA_TUNE_DEFAULT"] = "0"   # measure from the built-in model, not the table being replaced
     merged: dict = {}

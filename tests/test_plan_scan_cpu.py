@@ -17,7 +17,25 @@ def _up(a, b):
     return -(-a // b)
 
 
-def _scan(n, m, L, tile, chunk, sums):
+def _costs(table, key, L, sums):
+    """The tile and chunk costs of a launch of G groups, from the table beside the
+    library: (tile of G groups, further chunk of G groups of c chunks and T tiles)."""
+    get = lambda name, default: table.get(key + name, {}).get(str(L), default)
+    tile = table[key][str(L)][0]
+    few, chunk = get("_few", 0.0), get("_chunk", 0.7 * tile)
+    alone = get("_chunk_alone", chunk)
+    run = get("_chunk_run", alone)
+
+    def of(groups, c, tiles):
+        cached = tiles * L * (16 if key == "fp64" else 8) <= 240e6
+        chain = (7 * alone + (c - 8) * run) / (c - 1) if c > 8 else alone
+        base = min(alone, run, chunk) if cached else chunk
+        further = base + max(chain - base, 0.0) / groups
+        return max(tile, 12 * few / max(groups, 12)), further if sums and c > 1 else 0.0
+    return of
+
+
+def _scan(n, m, L, of, sums):
     """(chunks, windows, window bits) by the planner's rule, every number of windows
     tried: cheaper, or fewer tiles within 3%."""
     best = None
@@ -28,7 +46,8 @@ def _scan(n, m, L, tile, chunk, sums):
         outs, chunks = _up(m, bo), _up(n, min(L - bo + 1, n))
         group = _up(chunks, _up(chunks, 64)) if sums else 1
         groups = _up(chunks, group) * outs
-        cost = groups * tile + (chunks * outs - groups) * chunk
+        tile, further = of(groups, group, chunks * outs)
+        cost = groups * tile + (chunks * outs - groups) * further
         if best is None or cost < (1.03 if chunks * outs < best[0] * best[1] else 1.0) * best[3]:
             best = (chunks, outs, bo, cost)
         if best[:2] == (1, 1):
@@ -48,15 +67,14 @@ def test_scan_finds_the_plan_of_a_full_scan(pa, prec, key, L, monkeypatch):
     sums = key != "ntt" and L >= (1 << 15 if L & (L - 1) == 0 else 1 << 20)
     if str(L) not in table[key]:
         pytest.skip("class not in the table")
-    tile = table[key][str(L)][0]
-    chunk = table[key + "_chunk"][str(L)] if sums else tile
+    of = _costs(table, key, L, sums)
     for n, m in [(L // 2, L // 2 + 1), (L // 2, L // 2 + 2), (3 * L + 5, 1), (40 * L, 63), (3 * L, 2 * L + 77), (L, L),
                  (17 * L // 3, 9 * L // 2), (70 * L - 9, L // 3), (130 * L, 3 * L), (100, 9 * L), (1, 1), (2 * L, L - 64)]:
         p = pa.pa_plan_query(n, m, getattr(pa, prec))
         assert p["fft_len"] == L
         if key == "fp32" and p["windows"] >= 2 and p["chunk_bits"] == p["window_bits"] == L // 2:
             continue   # shared spectra
-        assert (p["chunks"], p["windows"], p["window_bits"]) == _scan(n, m, L, tile, chunk, sums), (n, m, p)
+        assert (p["chunks"], p["windows"], p["window_bits"]) == _scan(n, m, L, of, sums), (n, m, p)
 
 
 def test_summed_classes_plan_as_fast(pa):
