@@ -618,8 +618,51 @@ bool plan_batch_groups(const std::vector<uint64_t>& ns, const std::vector<uint64
         g.plans.push_back(p);
         g.cost += p.cost - cm.first(policy, p.cls);
     }
-    std::vector<BatchGroup> gs;
+    // A job's own class is the cheapest for a launch of its own, in which the fixed
+    // cost of a launch and a device partly idle count for much.  The jobs of a group go
+    // together to another class where that is cheaper by more than the noise of the
+    // costs (3%); a few of them choose it.
+    int ids[kMaxClassId + 1];
+    const int nid = class_ids(policy, ids);
+    std::map<int, BatchGroup> merged;
     for (auto& kv : by_class) {
+        BatchGroup& g = kv.second;
+        const double first = cm.first(policy, g.cls);
+        const size_t step = (g.jobs.size() + 3) / 4;
+        double least = HUGE_VAL;
+        int to = g.cls;
+        for (int q = 0; q < nid && g.jobs.size() > 1; ++q) {
+            double c = 0;
+            size_t sampled = 0;
+            for (size_t j = 0; j < g.jobs.size() && c < HUGE_VAL; j += step, ++sampled) {
+                TilePlan p;
+                c += at_class(g.jobs[j], ids[q], &p) ? p.cost - cm.first(policy, ids[q]) : HUGE_VAL;
+            }
+            c = c * (double)g.jobs.size() / (double)sampled + cm.first(policy, ids[q]);
+            if (c < least) {
+                least = c;
+                to = ids[q];
+            }
+        }
+        BatchGroup moved;
+        moved.cls = to;
+        for (size_t j = 0; j < g.jobs.size() && to != g.cls; ++j) {
+            TilePlan p;
+            moved.cost += at_class(g.jobs[j], to, &p) ? p.cost - cm.first(policy, to) : HUGE_VAL;
+            moved.plans.push_back(p);
+        }
+        if (to != g.cls && moved.cost + cm.first(policy, to) < 0.97 * (g.cost + first)) {
+            moved.jobs = std::move(g.jobs);
+            g = std::move(moved);
+        }
+        BatchGroup& m = merged[g.cls];
+        m.cls = g.cls;
+        m.cost += g.cost;
+        m.jobs.insert(m.jobs.end(), g.jobs.begin(), g.jobs.end());
+        m.plans.insert(m.plans.end(), g.plans.begin(), g.plans.end());
+    }
+    std::vector<BatchGroup> gs;
+    for (auto& kv : merged) {
         kv.second.cost += cm.first(policy, kv.second.cls);
         gs.push_back(std::move(kv.second));
     }

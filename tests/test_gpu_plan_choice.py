@@ -73,3 +73,14 @@ def test_single_keys(pa, n, m, monkeypatch):
     planned, length, beside = _choice(pa, 1, n, m, pa.PA_PREC_FP32_SEG, monkeypatch)
     print(f"n={n} m={m} planned {length}: {planned:.1f} us, fastest {min(beside)}", flush=True)
     assert planned <= 1.16 * min(beside)[0] + 2.0, (planned, length, sorted(beside)[:4])
+
+
+# batches of equal jobs: what is cheapest for one of them is not for all together
+@pytest.mark.parametrize("jobs,n,m,prec", [(64, 1_221_990, 640_930, "fp32"), (128, 919_382, 541_430, "fp32"),
+                                           (64, 777_751, 765_368, "fp32"), (256, 856_335, 537_706, "fp32"),
+                                           (64, 296_412, 16_745, "fp64"), (256, 310_750, 36_624, "fp64")])
+def test_batches(pa, jobs, n, m, prec, monkeypatch):
+    flags = pa.PA_PREC_FP32_SEG if prec == "fp32" else pa.PA_PREC_FP64
+    planned, length, beside = _choice(pa, jobs, n, m, flags, monkeypatch)
+    print(f"{jobs} x n={n} m={m} planned {length}: {planned:.1f} us, fastest {min(beside)}", flush=True)
+    assert planned <= 1.2 * min(beside)[0] + 2.0, (planned, length, sorted(beside)[:4])
