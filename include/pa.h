@@ -310,7 +310,7 @@ const char* pa_strerror(pa_status status);
  * of 4 to 256 (2^25 points): the marginal costs per tile of the few and of the many
  * and the rest of the first go to the class, the median of the latter to the
  * per-launch cost.  Classes that sum the products of several key chunks also run
- * the many with a second chunk each, and one job of 8 and one of 24 chunks, for the
+ * the many with four chunks each, and one job of 8 and one of 24 chunks, for the
  * costs of a further chunk.  With PA_PREC_AUTO
  * or PA_PREC_DIRECT it also times the direct GF(2) path at two output lengths
  * and takes the slope as its cost per output and key word (PA_PREC_DIRECT

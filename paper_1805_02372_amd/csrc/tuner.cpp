@@ -164,16 +164,21 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
             const double marginal = std::max((tn - t1) / (many - 1), 0.002 * t1);
             cm.set(prec, k, marginal);
             cm.set_few(prec, k, std::max((t4 - t1) / (kFew - 1), 0.0));
-            // the same jobs with a second chunk summed into each inverse
-            TilePlan p2;
-            double t2 = 1e30;
-            if (plan_at_class(L, L / 2 + 1, prec, k, cm, &p2) && p2.nchunks == 2 && p2.nouts == 1 && p2.cgroup == 2) {
-                st = time_launch(c, prec, k, p2, L, many, dseed, dkey, douts, stride, reps, &t2);
+            // the same jobs with more chunks summed into each inverse
+            for (uint64_t chunks : {4, 2}) {
+                TilePlan p2;
+                double t2 = 1e30;
+                if (chunks * L > kTuneBits || !plan_at_class(chunks * L / 2, L / 2 + 1, prec, k, cm, &p2, 0) ||
+                    p2.nchunks != chunks || p2.nouts != 1 || p2.cgroup != chunks)
+                    continue;
+                st = time_launch(c, prec, k, p2, chunks * L / 2, many, dseed, dkey, douts, stride, reps, &t2);
                 if (st != PA_OK) {
                     buf.release(c);
                     return st;
                 }
-                if (t2 < 1e30) cm.set_chunk(prec, k, std::min(marginal, std::max((t2 - tn) / many, 0.2 * marginal)));
+                if (t2 >= 1e30) continue;
+                cm.set_chunk(prec, k, std::min(marginal, std::max((t2 - tn) / (many * (double)(chunks - 1)), 0.2 * marginal)));
+                break;
             }
             cm.set_alone(prec, k, 0);
             cm.set_run(prec, k, 0);
