@@ -471,13 +471,18 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     prec = prec_;
     cls = cls_;
     const ClassCfg& cfg = K->cfg;
-    uint32_t total = 0;
+    uint32_t total = 0, all = 0;
     for (JobDesc& jd : js) {
         if (jd.shared && (!K->shared_bytes || prec != PREC_FP32)) jd.shared = 0;
         if (!jd.shared) total += jd.nchunks * jd.nouts;
+        all += jd.nchunks * jd.nouts;
     }
     Tables tb;
     pa_status st = lane_tables(c, *this, prec, cls, &tb);
+    if (st != PA_OK) return st;
+    // certificates of at most as many groups as tiles: before the workspace, which
+    // takes what the budget leaves
+    st = meta.ensure(c, (size_t)all * sizeof(TileMeta), stream);
     if (st != PA_OK) return st;
 
     if (js.size() > 1) {  // descriptors first: they are small but must fit
@@ -573,8 +578,6 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
         }
     }
     if (cur.ntiles) spans.push_back(cur);
-    st = meta.ensure(c, (size_t)groups * sizeof(TileMeta), stream);
-    if (st != PA_OK) return st;
 
     JobTable jt{};
     if (js.size() == 1) {

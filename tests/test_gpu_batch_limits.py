@@ -151,3 +151,29 @@ def test_fallback_budget_below_one_fp64_tile(pa, call):
         assert pa.pa_hash(c, s, n, m, k, o, pa.PA_PREC_FP32_SEG | pa.PA_NO_FALLBACK) == pa.PA_EPRECISION
     finally:
         pa.pa_destroy(c)
+
+
+def _job(pa, rng, n, m):
+    from gpu_util import to_dev, empty_dev
+    p = synth.random_problem(rng, n, m)
+    return to_dev(p.seed), to_dev(p.key), empty_dev(synth.words_for(m)), n, m
+
+
+def test_certificates_fit_beside_a_full_workspace(pa, monkeypatch):
+    """A batch whose tiles fill the budget to the last few kilobytes: the workspace
+    leaves room for their certificates."""
+    import torch
+    from gpu_util import from_dev
+    rng = np.random.default_rng(27)
+    c = pa.pa_create(0, 24 << 20, None)
+    try:
+        monkeypatch.setenv("PA_ONLY_LEN", str(1 << 12))
+        batch = [_job(pa, rng, 60_000, 5_000) for _ in range(100)]
+        print("100 jobs of tiles of 2^12", flush=True)
+        st, _ = pa.pa_hash_batch(c, batch, pa.PA_PREC_FP32_SEG)
+        torch.cuda.synchronize()
+        assert st == pa.PA_OK and pa.pa_last_stats(c)["tiles"] * (8 << 12) > 24 << 20, pa.pa_strerror(st)
+        for s, k, o, n, m in batch[:2] + batch[-2:]:
+            assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m))
+    finally:
+        pa.pa_destroy(c)
