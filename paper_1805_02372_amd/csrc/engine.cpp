@@ -464,8 +464,47 @@ static pa_status run_shared(const ClassKernels* K, const JobDesc& jd, Lane* ln, 
     return PA_OK;
 }
 
+bool Ctx::give_back(const Lane* keep) {
+    bool freed = false;
+    auto give = [&](Lane& ln) {
+        if (&ln == keep || ln.in_flight || !(ln.ws.ptr || ln.part.ptr)) return;
+        ln.ws.release(this);
+        ln.part.release(this);
+        freed = true;
+    };
+    give(main);
+    for (Lane& ln : side) give(ln);
+    return freed;
+}
+
+// A launch whose tables, descriptors or workspace do not fit the budget: once more
+// without the workspaces that the context's idle lanes and this one keep from
+// earlier calls.
 pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bool timing, bool fetch_meta,
                        pa_stats* stats) {
+    const std::vector<JobDesc> asked = js;
+    const pa_stats before = *stats;
+    pa_status st = launch_once(c, prec_, cls_, js, timing, fetch_meta, stats);
+    if (st == PA_ENOMEM && !ws.fixed) {
+        (void)hipStreamSynchronize(stream);   // what was enqueued reads the lane's buffers
+        bool freed = shares && c->give_back(this);
+        if (ws.ptr || part.ptr) {
+            ws.release(c);
+            part.release(c);
+            freed = true;
+        }
+        if (freed) {
+            js = asked;
+            *stats = before;
+            st = launch_once(c, prec_, cls_, js, timing, fetch_meta, stats);
+        }
+    }
+    if (st == PA_OK) in_flight = true;
+    return st;
+}
+
+pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bool timing, bool fetch_meta,
+                            pa_stats* stats) {
     const ClassKernels* K = class_kernels(prec_, cls_);
     if (!K || js.empty()) return PA_EINVAL;
     prec = prec_;
@@ -500,10 +539,17 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
     if (ws.fixed) {
         avail = ws.bytes;
     } else {
-        const uint64_t u = c->used.load();
-        const uint64_t mine = ws.bytes + part.bytes;
-        avail = c->budget > u ? c->budget - u + mine : mine;
-        if (cap) avail = std::min<uint64_t>(avail, cap);
+        auto left = [&] {
+            const uint64_t u = c->used.load(), mine = ws.bytes + part.bytes, a = c->budget > u ? c->budget - u + mine : mine;
+            return cap ? std::min<uint64_t>(a, cap) : a;
+        };
+        avail = left();
+        uint64_t want = total * (uint64_t)(tile_bytes + part_bytes);
+        for (const JobDesc& jd : js)
+            if (jd.shared)
+                want = std::max<uint64_t>(want, K->shared_bytes(shared_packs(jd, jd.cgroup), jd.nouts) +
+                                                    shared_packs(jd, jd.cgroup) * part_bytes);
+        if (want > avail && shares && c->give_back(this)) avail = left();
     }
     // a job with shared spectra: chunk groups as large as fit (those that the
     // plan asks for, if possible); too little space for a few chunks: plain tiles
@@ -678,6 +724,7 @@ hipError_t Lane::wait() {
 
 pa_status Lane::finish(Ctx* c, uint32_t flags, pa_stats* stats, std::vector<pa_status>* per_job) {
     if (wait() != hipSuccess) return PA_EDEVICE;
+    in_flight = false;
     if (flags & PA_TIMING) timer.collect(stats->ms_pass);
     const uint32_t total = total_groups;
     const TileMeta* mt = (const TileMeta*)meta_host.ptr;
@@ -977,6 +1024,7 @@ pa_status pa_create(pa_ctx** out, int device, uint64_t budget, void* hip_stream)
     (void)hipGetLastError();
     c->budget = budget ? budget : (8ull << 30);
     c->cost = default_cost_model();
+    c->main.shares = true;
     if (hip_stream) {
         c->main.stream = (hipStream_t)hip_stream;
         c->main.own_stream = false;
@@ -1115,6 +1163,7 @@ pa_status ensure_side_lanes(Ctx* c) {
             return PA_EDEVICE;
         }
         ln.own_stream = true;
+        ln.shares = true;
     }
     return PA_OK;
 }
@@ -1276,7 +1325,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
             if (on_lane[k] >= 0) continue;
             BatchGroup& g = groups[queue.front()];
             pa_status ls;
-            for (bool freed = false;; freed = true) {
+            for (;;) {
                 std::vector<JobDesc> jobs(g.jobs.size());
                 for (size_t q = 0; q < g.jobs.size(); ++q) {
                     const JobDesc& a = all[g.jobs[q]];
@@ -1286,23 +1335,14 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
                 ls = lanes[k]->launch(c, g.plans[0].prec, g.cls, jobs, flags & PA_TIMING, true, &lst[k]);
                 if (ls != PA_ENOMEM) break;
                 lst[k] = before;
-                (void)hipStreamSynchronize(lanes[k]->stream);   // what was enqueued reads the lane's buffers
                 if (!fifo.empty()) break;
-                // nothing in flight: the memory that the other lanes keep, then shorter classes
-                if (!freed) {
-                    for (Lane* other : lanes)
-                        if (other != lanes[k]) {
-                            other->ws.release(c);
-                            other->part.release(c);
-                        }
-                } else {
-                    std::vector<uint64_t> gn, gm;
-                    for (size_t q : g.jobs) {
-                        gn.push_back(ns[q]);
-                        gm.push_back(ms[q]);
-                    }
-                    if (!smaller_plans(gn, gm, policy, cm, &g.cls, &g.plans)) break;
+                // nothing in flight and no idle workspace left: shorter classes
+                std::vector<uint64_t> gn, gm;
+                for (size_t q : g.jobs) {
+                    gn.push_back(ns[q]);
+                    gm.push_back(ms[q]);
                 }
+                if (!smaller_plans(gn, gm, policy, cm, &g.cls, &g.plans)) break;
             }
             if (ls == PA_ENOMEM && !fifo.empty()) break;   // again when the group in flight has ended
             if (ls != PA_OK) {

@@ -96,6 +96,8 @@ struct Lane {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     uint64_t cap = 0;     // workspace cap in bytes (0: the context budget)
+    bool shares = false;  // one of the lanes (`main`, `side`) that give idle workspaces back to each other
+    bool in_flight = false;   // a launch that is not yet finished
     DevBuf ws, part, meta, jobs_dev, io;
     DevBuf aux;           // pa_hash_select: reversed key, indices and bits
     DevBuf direct_dev;    // descriptors of a batch of direct jobs
@@ -122,6 +124,7 @@ struct Lane {
     bool ended();
     hipError_t wait();
 
+    pa_status launch_once(Ctx* c, int prec, int cls, std::vector<JobDesc>& js, bool timing, bool fetch_meta, pa_stats* stats);
     pa_status rebuild_shorter(Ctx* c, uint32_t flags, const std::vector<size_t>& which, pa_stats* stats,
                               std::vector<pa_status>* per_job);
 
@@ -183,6 +186,9 @@ struct Ctx {
     std::mutex tab_mu;    // twiddle table cache
     Lane main;
     std::vector<Lane> side;   // extra streams for the length-class groups of a batch
+    // Free the workspaces of the lanes above that have nothing in flight, but for
+    // `keep`; false if there were none.  With `mu` held.
+    bool give_back(const Lane* keep);
     std::map<int, DevTables> tabs;
     CostModel cost;
     // Plans of recent single-job shapes (key: n, m, policy and the class

@@ -177,3 +177,52 @@ def test_certificates_fit_beside_a_full_workspace(pa, monkeypatch):
             assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m))
     finally:
         pa.pa_destroy(c)
+
+
+def test_full_budget_leaves_room_for_another_class(pa, monkeypatch):
+    """A batch whose tiles fill the budget to the last few kilobytes, then a hash of a
+    class whose tables are not there yet: it runs on its own class."""
+    import torch
+    rng = np.random.default_rng(27)
+    c = pa.pa_create(0, 24 << 20, None)
+    try:
+        monkeypatch.setenv("PA_ONLY_LEN", str(1 << 12))
+        batch = [_job(pa, rng, 60_000, 5_000) for _ in range(100)]
+        st, _ = pa.pa_hash_batch(c, batch, pa.PA_PREC_FP32_SEG)
+        assert st == pa.PA_OK and pa.pa_last_stats(c)["tiles"] > 1000
+        monkeypatch.delenv("PA_ONLY_LEN")
+        s, k, o, n, m = _job(pa, rng, 700_000, 200_000)
+        want = pa.pa_plan_query(n, m, pa.PA_PREC_FP64)["fft_len"]
+        print(f"n={n} m={m} class {want}", flush=True)
+        assert pa.pa_hash(c, s, n, m, k, o, pa.PA_PREC_FP64) == pa.PA_OK
+        torch.cuda.synchronize()
+        assert pa.pa_last_stats(c)["fft_len"] == want, pa.pa_last_stats(c)
+        from gpu_util import from_dev
+        assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m))
+    finally:
+        pa.pa_destroy(c)
+
+
+def test_idle_workspaces_are_given_back(pa, monkeypatch):
+    """A batch of two groups leaves a workspace with each of its two streams; a batch
+    of one group that needs most of the budget still runs in one go."""
+    import torch
+    from gpu_util import from_dev
+    rng = np.random.default_rng(28)
+    c = pa.pa_create(0, 64 << 20, None)
+    try:
+        two = [_job(pa, rng, 200_000, 60_000) for _ in range(9)] + [_job(pa, rng, 20_000, 3_000) for _ in range(40)]
+        st, _ = pa.pa_hash_batch(c, two, pa.PA_PREC_FP64)
+        assert st == pa.PA_OK and pa.pa_last_stats(c)["launches"] == 6, pa.pa_last_stats(c)
+        monkeypatch.setenv("PA_ONLY_LEN", str(1 << 18))
+        one = [_job(pa, rng, 200_000, 60_000) for _ in range(13)]   # a tile of 4 MB each
+        print("13 jobs of one tile of 2^18", flush=True)
+        st, _ = pa.pa_hash_batch(c, one, pa.PA_PREC_FP64)
+        torch.cuda.synchronize()
+        stats = pa.pa_last_stats(c)
+        assert st == pa.PA_OK and stats["tiles"] == 13 and stats["launches"] == 3, stats
+        monkeypatch.delenv("PA_ONLY_LEN")
+        for s, k, o, n, m in one[:3] + two[:2] + two[-2:]:
+            assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
+    finally:
+        pa.pa_destroy(c)
