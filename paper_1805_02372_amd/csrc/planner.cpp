@@ -328,7 +328,7 @@ int load_tune_table(CostModel& cm, const char* path) {
             }
         }
         const std::string tag = std::string("\"") + prec_key(prec) + "\"";
-        const size_t at = text.find(tag + ":");
+        const size_t at = text.find(tag);   // (the closing quote keeps "fp32_chunk" out)
         if (at == std::string::npos) continue;
         const size_t open = text.find('{', at), close = text.find('}', at);
         if (open == std::string::npos || close == std::string::npos || close < open) return -1;
