@@ -308,12 +308,15 @@ int load_tune_table(CostModel& cm, const char* path) {
         struct Section {
             const char* kind;
             void (CostModel::*set)(int, int, double);
-        };
-        for (const Section& sec : {Section{"_few", &CostModel::set_few}, Section{"_chunk", &CostModel::set_chunk},
-                                   Section{"_chunk_alone", &CostModel::set_alone},
-                                   Section{"_chunk_run", &CostModel::set_run}}) {
+            bool found;
+        } sections[] = {{"_few", &CostModel::set_few, false},
+                        {"_chunk", &CostModel::set_chunk, false},
+                        {"_chunk_alone", &CostModel::set_alone, false},
+                        {"_chunk_run", &CostModel::set_run, false}};
+        for (Section& sec : sections) {
             const size_t ca = text.find(std::string("\"") + prec_key(prec) + sec.kind + "\"");
             if (ca == std::string::npos) continue;
+            sec.found = true;
             const size_t o = text.find('{', ca), e = text.find('}', ca);
             if (o == std::string::npos || e == std::string::npos || e < o) return -1;
             const std::string body = text.substr(o + 1, e - o - 1);
@@ -347,6 +350,9 @@ int load_tune_table(CostModel& cm, const char* path) {
             if (!(v > 0 && v < 10.0)) continue;
             cm.set(prec, k, v);
             ++loaded;
+            // an older table has one cost for all launches: not beside other tables' ends
+            for (const Section& sec : sections)
+                if (!sec.found) (cm.*sec.set)(prec, k, 0);
             if (pair && end) {
                 while (*end == ' ' || *end == ',') ++end;
                 const double w = strtod(end, nullptr);

@@ -37,3 +37,11 @@ def test_white_space_before_a_section(pa, tmp_path, separators):
     rows = json.dumps({"655360": [1e-9, 0.0]}, separators=(",", ":"))
     path.write_text('{"launch":1e-5' + separators[0] + '"fp32"' + separators[1] + rows + "}")
     assert _planned(pa, path) == 655_360
+
+
+def test_one_cost_per_tile(pa, tmp_path):
+    """A table without the sections for few tiles and for chunks: its costs hold for
+    launches of any size, and are not mixed with those that ship with the library."""
+    path = tmp_path / "table.json"
+    path.write_text(json.dumps({"fp32": {"655360": [5e-6, 0.0], "524288": [7e-6, 0.0]}}))
+    assert _planned(pa, path) == 655_360
