@@ -477,26 +477,27 @@ bool Ctx::give_back(const Lane* keep) {
     return freed;
 }
 
-// A launch whose tables, descriptors or workspace do not fit the budget: once more
-// without the workspaces that the context's idle lanes and this one keep from
-// earlier calls.
+bool Ctx::alone(const Lane* ln) const {
+    if (queued) return false;
+    if (ln != &main && main.in_flight) return false;
+    for (const Lane& x : side)
+        if (ln != &x && x.in_flight) return false;
+    return true;
+}
+
+// A launch whose tables, descriptors or certificates do not fit beside workspaces
+// that fill the budget: once more without this lane's and those of the idle lanes.
 pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bool timing, bool fetch_meta,
                        pa_stats* stats) {
-    const std::vector<JobDesc> asked = js;
-    const pa_stats before = *stats;
-    pa_status st = launch_once(c, prec_, cls_, js, timing, fetch_meta, stats);
-    if (st == PA_ENOMEM && !ws.fixed) {
-        (void)hipStreamSynchronize(stream);   // what was enqueued reads the lane's buffers
-        bool freed = shares && c->give_back(this);
-        if (ws.ptr || part.ptr) {
+    bool crowded = false;
+    pa_status st = launch_once(c, prec_, cls_, js, timing, fetch_meta, stats, &crowded);
+    if (st == PA_ENOMEM && crowded) {   // (nothing is enqueued yet, and nothing changed)
+        (void)hipStreamSynchronize(stream);
+        const bool freed = shares && c->give_back(this);
+        if (freed || ws.ptr || part.ptr) {
             ws.release(c);
             part.release(c);
-            freed = true;
-        }
-        if (freed) {
-            js = asked;
-            *stats = before;
-            st = launch_once(c, prec_, cls_, js, timing, fetch_meta, stats);
+            st = launch_once(c, prec_, cls_, js, timing, fetch_meta, stats, &crowded);
         }
     }
     if (st == PA_OK) in_flight = true;
@@ -504,7 +505,7 @@ pa_status Lane::launch(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bo
 }
 
 pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& js, bool timing, bool fetch_meta,
-                            pa_stats* stats) {
+                            pa_stats* stats, bool* crowded) {
     const ClassKernels* K = class_kernels(prec_, cls_);
     if (!K || js.empty()) return PA_EINVAL;
     prec = prec_;
@@ -517,6 +518,7 @@ pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& j
         all += jd.nchunks * jd.nouts;
     }
     Tables tb;
+    *crowded = !ws.fixed;
     pa_status st = lane_tables(c, *this, prec, cls, &tb);
     if (st != PA_OK) return st;
     // certificates of at most as many groups as tiles: before the workspace, which
@@ -530,6 +532,7 @@ pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& j
         st = jobs_host.ensure(js.size() * sizeof(JobDesc));
         if (st != PA_OK) return st;
     }
+    *crowded = false;
     // tiles per launch: as many as the budget (and the lane cap) allows; on a
     // failed allocation halve until one tile
     const size_t elt = cfg.prec == 64 ? 16 : 8;
@@ -544,12 +547,18 @@ pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& j
             return cap ? std::min<uint64_t>(a, cap) : a;
         };
         avail = left();
+        // The idle lanes' workspaces go to a launch that nothing else runs beside, and
+        // to one that has no room for one tile.  A group of several leaves them: 256
+        // jobs in two classes, the first group with the whole budget and the second
+        // nearly tile by tile, took 13.7 ms, 4.7 with a workspace each.
+        const uint64_t one = total ? tile_bytes + part_bytes : 0;
         uint64_t want = total * (uint64_t)(tile_bytes + part_bytes);
         for (const JobDesc& jd : js)
             if (jd.shared)
                 want = std::max<uint64_t>(want, K->shared_bytes(shared_packs(jd, jd.cgroup), jd.nouts) +
                                                     shared_packs(jd, jd.cgroup) * part_bytes);
-        if (want > avail && shares && c->give_back(this)) avail = left();
+        if ((one > avail || (want > avail && c->alone(this))) && shares && c->give_back(this)) avail = left();
+        if (one > avail) return PA_ENOMEM;   // and the workspace stays as it is
     }
     // a job with shared spectra: chunk groups as large as fit (those that the
     // plan asks for, if possible); too little space for a few chunks: plain tiles
@@ -1332,6 +1341,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
                     fill_job(&jobs[q], a.seed, a.key, a.out, a.n, a.m, g.plans[q]);
                 }
                 const pa_stats before = lst[k];
+                c->queued = queue.size() - 1;
                 ls = lanes[k]->launch(c, g.plans[0].prec, g.cls, jobs, flags & PA_TIMING, true, &lst[k]);
                 if (ls != PA_ENOMEM) break;
                 lst[k] = before;
@@ -1368,6 +1378,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         if (!per_tile) stop = true;
         if (stop) queue.clear();
     }
+    c->queued = 0;
     if (ndirect && hipStreamSynchronize(ln.stream) != hipSuccess && s == PA_OK) s = PA_EDEVICE;
     lst.push_back(dst);
     pa_stats st{};

@@ -124,7 +124,8 @@ struct Lane {
     bool ended();
     hipError_t wait();
 
-    pa_status launch_once(Ctx* c, int prec, int cls, std::vector<JobDesc>& js, bool timing, bool fetch_meta, pa_stats* stats);
+    pa_status launch_once(Ctx* c, int prec, int cls, std::vector<JobDesc>& js, bool timing, bool fetch_meta, pa_stats* stats,
+                          bool* crowded);
     pa_status rebuild_shorter(Ctx* c, uint32_t flags, const std::vector<size_t>& which, pa_stats* stats,
                               std::vector<pa_status>* per_job);
 
@@ -189,6 +190,9 @@ struct Ctx {
     // Free the workspaces of the lanes above that have nothing in flight, but for
     // `keep`; false if there were none.  With `mu` held.
     bool give_back(const Lane* keep);
+    // Whether nothing of the running call is in flight or waits beside a launch on `ln`.
+    bool alone(const Lane* ln) const;
+    size_t queued = 0;        // groups of the running batch that wait for a lane
     std::map<int, DevTables> tabs;
     CostModel cost;
     // Plans of recent single-job shapes (key: n, m, policy and the class

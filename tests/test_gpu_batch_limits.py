@@ -226,3 +226,28 @@ def test_idle_workspaces_are_given_back(pa, monkeypatch):
             assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
     finally:
         pa.pa_destroy(c)
+
+
+def test_groups_of_a_batch_keep_their_workspaces(pa, monkeypatch):
+    """A batch of two groups, then one whose first group could use the whole budget: it
+    leaves the other group's workspace alone.  Twice the jobs of the first group are two
+    runs of tiles at most, the second group stays one; three passes each, and as much
+    again for another choice of classes."""
+    import torch
+    from gpu_util import from_dev
+    rng = np.random.default_rng(29)
+    c = pa.pa_create(0, 64 << 20, None)
+    try:
+        two = [_job(pa, rng, 200_000, 60_000) for _ in range(9)] + [_job(pa, rng, 20_000, 3_000) for _ in range(40)]
+        st, _ = pa.pa_hash_batch(c, two, pa.PA_PREC_FP64)
+        assert st == pa.PA_OK and pa.pa_last_stats(c)["launches"] == 6, pa.pa_last_stats(c)
+        more = two + [_job(pa, rng, 200_000, 60_000) for _ in range(9)]
+        for _ in range(3):
+            st, _ = pa.pa_hash_batch(c, more, pa.PA_PREC_FP64)
+            torch.cuda.synchronize()
+            stats = pa.pa_last_stats(c)
+            assert st == pa.PA_OK and stats["launches"] <= 18, stats
+        for s, k, o, n, m in more[:2] + more[20:22] + more[-2:]:
+            assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
+    finally:
+        pa.pa_destroy(c)
