@@ -542,11 +542,13 @@ pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& j
     if (ws.fixed) {
         avail = ws.bytes;
     } else {
-        auto left = [&] {
-            const uint64_t u = c->used.load(), mine = ws.bytes + part.bytes, a = c->budget > u ? c->budget - u + mine : mine;
-            return cap ? std::min<uint64_t>(a, cap) : a;
+        uint64_t room = 0;   // what the budget has left, this lane's included; one tile may take it beyond the cap
+        auto look = [&] {
+            const uint64_t u = c->used.load(), mine = ws.bytes + part.bytes;
+            room = c->budget > u ? c->budget - u + mine : mine;
+            avail = cap ? std::min<uint64_t>(room, cap) : room;
         };
-        avail = left();
+        look();
         // The idle lanes' workspaces go to a launch that nothing else runs beside, and
         // to one that has no room for one tile.  A group of several leaves them: 256
         // jobs in two classes, the first group with the whole budget and the second
@@ -557,8 +559,8 @@ pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& j
             if (jd.shared)
                 want = std::max<uint64_t>(want, K->shared_bytes(shared_packs(jd, jd.cgroup), jd.nouts) +
                                                     shared_packs(jd, jd.cgroup) * part_bytes);
-        if ((one > avail || (want > avail && c->alone(this))) && shares && c->give_back(this)) avail = left();
-        if (one > avail) return PA_ENOMEM;   // and the workspace stays as it is
+        if (shares && (one > room || (want > room && c->alone(this))) && c->give_back(this)) look();
+        if (one > room) return PA_ENOMEM;   // and the workspace stays as it is
     }
     // a job with shared spectra: chunk groups as large as fit (those that the
     // plan asks for, if possible); too little space for a few chunks: plain tiles

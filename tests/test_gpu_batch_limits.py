@@ -251,3 +251,24 @@ def test_groups_of_a_batch_keep_their_workspaces(pa, monkeypatch):
             assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
     finally:
         pa.pa_destroy(c)
+
+
+def test_serving_tile_beyond_a_lanes_share(pa):
+    """A tile that the budget holds and a serving lane's share of it (a third) does not:
+    the request still runs on its planned class."""
+    from gpu_util import from_dev
+    n, m = 1_436_744, 1_306_539
+    plan = pa.pa_plan_query(n, m, pa.PA_PREC_FP32_SEG)
+    budget = 24 << 20
+    assert budget // 3 < plan["fft_len"] * 8 < budget * 3 // 4, plan
+    s, k, o, n, m = _job(pa, np.random.default_rng(30), n, m)
+    c = pa.pa_create(0, budget, None)
+    try:
+        sid = pa.pa_seed_register(c, s, n + m - 1)
+        st, t = pa.pa_submit(c, sid, n, m, k, o)
+        assert st == pa.PA_OK and pa.pa_wait(c, t) == pa.PA_OK
+        stats = pa.pa_serve_stats(c)
+        assert stats["tiles"] == plan["chunks"] * plan["windows"], (stats, plan)
+        assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m))
+    finally:
+        pa.pa_destroy(c)
