@@ -94,7 +94,7 @@ void Ctx::serve_loop() {
     std::vector<uint8_t> busy(lanes.size(), 0);
     const uint64_t lane_budget = budget / (lanes.size() + 1);
     while (true) {
-        bool any_busy = false;
+        bool any_busy = false, crowded = false;
         // completions
         for (size_t i = 0; i < lanes.size(); ++i) {
             if (!busy[i]) continue;
@@ -130,7 +130,7 @@ void Ctx::serve_loop() {
             done_cv.notify_all();
         }
         // admissions
-        for (size_t i = 0; i < lanes.size() && !pending.empty() && !stop; ++i) {
+        for (size_t i = 0; i < lanes.size() && !pending.empty() && !stop && !crowded; ++i) {
             if (busy[i]) continue;
             // continuous batching: the oldest request and the waiting requests
             // of its kind (within a scan window), up to the lane's budget.  A
@@ -230,12 +230,35 @@ void Ctx::serve_loop() {
                 for (const TilePlan& tp : plans) fill_plan_stats(&lane_stats[i], tp);
                 s = lanes[i].launch(this, PREC_FP32, cls, jobs, false, true, &lane_stats[i]);
                 if (s != PA_ENOMEM) break;
-                // the memory is with the other lanes and calls: a shorter class
+                // The memory is with the idle lanes, which give it back; with a busy one,
+                // whose end the requests wait for; or with other calls: a shorter class.
                 (void)hipStreamSynchronize(lanes[i].stream);   // what was enqueued reads the lane's buffers
+                bool freed = false, others = false;
+                for (size_t q = 0; q < lanes.size(); ++q) {
+                    if (q == i) continue;
+                    others |= busy[q] != 0;
+                    if (busy[q] || !(lanes[q].ws.ptr || lanes[q].part.ptr)) continue;
+                    lanes[q].ws.release(this);
+                    lanes[q].part.release(this);
+                    freed = true;
+                }
+                if (freed) {
+                    s = PA_OK;
+                    continue;
+                }
+                if (others) {
+                    crowded = true;
+                    break;
+                }
                 if (smaller_plans(ns, ms, PREC_FP32, cm, &cls, &plans)) s = PA_OK;
             }
             lk.lock();
-            if (s != PA_OK) {
+            if (crowded) {
+                for (size_t k = batch.size(); k-- > 0;) {
+                    batch[k]->state = 0;
+                    pending.push_front(batch[k]);
+                }
+            } else if (s != PA_OK) {
                 const double t = now_seconds();
                 for (Request* r : batch) {
                     r->status = s;

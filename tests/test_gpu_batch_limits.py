@@ -272,3 +272,33 @@ def test_serving_tile_beyond_a_lanes_share(pa):
         assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m))
     finally:
         pa.pa_destroy(c)
+
+
+def test_serving_lanes_wait_for_each_others_memory(pa):
+    """Requests of two classes whose tiles do not fit the budget side by side: each runs
+    on its planned class, when the other lane has ended and given its workspace back."""
+    from gpu_util import from_dev
+    budget = 24 << 20
+    rng = np.random.default_rng(31)
+    shapes = [(1_436_744, 1_306_539), (1_491_755, 699_609)]
+    plans = [pa.pa_plan_query(n, m, pa.PA_PREC_FP32_SEG) for n, m in shapes]
+    assert plans[0]["fft_len"] != plans[1]["fft_len"]
+    assert all(p["fft_len"] * 8 < budget * 3 // 4 for p in plans) and sum(p["fft_len"] * 8 for p in plans) > budget, plans
+    c = pa.pa_create(0, budget, None)
+    try:
+        s = _job(pa, rng, *shapes[0])[0]
+        sid = pa.pa_seed_register(c, s, sum(shapes[0]) - 1)
+        reqs = [_job(pa, rng, *shapes[q % 2])[1:] for q in range(12)]
+        tickets = []
+        for k, o, n, m in reqs:
+            st, t = pa.pa_submit(c, sid, n, m, k, o)
+            assert st == pa.PA_OK
+            tickets.append(t)
+        got = [pa.pa_wait(c, t) for t in tickets]
+        assert got == [pa.PA_OK] * len(reqs), got
+        stats = pa.pa_serve_stats(c)
+        assert stats["tiles"] == 6 * sum(p["chunks"] * p["windows"] for p in plans), (stats, plans)
+        for k, o, n, m in reqs[:4]:
+            assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
+    finally:
+        pa.pa_destroy(c)
