@@ -106,7 +106,9 @@ static pa_status time_group(Ctx* c, int prec, int k, const CostModel& cm, uint64
 // the launch, and what one tile leaves of the device idle) to its first_s; the
 // median of the latter is the launch cost of the direct path.  With 16 tiles for N,
 // up to 2^20 points, and 4 above, tile_s came out up to twice as large (FP32 2^15: 0.45
-// us, 0.24 per tile in a batch of 256 jobs).
+// us, 0.24 per tile in a batch of 256 jobs).  The NTT sums no products, and its N tiles
+// are the chunks of one job, which all go to one window: 1.8 us each at 2^16, 1.4 as
+// jobs of their own.
 pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
     std::vector<int> precs;
     switch (flags & PA_PREC_MASK) {
@@ -155,7 +157,12 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
             st = time_launch(c, prec, k, p, L / 2, 1, dseed, dkey, douts, stride, reps, &t1);
             if (st == PA_OK) st = time_launch(c, prec, k, p, L / 2, kFew, dseed, dkey, douts, stride, reps, &t4);
             tn = t4;
-            if (st == PA_OK && many > kFew) st = time_launch(c, prec, k, p, L / 2, many, dseed, dkey, douts, stride, reps, &tn);
+            TilePlan pn;
+            if (st == PA_OK && prec == PREC_NTT && plan_at_class(many * L / 2, L / 2 + 1, prec, k, cm, &pn) &&
+                pn.tiles() == (uint64_t)many)
+                st = time_launch(c, prec, k, pn, many * L / 2, 1, dseed, dkey, douts, stride, reps, &tn);
+            else if (st == PA_OK && many > kFew)
+                st = time_launch(c, prec, k, p, L / 2, many, dseed, dkey, douts, stride, reps, &tn);
             if (st != PA_OK) {
                 buf.release(c);
                 return st;

@@ -84,3 +84,24 @@ def test_batches(pa, jobs, n, m, prec, monkeypatch):
     planned, length, beside = _choice(pa, jobs, n, m, flags, monkeypatch)
     print(f"{jobs} x n={n} m={m} planned {length}: {planned:.1f} us, fastest {min(beside)}", flush=True)
     assert planned <= 1.2 * min(beside)[0] + 2.0, (planned, length, sorted(beside)[:4])
+
+
+def test_ntt_of_many_chunks_beside_a_short_job(pa):
+    """The NTT sums no chunks: a long key does not follow a short job to its class, at
+    a tile for each of 51 chunks.  Both together take little more than the long one."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(7)
+    (n, m), (n2, m2) = (2_002_554, 25_360), (32_520, 21_266)
+    seed, key = _words(gen, n + m - 1), _words(gen, n)
+    outs = [torch.zeros(synth.words_for(x), dtype=torch.int64, device="cuda:0") for x in (m, m2)]
+    torch.cuda.synchronize()
+    ctx = pa.pa_create(0, 0, None)
+    try:
+        alone = _median_us(lambda: pa.pa_hash(ctx, seed, n, m, key, outs[0], pa.PA_PREC_NTT))
+        batch = pa.JobBatch([(seed, key, outs[0], n, m), (seed, key, outs[1], n2, m2)])
+        both = _median_us(lambda: pa.pa_hash_batch(ctx, batch, pa.PA_PREC_NTT))
+        print(f"alone {alone:.1f} us, both {both:.1f} us", flush=True)
+        assert both <= 1.2 * alone + 30.0, (alone, both)
+    finally:
+        pa.pa_destroy(ctx)
