@@ -463,9 +463,11 @@ static bool plan_shared(uint64_t n, uint64_t m, int prec, int cls, const CostMod
     groups = ceil_div(p.nchunks, p.cgroup);
     // Measured per 1000 points (2^21 to 2^23; 6, 16 and 40 chunks, 2 to 16 windows): a
     // pack takes 6.1 to 7.1 ns up to four windows, with more 8.0 to 8.7 ns up to eight
-    // and 9.6 to 10.6 up to sixteen (its spectrum is read once per eight), a
-    // window's inverse and columns 1.5 to 1.9 ns.
-    const double pack = p.nouts <= 4 ? 6.3e-12 : 6.6e-12 + 1.65e-12 * (double)ceil_div(p.nouts, 8);
+    // and 9.6 to 10.7 up to sixteen (its spectrum is read once per eight), a
+    // window's inverse and columns 1.5 to 1.9 ns.  Further reads cost less: 11.8 ns with
+    // 24 windows, 12.3 with 32 and 13.1 with 47 (keys of 140 to 150 M bits).
+    const double reads = (double)ceil_div(p.nouts, 8);
+    const double pack = p.nouts <= 4 ? 6.3e-12 : 6.6e-12 + 1.75e-12 * std::min(reads, 3.0) + 0.5e-12 * std::max(reads - 3.0, 0.0);
     p.cost = (double)p.L * (double)groups * ((double)p.packs(p.cgroup) * pack + (double)p.nouts * 1.9e-12);
     p.rigorous = rigorous_bound(prec, p.L, p.Bi, p.Bo, p.cgroup);
     *out = p;

@@ -90,3 +90,10 @@ def test_summed_classes_plan_as_fast(pa):
         return best
     ratio = min(took(pa.PA_PREC_FP32_SEG) / took(pa.PA_PREC_NTT) for _ in range(3))
     assert ratio < 3.8, ratio
+
+
+@pytest.mark.parametrize("n,m", [(142_795_849, 65_530_406), (153_272_179, 97_861_985), (150_254_723, 63_964_138)])
+def test_shared_spectra_of_many_windows(pa, n, m):
+    """Shared spectra with 16 to 47 windows: 2^22 points take 5.85, 14.4 and 5.93 ms on
+    MI355X, 2^23 points 6.14, 15.1 and 6.19."""
+    assert pa.pa_plan_query(n, m, pa.PA_PREC_FP32_SEG)["fft_len"] == 1 << 22
