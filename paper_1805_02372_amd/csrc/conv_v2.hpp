@@ -7,8 +7,9 @@
 //    into bit planes, and the columns are split into 3 to 8 parts whose first radix
 //    level is looked up from the bits; each wave transforms G columns of a part in
 //    registers (FP32 2^20 and 2^21: G whole columns, with the bits as inputs).  Rows
-//    of 512: the bits are staged through LDS and each wave transforms G whole columns.  An LDS transpose turns the column-major results
-//    into C-element row segments for the stores.
+//    of 512: the bits are staged through LDS and each wave transforms G whole
+//    columns.  An LDS transpose turns the column-major results into C-element row
+//    segments for the stores.
 //  * pass 2: a row of 4096 points is a radix-8 stage across the 8 waves
 //    (decimation in frequency, registers only) followed by one 512-point transform
 //    per wave; the inverse runs the same steps in reverse.  Two workgroup barriers

@@ -76,7 +76,7 @@ k_direct_prep(const uint64_t* __restrict__ key, uint64_t n, uint32_t* __restrict
 // Bound by the matrix cores for NB = 4 (16 products of 16 cycles per step beside
 // 44 vector operations of 4) and by the vector operations that prepare a step
 // for NB = 1 (23, and 4 products; 32 with every row block expanded by itself: call
-// 26.9 -> 26.0 us at n = 12,345,679, m = 1000).  Measured on MI355X, that job 10-13
+// 26.9 -> 26.0 us at n = 12,345,679, m = 1000).  Measured on MI355X, that job 12-16
 // us (the word-parallel kernel before it, one output per lane: 55 us); n = 10^6, m =
 // 200,000 3.1e15 bit products per second (2.2e14 before).
 typedef int v8i __attribute__((ext_vector_type(8)));

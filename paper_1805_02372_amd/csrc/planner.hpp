@@ -165,8 +165,8 @@ bool plan_at_class(uint64_t n, uint64_t m, int prec, int cls, const CostModel& c
 // Best plan over classes for one job.  policy: PREC_FP32 (segmented, bound
 // limited), PREC_FP64 and PREC_NTT (a single tile if one fits, else the
 // cheapest plan over the classes).  Among plans whose modeled costs differ by
-// less than 10% the one that moves fewer points wins.  Classes longer than
-// 2^cap_logL are not used.
+// less than 2% (1% where each is one tile) the one that moves fewer points wins.
+// Classes longer than 2^cap_logL are not used.
 bool plan_job(uint64_t n, uint64_t m, int policy, const CostModel& cm, TilePlan* out, int cap_logL = 24,
               uint64_t shared_bytes = kSharedBytes);
 
