@@ -477,6 +477,20 @@ bool Ctx::give_back(const Lane* keep) {
     return freed;
 }
 
+// A buffer that does not fit beside the workspaces of earlier calls: once more
+// without those that are idle.
+pa_status Ctx::reserve(DevBuf& b, size_t need, hipStream_t stream) {
+    const pa_status st = b.ensure(this, need, stream);
+    return st == PA_ENOMEM && give_back(nullptr) ? b.ensure(this, need, stream) : st;
+}
+
+pa_status Ctx::reserve_unlocked(DevBuf& b, size_t need, hipStream_t stream) {
+    const pa_status st = b.ensure(this, need, stream);
+    if (st != PA_ENOMEM) return st;
+    std::lock_guard<std::mutex> lk(mu);
+    return reserve(b, need, stream);
+}
+
 bool Ctx::alone(const Lane* ln) const {
     if (queued) return false;
     if (ln != &main && main.in_flight) return false;
@@ -936,7 +950,12 @@ pa_status Lane::direct_batch(Ctx* c, std::vector<DirectJob>& js, pa_stats* stats
         return st;
     }
     const size_t bytes = count * sizeof(DirectJob);
-    pa_status st = direct_dev.ensure(c, bytes, stream);
+    pa_status st = shares ? c->reserve(direct_dev, bytes, stream) : direct_dev.ensure(c, bytes, stream);
+    if (st == PA_ENOMEM && ws.ptr && !ws.fixed) {
+        ws.release(c);
+        part.release(c);
+        st = direct_dev.ensure(c, bytes, stream);
+    }
     if (st == PA_OK) st = direct_host.ensure(bytes);
     if (st != PA_OK) return st;
     memcpy(direct_host.ptr, js.data(), bytes);
@@ -1096,7 +1115,7 @@ pa_status pa_hash(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t m, con
     uint64_t* dout = out;
     const bool dev = flags & PA_DEVICE_PTRS;
     if (!dev) {  // stage host buffers through library memory
-        pa_status s = ln.io.ensure(c, (sw + kw + ow) * 8, ln.stream);
+        pa_status s = c->reserve(ln.io, (sw + kw + ow) * 8, ln.stream);
         if (s != PA_OK) return s;
         uint64_t* base = (uint64_t*)ln.io.ptr;
         void* dsts[2] = {base, base + sw};
@@ -1146,6 +1165,7 @@ pa_status pa_hash(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t m, con
             st = pa_stats{};
             fill_plan_stats(&st, plan);
         }
+        if (async) ln.in_flight = false;   // nothing waits for it; its workspace is given back in stream order
         if (s == PA_OK && !dev) s = fetch_outputs(ln, hsrc, hlen, 1);
         if (s == PA_OK && !async) s = ln.finish(c, flags, &st, nullptr);
         if (s == PA_OK && !dev && st.fallback_tiles) s = fetch_outputs(ln, hsrc, hlen, 1);
@@ -1260,7 +1280,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         uint64_t total_words = 0;
         for (uint64_t i = 0; i < count; ++i)
             total_words += words_of(ns[i] + ms[i] - 1) + words_of(ns[i]) + words_of(ms[i]);
-        pa_status s = ln.io.ensure(c, total_words * 8, ln.stream);
+        pa_status s = c->reserve(ln.io, total_words * 8, ln.stream);
         if (s != PA_OK) return s;
     }
     uint64_t off = 0;
@@ -1472,7 +1492,7 @@ pa_status pa_hash_select(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t
     const uint64_t *dseed = seed, *dkey = key;
     if (!(flags & PA_DEVICE_PTRS)) {
         const uint64_t sw = words_of(n + m - 1), kw = words_of(n);
-        pa_status s = ln.io.ensure(c, (sw + kw) * 8, ln.stream);
+        pa_status s = c->reserve(ln.io, (sw + kw) * 8, ln.stream);
         if (s != PA_OK) return s;
         uint64_t* base = (uint64_t*)ln.io.ptr;
         void* dsts[2] = {base, base + sw};
@@ -1486,7 +1506,7 @@ pa_status pa_hash_select(pa_ctx* ctx, const uint64_t* seed, uint64_t n, uint64_t
     // scratch: reversed key | indices | result bits (256-byte aligned sections)
     auto up = [](uint64_t b) { return (b + 255) & ~uint64_t(255); };
     const uint64_t kr_bytes = up(direct_key_words(n) * 4), idx_bytes = up(count * 8), res_words = words_of(count);
-    pa_status s = ln.aux.ensure(c, kr_bytes + idx_bytes + res_words * 8, ln.stream);
+    pa_status s = c->reserve(ln.aux, kr_bytes + idx_bytes + res_words * 8, ln.stream);
     if (s == PA_OK) s = ln.jobs_host.ensure(idx_bytes + res_words * 8);
     if (s != PA_OK) return s;
     uint8_t* dbase = (uint8_t*)ln.aux.ptr;

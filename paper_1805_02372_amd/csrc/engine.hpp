@@ -190,6 +190,9 @@ struct Ctx {
     // Free the workspaces of the lanes above that have nothing in flight, but for
     // `keep`; false if there were none.  With `mu` held.
     bool give_back(const Lane* keep);
+    // Reserve device memory, at the cost of idle workspaces; with `mu` held, or not.
+    pa_status reserve(DevBuf& b, size_t need, hipStream_t stream);
+    pa_status reserve_unlocked(DevBuf& b, size_t need, hipStream_t stream);
     // Whether nothing of the running call is in flight or waits beside a launch on `ln`.
     bool alone(const Lane* ln) const;
     size_t queued = 0;        // groups of the running batch that wait for a lane

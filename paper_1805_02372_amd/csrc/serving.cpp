@@ -292,7 +292,7 @@ pa_status pa_seed_register(pa_ctx* ctx, const uint64_t* seed, uint64_t nbits, ui
     if (hipSetDevice(c->device) != hipSuccess) return PA_EDEVICE;
     DevBuf b;
     const size_t bytes = words_of(nbits) * 8;
-    pa_status st = b.ensure(c, bytes);
+    pa_status st = c->reserve_unlocked(b, bytes, nullptr);
     if (st != PA_OK) return st;
     const hipMemcpyKind kind = (flags & PA_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     if (hipMemcpy(b.ptr, seed, bytes, kind) != hipSuccess) {

@@ -68,10 +68,19 @@ static pa_status drain(pa_stream* s) {
 // Enqueue the partial hash of an FFT block on a lane.
 static pa_status launch_fft(pa_stream* s, int lane, const uint64_t* dseed, const uint64_t* dkey, uint64_t len,
                             const TilePlan& plan) {
-    pa_stats st{};
-    std::vector<JobDesc> jobs(1);
-    fill_job(&jobs[0], dseed, dkey, (uint64_t*)s->r->part[lane].ptr, len, s->m, plan);
-    return s->r->lane(lane).launch(s->c, plan.prec, plan.cls, jobs, false, true, &st);
+    auto launch = [&] {
+        pa_stats st{};
+        std::vector<JobDesc> jobs(1);
+        fill_job(&jobs[0], dseed, dkey, (uint64_t*)s->r->part[lane].ptr, len, s->m, plan);
+        return s->r->lane(lane).launch(s->c, plan.prec, plan.cls, jobs, false, true, &st);
+    };
+    const pa_status st = launch();
+    if (st != PA_ENOMEM) return st;
+    {
+        std::lock_guard<std::mutex> lk(s->c->mu);   // the workspaces of idle calls
+        if (!s->c->give_back(nullptr)) return st;
+    }
+    return launch();
 }
 
 // Enqueue the partial hash of one block (device pointers) and settle the block
@@ -181,7 +190,7 @@ static pa_status take_res(Ctx* c, uint64_t m, StreamRes** out) {
                 hipEventRecord(r->used[b], r->ln[0].stream) != hipSuccess)
                 st = PA_EDEVICE;
     }
-    if (st == PA_OK) st = r->part[0].ensure(c, nwords(m) * 8, r->ln[0].stream);
+    if (st == PA_OK) st = c->reserve_unlocked(r->part[0], nwords(m) * 8, r->ln[0].stream);
     if (st != PA_OK) {
         r->release(c);
         delete r;
@@ -232,7 +241,7 @@ pa_status pa_stream_open(pa_ctx* ctx, uint64_t n, uint64_t m, uint32_t flags, pa
     s->m = m;
     s->flags = flags;
     pa_status st = take_res(c, m, &s->r);
-    if (st == PA_OK) st = s->acc.ensure(c, nwords(m) * 8, s->stream());
+    if (st == PA_OK) st = c->reserve_unlocked(s->acc, nwords(m) * 8, s->stream());
     // x ^ x = 0: clear the accumulator with the XOR kernel itself
     if (st == PA_OK &&
         launch_xor_words((uint64_t*)s->acc.ptr, (const uint64_t*)s->acc.ptr, nwords(m), s->stream()))
@@ -268,7 +277,7 @@ pa_status pa_stream_feed(pa_stream* s, const uint64_t* key_block, uint64_t lo, u
     if (st == PA_OK && s->r->in[b].bytes < off + kbytes) {
         // a larger block: the old buffer may be freed only after its reader
         if (hipStreamWaitEvent(s->r->copy, s->r->used[b], 0) != hipSuccess) return PA_EDEVICE;
-        st = s->r->in[b].ensure(c, off + kbytes, s->r->copy);
+        st = c->reserve_unlocked(s->r->in[b], off + kbytes, s->r->copy);
     }
     if (st != PA_OK) return st;
     unsigned char* h = (unsigned char*)s->r->pin[b].ptr;

@@ -128,7 +128,7 @@ pa_status tune_context(Ctx* c, uint32_t flags, int reps, const char* path) {
     uint64_t s = 0x9E3779B97F4A7C15ull;
     for (uint64_t& w : host) w = xorshift(s);
     DevBuf buf;
-    pa_status st = buf.ensure(c, (2 * words + kFew * out_words) * 8);
+    pa_status st = c->reserve(buf, (2 * words + kFew * out_words) * 8, nullptr);
     if (st != PA_OK) return st;
     uint64_t* dseed = (uint64_t*)buf.ptr;
     uint64_t* dkey = dseed + words;

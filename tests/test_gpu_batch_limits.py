@@ -302,3 +302,57 @@ def test_serving_lanes_wait_for_each_others_memory(pa):
             assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
     finally:
         pa.pa_destroy(c)
+
+
+@pytest.mark.parametrize("call", ["select", "host hash", "seed", "stream", "host batch", "direct batch"])
+def test_full_budget_leaves_room_for_other_calls(pa, call, monkeypatch):
+    """A batch whose tiles fill the budget to the last few kilobytes, then a call that
+    needs device memory for something else than tiles."""
+    import torch
+    from gpu_util import to_dev, from_dev
+    rng = np.random.default_rng(32)
+    c = pa.pa_create(0, 24 << 20, None)
+    try:
+        monkeypatch.setenv("PA_ONLY_LEN", str(1 << 12))
+        st, _ = pa.pa_hash_batch(c, [_job(pa, rng, 60_000, 5_000) for _ in range(100)], pa.PA_PREC_FP32_SEG)
+        torch.cuda.synchronize()
+        assert st == pa.PA_OK and pa.pa_last_stats(c)["tiles"] > 1000
+        monkeypatch.delenv("PA_ONLY_LEN")
+        n, m = 700_000, 200_000
+        p = synth.random_problem(rng, n, m)
+        ref = oracle.hash_words(p.seed, n, m, p.key)
+        out = np.zeros(synth.words_for(m), np.uint64)
+        print(call, flush=True)
+        if call == "select":
+            idx = [0, 1, 77_777, m - 1]
+            st, bits = pa.pa_hash_select(c, to_dev(p.seed), n, m, to_dev(p.key), idx)
+            assert st == pa.PA_OK
+            assert [int(b) for b in bits] == [int(ref[i >> 6] >> np.uint64(i & 63)) & 1 for i in idx]
+            return
+        if call == "host hash":
+            assert pa.pa_hash(c, p.seed, n, m, p.key, out, pa.PA_PREC_FP64) == pa.PA_OK
+        elif call == "host batch":
+            st, per = pa.pa_hash_batch(c, [(p.seed, p.key, out, n, m)], pa.PA_PREC_FP64)
+            assert st == pa.PA_OK and per == [pa.PA_OK]
+        elif call == "direct batch":
+            jobs = [_job(pa, rng, 3_000, 100) for _ in range(2_000)]
+            st, per = pa.pa_hash_batch(c, jobs, pa.PA_PREC_DIRECT)
+            assert st == pa.PA_OK and per == [pa.PA_OK] * len(jobs)
+            torch.cuda.synchronize()
+            s, k, o, n, m = jobs[-1]
+            assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m))
+            return
+        elif call == "seed":
+            sid = pa.pa_seed_register(c, to_dev(p.seed), n + m - 1)
+            o = to_dev(out)
+            st, t = pa.pa_submit(c, sid, n, m, to_dev(p.key), o)
+            assert st == pa.PA_OK and pa.pa_wait(c, t) == pa.PA_OK
+            out = from_dev(o)
+        else:
+            st, s = pa.pa_stream_open(c, n, m, pa.PA_PREC_FP64)
+            assert st == pa.PA_OK
+            assert pa.pa_stream_feed(s, p.key, 0, n, p.seed) == pa.PA_OK
+            assert pa.pa_stream_close(s, out) == pa.PA_OK
+        assert np.array_equal(out[:synth.words_for(m)], ref[:synth.words_for(m)])
+    finally:
+        pa.pa_destroy(c)
