@@ -1330,7 +1330,9 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         (void)hipEventDestroy(fork);
         if (!ok) return PA_EDEVICE;
     }
-    // direct jobs on the context's stream, beside the side streams' groups
+    // Direct jobs beside the largest group, which the context's stream takes at once (a
+    // key of 2,667 bits beside two tiles of 2^22: 134 us, 149 in turn).
+    Lane& dl = groups.empty() ? ln : *lanes.back();
     pa_stats dst{};
     const size_t ndirect = (size_t)std::count(is_direct.begin(), is_direct.end(), (char)1);
     if (ndirect) {
@@ -1338,7 +1340,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         dj.reserve(ndirect);
         for (uint64_t i = 0; i < count; ++i)
             if (is_direct[i]) dj.push_back(DirectJob{all[i].seed, all[i].key, all[i].out, all[i].n, all[i].m, 0, 0, 0, 0});
-        s = ln.direct_batch(c, dj, &dst);
+        s = dl.direct_batch(c, dj, &dst);
         if (s != PA_OK)
             for (uint64_t i = 0; i < count; ++i)
                 if (is_direct[i]) status[i] = s;
@@ -1401,7 +1403,7 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
         if (stop) queue.clear();
     }
     c->queued = 0;
-    if (ndirect && hipStreamSynchronize(ln.stream) != hipSuccess && s == PA_OK) s = PA_EDEVICE;
+    if (ndirect && hipStreamSynchronize(dl.stream) != hipSuccess && s == PA_OK) s = PA_EDEVICE;
     lst.push_back(dst);
     pa_stats st{};
     std::stable_sort(groups.begin(), groups.end(),   // the stats name the largest class
