@@ -575,6 +575,10 @@ pa_status Lane::launch_once(Ctx* c, int prec_, int cls_, std::vector<JobDesc>& j
                                                     shared_packs(jd, jd.cgroup) * part_bytes);
         if (shares && (one > room || (want > room && c->alone(this))) && c->give_back(this)) look();
         if (one > room) return PA_ENOMEM;   // and the workspace stays as it is
+        // A group that may wait for the one in flight does so rather than run in many
+        // small pieces: a quarter of it or less at a time, and less than 2^26 points,
+        // about what fills the device twice.
+        if (shares && c->may_wait && room < want / 4 && room < (uint64_t)elt << 26) return PA_ENOMEM;
     }
     // a job with shared spectra: chunk groups as large as fit (those that the
     // plan asks for, if possible); too little space for a few chunks: plain tiles
@@ -1366,7 +1370,9 @@ pa_status pa_hash_batch(pa_ctx* ctx, const pa_job* jobs_in, uint64_t count, uint
                 }
                 const pa_stats before = lst[k];
                 c->queued = queue.size() - 1;
+                c->may_wait = !fifo.empty();
                 ls = lanes[k]->launch(c, g.plans[0].prec, g.cls, jobs, flags & PA_TIMING, true, &lst[k]);
+                c->may_wait = false;
                 if (ls != PA_ENOMEM) break;
                 lst[k] = before;
                 if (!fifo.empty()) break;

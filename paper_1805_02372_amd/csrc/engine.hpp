@@ -196,6 +196,7 @@ struct Ctx {
     // Whether nothing of the running call is in flight or waits beside a launch on `ln`.
     bool alone(const Lane* ln) const;
     size_t queued = 0;        // groups of the running batch that wait for a lane
+    bool may_wait = false;    // the group being launched may wait for the one in flight
     std::map<int, DevTables> tabs;
     CostModel cost;
     // Plans of recent single-job shapes (key: n, m, policy and the class

@@ -356,3 +356,28 @@ def test_full_budget_leaves_room_for_other_calls(pa, call, monkeypatch):
         assert np.array_equal(out[:synth.words_for(m)], ref[:synth.words_for(m)])
     finally:
         pa.pa_destroy(c)
+
+
+def test_a_group_waits_rather_than_run_in_pieces(pa, monkeypatch):
+    """A batch of one group takes nearly the whole budget; of the next batch's two groups
+    the second finds room for a few tiles only and waits for the first.  Two or three
+    runs of tiles in all, three passes each."""
+    import torch
+    from gpu_util import from_dev
+    rng = np.random.default_rng(33)
+    c = pa.pa_create(0, 64 << 20, None)
+    try:
+        monkeypatch.setenv("PA_ONLY_LEN", str(1 << 18))
+        st, _ = pa.pa_hash_batch(c, [_job(pa, rng, 200_000, 60_000) for _ in range(16)], pa.PA_PREC_FP64)
+        assert st == pa.PA_OK
+        monkeypatch.delenv("PA_ONLY_LEN")
+        two = [_job(pa, rng, 200_000, 60_000) for _ in range(9)] + [_job(pa, rng, 20_000, 3_000) for _ in range(40)]
+        for _ in range(3):
+            st, _ = pa.pa_hash_batch(c, two, pa.PA_PREC_FP64)
+            torch.cuda.synchronize()
+            stats = pa.pa_last_stats(c)
+            assert st == pa.PA_OK and stats["launches"] <= 9, stats
+        for s, k, o, n, m in two[:2] + two[-2:]:
+            assert np.array_equal(from_dev(o)[:synth.words_for(m)], _direct(pa, c, s, k, n, m)), (n, m)
+    finally:
+        pa.pa_destroy(c)
